@@ -107,7 +107,12 @@ static int check_x(const void* x, int64_t M, int64_t ldx, int64_t K)
 // Two rows with K beyond 8192 also go to the tiles: the register form would take two passes and
 // the general GEMV is slower there (measured: 4096 x 11008 13.3 against 9.5 us, 8192 x 28672 48
 // against 34; at K = 8192 the GEMV still wins by 5 %).
-static int pick_path(int path, int64_t M, int64_t K, bool mfma_ok, bool reg_ok)
+// Beyond 16 rows, where the tiles would take a second pass over the weights, and from three rows on
+// where K is no multiple of 128 (or K is so long that the tiles cannot run without a workspace), the
+// blocks of gemm_wide.hip, which read the weights once per block of rows (us per launch, tiles or vector path -> blocks:
+// 12288 x 4096 at 32 rows 20.9 -> 15.2, 22016 x 4096 at 64 59.7 -> 26.5, 4096 x 1376 at 7 18.3 -> 4.6).
+constexpr int kPathWide = -2;           // gemm_wide.hip: AUTO only
+static int pick_path(int path, int64_t M, int64_t K, bool mfma_ok, bool reg_ok, bool wide_ok)
 {
     if (path != MXFP4_PATH_AUTO)
         return path;
@@ -118,6 +123,9 @@ static int pick_path(int path, int64_t M, int64_t K, bool mfma_ok, bool reg_ok)
     }
     if (env_path > 0)
         return env_path;
+    static const int wide_from = [] { const char* e = knob("MXFP4_WIDE_FROM"); return e ? atoi(e) : 17; }();   // measurement only
+    if (wide_ok && (M >= wide_from || (M >= 3 && !mfma_ok)))
+        return kPathWide;
     if (M >= 3 && mfma_ok)
         return MXFP4_PATH_MFMA;
     if (reg_ok)
@@ -219,7 +227,7 @@ static int run_gemm(const void* x, int64_t M, int64_t ldx, const void* q, const 
     }
     const int chosen = tiled ? -1
                              : pick_path(path, M, K, mfma_can_run(a, dev, splitk_ws != nullptr),
-                                         gemv_reg_can_run(a, dev) && gemv_reg_single_pass(a));
+                                         gemv_reg_can_run(a, dev) && gemv_reg_single_pass(a), gemm_wide_can_run(a, dev));
     hipStream_t st = static_cast<hipStream_t>(stream);
     int parts_used = 0;
     hipError_t e = hipSuccess;
@@ -253,6 +261,10 @@ static int run_gemm(const void* x, int64_t M, int64_t ldx, const void* q, const 
         }
         break;
     }
+    case kPathWide:
+        if (go)
+            e = launch_gemm_wide(a, dev, &parts_used, st, epi);
+        break;
     case MXFP4_PATH_VALU_BITS:
     case MXFP4_PATH_VALU_CVT:
     case MXFP4_PATH_VALU_LUT:

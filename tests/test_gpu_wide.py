@@ -1,0 +1,100 @@
+"""Parity of the block kernel for many activation rows and for K that is no multiple of 128
+(csrc/gemm_wide.hip; arXiv 2503.13565, section 3.4.3): plain, fused and pick forms against the CPU oracle
+at the edges of its blocks, one case at least per block shape."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2503_13565_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+from helpers import DEV, assert_argmax_ok, assert_cast_bit_exact, assert_gemm_close  # noqa: E402
+
+
+def check(m, n, k):
+    tag = "M=%d N=%d K=%d" % (m, n, k)
+    print(tag, flush=True)
+    w = synth.weights_student_t(n, k, seed=9000 + n + k)
+    xb = synth.activations_outlier_channels(m, k + 8, seed=9100 + m).to(DEV)
+    x = xb[:, :k]                                           # rows farther apart than K
+    q, s, q_ref, s_ref = assert_cast_bit_exact(w, tag)
+    y_ref, a_ref = oracle.woq_gemm(synth.to_bits(x.contiguous()), q_ref, s_ref)
+    ybuf = torch.full((m, n + 4), 7.0, dtype=torch.bfloat16, device=DEV)
+    binding.mxfp4_woq_gemm(x, q, s, y=ybuf[:, :n])
+    torch.cuda.synchronize()
+    assert_gemm_close(ybuf[:, :n], y_ref, a_ref, tag)
+    assert bool((ybuf[:, n:] == 7.0).all()), tag            # nothing written past N
+    again = binding.mxfp4_woq_gemm(x, q, s)
+    assert torch.equal(again, ybuf[:, :n]), tag             # same bits whatever the strides
+    idx, val = binding.mxfp4_woq_gemm_argmax(x, q, s)
+    torch.cuda.synchronize()
+    assert_argmax_ok(idx, val, y_ref, a_ref, tag)
+    g = torch.Generator().manual_seed(m + n)
+    for act in ([0, 1] if n % 2 == 0 else [0]):
+        c = n // 2 if act else n
+        bias = (torch.randn(n, generator=g) * 0.3).to(torch.bfloat16)
+        res = (torch.randn(m, c, generator=g) * 0.3).to(torch.bfloat16)
+        out_ref, a_out = oracle.epilogue(y_ref, a_ref, synth.to_bits(bias), synth.to_bits(res), act)
+        y = res.to(DEV)                                     # the residual updated in place
+        binding.mxfp4_woq_gemm_fused(x, q, s, bias=bias.to(DEV), act=act, residual=y, y=y)
+        torch.cuda.synchronize()
+        assert_gemm_close(y, out_ref, a_out, "%s act %d" % (tag, act))
+
+
+@pytest.mark.parametrize("m,n,k", [(3, 1, 96), (7, 4096, 1376), (16, 17, 32), (5, 5001, 32), (17, 5001, 32),
+                                   (5, 16000, 160), (5, 22000, 160), (5, 32000, 1376)])
+def test_few_rows_ragged_k(m, n, k):
+    check(m, n, k)
+
+
+@pytest.mark.parametrize("m,n,k", [(17, 16, 128), (17, 8200, 1376), (33, 4096, 160), (33, 1000, 4096), (17, 16000, 1376),
+                                   (32, 4098, 11008), (17, 22000, 1376), (17, 32000, 1376), (17, 8200, 160), (17, 22000, 160),
+                                   (16, 32000, 288), (64, 259, 288)])
+def test_several_sequences(m, n, k):
+    check(m, n, k)
+
+
+@pytest.mark.parametrize("m,n,k", [(65, 5001, 160), (65, 8200, 160), (129, 8200, 160), (300, 258, 1024), (129, 16000, 288),
+                                   (128, 4096, 96), (129, 22000, 32), (300, 16000, 32), (300, 22000, 32), (300, 32000, 32),
+                                   (509, 1, 64), (513, 130, 672)])
+def test_prompts(m, n, k):
+    check(m, n, k)
+
+
+def test_nan_stays_in_its_row_and_block():
+    # a NaN scale byte poisons its weight row, a NaN activation its own row: also in the rows that
+    # repeat past M and N and in the blocks that round K up
+    n, k, m = 35, 160, 19
+    q = torch.randint(0, 256, (n, k // 2), dtype=torch.uint8, device=DEV)
+    s = torch.full((n, k // 32), 120, dtype=torch.uint8, device=DEV)
+    s[34, 4] = 255
+    x = synth.activations_gaussian(m, k, seed=4).to(DEV)
+    x[18, 159] = float("nan")
+    y = binding.mxfp4_woq_gemm(x, q, s)
+    torch.cuda.synchronize()
+    want = torch.zeros((m, n), dtype=torch.bool, device=DEV)
+    want[18, :] = True
+    want[:, 34] = True
+    assert torch.equal(torch.isnan(y), want)
+
+
+def test_replays_from_a_graph():
+    n, k, m = 600, 1184, 40
+    w = synth.weights_student_t(n, k, seed=3).to(DEV)
+    q, s = binding.mxfp4_direct_cast(w)
+    x = synth.activations_gaussian(m, k, seed=5).to(DEV)
+    y = torch.empty((m, n), dtype=torch.bfloat16, device=DEV)
+    binding.mxfp4_woq_gemm(x, q, s, y=y)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        binding.mxfp4_woq_gemm(x, q, s, y=y)
+    for i in range(3):
+        x.copy_(synth.activations_gaussian(m, k, seed=50 + i))
+        want = binding.mxfp4_woq_gemm(x, q, s)
+        y.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want)
