@@ -17,13 +17,18 @@
 //     one barrier per phase, which waits for LDS traffic only.
 //   - LDS layout [step of the phase][row][16 chunks], chunk c of row r at position c ^ (r % 16): the
 //     threads of a store cover whole rows and the 16 rows of an operand read hit different banks.
-//   - Bound by the matrix pipe for prompts, by the activations' way through the L2 and LDS for some tens
-//     of rows.  Measured, us per call, before (16-row passes) -> here: 22016 x 4096 with the gate at 509 rows
-//     436 -> 120, 12288 x 4096 at 32 rows 18.6 -> 13.2 (host time included), 4096 x 1376 at 7 rows (two rows
-//     per pass on the vector ALUs before) 18.3 -> 4.6.
+//   - The scale bytes of two phases travel together, one dword per step and row, through the LDS: as byte
+//     loads by the lanes that use them (which the kernel does where K % 128 != 0 leaves the dwords
+//     unaligned) every byte pulled a cache line, 104 us instead of 130 on the example below.
+//   - Prompts take blocks of 128 rows with all eight waves side by side along the weight rows, so that no
+//     weight is decoded or fetched twice in a block: 92 us against 104 for 2 x 4 waves.
+//   - Bound by the matrix pipe at the clock the power limit leaves (with the loads and the LDS reads taken out
+//     the example takes 69 us, with all-zero operands 80), by the activations' way through the L2 and LDS for some
+//     tens of rows.  Measured, us per call, 16-row passes -> here: 22016 x 4096 with the gate at 509 rows
+//     436 -> 79 (a library product of BF16 weights of that shape: 91), 12288 x 4096 at 32 rows 18.6 -> 12.2
+//     (host time included), 4096 x 1376 at 7 rows (two rows per pass on the vector ALUs before) 18.3 -> 4.7.
 //   - A block past the end of K (K % 128 != 0, the steps that round a phase up) is a load past the
 //     descriptor: zero weights against zero activations.
-#include <math.h>
 #include <stdlib.h>
 
 #include "common.h"
@@ -50,15 +55,21 @@ struct WideArgs {
     int n, k, m, parts, ldr, act, tiles_m, tiles_n;
 };
 
+// Scale bytes of a block's weight rows for two phases, one row behind the other with a dword of padding
+// (the rows of an operand read hit different banks).
+constexpr int scale_row_bytes(int wk) { return wk * 8 + 4; }
+
 constexpr size_t wide_lds_bytes(int wm, int wn, int wk, int mf, int nf)
 {
-    const size_t xs = (size_t)2 * wk * wm * mf * 16 * 256;              // two buffers of one phase
+    const size_t xs = (size_t)2 * wk * wm * mf * 16 * 256 +             // two buffers of one phase
+                      (size_t)2 * wn * nf * 16 * scale_row_bytes(wk);   // and two of the scales
     const size_t red = wk > 1 ? (size_t)8 * mf * nf * 1024 : 0;         // the waves' partial sums, afterwards
     const size_t table = (size_t)wm * wn * mf * nf * 16 * 8;            // argmax: a winner per fragment and row
-    return (xs > red ? xs : red) + table;
+    const size_t most = xs > red ? xs : red;
+    return wk > 1 ? most + table : most > table ? most : table;         // (WK = 1: the table takes the buffers' place)
 }
 
-template <int WM, int WN, int WK, int MF, int NF>
+template <int WM, int WN, int WK, int MF, int NF, bool kRagged>
 __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(WideArgs a)
 {
     static_assert(WM * WN * WK == 8, "eight waves");
@@ -68,8 +79,11 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(WideArgs a)
     constexpr int kRowChunks = WK * 16;                                 // chunks of one row in a phase
     constexpr int kRowStep = kThreads / kRowChunks;                     // rows between a thread's chunks
     constexpr int kBuf = WK * BM * 16;                                  // chunks of one LDS buffer
+    constexpr int kSRow = scale_row_bytes(WK), kSBuf = BN * kSRow;
+    constexpr int SC = kRagged ? 0 : (BN * WK * 2 + kThreads - 1) / kThreads;   // scale dwords per thread and two phases
     extern __shared__ __align__(16) uint8_t smem[];
     u32x4_t* xs = reinterpret_cast<u32x4_t*>(smem);
+    uint8_t* ss = smem + (size_t)2 * kBuf * 16;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, li = lane & 15, lg = lane >> 4;
@@ -104,29 +118,55 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(WideArgs a)
         q_off[f] = row * (k >> 1) + lg * 16;
         s_off[f] = row * nblk + lg;
     }
+    // (K % 128 == 0) dword e of the block's scales: step e % (2 WK) of the two phases, row e / (2 WK)
+    int sc_off[SC + 1], sc_at[SC + 1];
+#pragma unroll
+    for (int i = 0; i < SC; ++i) {
+        const int e = min(tid + i * kThreads, BN * WK * 2 - 1), r = e / (WK * 2), c = e % (WK * 2);
+        sc_off[i] = min(n0 + r, n - 1) * nblk + c * 4;
+        sc_at[i] = r * kSRow + c * 4;
+    }
 
     struct Slot {
         u32x4_t x[CA];
         u32x4_t q[NF];
-        uint32_t s[NF];
+        uint32_t s[kRagged ? NF : 1];
     };
     Slot buf[2];
+    uint32_t sc[SC + 1];
+    // Always the same loads, and every condition on the position arithmetic (a branch around a load makes
+    // the compiler wait for all of them): what lies past K gets an offset past the descriptor.  The
+    // scalar offset stays inside the descriptor then too.
+    auto past = [](int last, int at) { return ((last - at) >> 31) & kOob; };    // 0 where at <= last
     int ld_ph = 0;
-    auto issue = [&](Slot& sl) {                                        // always the same loads, so the waits stay exact
-        // (the scalar offset must stay inside the descriptor also where every lane's offset is outside)
-        const bool have_x = ld_ph * kRowChunks + xc < (k >> 3);
+    auto issue_scales = [&](int sp) {                                   // of the phases 2 sp and 2 sp + 1
+        const int at = sp * (WK * 8) < nblk ? sp * (WK * 8) : 0;
+#pragma unroll
+        for (int i = 0; i < SC; ++i)
+            sc[i] = __builtin_amdgcn_raw_buffer_load_b32(
+                rs, sc_off[i] | past(nblk - 1, sp * (WK * 8) + (tid + i * kThreads) % (WK * 2) * 4), at, 0);
+    };
+    auto store_scales = [&](int b) {
+#pragma unroll
+        for (int i = 0; i < SC; ++i)
+            *reinterpret_cast<uint32_t*>(ss + b * kSBuf + sc_at[i]) = sc[i];
+    };
+    auto issue = [&](Slot& sl) {
+        const int x_past = past((k >> 3) - 1, ld_ph * kRowChunks + xc);
         const int x_at = ld_ph < phases ? ld_ph * (kRowChunks * 16) : 0;
 #pragma unroll
         for (int i = 0; i < CA; ++i)
-            sl.x[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, have_x ? x_off[i] : kOob, x_at, 0);
-        const bool have = 4 * (ld_ph * WK + wk) + lg < nblk;
+            sl.x[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, x_off[i] | x_past, x_at, 0);
+        const int q_past = past(nblk - 1, 4 * (ld_ph * WK + wk) + lg);
         const int T = ld_ph * WK + wk < steps ? ld_ph * WK + wk : 0;
+        if constexpr (kRagged) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+                sl.s[f] = __builtin_amdgcn_raw_buffer_load_b8(rs, s_off[f] | q_past, T * 4, 0);
+        }
 #pragma unroll
         for (int f = 0; f < NF; ++f)
-            sl.s[f] = __builtin_amdgcn_raw_buffer_load_b8(rs, have ? s_off[f] : kOob, T * 4, 0);
-#pragma unroll
-        for (int f = 0; f < NF; ++f)
-            sl.q[f] = __builtin_amdgcn_raw_buffer_load_b128(rq, have ? q_off[f] : kOob, T * 64, 0);
+            sl.q[f] = __builtin_amdgcn_raw_buffer_load_b128(rq, q_off[f] | q_past, T * 64, 0);
         ++ld_ph;
     };
     auto x_store = [&](const Slot& sl, int b) {
@@ -136,10 +176,12 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(WideArgs a)
             xs[b * kBuf + ((xc >> 4) * BM + r) * 16 + ((xc & 15) ^ (r & 15))] = sl.x[i];
         }
     };
+    issue_scales(0);
     issue(buf[0]);
     __builtin_amdgcn_sched_barrier(0);                                  // keep the slots' loads in issue order
     issue(buf[1]);
     __builtin_amdgcn_sched_barrier(0);
+    store_scales(0);
     x_store(buf[0], 0);
     lds_barrier();
 
@@ -150,6 +192,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(WideArgs a)
         for (int f = 0; f < NF; ++f)
             acc[i][f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const int x_read = (wk * BM + wm * MF * 16 + li) * 16;
+    const int s_read = (wn * NF * 16 + li) * kSRow + wk * 4 + lg;
 
     for (int u0 = 0; u0 < phases; u0 += 2) {
 #pragma unroll
@@ -157,10 +200,11 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(WideArgs a)
             const Slot& sl = buf[d];
             if ((u0 + d) * WK + wk < steps) {
                 const u32x4_t* xb = xs + d * kBuf + x_read;
+                const uint8_t* sb = ss + ((u0 >> 1) & 1) * kSBuf + s_read + d * (WK * 4);
                 float scl[NF];
 #pragma unroll
                 for (int f = 0; f < NF; ++f)
-                    scl[f] = __uint_as_float(sl.s[f] << 23);
+                    scl[f] = __uint_as_float((kRagged ? sl.s[f] : (uint32_t)sb[f * 16 * kSRow]) << 23);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     u32x4_t xf[MF];
@@ -184,6 +228,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(WideArgs a)
             }
             // the next phase's activations go to the buffer that the phase before this one read
             x_store(buf[1 - d], 1 - d);
+            if (d == 1)
+                store_scales(((u0 >> 1) + 1) & 1);
+            if (d == 0)
+                issue_scales((u0 >> 1) + 1);
             issue(buf[d]);
             lds_barrier();
         }
@@ -191,8 +239,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(WideArgs a)
 
     // Output fragment (i, f) of block position (wm, wn): lane (li, lg) holds weight rows 4 lg + r for
     // activation row li.
-    constexpr size_t kXBytes = (size_t)2 * kBuf * 16, kRedBytes = WK > 1 ? (size_t)8 * MF * NF * 1024 : 0;
-    float2* table = reinterpret_cast<float2*>(smem + (kXBytes > kRedBytes ? kXBytes : kRedBytes));
+    constexpr size_t kXBytes = (size_t)2 * kBuf * 16 + 2 * kSBuf, kRedBytes = WK > 1 ? (size_t)8 * MF * NF * 1024 : 0;
+    float2* table = reinterpret_cast<float2*>(smem + (WK == 1 ? 0 : kXBytes > kRedBytes ? kXBytes : kRedBytes));
     const bool pick = a.part_val != nullptr, gated = a.act == MXFP4_ACT_SWIGLU;
     const bool wide_store = !gated && (a.ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(a.y) & 7) == 0;
     auto emit = [&](const f32x4_t sum, int i, int f) {
@@ -289,51 +337,70 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(WideArgs a)
     }
 }
 
-// The block shapes there are.
+// The block shapes there are, each with what it took, in microseconds: the first block of a compute unit
+// and every further one as start + step x (steps of 128 along K, whole phases), measured with 256, 512 and 1024
+// blocks over K = 1024 and 4096.  (Two blocks share a unit where LDS and registers allow.)
 struct Shape {
     int wm, wn, wk, mf, nf;
+    float first_start, first_step, next_start, next_step;
     hipError_t (*launch)(const WideArgs&, const DeviceInfo&, hipStream_t);
 };
 
 template <int WM, int WN, int WK, int MF, int NF>
 hipError_t launch_shape(const WideArgs& a, const DeviceInfo& dev, hipStream_t stream)
 {
-    auto kern = gemm_wide_kernel<WM, WN, WK, MF, NF>;
-    static LdsLimit lds_limit;                      // of this kernel instance
-    if (hipError_t e = lds_limit.raise(reinterpret_cast<const void*>(kern), dev.lds_bytes); e != hipSuccess)
+    auto kern = gemm_wide_kernel<WM, WN, WK, MF, NF, false>;
+    auto kern_ragged = gemm_wide_kernel<WM, WN, WK, MF, NF, true>;
+    static LdsLimit lds_limit, lds_limit_ragged;    // of these kernel instances
+    const bool ragged = a.k % 128 != 0;
+    if (hipError_t e = (ragged ? lds_limit_ragged : lds_limit)
+                           .raise(reinterpret_cast<const void*>(ragged ? kern_ragged : kern), dev.lds_bytes);
+        e != hipSuccess)
         return e;
+    if (ragged)
+        kern = kern_ragged;
     hipLaunchKernelGGL(kern, dim3(a.tiles_m * a.tiles_n), dim3(kThreads), wide_lds_bytes(WM, WN, WK, MF, NF), stream, a);
     return hipGetLastError();
 }
 
-#define MXFP4_WIDE(WM_, WN_, WK_, MF_, NF_) {WM_, WN_, WK_, MF_, NF_, launch_shape<WM_, WN_, WK_, MF_, NF_>}
+#define MXFP4_WIDE(WM_, WN_, WK_, MF_, NF_, A_, B_, C_, D_) \
+    {WM_, WN_, WK_, MF_, NF_, A_, B_, C_, D_, launch_shape<WM_, WN_, WK_, MF_, NF_>}
 const Shape kShapes[] = {
-    MXFP4_WIDE(1, 1, 8, 1, 1), MXFP4_WIDE(1, 1, 8, 1, 2), MXFP4_WIDE(1, 1, 8, 1, 3), MXFP4_WIDE(1, 1, 8, 1, 4),
-    MXFP4_WIDE(1, 1, 8, 1, 6), MXFP4_WIDE(1, 1, 8, 1, 8),
-    MXFP4_WIDE(1, 1, 8, 2, 1), MXFP4_WIDE(1, 1, 8, 2, 2), MXFP4_WIDE(1, 1, 8, 2, 3), MXFP4_WIDE(1, 1, 8, 2, 4),
-    MXFP4_WIDE(1, 1, 8, 2, 6), MXFP4_WIDE(1, 1, 8, 2, 8),
-    MXFP4_WIDE(1, 2, 4, 4, 1), MXFP4_WIDE(1, 2, 4, 4, 2), MXFP4_WIDE(1, 2, 4, 4, 3), MXFP4_WIDE(1, 2, 4, 4, 4),
-    MXFP4_WIDE(2, 2, 2, 4, 1), MXFP4_WIDE(2, 2, 2, 4, 2), MXFP4_WIDE(2, 2, 2, 4, 3), MXFP4_WIDE(2, 2, 2, 4, 4),
-    MXFP4_WIDE(2, 4, 1, 4, 2), MXFP4_WIDE(2, 4, 1, 4, 3), MXFP4_WIDE(2, 4, 1, 4, 4), MXFP4_WIDE(2, 4, 1, 4, 5),
-    MXFP4_WIDE(2, 4, 1, 4, 6),
+    MXFP4_WIDE(1, 1, 8, 1, 1, 4.29f, 0.060f, 1.20f, 0.047f),
+    MXFP4_WIDE(1, 1, 8, 1, 2, 4.71f, 0.070f, 1.46f, 0.078f),
+    MXFP4_WIDE(1, 1, 8, 1, 3, 5.05f, 0.107f, 1.73f, 0.099f),
+    MXFP4_WIDE(1, 1, 8, 1, 4, 5.04f, 0.145f, 1.82f, 0.125f),
+    MXFP4_WIDE(1, 1, 8, 1, 6, 5.46f, 0.224f, 4.12f, 0.185f),
+    MXFP4_WIDE(1, 1, 8, 1, 8, 6.23f, 0.282f, 4.93f, 0.248f),
+    MXFP4_WIDE(1, 1, 8, 2, 1, 5.18f, 0.101f, 3.47f, 0.101f),
+    MXFP4_WIDE(1, 1, 8, 2, 2, 5.56f, 0.145f, 3.83f, 0.134f),
+    MXFP4_WIDE(1, 1, 8, 2, 3, 5.98f, 0.182f, 4.27f, 0.164f),
+    MXFP4_WIDE(1, 1, 8, 2, 4, 6.22f, 0.219f, 4.80f, 0.192f),
+    MXFP4_WIDE(1, 1, 8, 2, 6, 7.51f, 0.290f, 6.36f, 0.240f),
+    MXFP4_WIDE(1, 2, 4, 4, 1, 4.28f, 0.332f, 2.83f, 0.297f),
+    MXFP4_WIDE(1, 2, 4, 4, 2, 5.42f, 0.378f, 4.55f, 0.310f),
+    MXFP4_WIDE(1, 2, 4, 4, 3, 6.60f, 0.465f, 5.28f, 0.416f),
+    MXFP4_WIDE(2, 2, 2, 4, 2, 7.37f, 0.685f, 5.26f, 0.647f),
+    MXFP4_WIDE(2, 2, 2, 4, 3, 9.18f, 0.845f, 5.97f, 0.860f),
+    MXFP4_WIDE(2, 4, 1, 4, 2, 8.47f, 0.990f, 0.57f, 1.088f),
+    MXFP4_WIDE(2, 4, 1, 4, 3, 11.68f, 1.322f, 5.43f, 1.589f),
+    MXFP4_WIDE(1, 8, 1, 8, 2, 13.11f, 1.649f, 10.94f, 1.719f),
+    MXFP4_WIDE(1, 8, 1, 8, 3, 17.49f, 2.228f, 15.91f, 2.251f),
+    MXFP4_WIDE(1, 4, 2, 4, 1, 4.52f, 0.447f, 1.79f, 0.317f),
+    MXFP4_WIDE(1, 4, 2, 4, 2, 6.33f, 0.526f, 2.02f, 0.463f),
+    MXFP4_WIDE(1, 4, 2, 4, 3, 8.68f, 0.704f, 4.44f, 0.877f),
 };
 #undef MXFP4_WIDE
 
-// Cost of a call with a shape, in clocks of one compute unit: rounds of blocks times what bounds a
-// block -- the matrix pipe (16 clocks per instruction, two waves to a SIMD), the converts, or the texture
-// path (64 bytes per clock) -- plus a start and an end per block.
-double shape_clocks(const Shape& c, int m, int n, int k, int cus, int* tiles_m, int* tiles_n)
+// What a call would take with a shape, in microseconds.
+float shape_time(const Shape& c, int m, int n, int k, int cus, int* tiles_m, int* tiles_n)
 {
     const int bm = c.wm * c.mf * 16, bn = c.wn * c.nf * 16;
     *tiles_m = (m + bm - 1) / bm;
     *tiles_n = (n + bn - 1) / bn;
-    const double rounds = ((double)*tiles_m * *tiles_n + cus - 1) / cus;
-    const int phases = ((k + 127) / 128 + c.wk - 1) / c.wk;
-    const double mfma = 2.0 * c.mf * c.nf * 64, convert = 2.0 * c.nf * 16 * 4.4;
-    const double tex = c.wk * bm * 4.0 + 8.0 * c.nf * 32;
-    double phase = mfma > convert ? mfma : convert;
-    phase = (phase > tex ? phase : tex) + 300;
-    return floor(rounds) * (phases * phase + 4000 + c.mf * c.nf * 60);
+    const int rounds = (int)(((int64_t)*tiles_m * *tiles_n + cus - 1) / cus);
+    const int steps = ((k + 127) / 128 + c.wk - 1) / c.wk * c.wk;
+    return c.first_start + c.first_step * steps + (rounds - 1) * (c.next_start + c.next_step * steps);
 }
 
 const Shape* pick_shape(int m, int n, int k, int cus, int max_cols, int* tiles_m, int* tiles_n)
@@ -341,15 +408,15 @@ const Shape* pick_shape(int m, int n, int k, int cus, int max_cols, int* tiles_m
     const char* forced_shape = knob("MXFP4_WIDE_SHAPE");            // measurement only
     const int env = forced_shape ? atoi(forced_shape) : -1;
     const Shape* best = nullptr;
-    double best_clocks = 0;
+    float best_time = 0;
     int i = 0;
     for (const Shape& c : kShapes) {
         int tm, tn;
-        const double clocks = shape_clocks(c, m, n, k, cus, &tm, &tn);
+        const float time = shape_time(c, m, n, k, cus, &tm, &tn);
         const bool forced = env == i++;
-        if (tn <= max_cols && (!best || clocks < best_clocks || forced)) {
+        if (tn <= max_cols && (!best || time < best_time || forced)) {
             best = &c;
-            best_clocks = forced ? -1 : clocks;
+            best_time = forced ? -1.f : time;
             *tiles_m = tm;
             *tiles_n = tn;
         }

@@ -44,23 +44,43 @@ def check(m, n, k):
 
 
 @pytest.mark.parametrize("m,n,k", [(3, 1, 96), (7, 4096, 1376), (16, 17, 32), (5, 5001, 32), (17, 5001, 32),
-                                   (5, 16000, 160), (5, 22000, 160), (5, 32000, 1376)])
+                                   (5, 16000, 160), (5, 22000, 160), (5, 32000, 1376), (3, 12636, 288), (3, 32924, 32)])
 def test_few_rows_ragged_k(m, n, k):
     check(m, n, k)
 
 
 @pytest.mark.parametrize("m,n,k", [(17, 16, 128), (17, 8200, 1376), (33, 4096, 160), (33, 1000, 4096), (17, 16000, 1376),
                                    (32, 4098, 11008), (17, 22000, 1376), (17, 32000, 1376), (17, 8200, 160), (17, 22000, 160),
-                                   (16, 32000, 288), (64, 259, 288)])
+                                   (16, 32000, 288), (64, 259, 288), (17, 4596, 320), (35, 16599, 800), (34, 11208, 2016)])
 def test_several_sequences(m, n, k):
     check(m, n, k)
 
 
 @pytest.mark.parametrize("m,n,k", [(65, 5001, 160), (65, 8200, 160), (129, 8200, 160), (300, 258, 1024), (129, 16000, 288),
                                    (128, 4096, 96), (129, 22000, 32), (300, 16000, 32), (300, 22000, 32), (300, 32000, 32),
-                                   (509, 1, 64), (513, 130, 672)])
+                                   (509, 1, 64), (513, 130, 672), (66, 34424, 576), (536, 477, 544), (454, 260, 2080),
+                                   (378, 8148, 768)])
 def test_prompts(m, n, k):
     check(m, n, k)
+
+
+@pytest.mark.parametrize("m,n,k", [(196, 26152, 1216), (138, 44350, 1120), (509, 22016, 4096)])
+def test_largest_blocks(m, n, k):
+    # checked on sampled weight rows, the edges among them
+    w = synth.weights_student_t(n, k, seed=9300 + n, device=DEV)
+    x = synth.activations_outlier_channels(m, k, seed=9400 + m, device=DEV)
+    q, s = binding.mxfp4_direct_cast(w)
+    g = torch.Generator().manual_seed(n)
+    even = 2 * torch.cat([torch.arange(8), torch.randint(0, n // 2, (60,), generator=g), torch.arange(n // 2 - 8, n // 2)])
+    rows = torch.stack([even, even + 1], dim=1).reshape(-1)         # whole (gate, up) pairs
+    y_ref, a_ref = oracle.woq_gemm(synth.to_bits(x), q.cpu()[rows].numpy(), s.cpu()[rows].numpy())
+    y = binding.mxfp4_woq_gemm(x, q, s)
+    gated = binding.mxfp4_woq_gemm_fused(x, q, s, act=1)
+    torch.cuda.synchronize()
+    tag = "M=%d N=%d K=%d" % (m, n, k)
+    assert_gemm_close(y[:, rows.to(DEV)], y_ref, a_ref, tag)
+    out_ref, a_out = oracle.epilogue(y_ref, a_ref, None, None, 1)
+    assert_gemm_close(gated[:, even.to(DEV) // 2], out_ref, a_out, tag)
 
 
 def test_nan_stays_in_its_row_and_block():
