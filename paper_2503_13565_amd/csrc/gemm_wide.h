@@ -1,0 +1,411 @@
+// The product for more activation rows than one matrix-core tile column holds (a prompt, several
+// sequences verified together) and, at any row count from three on, for MXFP4 weights whose K is no multiple of
+// 128 (arXiv 2503.13565, section 3.4.3, Eq. 2 for the arithmetic; every weight is read once per block of rows).
+//
+// The tile kernels keep all of K of at most 16 activation rows in the LDS, so more rows take more
+// passes, and every pass streams and decodes the weights again.  Here a workgroup of eight waves
+// computes a BM x BN block of the output and walks K once: the activation rows of one phase of K
+// (WK steps of 128 elements) sit in one of two LDS buffers, shared by all waves; a wave loads the weights of
+// its 16 NF rows straight into registers, in the layout of the tile kernels (lane i + 16 g: block 4 T + g of row
+// i), decodes them once and uses them for MF fragments of 16 activation
+// rows.  The eight waves are WM x WN x WK: WM and WN split the block, WK splits the steps of a phase (few
+// rows: the block is small and K is what there is to share), and then the WK partial sums of a
+// fragment meet in the LDS at the end and are added in wave order.
+//   - A phase's activations (16-byte chunks, one row's chunks to neighbouring threads) and its weights
+//     are requested two phases ahead into registers, the activations written to the LDS one phase ahead:
+//     one barrier per phase, which waits for LDS traffic only.
+//   - LDS layout [step of the phase][row][16 chunks], chunk c of row r at position c ^ (r % 16): the
+//     threads of a store cover whole rows and the 16 rows of an operand read hit different banks.
+//   - The scale bytes of two phases travel together, one dword per step and row, through the LDS: as byte
+//     loads by the lanes that use them (which the kernel does where K % 128 != 0 leaves the dwords
+//     unaligned) every byte pulled a cache line, 104 us instead of 130 on the example below.
+//   - Prompts take blocks of 128 rows with all eight waves side by side along the weight rows, so that no
+//     weight is decoded or fetched twice in a block: 92 us against 104 for 2 x 4 waves.
+//   - Bound by the matrix pipe at the clock the power limit leaves (with the loads and the LDS reads taken out
+//     the example takes 69 us, with all-zero operands 80), by the activations' way through the L2 and LDS for some
+//     tens of rows.  Measured, us per call, 16-row passes -> here: 22016 x 4096 with the gate at 509 rows
+//     436 -> 79 (a library product of BF16 weights of that shape: 91), 12288 x 4096 at 32 rows 18.6 -> 12.2
+//     (host time included), 4096 x 1376 at 7 rows (two rows per pass on the vector ALUs before) 18.3 -> 4.7.
+//   - A block past the end of K (K % 128 != 0, the steps that round a phase up) is a load past the
+//     descriptor: zero weights against zero activations.
+#pragma once
+
+#include "block_out.h"
+#include "common.h"
+#include "kernels.h"
+
+namespace mxfp4 {
+namespace wide {
+
+constexpr int kOob = 0x7FFFFFF0;        // lane offset beyond any descriptor: the load returns zero
+constexpr int kThreads = 512;
+
+typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
+typedef __attribute__((ext_vector_type(6))) unsigned int u32x6_t;
+typedef __attribute__((ext_vector_type(16))) unsigned int u32x16_t;
+
+// The weights: MXFP4 row-major, MXFP4 tile-major, MXFP4 row-major with K % 128 != 0, E4M3 and E5M2 bytes,
+// E2M3 and E3M2 blocks of 24 bytes, ternary blocks of 8 bytes, unquantised BF16 (any K % 8 == 0).
+enum Kind { kMx, kMxTiled, kMxRagged, kE4m3, kE5m2, kE2m3, kE3m2, kT2, kBf16 };
+constexpr int kind_bits(Kind w)
+{
+    return w == kBf16 ? 16 : w == kE4m3 || w == kE5m2 ? 8 : w == kE2m3 || w == kE3m2 ? 6 : w == kT2 ? 2 : 4;
+}
+
+struct Args {
+    const uint16_t* x;
+    const uint8_t* q;
+    const uint8_t* s;
+    int n, k, m, ldx, ldw, tiles_m, tiles_n;    // ldw: BF16 weights only
+    BlockOut out;
+};
+
+// Scale bytes of a block's weight rows for two phases, one row behind the other with a dword of padding
+// (the rows of an operand read hit different banks).
+constexpr int scale_row_bytes(int wk) { return wk * 8 + 4; }
+
+constexpr size_t lds_bytes(Kind w, int wm, int wn, int wk, int mf, int nf)
+{
+    const size_t xs = (size_t)2 * wk * wm * mf * 16 * 256 +             // two buffers of one phase
+                      (w == kBf16 ? 0 : (size_t)2 * wn * nf * 16 * scale_row_bytes(wk));    // and two of the scales
+    const size_t red = wk > 1 ? (size_t)8 * mf * nf * 1024 : 0;         // the waves' partial sums, afterwards
+    const size_t table = (size_t)wm * wn * mf * nf * 16 * 8;            // pick: a winner per fragment and row
+    const size_t most = xs > red ? xs : red;
+    return wk > 1 ? most + table : most > table ? most : table;         // (WK = 1: the table takes the buffers' place)
+}
+
+// Two codes of the 2-bit format per byte -> two MXFP4 nibbles (sign, 1.0 or 0): eight codes of `c`, a dword.
+__device__ __forceinline__ uint32_t t2_to_nibbles(uint32_t c)
+{
+    c = (c | c << 8) & 0x00FF00FFu;
+    c = (c | c << 4) & 0x0F0F0F0Fu;
+    c = (c | c << 2) & 0x33333333u;
+    return (c & 0x22222222u) << 2 | (c & 0x11111111u) << 1;
+}
+
+// The eight BF16 weights of matrix instruction j out of the dwords of a lane's block.
+template <Kind kW>
+__device__ __forceinline__ u32x4_t operand(const uint32_t* r, const u32x16_t& six, float scl, int j)
+{
+    u32x4_t w;
+    if constexpr (kW == kBf16) {
+        w = u32x4_t{r[4 * j], r[4 * j + 1], r[4 * j + 2], r[4 * j + 3]};
+    } else if constexpr (kind_bits(kW) == 6) {
+        const uint32_t w0 = six[4 * j], w1 = six[4 * j + 1], w2 = six[4 * j + 2], w3 = six[4 * j + 3];
+        w = u32x4_t{w0, w1, w2, w3};
+    } else if constexpr (kW == kE4m3) {
+        w[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(r[2 * j], scl, false));
+        w[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(r[2 * j], scl, true));
+        w[2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(r[2 * j + 1], scl, false));
+        w[3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(r[2 * j + 1], scl, true));
+    } else if constexpr (kW == kE5m2) {
+        w[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_bf8(r[2 * j], scl, false));
+        w[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_bf8(r[2 * j], scl, true));
+        w[2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_bf8(r[2 * j + 1], scl, false));
+        w[3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_bf8(r[2 * j + 1], scl, true));
+    } else {
+        const uint32_t qd = kW == kT2 ? t2_to_nibbles(r[j >> 1] >> (16 * (j & 1)) & 0xFFFFu) : r[j];
+        w[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(qd, scl, 0));
+        w[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(qd, scl, 1));
+        w[2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(qd, scl, 2));
+        w[3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(qd, scl, 3));
+    }
+    return w;
+}
+
+// The leading arguments are scalars that arrive in registers when a wave starts; `out` is for the end.
+template <Kind kW, int WM, int WN, int WK, int MF, int NF>
+__global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* __restrict__ x,
+                                                                const uint8_t* __restrict__ q,
+                                                                const uint8_t* __restrict__ s, int n, int k, int m,
+                                                                int ldx, int ldw, int tiles_m, int tiles_n, BlockOut out)
+{
+    static_assert(WM * WN * WK == 8, "eight waves");
+    constexpr int BM = WM * MF * 16, BN = WN * NF * 16;
+    constexpr int CA = WK * BM * 16 / kThreads;                         // activation chunks per thread and phase
+    static_assert(CA >= 1 && CA * kThreads == WK * BM * 16, "whole chunks");
+    constexpr int kRowChunks = WK * 16;                                 // chunks of one row in a phase
+    constexpr int kRowStep = kThreads / kRowChunks;                     // rows between a thread's chunks
+    constexpr int kBuf = WK * BM * 16;                                  // chunks of one LDS buffer
+    constexpr bool kScaled = kW != kBf16, kRagged = kW == kMxRagged, kTiled = kW == kMxTiled;
+    constexpr int kBits = kind_bits(kW), kBlock = 4 * kBits;            // dwords and bytes of a block of 32
+    constexpr int kSRow = scale_row_bytes(WK), kSBuf = BN * kSRow;
+    // scale dwords per thread and two phases
+    constexpr int SC = kScaled && !kRagged ? (BN * WK * 2 + kThreads - 1) / kThreads : 0;
+    extern __shared__ __align__(16) uint8_t smem[];
+    u32x4_t* xs = reinterpret_cast<u32x4_t*>(smem);
+    uint8_t* ss = smem + (size_t)2 * kBuf * 16;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, li = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wk = wave % WK, wn = wave / WK % WN, wm = wave / WK / WN;
+    const int nblk = k >> 5, steps = (k + 127) >> 7, phases = (steps + WK - 1) / WK;
+    const int n_tiles = (n + 15) >> 4, n_items = (steps + 3) >> 2;      // of the tile-major copy
+
+    const int at = block_on_die(tiles_m * tiles_n, blockIdx.x);
+    const int tm = at % tiles_m, tn = at / tiles_m;
+    const int m0 = tm * BM, n0 = tn * BN;
+
+    const int row_bytes = kW == kBf16 ? ldw * 2 : nblk * kBlock;
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t*>(x + (int64_t)m0 * ldx), 0, ((min(BM, m - m0) - 1) * ldx + k) * 2, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t*>(q), 0, kTiled ? n_tiles * 16 * row_bytes : kW == kBf16 ? ((n - 1) * ldw + k) * 2 : n * row_bytes,
+        0x00020000);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t*>(s), 0, !kScaled ? 0 : kTiled ? n_tiles * n_items * 256 : n * nblk, 0x00020000);
+
+    const int xc = tid % kRowChunks, xr = tid / kRowChunks;             // this thread's chunk of a row, first row
+    int x_off[CA];
+#pragma unroll
+    for (int i = 0; i < CA; ++i)
+        x_off[i] = (min(m0 + xr + i * kRowStep, m - 1) - m0) * ldx * 2 + xc * 16;       // ragged M: repeat the last row
+    int q_off[NF], s_off[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {                                      // ragged N: repeat the last row (or tile)
+        const int row0 = n0 + (wn * NF + f) * 16, row = min(row0 + li, n - 1);
+        q_off[f] = kTiled ? min(row0 >> 4, n_tiles - 1) * steps * 1024 + lane * 16
+                          : row * row_bytes + lg * (kW == kBf16 ? 16 : kBlock);
+        s_off[f] = row * nblk + lg;
+    }
+    // dword e of the block's scales: step e % (2 WK) of the two phases, row e / (2 WK)
+    int sc_off[SC + 1], sc_at[SC + 1];
+#pragma unroll
+    for (int i = 0; i < SC; ++i) {
+        const int e = min(tid + i * kThreads, BN * WK * 2 - 1), r = e / (WK * 2), c = e % (WK * 2);
+        sc_off[i] = kTiled ? (min((n0 + r) >> 4, n_tiles - 1) * n_items * 16 + (r & 15)) * 16
+                           : min(n0 + r, n - 1) * nblk + c * 4;
+        sc_at[i] = r * kSRow + c * 4;
+    }
+
+    struct Slot {
+        u32x4_t x[CA];
+        uint32_t q[NF][kBits];
+        uint32_t s[kRagged ? NF : 1];
+    };
+    Slot buf[2];
+    uint32_t sc[SC + 1];
+    // Always the same loads, and every condition on the position arithmetic (a branch around a load makes
+    // the compiler wait for all of them): what lies past K gets an offset past the descriptor.  The
+    // scalar offset stays inside the descriptor then too.
+    auto past = [](int last, int at) { return ((last - at) >> 31) & kOob; };    // 0 where at <= last
+    int ld_ph = 0;
+    auto issue_scales = [&](int sp) {                                   // of the phases 2 sp and 2 sp + 1
+        const int at = sp * (WK * 8) < nblk ? sp * (WK * 8) : 0;
+#pragma unroll
+        for (int i = 0; i < SC; ++i) {
+            const int T = sp * (WK * 2) + (tid + i * kThreads) % (WK * 2);
+            if constexpr (kTiled)
+                sc[i] = __builtin_amdgcn_raw_buffer_load_b32(
+                    rs, (sc_off[i] + (T >> 2) * 256 + (T & 3) * 4) | past(steps - 1, T), 0, 0);
+            else
+                sc[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, sc_off[i] | past(steps - 1, T), at, 0);
+        }
+    };
+    auto store_scales = [&](int b) {
+#pragma unroll
+        for (int i = 0; i < SC; ++i)
+            *reinterpret_cast<uint32_t*>(ss + b * kSBuf + sc_at[i]) = sc[i];
+    };
+    auto issue = [&](Slot& sl) {
+        const int x_past = past((k >> 3) - 1, ld_ph * kRowChunks + xc);
+        const int x_at = ld_ph < phases ? ld_ph * (kRowChunks * 16) : 0;
+#pragma unroll
+        for (int i = 0; i < CA; ++i)
+            sl.x[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, x_off[i] | x_past, x_at, 0);
+        const int step = ld_ph * WK + wk, T = step < steps ? step : 0;
+        const int q_past = past(nblk - 1, 4 * step + lg);
+        if constexpr (kRagged) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+                sl.s[f] = __builtin_amdgcn_raw_buffer_load_b8(rs, s_off[f] | q_past, T * 4, 0);
+        }
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            auto take = [&](int i, u32x4_t v) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    sl.q[f][4 * i + e] = v[e];
+            };
+            auto take2 = [&](int i, u32x2_t v) {
+                sl.q[f][i] = v[0];
+                sl.q[f][i + 1] = v[1];
+            };
+            if constexpr (kW == kBf16) {                                // 64 bytes of a row per instruction
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    take(j, __builtin_amdgcn_raw_buffer_load_b128(
+                                rq, (q_off[f] + j * 64) | past((k >> 3) - 1, step * 16 + 4 * j + lg), T * 256, 0));
+            } else {
+                const int off = q_off[f] | q_past, row_at = T * (kTiled ? 1024 : 4 * kBlock);
+                if constexpr (kBits == 2)
+                    take2(0, __builtin_amdgcn_raw_buffer_load_b64(rq, off, row_at, 0));
+                else
+                    take(0, __builtin_amdgcn_raw_buffer_load_b128(rq, off, row_at, kTiled ? 2 : 0));
+                if constexpr (kBits == 8)
+                    take(1, __builtin_amdgcn_raw_buffer_load_b128(rq, (q_off[f] + 16) | q_past, row_at, 0));
+                if constexpr (kBits == 6)
+                    take2(4, __builtin_amdgcn_raw_buffer_load_b64(rq, (q_off[f] + 16) | q_past, row_at, 0));
+            }
+        }
+        ++ld_ph;
+    };
+    auto x_store = [&](const Slot& sl, int b) {
+#pragma unroll
+        for (int i = 0; i < CA; ++i) {
+            const int r = xr + i * kRowStep;
+            xs[b * kBuf + ((xc >> 4) * BM + r) * 16 + ((xc & 15) ^ (r & 15))] = sl.x[i];
+        }
+    };
+    issue_scales(0);
+    issue(buf[0]);
+    __builtin_amdgcn_sched_barrier(0);                                  // keep the slots' loads in issue order
+    issue(buf[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    store_scales(0);
+    x_store(buf[0], 0);
+    lds_barrier();
+
+    f32x4_t acc[MF][NF];
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+            acc[i][f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const int x_read = (wk * BM + wm * MF * 16 + li) * 16;
+    const int s_read = (wn * NF * 16 + li) * kSRow + wk * 4 + lg;
+
+    for (int u0 = 0; u0 < phases; u0 += 2) {
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+            const Slot& sl = buf[d];
+            if ((u0 + d) * WK + wk < steps) {
+                const u32x4_t* xb = xs + d * kBuf + x_read;
+                const uint8_t* sb = ss + ((u0 >> 1) & 1) * kSBuf + s_read + d * (WK * 4);
+                float scl[NF];
+                u32x16_t six[kBits == 6 ? NF : 1] = {};                 // 6-bit: one convert for the whole block
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    scl[f] = !kScaled ? 1.f : __uint_as_float((kRagged ? sl.s[f] : (uint32_t)sb[f * 16 * kSRow]) << 23);
+                    if constexpr (kBits == 6) {
+                        const u32x6_t packed = {sl.q[f][0], sl.q[f][1], sl.q[f][2], sl.q[f][3], sl.q[f][4], sl.q[f][5]};
+                        if constexpr (kW == kE3m2)
+                            six[f] = __builtin_bit_cast(u32x16_t, __builtin_amdgcn_cvt_scalef32_pk32_bf16_bf6(packed, scl[f]));
+                        else
+                            six[f] = __builtin_bit_cast(u32x16_t, __builtin_amdgcn_cvt_scalef32_pk32_bf16_fp6(packed, scl[f]));
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    u32x4_t xf[MF];
+#pragma unroll
+                    for (int i = 0; i < MF; ++i)
+                        xf[i] = xb[i * 256 + ((kW == kBf16 ? 4 * j + lg : 4 * lg + j) ^ li)];
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) {
+                        const u32x4_t w = operand<kW>(sl.q[f], six[kBits == 6 ? f : 0], scl[f], j);
+#pragma unroll
+                        for (int i = 0; i < MF; ++i)
+                            acc[i][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                __builtin_bit_cast(bf16x8_t, w), __builtin_bit_cast(bf16x8_t, xf[i]), acc[i][f], 0, 0, 0);
+                    }
+                }
+            }
+            // the next phase's activations go to the buffer that the phase before this one read
+            x_store(buf[1 - d], 1 - d);
+            if (d == 1)
+                store_scales(((u0 >> 1) + 1) & 1);
+            if (d == 0)
+                issue_scales((u0 >> 1) + 1);
+            issue(buf[d]);
+            lds_barrier();
+        }
+    }
+
+    // Output fragment (i, f) of block position (wm, wn): lane (li, lg) holds weight rows 4 lg + r for
+    // activation row li.
+    constexpr size_t kXBytes = (size_t)2 * kBuf * 16 + (kScaled ? 2 * kSBuf : 0);
+    constexpr size_t kRedBytes = WK > 1 ? (size_t)8 * MF * NF * 1024 : 0;
+    float2* table = reinterpret_cast<float2*>(smem + (WK == 1 ? 0 : kXBytes > kRedBytes ? kXBytes : kRedBytes));
+    auto emit = [&](const f32x4_t sum, int i, int f) {
+        const int r = (wm * MF + i) * 16 + li, c = wn * NF + f;
+        emit_fragment(out, sum, m0 + r, n0 + c * 16 + 4 * lg, &table[r * (WN * NF) + c]);
+    };
+    if constexpr (WK == 1) {
+#pragma unroll
+        for (int i = 0; i < MF; ++i)
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+                emit(acc[i][f], i, f);
+    } else {
+        f32x4_t* red = reinterpret_cast<f32x4_t*>(smem);               // [position][fragment][wk][lane]
+        const int base = (wm * WN + wn) * MF * NF;
+#pragma unroll
+        for (int i = 0; i < MF; ++i)
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+                red[((base + i * NF + f) * WK + wk) * 64 + lane] = acc[i][f];
+        lds_barrier();
+        for (int e = wk; e < MF * NF; e += WK) {                        // a fragment's sums, in wave order
+            f32x4_t sum = red[(base + e) * WK * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < WK; ++w)
+                sum += red[((base + e) * WK + w) * 64 + lane];
+            emit(sum, e / NF, e % NF);
+        }
+    }
+    if (out.part_val != nullptr) {
+        lds_barrier();
+        if (tid < BM && m0 + tid < m)
+            publish_winner(out, &table[tid * (WN * NF)], WN * NF, m0 + tid, tn);
+    }
+}
+
+template <Kind kW, int WM, int WN, int WK, int MF, int NF>
+hipError_t launch_block(const Args& a, const DeviceInfo& dev, hipStream_t stream)
+{
+    auto kern = gemm_wide_kernel<kW, WM, WN, WK, MF, NF>;
+    static LdsLimit lds_limit;                      // of this kernel instance
+    if (hipError_t e = lds_limit.raise(reinterpret_cast<const void*>(kern), dev.lds_bytes); e != hipSuccess)
+        return e;
+    hipLaunchKernelGGL(kern, dim3(a.tiles_m * a.tiles_n), dim3(kThreads), lds_bytes(kW, WM, WN, WK, MF, NF), stream, a.x, a.q,
+                       a.s, a.n, a.k, a.m, a.ldx, a.ldw, a.tiles_m, a.tiles_n, a.out);
+    return hipGetLastError();
+}
+
+// A block shape with what it took, in microseconds: the first block of a compute unit and every further one
+// as start + step x (steps of 128 along K, whole phases), measured with 256, 512 and 1024 blocks over K = 1024 and
+// 4096.  (Two blocks share a unit where LDS and registers allow.)
+struct Cost {
+    int wm, wn, wk, mf, nf;
+    float first_start, first_step, next_start, next_step;
+};
+
+// The cheapest of `count` shapes for a call (-1: none with at most `max_cols` block columns).
+inline int pick_shape(const Cost* costs, int count, int m, int n, int k, int cus, int max_cols, Args* a)
+{
+    const char* forced_shape = knob("MXFP4_WIDE_SHAPE");            // measurement only
+    const int forced = forced_shape ? atoi(forced_shape) : -1;
+    int best = -1;
+    float best_time = 0;
+    for (int i = 0; i < count; ++i) {
+        const Cost& c = costs[i];
+        const int bm = c.wm * c.mf * 16, bn = c.wn * c.nf * 16;
+        const int tiles_m = (m + bm - 1) / bm, tiles_n = (n + bn - 1) / bn;
+        const int rounds = (int)(((int64_t)tiles_m * tiles_n + cus - 1) / cus);
+        const int steps = ((k + 127) / 128 + c.wk - 1) / c.wk * c.wk;
+        const float time = i == forced ? -1.f
+                                       : c.first_start + c.first_step * steps + (rounds - 1) * (c.next_start + c.next_step * steps);
+        if (tiles_n <= max_cols && (best < 0 || time < best_time)) {
+            best = i;
+            best_time = time;
+            a->tiles_m = tiles_m;
+            a->tiles_n = tiles_n;
+        }
+    }
+    return best;
+}
+
+}  // namespace wide
+}  // namespace mxfp4

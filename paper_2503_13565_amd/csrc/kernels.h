@@ -106,10 +106,10 @@ hipError_t launch_mfma_tile(const GemmArgs& a, const DeviceInfo& dev, int* parts
                             bool tiled = false, const Epilogue* epi = nullptr);
 
 // Many activation rows (a prompt) in blocks that walk K once, and any K % 32 == 0 (gemm_wide.hip):
-// plain, fused and argmax forms on the row-major weights.
+// plain, fused and argmax forms.  `tiled`: a.q / a.s are the tile-major copy (K % 128 == 0).
 bool gemm_wide_can_run(const GemmArgs& a, const DeviceInfo& dev);
 hipError_t launch_gemm_wide(const GemmArgs& a, const DeviceInfo& dev, int* parts_used, hipStream_t stream,
-                            const Epilogue* epi = nullptr);
+                            bool tiled = false, const Epilogue* epi = nullptr);
 
 // The 8-bit (a.q = q8 [N, K]) and 6-bit (a.q = q6) draft formats on the same tiles; shapes as
 // mfma_tile_can_run; `bits` 8 or 6.

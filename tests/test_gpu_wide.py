@@ -83,6 +83,22 @@ def test_largest_blocks(m, n, k):
     assert_gemm_close(gated[:, even.to(DEV) // 2], out_ref, a_out, tag)
 
 
+@pytest.mark.parametrize("m,n,k", [(9, 4100, 4096), (16, 2050, 896), (5, 300, 11008), (17, 17, 128), (33, 1000, 1152),
+                                   (48, 11000, 640), (130, 259, 2048), (300, 5001, 384)])
+def test_tile_major_copy_gives_the_same_bits(m, n, k):
+    w = synth.weights_student_t(n, k, seed=9500 + n, device=DEV)
+    x = synth.activations_outlier_channels(m, k, seed=9600 + m, device=DEV)
+    q, s = binding.mxfp4_direct_cast(w)
+    tw = binding.mxfp4_tile_repack(q, s)
+    ws = torch.empty((max(8, binding.mxfp4_woq_gemm_workspace_bytes(m, n, k)),), dtype=torch.uint8, device=DEV)
+    want = binding.mxfp4_woq_gemm(x, q, s)
+    assert torch.equal(binding.mxfp4_woq_gemm_tiled(x, tw, workspace=ws), want)
+    assert_gemm_close(want[:, :17], *oracle.woq_gemm(synth.to_bits(x), q.cpu()[:17].numpy(), s.cpu()[:17].numpy()))
+    idx, val = binding.mxfp4_woq_gemm_argmax(x, q, s)
+    idx_t, val_t = binding.mxfp4_woq_gemm_tiled_argmax(x, tw)
+    assert torch.equal(idx, idx_t) and torch.equal(val, val_t)
+
+
 def test_nan_stays_in_its_row_and_block():
     # a NaN scale byte poisons its weight row, a NaN activation its own row: also in the rows that
     # repeat past M and N and in the blocks that round K up
