@@ -334,6 +334,33 @@ static int run_gemm(const void* x, int64_t M, int64_t ldx, const void* q, const 
     return MXFP4_OK;
 }
 
+// Whether a product on one of the other formats (`code` as in launch_gemv_reg) takes the blocks of gemm_wide.h
+// (us per launch, before -> blocks):
+//   - beyond 16 rows always (E4M3 12288 x 4096 at 32 rows 33 -> 18, E2M3 28 -> 18);
+//   - the ternary codes from three rows on, where the vector ALUs took passes of four rows (22016 x 4096 at 8 rows 51
+//     -> 16, at 64 401 -> 26), short matrices from four (896 x 4864 at three 6.6 -> 7.1);
+//   - five to 16 rows that do not fit the LDS whole, which ran as passes of four (E4M3 4096 x 11008 at 16 rows
+//     54 -> 15), else while a compute unit has few tiles: 8-bit elements up to four (12288 x 4096 at 8 rows 16.7
+//     -> 14.9, but 22016 x 4096 24.7 -> 26.3), 6-bit up to two and a half (9728 x 896 9.2 -> 7.1, but 12288 x 4096
+//     14.0 -> 14.9), these from three rows on unless N is small too (896 x 4864 at three rows 7.0 -> 7.3).
+static bool fmt_blocks_preferred(const GemmArgs& a, const DeviceInfo& dev, int code)
+{
+    const char* from = knob("MXFP4_WIDE_FROM");                      // measurement only
+    if (!gemm_wide_fmt_can_run(a, dev))
+        return false;
+    if (from)
+        return a.m >= atoi(from);
+    if (a.m > 16)
+        return true;
+    if (code == 2)
+        return a.m >= 4 || (a.m == 3 && a.n >= 1024);
+    if (a.m >= 5 && !mfma_tile_can_run(a, dev))
+        return true;
+    if (code == 8 || code == 24)
+        return a.m >= 5 && a.n <= 64 * dev.cus;
+    return a.n <= 40 * dev.cus && (a.m >= 5 || (a.m >= 3 && a.n >= 2048));
+}
+
 // ---- BF16-weight product ----------------------------------------------------------------
 
 extern "C" size_t mxfp4_bf16_gemm_argmax_workspace_bytes(int64_t M, int64_t N, int64_t K);
@@ -1021,9 +1048,11 @@ static int run_e4m3(const void* x, int64_t M, int64_t ldx, const void* q8, const
     // five and more rows: the matrix-core tiles when a pass's activation rows fit the LDS (up to
     // four rows the vector-ALU kernel is faster: 13.5 against 16.8 us on the 7B qkv shape)
     const bool tiles = !general_only && !reg && a.m >= 5 && aligned(s, 4) && aligned(q8, 16) && mfma_tile_fmt_can_run(a, dev);
-    hipError_t e = reg     ? launch_gemv_reg(a, dev, &parts_used, st, nullptr, 8)
-                   : tiles ? launch_mfma_tile8(a, dev, &parts_used, st)
-                           : launch_e4m3_gemv(a, dev, &parts_used, st);
+    const bool blocks = !general_only && !reg && fmt_blocks_preferred(a, dev, 8);
+    hipError_t e = reg      ? launch_gemv_reg(a, dev, &parts_used, st, nullptr, 8)
+                   : blocks ? launch_gemm_wide_fmt(8, a, dev, &parts_used, st)
+                   : tiles  ? launch_mfma_tile8(a, dev, &parts_used, st)
+                            : launch_e4m3_gemv(a, dev, &parts_used, st);
     if (e != hipSuccess)
         return hip_fail(e, "8-bit product launch");
     if (argmax) {
@@ -1174,8 +1203,10 @@ static int run_e2m3(const void* x, int64_t M, int64_t ldx, const void* q6, const
     // passes of the decode kernel over the weights.  One and two rows: the decode kernel; the
     // tiles (any N) for the shapes it does not take.
     const bool tiles = tiles_ok && (a.m >= 3 || !reg_ok);
-    hipError_t e = tiles ? launch_mfma_tile8(a, dev, &parts_used, st, 6)
-                         : launch_gemv_reg(a, dev, &parts_used, st, nullptr, 6);
+    const bool blocks = fmt_blocks_preferred(a, dev, 6);
+    hipError_t e = blocks  ? launch_gemm_wide_fmt(6, a, dev, &parts_used, st)
+                   : tiles ? launch_mfma_tile8(a, dev, &parts_used, st, 6)
+                           : launch_gemv_reg(a, dev, &parts_used, st, nullptr, 6);
     if (e != hipSuccess)
         return hip_fail(e, "6-bit product launch");
     if (argmax) {
@@ -1388,9 +1419,11 @@ static int run_fmt(int fmt, const void* x, int64_t M, int64_t ldx, const void* q
     const bool tiles = fmt != MXFP4_FMT_T2 && !reg && a.m >= 3 && a.k % 128 == 0 &&
                        aligned(s, 4) && aligned(q, 16) && mfma_tile_fmt_can_run(a, dev);
     const int code = fmt == MXFP4_FMT_E5M2 ? 24 : (fmt == MXFP4_FMT_E3M2 ? 22 : 2);
-    hipError_t e = reg     ? launch_gemv_reg(a, dev, &parts_used, st, nullptr, code)
-                   : tiles ? launch_mfma_tile8(a, dev, &parts_used, st, code)
-                           : launch_mxfmt_gemv(fmt, a, dev, &parts_used, st);
+    const bool blocks = !reg && fmt_blocks_preferred(a, dev, code);
+    hipError_t e = reg      ? launch_gemv_reg(a, dev, &parts_used, st, nullptr, code)
+                   : blocks ? launch_gemm_wide_fmt(code, a, dev, &parts_used, st)
+                   : tiles  ? launch_mfma_tile8(a, dev, &parts_used, st, code)
+                            : launch_mxfmt_gemv(fmt, a, dev, &parts_used, st);
     if (e != hipSuccess)
         return hip_fail(e, "block-format product launch");
     if (argmax) {

@@ -886,6 +886,25 @@ hipError_t launch_rows(const Bf16Args& a, int m0, int r, int nw, int blocks, siz
 
 }  // namespace
 
+// Whether the blocks of gemm_wide.h take a call (us per launch, before -> blocks): always beyond 16 rows (12288 x 4096 at
+// 32 rows 42 -> 27, 4096 x 11008 103 -> 31); nine to 16 rows that the tiles above cannot take (4096 x 11008 at 16
+// rows 53 -> 26, 5001 x 2056 21 -> 9.6) or that leave compute units few of them (4096 x 4096 10.4 -> 9.2, but 12288 x
+// 4096 22.5 -> 24.4); five to eight rows of a matrix of middling size (4096 x 4096 at 8 rows 12.0 -> 8.9, 9728 x 896
+// 10.4 -> 8.2, but 22016 x 4096 37 -> 41, 896 x 4864 9.5 -> 9.5, 4096 x 11008 at five rows 21.6 -> 23.3).
+static bool blocks_preferred(const Bf16Args& a, const DeviceInfo& dev)
+{
+    const char* from = knob("MXFP4_WIDE_FROM");                      // measurement only
+    if (!gemm_wide_bf16_can_run(a, dev))
+        return false;
+    if (from)
+        return a.m >= atoi(from);
+    if (a.m > 16)
+        return true;
+    if (a.m > 8)
+        return !bf16_mfma_can_run(a, dev) || (a.n >= 2048 && a.n <= 20 * dev.cus);
+    return a.m >= 5 && a.n >= 2048 && a.n <= 40 * dev.cus && (a.k <= 8192 || a.m > 6);
+}
+
 // Largest K whose activation copy (one row) fits the LDS.
 bool bf16_can_run(const Bf16Args& a, const DeviceInfo& dev) { return (size_t)a.k * 2 <= (size_t)dev.lds_bytes; }
 
@@ -897,6 +916,8 @@ hipError_t launch_bf16_gemv(const Bf16Args& a, const DeviceInfo& dev, int* parts
     }();
     if (!general_only && bf16_reg_can_run(a, dev))
         return launch_bf16_reg(a, dev, parts_used, stream);
+    if (!general_only && blocks_preferred(a, dev))
+        return launch_gemm_wide_bf16(a, dev, parts_used, stream);
     // Up to eight rows the vector-ALU kernel below is as fast or faster in one pass (7B shapes, µs:
     // 20.1 / 33.0 / 46.3 against 21.2 / 36.8 / 48.6 at four rows, equal at eight); from nine rows on
     // it needs two passes and the matrix cores one.

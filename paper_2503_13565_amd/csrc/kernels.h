@@ -152,6 +152,11 @@ struct Bf16Args {
     int parts;
 };
 bool bf16_can_run(const Bf16Args& a, const DeviceInfo& dev);
+// The blocks of gemm_wide.h on BF16 weights and on the other formats (`code` as in launch_gemv_reg).
+bool gemm_wide_bf16_can_run(const Bf16Args& a, const DeviceInfo& dev);
+hipError_t launch_gemm_wide_bf16(const Bf16Args& a, const DeviceInfo& dev, int* parts_used, hipStream_t stream);
+bool gemm_wide_fmt_can_run(const GemmArgs& a, const DeviceInfo& dev);
+hipError_t launch_gemm_wide_fmt(int code, const GemmArgs& a, const DeviceInfo& dev, int* parts_used, hipStream_t stream);
 hipError_t launch_bf16_gemv(const Bf16Args& a, const DeviceInfo& dev, int* parts_used, hipStream_t stream);
 
 // The decode step (one or two activation rows) on the tile-major tensors (a.q = q_tiled, a.s =

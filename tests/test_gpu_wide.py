@@ -1,7 +1,8 @@
 """Parity of the block kernel for many activation rows and for K that is no multiple of 128
 (csrc/gemm_wide.hip; arXiv 2503.13565, section 3.4.3): plain, fused and pick forms against the CPU oracle
 at the edges of its blocks, one case at least per block shape."""
-import numpy as np
+import functools
+
 import pytest
 import torch
 
@@ -97,6 +98,54 @@ def test_tile_major_copy_gives_the_same_bits(m, n, k):
     idx, val = binding.mxfp4_woq_gemm_argmax(x, q, s)
     idx_t, val_t = binding.mxfp4_woq_gemm_tiled_argmax(x, tw)
     assert torch.equal(idx, idx_t) and torch.equal(val, val_t)
+
+
+FORMATS = {"e4m3": (oracle.e4m3_woq_gemm, binding.mxfp4_e4m3_direct_cast, binding.mxfp4_e4m3_woq_gemm,
+                    binding.mxfp4_e4m3_woq_gemm_argmax),
+           "e2m3": (oracle.e2m3_woq_gemm, binding.mxfp4_e2m3_direct_cast, binding.mxfp4_e2m3_woq_gemm,
+                    binding.mxfp4_e2m3_woq_gemm_argmax)}
+for _name, _id in (("e5m2", binding.FMT_E5M2), ("e3m2", binding.FMT_E3M2), ("t2", binding.FMT_T2)):
+    FORMATS[_name] = tuple(functools.partial(f, _id) for f in (
+        oracle.mx_woq_gemm, binding.mxfp4_fmt_direct_cast, binding.mxfp4_fmt_woq_gemm, binding.mxfp4_fmt_woq_gemm_argmax))
+
+
+@pytest.mark.parametrize("fmt", sorted(FORMATS))
+@pytest.mark.parametrize("m,n,k", [(3, 2050, 128), (5, 17, 1408), (8, 12288, 256), (16, 900, 5632), (17, 4099, 384), (33, 1000, 2176),
+                                   (64, 9000, 128), (70, 5001, 256), (129, 259, 1152), (200, 8200, 256), (300, 16000, 128)])
+def test_other_formats(fmt, m, n, k):
+    ref, cast, product, pick = FORMATS[fmt]
+    tag = "%s M=%d N=%d K=%d" % (fmt, m, n, k)
+    print(tag, flush=True)
+    w = synth.weights_student_t(n, k, seed=9700 + n, device=DEV)
+    x = synth.activations_outlier_channels(m, k, seed=9800 + m, device=DEV)
+    q, s = cast(w)
+    y_ref, a_ref = ref(synth.to_bits(x), q.cpu().numpy(), s.cpu().numpy())
+    y = product(x, q, s)
+    idx, val = pick(x, q, s)
+    torch.cuda.synchronize()
+    assert_gemm_close(y, y_ref, a_ref, tag)
+    assert_argmax_ok(idx, val, y_ref, a_ref, tag)
+    s[n - 1, k // 32 - 1] = 255                             # a NaN block poisons its weight row only
+    nan = torch.isnan(product(x, q, s))
+    assert bool(nan[:, n - 1].all()) and not bool(nan[:, :n - 1].any()), tag
+
+
+@pytest.mark.parametrize("m,n,k", [(5, 2050, 8), (7, 5001, 2056), (9, 259, 1000), (16, 4100, 11008), (17, 33, 40), (40, 1000, 136),
+                                   (64, 9000, 120), (70, 5001, 264), (129, 259, 1152), (200, 8200, 248), (300, 16000, 128)])
+def test_unquantised_weights(m, n, k):
+    tag = "BF16 M=%d N=%d K=%d" % (m, n, k)
+    print(tag, flush=True)
+    wide = synth.weights_student_t(n, k + 16, seed=9900 + n, device=DEV)
+    x = synth.activations_outlier_channels(m, k, seed=9950 + m, device=DEV)
+    for w in (wide[:, :k], wide[:, :k].contiguous()):       # rows farther apart than K, and not
+        y_ref, a_ref = oracle.bf16_gemm(synth.to_bits(x), synth.to_bits(w.contiguous()))
+        y = binding.mxfp4_bf16_gemm(x, w)
+        idx, val = binding.mxfp4_bf16_gemm_argmax(x, w)
+        torch.cuda.synchronize()
+        assert_gemm_close(y, y_ref, a_ref, tag)
+        assert_argmax_ok(idx, val, y_ref, a_ref, tag)
+    wide[:, k:] = float("nan")                              # what lies between the rows is not read into them
+    assert torch.equal(binding.mxfp4_bf16_gemm(x, wide[:, :k]), y), tag
 
 
 def test_nan_stays_in_its_row_and_block():
