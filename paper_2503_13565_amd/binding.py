@@ -6,6 +6,7 @@ memory and the current stream.  There is no fallback: if the library has not bee
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 from typing import Optional, Tuple
@@ -184,12 +185,27 @@ def _check(rc: int) -> None:
         raise Mxfp4Error(rc, load().mxfp4_last_error().decode())
 
 
-def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+# What surrounds a call costs more host time than the call's checks and as much as its launch, and most of the
+# products here are shorter on the device than that.  So addresses go to ctypes as plain integers, the stream is
+# asked for as the integer it is, and the device is switched only where another one is current (one product
+# 10.9 -> 7.1 us of host time; the launch itself is 3.5 of them).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+_stay = contextlib.nullcontext()
 
 
-def _ptr(t: Optional[torch.Tensor]) -> ctypes.c_void_p:
-    return ctypes.c_void_p(0 if t is None else t.data_ptr())
+def _on(device: torch.device):
+    """Context in which ``device`` is the current device."""
+    return _stay if device.index == _current_device() else torch.cuda.device(device)
+
+
+def _stream() -> int:
+    """The current stream of the current device."""
+    return torch.cuda.current_stream().cuda_stream if _raw_stream is None else _raw_stream(_current_device())
+
+
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
 def _dev(t: torch.Tensor) -> None:
@@ -215,7 +231,7 @@ def mxfp4_direct_cast(w: torch.Tensor, q: Optional[torch.Tensor] = None,
     if s is None:
         s = torch.empty((n, k // 32), dtype=torch.uint8, device=w.device)
     ldw = w.stride(0) if n > 1 else max(k, 1)
-    with torch.cuda.device(w.device):
+    with _on(w.device):
         fn = load().mxfp4_direct_cast_bits if integer_rule else load().mxfp4_direct_cast
         _check(fn(_ptr(w), n, k, ldw, _ptr(q), _ptr(s), _stream()))
     return q, s
@@ -226,7 +242,7 @@ def mxfp4_dequant(q: torch.Tensor, s: torch.Tensor, hw_convert: bool = False) ->
     n, k = q.shape[0], q.shape[1] * 2
     w = torch.empty((n, k), dtype=torch.bfloat16, device=q.device)
     fn = load().mxfp4_dequant_hwcvt if hw_convert else load().mxfp4_dequant
-    with torch.cuda.device(q.device):
+    with _on(q.device):
         _check(fn(_ptr(q), _ptr(s), n, k, _ptr(w), k, _stream()))
     return w
 
@@ -253,7 +269,7 @@ def mxfp4_woq_gemm(x: torch.Tensor, q: torch.Tensor, s: torch.Tensor, y: Optiona
     if y is None:
         y = torch.empty((m, n), dtype=torch.bfloat16, device=x.device)
     ldy = y.stride(0) if m > 1 else n
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         if workspace is None:
             _check(load().mxfp4_woq_gemm_path(_ptr(x), m, ldx, _ptr(q), _ptr(s), n, k, _ptr(y), ldy, path,
                                              _stream()))
@@ -286,7 +302,7 @@ def mxfp4_woq_gemm_argmax(x: torch.Tensor, q: torch.Tensor, s: torch.Tensor,
         val = torch.empty((m,), dtype=torch.float32, device=x.device)
     else:
         idx, val = out
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(load().mxfp4_woq_gemm_argmax_path(_ptr(x), m, ldx, _ptr(q), _ptr(s), n, k, _ptr(idx), _ptr(val),
                                                 _ptr(workspace), workspace.numel() * workspace.element_size(),
                                                 path, _stream()))
@@ -302,7 +318,7 @@ def mxfp4_woq_gemm_argmax_noalloc(x: torch.Tensor, q: torch.Tensor, s: torch.Ten
     if (idx.dtype != torch.int32 or val.dtype != torch.float32 or idx.shape != (m,) or val.shape != (m,)
             or not idx.is_contiguous() or not val.is_contiguous()):
         raise ValueError("out must be (int32 [M], float32 [M]), contiguous")
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(load().mxfp4_woq_gemm_argmax_noalloc(_ptr(x), m, ldx, _ptr(q), _ptr(s), n, k, _ptr(idx), _ptr(val),
                                                     _stream()))
     return idx, val
@@ -325,7 +341,7 @@ def mxfp4_bf16_gemm(x: torch.Tensor, w: torch.Tensor, y: Optional[torch.Tensor] 
     m, n, k, ldx, ldw = _bf16_shapes(x, w)
     if y is None:
         y = torch.empty((m, n), dtype=torch.bfloat16, device=x.device)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(load().mxfp4_bf16_gemm(_ptr(x), m, ldx, _ptr(w), n, k, ldw, _ptr(y),
                                      y.stride(0) if m > 1 else n, _stream()))
     return y
@@ -348,7 +364,7 @@ def mxfp4_bf16_gemm_argmax(x: torch.Tensor, w: torch.Tensor, workspace: Optional
         val = torch.empty((m,), dtype=torch.float32, device=x.device)
     else:
         idx, val = out
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(load().mxfp4_bf16_gemm_argmax(_ptr(x), m, ldx, _ptr(w), n, k, ldw, _ptr(idx), _ptr(val),
                                             _ptr(workspace), workspace.numel() * workspace.element_size(),
                                             _stream()))
@@ -372,7 +388,7 @@ def mxfp4_woq_gemm_verify(x: torch.Tensor, q: torch.Tensor, s: torch.Tensor, dra
     m, n, k, ldx = _gemm_shapes(x, q, s)
     workspace, accept, idx, val = _verify_buffers(x, m, draft, mxfp4_woq_gemm_argmax_workspace_bytes(m, n, k),
                                                   workspace)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(load().mxfp4_woq_gemm_verify(_ptr(x), m, ldx, _ptr(q), _ptr(s), n, k, _ptr(draft), _ptr(accept),
                                            _ptr(idx), _ptr(val), _ptr(workspace),
                                            workspace.numel() * workspace.element_size(), _stream()))
@@ -388,7 +404,7 @@ def mxfp4_e4m3_direct_cast(w: torch.Tensor, integer_rule: bool = False) -> Tuple
     q8 = torch.empty((n, k), dtype=torch.uint8, device=w.device)
     s = torch.empty((n, k // 32), dtype=torch.uint8, device=w.device)
     fn = load().mxfp4_e4m3_direct_cast_bits if integer_rule else load().mxfp4_e4m3_direct_cast
-    with torch.cuda.device(w.device):
+    with _on(w.device):
         _check(fn(_ptr(w), n, k, w.stride(0) if n > 1 else k, _ptr(q8), _ptr(s), _stream()))
     return q8, s
 
@@ -397,7 +413,7 @@ def mxfp4_e4m3_dequant(q8: torch.Tensor, s: torch.Tensor) -> torch.Tensor:
     _dev(q8)
     n, k = q8.shape
     w = torch.empty((n, k), dtype=torch.bfloat16, device=q8.device)
-    with torch.cuda.device(q8.device):
+    with _on(q8.device):
         _check(load().mxfp4_e4m3_dequant(_ptr(q8), _ptr(s), n, k, _ptr(w), k, _stream()))
     return w
 
@@ -420,7 +436,7 @@ def mxfp4_e4m3_woq_gemm(x: torch.Tensor, q8: torch.Tensor, s: torch.Tensor,
     m, n, k, ldx = _e4m3_shapes(x, q8, s)
     if y is None:
         y = torch.empty((m, n), dtype=torch.bfloat16, device=x.device)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(load().mxfp4_e4m3_woq_gemm(_ptr(x), m, ldx, _ptr(q8), _ptr(s), n, k, _ptr(y),
                                          y.stride(0) if m > 1 else n, _stream()))
     return y
@@ -439,7 +455,7 @@ def mxfp4_e4m3_woq_gemm_argmax(x: torch.Tensor, q8: torch.Tensor, s: torch.Tenso
         val = torch.empty((m,), dtype=torch.float32, device=x.device)
     else:
         idx, val = out
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(load().mxfp4_e4m3_woq_gemm_argmax(_ptr(x), m, ldx, _ptr(q8), _ptr(s), n, k, _ptr(idx), _ptr(val),
                                                 _ptr(workspace), workspace.numel() * workspace.element_size(),
                                                 _stream()))
@@ -455,7 +471,7 @@ def mxfp4_e2m3_direct_cast(w: torch.Tensor, integer_rule: bool = False) -> Tuple
     q6 = torch.empty((n, k // 32 * 24), dtype=torch.uint8, device=w.device)
     s = torch.empty((n, k // 32), dtype=torch.uint8, device=w.device)
     fn = load().mxfp4_e2m3_direct_cast_bits if integer_rule else load().mxfp4_e2m3_direct_cast
-    with torch.cuda.device(w.device):
+    with _on(w.device):
         _check(fn(_ptr(w), n, k, w.stride(0) if n > 1 else k, _ptr(q6), _ptr(s), _stream()))
     return q6, s
 
@@ -464,7 +480,7 @@ def mxfp4_e2m3_dequant(q6: torch.Tensor, s: torch.Tensor) -> torch.Tensor:
     _dev(q6)
     n, k = s.shape[0], s.shape[1] * 32
     w = torch.empty((n, k), dtype=torch.bfloat16, device=q6.device)
-    with torch.cuda.device(q6.device):
+    with _on(q6.device):
         _check(load().mxfp4_e2m3_dequant(_ptr(q6), _ptr(s), n, k, _ptr(w), k, _stream()))
     return w
 
@@ -487,7 +503,7 @@ def mxfp4_e2m3_woq_gemm(x: torch.Tensor, q6: torch.Tensor, s: torch.Tensor,
     m, n, k, ldx = _e2m3_shapes(x, q6, s)
     if y is None:
         y = torch.empty((m, n), dtype=torch.bfloat16, device=x.device)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(load().mxfp4_e2m3_woq_gemm(_ptr(x), m, ldx, _ptr(q6), _ptr(s), n, k, _ptr(y),
                                          y.stride(0) if m > 1 else n, _stream()))
     return y
@@ -506,7 +522,7 @@ def mxfp4_e2m3_woq_gemm_argmax(x: torch.Tensor, q6: torch.Tensor, s: torch.Tenso
         val = torch.empty((m,), dtype=torch.float32, device=x.device)
     else:
         idx, val = out
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(load().mxfp4_e2m3_woq_gemm_argmax(_ptr(x), m, ldx, _ptr(q6), _ptr(s), n, k, _ptr(idx), _ptr(val),
                                                 _ptr(workspace), workspace.numel() * workspace.element_size(),
                                                 _stream()))
@@ -534,7 +550,7 @@ def mxfp4_woq_gemm_t(x: torch.Tensor, q: torch.Tensor, s: torch.Tensor, y: Optio
     if workspace is None:
         workspace = torch.empty((max(mxfp4_woq_gemm_t_workspace_bytes(m, n, k), 4),), dtype=torch.uint8,
                                 device=x.device)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(load().mxfp4_woq_gemm_t(_ptr(x), m, x.stride(0) if m > 1 else n, _ptr(q), _ptr(s), n, k, _ptr(y),
                                       y.stride(0) if m > 1 else k, _ptr(workspace),
                                       workspace.numel() * workspace.element_size(), _stream()))
@@ -558,7 +574,7 @@ def mxfp4_fmt_direct_cast(fmt: int, w: torch.Tensor, integer_rule: bool = False)
     q = torch.empty((n, k // 32 * max(mxfp4_fmt_block_bytes(fmt), 1)), dtype=torch.uint8, device=w.device)
     s = torch.empty((n, k // 32), dtype=torch.uint8, device=w.device)
     fn = load().mxfp4_fmt_direct_cast_bits if integer_rule else load().mxfp4_fmt_direct_cast
-    with torch.cuda.device(w.device):
+    with _on(w.device):
         _check(fn(fmt, _ptr(w), n, k, w.stride(0) if n > 1 else k, _ptr(q), _ptr(s), _stream()))
     return q, s
 
@@ -567,7 +583,7 @@ def mxfp4_fmt_dequant(fmt: int, q: torch.Tensor, s: torch.Tensor) -> torch.Tenso
     _dev(q)
     n, k = s.shape[0], s.shape[1] * 32
     w = torch.empty((n, k), dtype=torch.bfloat16, device=q.device)
-    with torch.cuda.device(q.device):
+    with _on(q.device):
         _check(load().mxfp4_fmt_dequant(fmt, _ptr(q), _ptr(s), n, k, _ptr(w), k, _stream()))
     return w
 
@@ -591,7 +607,7 @@ def mxfp4_fmt_woq_gemm(fmt: int, x: torch.Tensor, q: torch.Tensor, s: torch.Tens
     m, n, k, ldx = _fmt_shapes(fmt, x, q, s)
     if y is None:
         y = torch.empty((m, n), dtype=torch.bfloat16, device=x.device)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(load().mxfp4_fmt_woq_gemm(fmt, _ptr(x), m, ldx, _ptr(q), _ptr(s), n, k, _ptr(y),
                                         y.stride(0) if m > 1 else n, _stream()))
     return y
@@ -610,7 +626,7 @@ def mxfp4_fmt_woq_gemm_argmax(fmt: int, x: torch.Tensor, q: torch.Tensor, s: tor
         val = torch.empty((m,), dtype=torch.float32, device=x.device)
     else:
         idx, val = out
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(load().mxfp4_fmt_woq_gemm_argmax(fmt, _ptr(x), m, ldx, _ptr(q), _ptr(s), n, k, _ptr(idx), _ptr(val),
                                                _ptr(workspace), workspace.numel() * workspace.element_size(),
                                                _stream()))
@@ -638,7 +654,7 @@ def mxfp4_woq_gemm_fused(x: torch.Tensor, q: torch.Tensor, s: torch.Tensor, bias
         y = torch.empty((m, c), dtype=torch.bfloat16, device=x.device)
     ldy = y.stride(0) if m > 1 else c
     ldr = (residual.stride(0) if m > 1 else c) if residual is not None else 0
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(load().mxfp4_woq_gemm_fused(
             _ptr(x), m, ldx, _ptr(q), _ptr(s), n, k, _ptr(bias), act, _ptr(residual), ldr, _ptr(y), ldy,
             _ptr(workspace), workspace.numel() * workspace.element_size() if workspace is not None else 0, path,
@@ -728,7 +744,7 @@ class GemmGroup:
 
     def chain_reset(self) -> None:
         """Prepare the chain workspace again (after a wait that was given up)."""
-        with torch.cuda.device(self.device):
+        with _on(self.device):
             _check(load().mxfp4_woq_gemm_chain_init(_ptr(self.chain_ws), self.chain_ws.numel(), _stream()))
 
     def chain_status(self) -> int:
@@ -739,11 +755,11 @@ class GemmGroup:
         if self.count == 0:
             return
         if self.chained:
-            with torch.cuda.device(self.device):
+            with _on(self.device):
                 _check(load().mxfp4_woq_gemm_chain(self._descs, self.count, _ptr(self.chain_ws),
                                                    self.chain_ws.numel(), ctypes.byref(self._opts), _stream()))
             return
-        with torch.cuda.device(self.device):
+        with _on(self.device):
             _check(load().mxfp4_woq_gemm_grouped(
                 self._descs, self.count, _ptr(self.workspace),
                 self.workspace.numel() if self.workspace is not None else 0, _stream()))
@@ -763,7 +779,7 @@ def mxfp4_tile_repack(q: torch.Tensor, s: torch.Tensor) -> TiledWeights:
     n, k = q.shape[0], q.shape[1] * 2
     qt = torch.empty((int(load().mxfp4_tile_repack_q_bytes(n, k)),), dtype=torch.uint8, device=q.device)
     st = torch.empty((int(load().mxfp4_tile_repack_s_bytes(n, k)),), dtype=torch.uint8, device=q.device)
-    with torch.cuda.device(q.device):
+    with _on(q.device):
         _check(load().mxfp4_tile_repack(_ptr(q), _ptr(s), n, k, _ptr(qt), _ptr(st), _stream()))
     return TiledWeights(qt, st, n, k)
 
@@ -784,7 +800,7 @@ def mxfp4_woq_gemm_tiled(x: torch.Tensor, w: TiledWeights, y: Optional[torch.Ten
     if y is None:
         y = torch.empty((m, n), dtype=torch.bfloat16, device=x.device)
     ldy = y.stride(0) if m > 1 else n
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         if workspace is None:
             _check(load().mxfp4_woq_gemm_tiled(_ptr(x), m, ldx, _ptr(w.q), _ptr(w.s), n, k, _ptr(y), ldy, _stream()))
         else:
@@ -810,7 +826,7 @@ def mxfp4_woq_gemm_tiled_fused(x: torch.Tensor, w: TiledWeights, bias: Optional[
         y = torch.empty((m, c), dtype=torch.bfloat16, device=x.device)
     ldy = y.stride(0) if m > 1 else c
     ldr = (residual.stride(0) if m > 1 else c) if residual is not None else 0
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(load().mxfp4_woq_gemm_tiled_fused(_ptr(x), m, ldx, _ptr(w.q), _ptr(w.s), n, k, _ptr(bias), act,
                                                 _ptr(residual), ldr, _ptr(y), ldy, _stream()))
     return y
@@ -828,7 +844,7 @@ def mxfp4_woq_gemm_tiled_argmax(x: torch.Tensor, w: TiledWeights, workspace: Opt
         val = torch.empty((m,), dtype=torch.float32, device=x.device)
     else:
         idx, val = out
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(load().mxfp4_woq_gemm_tiled_argmax(_ptr(x), m, ldx, _ptr(w.q), _ptr(w.s), n, k, _ptr(idx),
                                                  _ptr(val), _ptr(workspace),
                                                  workspace.numel() * workspace.element_size(), _stream()))
@@ -840,7 +856,7 @@ def mxfp4_woq_gemm_tiled_verify(x: torch.Tensor, w: TiledWeights, draft: Optiona
     m, n, k, ldx = _tiled_shapes(x, w)
     workspace, accept, idx, val = _verify_buffers(x, m, draft, mxfp4_woq_gemm_argmax_workspace_bytes(m, n, k),
                                                   workspace)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(load().mxfp4_woq_gemm_tiled_verify(_ptr(x), m, ldx, _ptr(w.q), _ptr(w.s), n, k, _ptr(draft),
                                                  _ptr(accept), _ptr(idx), _ptr(val), _ptr(workspace),
                                                  workspace.numel() * workspace.element_size(), _stream()))
@@ -853,7 +869,7 @@ def mxfp4_bf16_gemm_verify(x: torch.Tensor, w: torch.Tensor, draft: Optional[tor
     m, n, k, ldx, ldw = _bf16_shapes(x, w)
     workspace, accept, idx, val = _verify_buffers(x, m, draft, mxfp4_bf16_gemm_argmax_workspace_bytes(m, n, k),
                                                   workspace)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(load().mxfp4_bf16_gemm_verify(_ptr(x), m, ldx, _ptr(w), n, k, ldw, _ptr(draft), _ptr(accept),
                                             _ptr(idx), _ptr(val), _ptr(workspace),
                                             workspace.numel() * workspace.element_size(), _stream()))
@@ -861,10 +877,10 @@ def mxfp4_bf16_gemm_verify(x: torch.Tensor, w: torch.Tensor, draft: Optional[tor
 
 
 def mxfp4_diag_stream_read(src: torch.Tensor, sink: torch.Tensor) -> None:
-    with torch.cuda.device(src.device):
+    with _on(src.device):
         _check(load().mxfp4_diag_stream_read(_ptr(src), src.numel() * src.element_size(), _ptr(sink), _stream()))
 
 
 def mxfp4_diag_stream_copy(src: torch.Tensor, dst: torch.Tensor) -> None:
-    with torch.cuda.device(src.device):
+    with _on(src.device):
         _check(load().mxfp4_diag_stream_copy(_ptr(src), _ptr(dst), src.numel() * src.element_size(), _stream()))
