@@ -933,11 +933,14 @@ hipError_t launch_bf16_gemv(const Bf16Args& a, const DeviceInfo& dev, int* parts
     int first_blocks = 0;
     for (int m0 = 0; m0 < a.m;) {
         const int left = a.m - m0;
-        // the narrowest pass that takes all remaining rows (a ragged pass repeats its last row)
-        int mt = left > 4 ? 8 : (left > 2 ? 4 : (left > 1 ? 2 : 1));
-        if (mt == 8 && left <= 6 && (size_t)8 * a.k * 2 > (size_t)dev.lds_bytes &&
-            (size_t)6 * a.k * 2 <= (size_t)dev.lds_bytes)
-            mt = 6;                                                 // five or six rows that fit where eight do not
+        // As many rows as are left, up to eight: every row of a pass costs its share of the LDS reads and the
+        // dot products (five rows in a pass of eight before: 12288 x 4096 21.9 -> 20.5 us, 22016 x 4096 36.3 ->
+        // 34.1, 9728 x 896 at three rows 7.8 -> 6.9).  Rows that do not fit the LDS whole keep the widths of
+        // the phased kernel.
+        int mt = left > 8 ? 8 : left;
+        if ((size_t)mt * a.k * 2 > (size_t)dev.lds_bytes)
+            mt = left > 4 ? (left <= 6 && (size_t)6 * a.k * 2 <= (size_t)dev.lds_bytes ? 6 : 8)
+                          : (left > 2 ? 4 : (left > 1 ? 2 : 1));
         // The rows of the pass do not fit the LDS whole: K in phases, still one pass over the weights,
         // when a wave's rows fit its 64 lanes (one workgroup of 16 waves per compute unit).
         if (mt >= 2 && (size_t)mt * a.k * 2 > (size_t)dev.lds_bytes && !general_only) {
@@ -968,10 +971,14 @@ hipError_t launch_bf16_gemv(const Bf16Args& a, const DeviceInfo& dev, int* parts
             }
         }
         while (mt > 1 && (size_t)mt * a.k * 2 > (size_t)dev.lds_bytes)
-            mt = mt == 6 ? 4 : mt >> 1;
+            mt = mt > 4 ? 4 : mt >> 1;
         const size_t lds = (size_t)mt * a.k * 2 < 256 ? 256 : (size_t)mt * a.k * 2;   // the argmax combine needs a few bytes
         int per_cu = (int)((size_t)dev.lds_bytes / lds);
         per_cu = per_cu < 1 ? 1 : (per_cu > 4 ? 4 : per_cu);
+        // five and more long rows: two workgroups of eight waves (12288 x 4096 at five rows 20.5 us, 21.6 with
+        // three of four; 9728 x 896 8.5 against 8.2)
+        if (mt > 4 && a.k >= 2048 && per_cu > 2)
+            per_cu = 2;
         // 16 waves per CU: larger workgroups when the activation copy leaves room for fewer of them
         const int nw = per_cu >= 3 ? 4 : (per_cu == 2 ? 8 : 16);
         int blocks = (n_groups + nw - 1) / nw;
@@ -989,8 +996,17 @@ hipError_t launch_bf16_gemv(const Bf16Args& a, const DeviceInfo& dev, int* parts
         case 8:
             e = launch_rows<8>(a, m0, r, nw, blocks, lds, dev.lds_bytes, stream);
             break;
+        case 7:
+            e = launch_rows<7>(a, m0, r, nw, blocks, lds, dev.lds_bytes, stream);
+            break;
         case 6:
             e = launch_rows<6>(a, m0, r, nw, blocks, lds, dev.lds_bytes, stream);
+            break;
+        case 5:
+            e = launch_rows<5>(a, m0, r, nw, blocks, lds, dev.lds_bytes, stream);
+            break;
+        case 3:
+            e = launch_rows<3>(a, m0, r, nw, blocks, lds, dev.lds_bytes, stream);
             break;
         case 4:
             e = launch_rows<4>(a, m0, r, nw, blocks, lds, dev.lds_bytes, stream);

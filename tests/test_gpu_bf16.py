@@ -170,3 +170,12 @@ def test_errors_are_reported():
     assert lib.mxfp4_bf16_gemm(x.data_ptr(), 1, 64, w.data_ptr(), 4, 60, 64, w.data_ptr(), 4, st) == 2
     assert lib.mxfp4_bf16_gemm(x.data_ptr(), 1, 64, w.data_ptr() + 2, 4, 64, 64, w.data_ptr(), 4, st) == 3
     assert lib.mxfp4_bf16_gemm_argmax(x.data_ptr(), 1, 64, w.data_ptr(), 4, 64, 64, w.data_ptr(), None, None, 0, st) == 4
+
+
+@pytest.mark.parametrize("m", [3, 5, 6, 7, 10])
+@pytest.mark.parametrize("n,k", [(12, 16), (8201, 520), (10300, 2056), (12300, 4096), (64, 11008), (2050, 13104)])
+def test_odd_row_counts(n, k, m):
+    # passes exactly as wide as the rows that are left, one and two weight rows per group, workgroups of four,
+    # eight and sixteen waves, the last pass narrower than the first
+    run_case(synth.weights_student_t(n, k, seed=40 + n), synth.activations_outlier_channels(m, k, seed=41 + m),
+             "BF16 odd rows N=%d K=%d M=%d" % (n, k, m))
