@@ -25,9 +25,10 @@ namespace mxfp4 {
 
 namespace {
 
-// The kernel arguments are 15 dwords of plain scalars so that they can be preloaded into scalar
-// registers when the wave starts (the build passes -amdgpu-kernarg-preload-count=16): every wave
-// needs them before it can send its first load.  Measured per launch: a second 64-byte line of
+// The kernel arguments are plain scalars so that they can be preloaded into scalar
+// registers when the wave starts (the build passes -amdgpu-kernarg-preload-count=16; fourteen dwords are): every wave
+// needs them before it can send its first load, the grid's size too, which the kernel would else
+// fetch from memory in front of its first weights (12288 x 4096 7.08 -> 6.90 us, 4096 x 11008 6.85 -> 6.65).  Measured per launch: a second 64-byte line of
 // arguments costs 0.4 us, fetching one line instead of having it preloaded 0.15 us.
 struct RegArgs {
     const uint16_t* x;
@@ -38,6 +39,7 @@ struct RegArgs {
     int n, k, m, m0;
     int ldx, ldy;
     int parts;           // > 0: argmax form
+    int blocks;          // gridDim.x (the built-in value comes from memory, behind the first load's address)
 };
 
 // MT activation rows, STEPS (even) steps of 64 blocks cover K (the last ones may be ragged or
@@ -65,6 +67,13 @@ typedef __attribute__((ext_vector_type(6))) unsigned int u32x6_t;
 typedef __attribute__((ext_vector_type(16))) unsigned int u32x16_t;
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
 
+// The gate alone, no bias and no residual: no loads for them (two broadcast loads per weight row behind empty
+// descriptors are half as many load instructions again as a K = 4096 row's weights and scales).  Used at two steps
+// only: 22016 x 4096 with the gate 10.9 -> 10.5 us, but 57344 x 8192 39.4 -> 40.6.
+struct GateOnly {
+    int act;
+};
+
 template <int MT, int R, int STEPS, int D, int NW, bool kRagged, class Epi, int kFmt = 4>
 __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
 {
@@ -79,6 +88,7 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
     // kernel a block's 8 bytes of weights pull 64 bytes of activations out of the LDS.
     constexpr int kBlkBytes = kBits == 8 ? 32 : (kBits == 6 ? 24 : (kBits == 2 ? 8 : 16));
     constexpr bool kEpi = !__is_same(Epi, NoEpilogue);
+    constexpr bool kOperands = __is_same(Epi, Epilogue);
     const int m0 = a.m0;
     static_assert(STEPS % D == 0, "the buffer of a step must be known at compile time");
     constexpr int T = NW * 64;
@@ -95,8 +105,7 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
     u32x4_t xl[MT][XPR];
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
-        const int msrc = min(m0 + m, a.m - 1);                       // ragged M: repeat the last row
-        const u32x4_t* xp = reinterpret_cast<const u32x4_t*>(a.x + (int64_t)msrc * a.ldx);
+        const u32x4_t* xp = reinterpret_cast<const u32x4_t*>(a.x + (int64_t)(m0 + m) * a.ldx);    // (a pass has all its rows)
 #pragma unroll
         for (int i = 0; i < XPR; ++i)
             xl[m][i] = xp[min(tid + i * T, chunks - 1)];
@@ -115,7 +124,7 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
     uint8_t* stage = smem + (size_t)MT * 4 * xrow * 16 + 64 + (size_t)wave * (R * 1536);
     const int q_row_bytes = (a.k >> 5) * kBlkBytes;
     const bool argmax = a.parts > 0;
-    const int G = gridDim.x, b = blockIdx.x;
+    const int G = kBits == 4 ? a.blocks : (int)gridDim.x, b = blockIdx.x;    // (no gain in the other formats)
     bool gated = false;
     if constexpr (kEpi)
         gated = epi.act == MXFP4_ACT_SWIGLU;
@@ -135,7 +144,7 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
     // each, behind descriptors that cover nothing when the operand is absent) and kept with its
     // slot, so the flush has nothing to wait for.
     Epilogue ep{nullptr, nullptr, 0, 0};
-    if constexpr (kEpi)
+    if constexpr (kOperands)
         ep = epi;
     float bias_s = 0.f, res_s[MT];
 #pragma unroll
@@ -201,6 +210,10 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
 #pragma unroll
     for (int d = 0; d < D; ++d)
         issue(grp, d, d, nblk);
+    // The operands' addresses are not preloaded: fetched here, while the activations are on their way, and not in
+    // the first trip.
+    if constexpr (kOperands)
+        asm volatile("" ::"s"(ep.bias), "s"(ep.residual), "s"(ep.ldr));
 
 #pragma unroll
     for (int m = 0; m < MT; ++m)
@@ -316,7 +329,7 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
         if constexpr (kBits != 4)
             asm volatile("" : "+s"(nb));
         uint32_t bias_l[R], res_l[R][MT];
-        if constexpr (kEpi) {
+        if constexpr (kOperands) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const int row = grp * R + r;                // past N: outside the descriptors, reads zero
@@ -497,7 +510,7 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
             }
             if (!argmax)
                 rowv = (lane == slots + r) ? row : rowv;
-            if constexpr (kEpi) {
+            if constexpr (kOperands) {
                 bias_s = (lane == slots + r) ? bf16_bits_to_f32(bias_l[r]) : bias_s;
 #pragma unroll
                 for (int m = 0; m < MT; ++m)
@@ -549,33 +562,41 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
 
 template <int MT, int R, int STEPS, int D, int NW, bool kRagged>
 __global__ __launch_bounds__(NW * 64) void gemv_reg_kernel(const uint16_t* x, const uint8_t* q, const uint8_t* s,
-                                                           void* out, int n, int k, int m, int m0, int ldx,
-                                                           int ldy, int parts)
+                                                           void* out, int n, int k, int m0, int ldx, int blocks,
+                                                           int parts, int m, int ldy)
 {
-    gemv_reg_body<MT, R, STEPS, D, NW, kRagged>(RegArgs{x, q, s, out, n, k, m, m0, ldx, ldy, parts}, NoEpilogue{});
+    gemv_reg_body<MT, R, STEPS, D, NW, kRagged>(RegArgs{x, q, s, out, n, k, m, m0, ldx, ldy, parts, blocks}, NoEpilogue{});
 }
 
 // The fused form: `act` decides which rows a wave starts with, so it takes the last preloaded
 // slot; the other epilogue arguments come behind and are first needed when the first trip starts.
 template <int MT, int R, int STEPS, int D, int NW, bool kRagged>
 __global__ __launch_bounds__(NW * 64) void gemv_reg_fused_kernel(const uint16_t* x, const uint8_t* q,
-                                                                 const uint8_t* s, void* out, int n, int k, int m,
-                                                                 int m0, int ldx, int ldy, int parts, int act,
+                                                                 const uint8_t* s, void* out, int n, int k, int m0,
+                                                                 int ldx, int blocks, int act, int m, int ldy,
                                                                  const uint16_t* bias, const uint16_t* residual,
                                                                  int ldr)
 {
-    gemv_reg_body<MT, R, STEPS, D, NW, kRagged>(RegArgs{x, q, s, out, n, k, m, m0, ldx, ldy, parts},
+    gemv_reg_body<MT, R, STEPS, D, NW, kRagged>(RegArgs{x, q, s, out, n, k, m, m0, ldx, ldy, 0, blocks},
                                                 Epilogue{bias, residual, ldr, act});
+}
+
+template <int MT, int R, int STEPS, int D, int NW, bool kRagged>
+__global__ __launch_bounds__(NW * 64) void gemv_reg_gate_kernel(const uint16_t* x, const uint8_t* q, const uint8_t* s,
+                                                                void* out, int n, int k, int m0, int ldx, int blocks,
+                                                                int act, int m, int ldy)
+{
+    gemv_reg_body<MT, R, STEPS, D, NW, kRagged>(RegArgs{x, q, s, out, n, k, m, m0, ldx, ldy, 0, blocks}, GateOnly{act});
 }
 
 // The 6-bit format (q = q6, 24 bytes per block) and the 8-bit format (q = q8, 32 bytes per block).
 template <int MT, int R, int STEPS, int D, int NW, bool kRagged, int kBits>
 __global__ __launch_bounds__(NW * 64) void gemv_reg6_kernel(const uint16_t* x, const uint8_t* q, const uint8_t* s,
-                                                            void* out, int n, int k, int m, int m0, int ldx,
-                                                            int ldy, int parts)
+                                                            void* out, int n, int k, int m0, int ldx, int blocks,
+                                                            int parts, int m, int ldy)
 {
     gemv_reg_body<MT, R, STEPS, D, NW, kRagged, NoEpilogue, kBits>(
-        RegArgs{x, q, s, out, n, k, m, m0, ldx, ldy, parts}, NoEpilogue{});
+        RegArgs{x, q, s, out, n, k, m, m0, ldx, ldy, parts, blocks}, NoEpilogue{});
 }
 
 template <int MT, int R, int STEPS, int D, int NW, bool kRagged, int kBits>
@@ -594,7 +615,7 @@ hipError_t launch_one6(const GemmArgs& g, int m0, int blocks, size_t lds, hipStr
             return e;
     hipLaunchKernelGGL((gemv_reg6_kernel<MT, R, STEPS, D, NW, kRagged, kBits>), dim3(blocks), dim3(NW * 64), lds, stream,
                        g.x, g.q, g.s, argmax ? static_cast<void*>(g.part_val) : static_cast<void*>(g.y), g.n, g.k,
-                       g.m, m0, (int)g.ldx, (int)g.ldy, argmax ? g.parts : 0);
+                       m0, (int)g.ldx, blocks, argmax ? g.parts : 0, g.m, (int)g.ldy);
     return hipGetLastError();
 }
 
@@ -604,24 +625,33 @@ hipError_t launch_one(const GemmArgs& g, int m0, int blocks, size_t lds, hipStre
     const bool argmax = g.part_val != nullptr;
     if (MT * STEPS >= 6)
         lds = (size_t)MT * STEPS * 4096 + 64;       // padded activation rows
-    static LdsLimit lds_limit, lds_limit_fused;     // of these kernel instances
-    if (lds > 64 * 1024) {
-        hipError_t e = lds_limit_fused.raise(
-            reinterpret_cast<const void*>(gemv_reg_fused_kernel<MT, R, STEPS, D, NW, kRagged>), 160 * 1024);
-        if (e == hipSuccess)
-            e = lds_limit.raise(reinterpret_cast<const void*>(gemv_reg_kernel<MT, R, STEPS, D, NW, kRagged>), 160 * 1024);
-        if (e != hipSuccess)
-            return e;
+    if constexpr (STEPS == 2) {
+        if (epi && !epi->bias && !epi->residual) {  // (at most 32 KiB of LDS)
+            hipLaunchKernelGGL((gemv_reg_gate_kernel<MT, R, STEPS, D, NW, kRagged>), dim3(blocks), dim3(NW * 64), lds, stream,
+                               g.x, g.q, g.s, static_cast<void*>(g.y), g.n, g.k, m0, (int)g.ldx, blocks, epi->act, g.m,
+                               (int)g.ldy);
+            return hipGetLastError();
+        }
     }
-    if (epi)
-        hipLaunchKernelGGL((gemv_reg_fused_kernel<MT, R, STEPS, D, NW, kRagged>), dim3(blocks), dim3(NW * 64), lds,
-                           stream, g.x, g.q, g.s, static_cast<void*>(g.y), g.n, g.k, g.m, m0, (int)g.ldx,
-                           (int)g.ldy, 0, epi->act, epi->bias, epi->residual, epi->ldr);
-    else
-        hipLaunchKernelGGL((gemv_reg_kernel<MT, R, STEPS, D, NW, kRagged>), dim3(blocks), dim3(NW * 64), lds,
-                           stream, g.x, g.q, g.s,
-                           argmax ? static_cast<void*>(g.part_val) : static_cast<void*>(g.y), g.n, g.k, g.m, m0,
-                           (int)g.ldx, (int)g.ldy, argmax ? g.parts : 0);
+    if (epi) {
+        auto kern = gemv_reg_fused_kernel<MT, R, STEPS, D, NW, kRagged>;
+        static LdsLimit lds_limit;                  // of this kernel instance
+        if (lds > 64 * 1024)
+            if (hipError_t e = lds_limit.raise(reinterpret_cast<const void*>(kern), 160 * 1024); e != hipSuccess)
+                return e;
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(NW * 64), lds, stream, g.x, g.q, g.s, static_cast<void*>(g.y), g.n, g.k,
+                           m0, (int)g.ldx, blocks, epi->act, g.m, (int)g.ldy, epi->bias, epi->residual, epi->ldr);
+        return hipGetLastError();
+    }
+    static LdsLimit lds_limit;                      // of this kernel instance
+    if (lds > 64 * 1024)
+        if (hipError_t e = lds_limit.raise(reinterpret_cast<const void*>(gemv_reg_kernel<MT, R, STEPS, D, NW, kRagged>),
+                                           160 * 1024);
+            e != hipSuccess)
+            return e;
+    hipLaunchKernelGGL((gemv_reg_kernel<MT, R, STEPS, D, NW, kRagged>), dim3(blocks), dim3(NW * 64), lds, stream, g.x, g.q,
+                       g.s, argmax ? static_cast<void*>(g.part_val) : static_cast<void*>(g.y), g.n, g.k, m0, (int)g.ldx,
+                       blocks, argmax ? g.parts : 0, g.m, (int)g.ldy);
     return hipGetLastError();
 }
 
