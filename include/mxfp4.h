@@ -61,7 +61,8 @@ enum {
 };
 
 /* Kernel families the dispatcher can be forced to (tests and measurements); AUTO picks by M:
- * one or two rows take VALU_REG when the shape allows it, else VALU_CVT; three or more take MFMA. */
+ * one or two rows take VALU_REG when the shape allows it, else VALU_CVT; three or more take MFMA or, with many
+ * rows or a K that is no multiple of 128, blocks of rows that walk K once (a family that cannot be forced). */
 enum {
     MXFP4_PATH_AUTO = 0,
     MXFP4_PATH_VALU_BITS = 1, /* wave-per-row GEMV, nibbles decoded with plain integer/FP32 ops  */
@@ -241,7 +242,7 @@ int mxfp4_dequant(const void* q_packed, const void* scales_e8m0, int64_t N, int6
  *   x_bf16 in  BF16 [M, K], row stride ldx (ldx >= K, ldx % 8 == 0, base 16-byte aligned)
  *   q_packed, scales_e8m0  in, as written by mxfp4_direct_cast (q 16-byte, scales 4-byte aligned)
  *   y_bf16 out BF16 [M, N], row stride ldy (ldy >= N)
- * M >= 1 (any size; M <= 32 is the designed range), N >= 1, K a positive multiple of 32 and at
+ * M >= 1 (any size: one token, a verification pass, a prompt), N >= 1, K a positive multiple of 32 and at
  * most MXFP4_MAX_K; the packed weights of one call stay below 2 GiB.  The summation order is fixed per (M, N, K, path), not specified.
  */
 #define MXFP4_MAX_K 65536
@@ -461,7 +462,8 @@ int mxfp4_woq_gemm_argmax_noalloc(const void* x_bf16, int64_t M, int64_t ldx,
  *   K a positive multiple of 8, at most MXFP4_MAX_K; the weights of one call stay below 2 GiB.
  * Other arguments as for mxfp4_woq_gemm.  Up to 8 activation rows share one pass over the weights
  * on the vector ALUs (K in phases inside the kernel when the rows do not fit the LDS whole), up
- * to 16 on the matrix cores (M > 8, K % 128 == 0, rows that fit the LDS); more rows take passes.
+ * to 16 on the matrix cores (M > 8, K % 128 == 0, rows that fit the LDS); more rows, and fewer where it
+ * is faster, take blocks of up to 128 rows that walk K once.
  */
 int mxfp4_bf16_gemm(const void* x_bf16, int64_t M, int64_t ldx,
                     const void* w_bf16, int64_t N, int64_t K, int64_t ldw,

@@ -77,7 +77,7 @@ constexpr size_t lds_bytes(Kind w, int wm, int wn, int wk, int mf, int nf)
     return wk > 1 ? most + table : most > table ? most : table;         // (WK = 1: the table takes the buffers' place)
 }
 
-// Two codes of the 2-bit format per byte -> two MXFP4 nibbles (sign, 1.0 or 0): eight codes of `c`, a dword.
+// Eight codes of the 2-bit format (16 bits of `c`) -> eight MXFP4 nibbles with the same values (+-1.0 or +-0).
 __device__ __forceinline__ uint32_t t2_to_nibbles(uint32_t c)
 {
     c = (c | c << 8) & 0x00FF00FFu;
