@@ -8,29 +8,29 @@ namespace {
 using namespace wide;
 
 const Cost kCosts[] = {
-    {1, 1, 8, 1, 1, 4.29f, 0.060f, 1.20f, 0.047f},
-    {1, 1, 8, 1, 2, 4.71f, 0.070f, 1.46f, 0.078f},
-    {1, 1, 8, 1, 3, 5.05f, 0.107f, 1.73f, 0.099f},
-    {1, 1, 8, 1, 4, 5.04f, 0.145f, 1.82f, 0.125f},
-    {1, 1, 8, 1, 6, 5.46f, 0.224f, 4.12f, 0.185f},
-    {1, 1, 8, 1, 8, 6.23f, 0.282f, 4.93f, 0.248f},
-    {1, 1, 8, 2, 1, 5.18f, 0.101f, 3.47f, 0.101f},
-    {1, 1, 8, 2, 2, 5.56f, 0.145f, 3.83f, 0.134f},
-    {1, 1, 8, 2, 3, 5.98f, 0.182f, 4.27f, 0.164f},
-    {1, 1, 8, 2, 4, 6.22f, 0.219f, 4.80f, 0.192f},
-    {1, 1, 8, 2, 6, 7.51f, 0.290f, 6.36f, 0.240f},
-    {1, 2, 4, 4, 1, 4.28f, 0.332f, 2.83f, 0.297f},
-    {1, 2, 4, 4, 2, 5.42f, 0.378f, 4.55f, 0.310f},
-    {1, 2, 4, 4, 3, 6.60f, 0.465f, 5.28f, 0.416f},
-    {2, 2, 2, 4, 2, 7.37f, 0.685f, 5.26f, 0.647f},
-    {2, 2, 2, 4, 3, 9.18f, 0.845f, 5.97f, 0.860f},
-    {2, 4, 1, 4, 2, 8.47f, 0.990f, 0.57f, 1.088f},
-    {2, 4, 1, 4, 3, 11.68f, 1.322f, 5.43f, 1.589f},
-    {1, 8, 1, 8, 2, 13.11f, 1.649f, 10.94f, 1.719f},
-    {1, 8, 1, 8, 3, 17.49f, 2.228f, 15.91f, 2.251f},
-    {1, 4, 2, 4, 1, 4.52f, 0.447f, 1.79f, 0.317f},
-    {1, 4, 2, 4, 2, 6.33f, 0.526f, 2.02f, 0.463f},
-    {1, 4, 2, 4, 3, 8.68f, 0.704f, 4.44f, 0.877f},
+    {1, 1, 8, 1, 1, 4.23f, 0.055f, 1.16f, 0.049f},
+    {1, 1, 8, 1, 2, 4.51f, 0.075f, 1.40f, 0.073f},
+    {1, 1, 8, 1, 3, 4.66f, 0.112f, 1.62f, 0.096f},
+    {1, 1, 8, 1, 4, 4.67f, 0.155f, 1.73f, 0.123f},
+    {1, 1, 8, 1, 6, 5.29f, 0.211f, 3.88f, 0.179f},
+    {1, 1, 8, 1, 8, 5.86f, 0.276f, 4.65f, 0.240f},
+    {1, 1, 8, 2, 1, 5.10f, 0.099f, 3.34f, 0.103f},
+    {1, 1, 8, 2, 2, 5.59f, 0.129f, 3.95f, 0.108f},
+    {1, 1, 8, 2, 3, 5.68f, 0.175f, 4.01f, 0.155f},
+    {1, 1, 8, 2, 4, 6.05f, 0.192f, 4.71f, 0.156f},
+    {1, 1, 8, 2, 6, 7.21f, 0.287f, 5.86f, 0.240f},
+    {1, 2, 4, 4, 1, 4.45f, 0.304f, 2.94f, 0.259f},
+    {1, 2, 4, 4, 2, 5.60f, 0.346f, 4.50f, 0.296f},
+    {1, 2, 4, 4, 3, 6.92f, 0.426f, 5.63f, 0.365f},
+    {2, 2, 2, 4, 2, 7.68f, 0.609f, 5.36f, 0.601f},
+    {2, 2, 2, 4, 3, 9.76f, 0.749f, 7.03f, 0.718f},
+    {2, 4, 1, 4, 2, 9.24f, 0.924f, 0.75f, 0.972f},
+    {2, 4, 1, 4, 3, 11.60f, 1.275f, 5.75f, 1.423f},
+    {1, 8, 1, 8, 2, 14.14f, 1.536f, 10.05f, 1.691f},
+    {1, 8, 1, 8, 3, 17.04f, 2.171f, 14.60f, 2.183f},
+    {1, 4, 2, 4, 1, 4.45f, 0.401f, 1.63f, 0.305f},
+    {1, 4, 2, 4, 2, 6.68f, 0.500f, 2.07f, 0.422f},
+    {1, 4, 2, 4, 3, 8.60f, 0.643f, 4.77f, 0.792f},
 };
 
 #define MXFP4_WIDE(...)                                                                             \
