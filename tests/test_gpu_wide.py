@@ -52,7 +52,8 @@ def test_few_rows_ragged_k(m, n, k):
 
 @pytest.mark.parametrize("m,n,k", [(17, 16, 128), (17, 8200, 1376), (33, 4096, 160), (33, 1000, 4096), (17, 16000, 1376),
                                    (32, 4098, 11008), (17, 22000, 1376), (17, 32000, 1376), (17, 8200, 160), (17, 22000, 160),
-                                   (16, 32000, 288), (64, 259, 288), (17, 4596, 320), (35, 16599, 800), (34, 11208, 2016)])
+                                   (16, 32000, 288), (64, 259, 288), (17, 4596, 320), (35, 16599, 800), (34, 11208, 2016),
+                                   (17, 6556, 288), (33, 11134, 3008)])
 def test_several_sequences(m, n, k):
     check(m, n, k)
 
@@ -65,7 +66,8 @@ def test_prompts(m, n, k):
     check(m, n, k)
 
 
-@pytest.mark.parametrize("m,n,k", [(196, 26152, 1216), (138, 44350, 1120), (509, 22016, 4096)])
+@pytest.mark.parametrize("m,n,k", [(196, 26152, 1216), (138, 44350, 1120), (509, 22016, 4096), (1052, 98, 4192),
+                                   (353, 5378, 2208), (590, 4838, 1056), (271, 20346, 1440)])
 def test_largest_blocks(m, n, k):
     # checked on sampled weight rows, the edges among them
     w = synth.weights_student_t(n, k, seed=9300 + n, device=DEV)
