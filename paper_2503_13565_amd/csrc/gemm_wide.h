@@ -36,12 +36,12 @@
 #include "block_out.h"
 #include "common.h"
 #include "kernels.h"
+#include "scale_stage.h"
 
 namespace mxfp4 {
 namespace wide {
 
 constexpr int kOob = 0x7FFFFFF0;        // lane offset beyond any descriptor: the load returns zero
-constexpr int kThreads = 512;
 
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
 typedef __attribute__((ext_vector_type(6))) unsigned int u32x6_t;
@@ -62,10 +62,6 @@ struct Args {
     int n, k, m, ldx, ldw, tiles_m, tiles_n;    // ldw: BF16 weights only
     BlockOut out;
 };
-
-// Scale bytes of a block's weight rows for two phases, one row behind the other with a dword of padding
-// (the rows of an operand read hit different banks).
-constexpr int scale_row_bytes(int wk) { return wk * 8 + 4; }
 
 constexpr size_t lds_bytes(Kind w, int wm, int wn, int wk, int mf, int nf)
 {
@@ -133,8 +129,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
     constexpr bool kScaled = kW != kBf16, kRagged = kW == kMxRagged, kTiled = kW == kMxTiled;
     constexpr int kBits = kind_bits(kW), kBlock = 4 * kBits;            // dwords and bytes of a block of 32
     constexpr int kSRow = scale_row_bytes(WK), kSBuf = BN * kSRow;
-    // scale dwords per thread and two phases
-    constexpr int SC = kScaled && !kRagged ? (BN * WK * 2 + kThreads - 1) / kThreads : 0;
+    constexpr int SC = kScaled && !kRagged ? scale_rounds(BN, WK) : 0;  // scale dwords per thread and two phases
     extern __shared__ __align__(16) uint8_t smem[];
     u32x4_t* xs = reinterpret_cast<u32x4_t*>(smem);
     uint8_t* ss = smem + (size_t)2 * kBuf * 16;
@@ -172,15 +167,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
                           : row * row_bytes + lg * (kW == kBf16 ? 16 : kBlock);
         s_off[f] = row * nblk + lg;
     }
-    // dword e of the block's scales: step e % (2 WK) of the two phases, row e / (2 WK)
-    int sc_off[SC + 1], sc_at[SC + 1];
+    int sc_off[SC + 1];
 #pragma unroll
-    for (int i = 0; i < SC; ++i) {
-        const int e = min(tid + i * kThreads, BN * WK * 2 - 1), r = e / (WK * 2), c = e % (WK * 2);
-        sc_off[i] = kTiled ? (min((n0 + r) >> 4, n_tiles - 1) * n_items * 16 + (r & 15)) * 16
-                           : min(n0 + r, n - 1) * nblk + c * 4;
-        sc_at[i] = r * kSRow + c * 4;
-    }
+    for (int i = 0; i < SC; ++i)
+        sc_off[i] = scale_row_offset(kTiled, n0 + scale_row(WK, tid, i), n, nblk, n_tiles, n_items);
 
     struct Slot {
         uint32_t q[NF][kBits];
@@ -195,21 +185,19 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
     auto past = [](int last, int at) { return ((last - at) >> 31) & kOob; };    // 0 where at <= last
     int ld_x = 0, ld_q = 0;                                             // phases to ask for next
     auto issue_scales = [&](int sp) {                                   // of the phases 2 sp and 2 sp + 1
-        const int at = sp * (WK * 8) < nblk ? sp * (WK * 8) : 0;
 #pragma unroll
         for (int i = 0; i < SC; ++i) {
-            const int T = sp * (WK * 2) + (tid + i * kThreads) % (WK * 2);
-            if constexpr (kTiled)
-                sc[i] = __builtin_amdgcn_raw_buffer_load_b32(
-                    rs, (sc_off[i] + (T >> 2) * 256 + (T & 3) * 4) | past(steps - 1, T), 0, 0);
-            else
-                sc[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, sc_off[i] | past(steps - 1, T), at, 0);
+            const int T = sp * (WK * 2) + scale_step(WK, tid, i);
+            sc[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, (sc_off[i] + scale_step_offset(kTiled, T)) |
+                                                                 past(steps - 1, T) |
+                                                                 past(BN * WK * 2 - 1, scale_index(tid, i)), 0, 0);
         }
     };
     auto store_scales = [&](int b) {
 #pragma unroll
         for (int i = 0; i < SC; ++i)
-            *reinterpret_cast<uint32_t*>(ss + b * kSBuf + sc_at[i]) = sc[i];
+            if (scale_owned(BN, WK, tid, i))
+                *reinterpret_cast<uint32_t*>(ss + b * kSBuf + scale_lds(WK, tid, i)) = sc[i];
     };
     auto issue_x = [&]() {
         const int x_past = past((k >> 3) - 1, ld_x * kRowChunks + xc);
