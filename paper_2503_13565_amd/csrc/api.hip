@@ -11,6 +11,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "routes.h"
 #include "../../include/mxfp4.h"
 
 namespace mxfp4 {
@@ -103,30 +104,16 @@ static int check_x(const void* x, int64_t M, int64_t ldx, int64_t K)
 
 constexpr int kPathWide = -2;           // gemm_wide.hip: AUTO only
 
-// Whether three and more rows with K % 128 == 0 take the blocks of gemm_wide.hip (us per launch, tiles -> blocks,
-// row-major / tile-major):
-//   - always beyond 16 rows, where the tiles take a second pass over the weights: 12288 x 4096 at 32 rows 20.6 ->
-//     13.4 / 18.9 -> 12.2, 22016 x 4096 at 64 59 -> 24 / 52 -> 22;
-//   - from nine rows on while every compute unit has one block of up to six tiles: 4096 x 4096 at 16 rows 6.7 ->
-//     6.0 / 6.5 -> 6.2, 22016 x 4096 15.8 -> 15.4 / 13.2 -> 12.8, 9728 x 896 7.3 -> 5.5, but 32000 x 4096 19.1 ->
-//     19.2 / 16.1 -> 16.6, 57344 x 8192 61 -> 66; a matrix that is small both ways starts faster on the tiles
-//     (1000 x 1024 4.0 -> 4.2);
-//   - fewer rows where they do not fit the LDS whole (4096 x 11008 at 8 rows 12.2 -> 10.8 / 11.3 -> 10.4), and up to
-//     16 then, unless K is so long that every block's own walk over the rows costs more than K split over the
-//     units (8192 x 28672 at 16 rows 34.1 -> 38.6 row-major, 29.4 -> 29.9 tile-major, 28.6 -> 25.9 at 9).
-static bool wide_preferred(const GemmArgs& a, const DeviceInfo& dev, bool tiled)
+// Whether an MXFP4 call takes the blocks of gemm_wide.hip (the lines and their figures: routes.h).  `split`: the
+// tile kernels could split K through the caller's workspace.
+static bool blocks_preferred(const GemmArgs& a, const DeviceInfo& dev, bool tiled, bool split, bool fused)
 {
     const char* from = knob("MXFP4_WIDE_FROM");                      // measurement only
     if (from)
         return a.m >= atoi(from);
-    if (a.m > 16)
-        return true;
-    if (a.m < 3)
-        return false;
-    const bool one_round = a.n <= 96 * dev.cus;
-    if (!mfma_tile_can_run(a, dev))
-        return one_round ? tiled || a.m <= 8 || a.k <= 16384 : tiled && a.m > 8;
-    return a.m > 8 && one_round && (a.n > 2048 || a.k > 2048);
+    if (a.k % 128 != 0)
+        return wide_ragged_preferred(a.m, a.n, a.k, dev.cus, dev.lds_bytes);
+    return wide_preferred({a.m, a.n, a.k, dev.cus, mfma_tile_can_run(a, dev), split, tiled, fused, a.part_val != nullptr});
 }
 
 // AUTO: the vector-ALU GEMV for one or two activation rows (its register-resident form when the
@@ -135,8 +122,7 @@ static bool wide_preferred(const GemmArgs& a, const DeviceInfo& dev, bool tiled)
 // Two rows with K beyond 8192 also go to the tiles: the register form would take two passes and
 // the general GEMV is slower there (measured: 4096 x 11008 13.3 against 9.5 us, 8192 x 28672 48
 // against 34; at K = 8192 the GEMV still wins by 5 %).
-static int pick_path(int path, int64_t M, int64_t K, bool mfma_ok, bool reg_ok, bool wide_ok,
-                     bool wide_better)
+static int pick_path(int path, int64_t M, int64_t K, bool mfma_ok, bool reg_ok, bool wide)
 {
     if (path != MXFP4_PATH_AUTO)
         return path;
@@ -147,8 +133,7 @@ static int pick_path(int path, int64_t M, int64_t K, bool mfma_ok, bool reg_ok, 
     }
     if (env_path > 0)
         return env_path;
-    // (from three rows on also where the tiles cannot run: K % 128 != 0, or too long without a workspace)
-    if (wide_ok && M >= 3 && (wide_better || !mfma_ok))
+    if (wide)
         return kPathWide;
     if (M >= 3 && mfma_ok)
         return MXFP4_PATH_MFMA;
@@ -251,8 +236,9 @@ static int run_gemm(const void* x, int64_t M, int64_t ldx, const void* q, const 
     }
     const int chosen = tiled ? -1
                              : pick_path(path, M, K, mfma_can_run(a, dev, splitk_ws != nullptr),
-                                         gemv_reg_can_run(a, dev) && gemv_reg_single_pass(a), gemm_wide_can_run(a, dev),
-                                         wide_preferred(a, dev, false));
+                                         gemv_reg_can_run(a, dev) && gemv_reg_single_pass(a),
+                                         gemm_wide_can_run(a, dev) &&
+                                             blocks_preferred(a, dev, false, splitk_ws != nullptr, epi != nullptr));
     hipStream_t st = static_cast<hipStream_t>(stream);
     int parts_used = 0;
     hipError_t e = hipSuccess;
@@ -270,7 +256,7 @@ static int run_gemm(const void* x, int64_t M, int64_t ldx, const void* q, const 
         if (tiled_decode && !epi && gemv_tile_can_run(a, dev) && (a.m == 1 || !mfma_tile_can_run(a, dev))) {
             if (go)
                 e = launch_gemv_tile(a, dev, &parts_used, st);
-        } else if (wide_preferred(a, dev, true) && gemm_wide_can_run(a, dev) &&
+        } else if (gemm_wide_can_run(a, dev) && blocks_preferred(a, dev, true, split, epi != nullptr) &&
                    (mfma_tile_can_run(a, dev) || split || (!epi && mfma_tile_phased_preferred(a, dev, false)))) {
             if (go)
                 e = launch_gemm_wide(a, dev, &parts_used, st, true, epi);

@@ -1,0 +1,94 @@
+// Which products take the block kernel (gemm_wide.h) and which the kernels that hold their activation rows in the LDS.
+// Plain integer arithmetic without any device header, so that the rules can be checked on the CPU.
+//
+// The blocks win where the other kernels would stream and decode the weights several times (more rows than a
+// pass, rows that do not fit the LDS whole) and where every compute unit has one block.  They lose where a matrix has
+// few rows and K is long: a block walks all of K by itself, while the other kernels split K over the units or
+// keep a unit's tile beside its rows.  Every line below was measured on both sides over N = 16 .. 64000 and
+// K = 128 .. 65536; `unit` is a number of weight rows per compute unit.
+#pragma once
+
+namespace mxfp4 {
+
+// What the tile kernels would do with an MXFP4 call.
+struct TileCall {
+    int m, n, k, cus;
+    bool fits;      // a pass of 16 (8, 4) rows fits the LDS whole
+    bool split;     // else: K can be split over the units through the caller's workspace
+    bool tiled;     // tile-major weights
+    bool fused;     // bias, gate or residual behind the product
+    bool pick;      // the pick instead of the product
+};
+
+// From three rows on, K % 128 == 0.  Figures: us per launch, tiles -> blocks, or blocks as a part of what the tiles take.
+inline bool wide_preferred(const TileCall& c)
+{
+    const int m = c.m, n = c.n, k = c.k, unit = c.cus, passes = (m + 15) / 16;
+    const bool plain = !c.fused && !c.pick;
+    if (m < 3)
+        return false;
+    if (c.fits) {
+        // Beyond 16 rows always: 12288 x 4096 at 32 rows 20.6 -> 12.0, tile-major 18.9 -> 12.2, 22016 x 4096 at 64 59 -> 24.
+        // From nine rows on while a unit has one block (9728 x 896 7.3 -> 5.5, but 32000 x 4096 19.1 -> 19.2, 57344 x
+        // 8192 61 -> 66): blocks of 96 rows pay for the rows that they lack (18432 x 4096 13.9 -> 14.6, 22016 15.8 ->
+        // 15.4) unless the epilogue's loads are hidden by it (18432 x 4096 with residual 0.9 of the tiles); one tile per
+        // unit starts faster on the tiles (2560 x 2048 tile-major 4.7 -> 5.0) unless K is long enough (4096 x 4096 6.7 -> 6.0).
+        if (m > 16)
+            return true;
+        if (m <= 8 || n > 96 * unit)
+            return false;
+        if (n <= 16 * unit)
+            return k > 3072 && !(c.tiled && c.fused);
+        return c.fused || n <= 64 * unit || n >= 84 * unit || k <= 2560;
+    }
+    if (m <= 8) {
+        if (n > 96 * unit)
+            return false;
+        // Plain products: K in phases inside a tile kernel, which walks one tile per unit as fast as a block and
+        // starts earlier: 4096 x 11008 at 8 rows 12.2 -> 10.8, 4096 x 28672 18.9 -> 22.8 at three; tile-major 1000 x 28672
+        // 15.0 -> 19.9.  Every further tile fetches the rows again: 12288 x 14336 at 5 rows 0.74 of it.
+        if (plain && (n <= 16 * unit || !c.split))
+            return n <= 16 * unit ? m > 4 && k <= (c.tiled ? 11264 : 14336) : c.tiled ? m > 3 || k <= 28672 : m > 4 || k <= 20480;
+        // No workspace: narrower passes over the weights (five rows and more 0.6 to 0.9 of them, but 18432 x 24576 at 8
+        // rows 1.12; at three and four rows 0.9 to 1.2).
+        if (!c.split)
+            return m > 4 && (n <= 48 * unit || k <= 14336);
+        // K split: 8192 x 11008 at 5 rows 0.87 of it, 12288 x 28672 1.0, 18432 x 11008 1.07; pick 1000 x 20480 1.12;
+        // tile-major pick 1000 x 11008 1.04, 8192 x 20480 0.84, 16384 x 32768 1.06.
+        if (c.tiled)
+            return k <= (n < 16 * unit ? 10240 : n < 24 * unit ? 16384 : 20480);
+        return m > 4 && n <= 64 * unit && (n < 4 * unit ? c.pick && k <= 10240 : k <= 14336);
+    }
+    // No workspace (row-major): narrower passes of eight or four rows, 0.3 to 0.8 of them.
+    if (!c.split)
+        return m > 16 || (n <= 96 * unit && k <= 16384);
+    // One pass of K split over the units: at 16 rows 4096 x 11008 0.83 of it, 256 x 14336 1.13, 5000 x 11008 1.05, 18432 x 12288
+    // 1.05; tile-major 1000 x 10240 1.07, 2048 x 14336 1.08, 4096 x 20480 1.03, 16384 x 28672 1.09, 24000 x 65536 0.94.
+    if (passes == 1 && c.tiled)
+        return n > 64 * unit ||
+               k <= (n < 8 * unit ? 8192 : n < 16 * unit ? 12288 : n < 32 * unit ? 16384 : 20480);
+    if (passes == 1)
+        return n <= 96 * unit && (n <= 64 * unit || n >= 84 * unit) &&
+               k <= (n < 8 * unit || (n > 16 * unit && n < 32 * unit) ? 10240 : 14336);
+    // Several passes: each of them streams the weights again, so the line moves with their number.  At 17 to 32
+    // rows 256 x 24576 1.0 of them, 256 x 65536 1.9, 500 x 32768 1.19, 1500 x 49152 1.14, 3000 x 65536 1.09, 4096 x 65536 0.84;
+    // tile-major 64 x 20480 1.14, 64 x 65536 2.5, 1000 x 28672 1.05, 1500 x 49152 1.14; at 64 rows 16 x 65536 1.2, 1.6.
+    int pass = 0x7FFFFFFF / passes;
+    if (c.tiled)
+        pass = n <= 2 * unit ? 8192 : n <= 4 * unit ? 12288 : n < 8 * unit ? 16384 : n < 12 * unit ? 24576 : pass;
+    else
+        pass = n <= unit ? 10240 : n <= 2 * unit ? 12288 : n < 16 * unit ? 16384 : pass;
+    return k <= passes * pass;
+}
+
+// K that is no multiple of 128, from three rows on, where the vector ALUs take passes of two rows: 4096 x 1376 at 7 rows
+// 18.3 -> 4.5.  Three rows of a handful of weight rows, or of up to four per unit with a long K, stay there while
+// two rows fit the LDS (1 x 8224 6.8 -> 7.6, 256 x 28704 20.3 -> 21.9, 1000 x 40992 0.78 of it).
+inline bool wide_ragged_preferred(int m, int n, int k, int cus, int lds_bytes)
+{
+    if (m == 3 && 4 * k <= lds_bytes && (n < 8 ? k > 4096 : n <= 4 * cus && k > 16384))
+        return false;
+    return m >= 3;
+}
+
+}  // namespace mxfp4

@@ -1,0 +1,79 @@
+"""The rules of csrc/routes.h on both sides of their lines, on the CPU: which calls take the block kernel and which stay on
+the kernels that were measured faster for them (256 compute units, 160 KiB of LDS)."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2503_13565_amd", "csrc")
+
+RULES = r"""
+#include "routes.h"
+using namespace mxfp4;
+extern "C" int mx(int m, int n, int k, int fits, int split, int tiled, int fused, int pick)
+{
+    return wide_preferred({m, n, k, 256, fits != 0, split != 0, tiled != 0, fused != 0, pick != 0});
+}
+extern "C" int ragged(int m, int n, int k) { return wide_ragged_preferred(m, n, k, 256, 160 * 1024); }
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("routes")
+    (d / "routes.cpp").write_text(RULES)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(d / "routes.cpp"),
+                           "-o", str(d / "routes.so")])
+    return ctypes.CDLL(str(d / "routes.so"))
+
+
+# (m, n, k, form): form of w = workspace, t = tile-major, f = fused, p = pick
+SLOWER = [                                                  # us per launch on the other kernels -> in blocks
+    (3, 16, 65536, ""), (3, 2048, 24576, "w"), (5, 1000, 49152, ""), (8, 4096, 65536, ""),        # 26.3 -> 34.1, ...
+    (8, 6144, 65536, "w"), (5, 24000, 24576, "w"), (5, 18432, 12288, "wf"),
+    (9, 16, 16384, "w"), (12, 1000, 16384, "w"), (16, 18432, 4096, ""), (16, 4096, 512, ""),
+    (17, 16, 65536, "w"), (32, 256, 65536, "w"), (17, 1000, 65536, "w"), (48, 16, 65536, "w"), (64, 16, 65536, "w"),
+    (8, 4096, 65536, "tw"), (5, 1000, 16384, "tw"), (3, 256, 24576, "t"), (8, 6144, 28672, "tw"),
+    (9, 16, 28672, "tw"), (16, 1000, 11008, "tw"), (9, 2560, 2048, "t"), (16, 16384, 28672, "tw"),
+    (17, 16, 28672, "tw"), (32, 1000, 65536, "tw"), (48, 16, 32768, "tw"), (64, 16, 49152, "tw"),
+    (5, 256, 24576, "wp"), (8, 1000, 20480, "wp"), (5, 1000, 12288, "twp"), (3, 2048, 20480, "wf"),
+    (8, 18432, 24576, "f"), (4, 2048, 24576, "f"), (17, 500, 32768, "w"), (32, 3000, 65536, "w"), (16, 5000, 11008, "w"),
+]
+FASTER = [
+    (32, 12288, 4096, "w"), (17, 16, 128, ""), (509, 22016, 4096, ""), (64, 4096, 65536, "w"), (32, 2048, 28672, "w"),
+    (8, 4096, 11008, "w"), (8, 4096, 11008, "t"), (5, 12288, 14336, ""), (5, 24000, 65536, "t"), (8, 8192, 11008, "w"),
+    (9, 4096, 11008, "w"), (16, 12288, 14336, "w"), (16, 1000, 11008, ""), (9, 22016, 4096, "f"), (16, 8192, 1024, "t"),
+    (16, 24000, 65536, "tw"), (9, 8192, 20480, "tw"), (17, 256, 65536, ""), (96, 16, 49152, "w"), (16, 18432, 4096, "f"),
+    (8, 12288, 11008, "wp"), (8, 8192, 14336, "wf"), (5, 16, 11008, "f"), (16, 32000, 11008, "tw"),
+]
+
+
+def asked(rules, m, n, k, form):
+    width = 4 if m <= 4 else 8 if m <= 8 else 16
+    fits = (k // 128 + 3) // 4 * 1024 * width + 16384 <= 160 * 1024       # the rows of a pass and the waves' partial tiles
+    return bool(rules.mx(m, n, k, int(fits), int("w" in form), int("t" in form), int("f" in form), int("p" in form)))
+
+
+@pytest.mark.parametrize("m,n,k,form", SLOWER)
+def test_calls_that_were_slower_in_blocks(rules, m, n, k, form):
+    assert not asked(rules, m, n, k, form)
+
+
+@pytest.mark.parametrize("m,n,k,form", FASTER)
+def test_calls_that_are_faster_in_blocks(rules, m, n, k, form):
+    assert asked(rules, m, n, k, form)
+
+
+def test_rows_that_the_other_kernels_take_in_one_pass_stay(rules):
+    for m in range(1, 9):
+        for n in (1, 16, 4096, 24576, 64000):
+            for k in (128, 4096):
+                assert not asked(rules, m, n, k, "") and not asked(rules, m, n, k, "tw")
+
+
+def test_ragged_k(rules):
+    assert all(rules.ragged(m, n, k) for m in (4, 7, 16, 500) for n in (1, 300, 32000) for k in (32, 1376, 65504))
+    assert not rules.ragged(1, 4096, 1376) and not rules.ragged(2, 4096, 1376)
+    assert rules.ragged(3, 4096, 1376) and rules.ragged(3, 1, 544) and rules.ragged(3, 1, 65504)
+    assert not rules.ragged(3, 1, 8224) and not rules.ragged(3, 4, 28704) and not rules.ragged(3, 256, 28704)
