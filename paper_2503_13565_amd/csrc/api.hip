@@ -320,15 +320,8 @@ static int run_gemm(const void* x, int64_t M, int64_t ldx, const void* q, const 
     return MXFP4_OK;
 }
 
-// Whether a product on one of the other formats (`code` as in launch_gemv_reg) takes the blocks of gemm_wide.h
-// (us per launch, before -> blocks):
-//   - beyond 16 rows always (E4M3 12288 x 4096 at 32 rows 33 -> 18, E2M3 28 -> 18);
-//   - the ternary codes from three rows on, where the vector ALUs took passes of four rows (22016 x 4096 at 8 rows 51
-//     -> 16, at 64 401 -> 26), short matrices from four (896 x 4864 at three 6.6 -> 7.1);
-//   - five to 16 rows that do not fit the LDS whole, which ran as passes of four (E4M3 4096 x 11008 at 16 rows
-//     54 -> 15), else while a compute unit has few tiles: 8-bit elements up to four (12288 x 4096 at 8 rows 16.7
-//     -> 14.9, but 22016 x 4096 24.7 -> 26.3), 6-bit up to two and a half (9728 x 896 9.2 -> 7.1, but 12288 x 4096
-//     14.0 -> 14.9), these from three rows on unless N is small too (896 x 4864 at three rows 7.0 -> 7.3).
+// Whether a product on one of the other formats (`code` as in launch_gemv_reg) takes the blocks of gemm_wide.h (the
+// lines and their figures: routes.h).
 static bool fmt_blocks_preferred(const GemmArgs& a, const DeviceInfo& dev, int code)
 {
     const char* from = knob("MXFP4_WIDE_FROM");                      // measurement only
@@ -336,15 +329,8 @@ static bool fmt_blocks_preferred(const GemmArgs& a, const DeviceInfo& dev, int c
         return false;
     if (from)
         return a.m >= atoi(from);
-    if (a.m > 16)
-        return true;
-    if (code == 2)
-        return a.m >= 4 || (a.m == 3 && a.n >= 1024);
-    if (a.m >= 5 && !mfma_tile_can_run(a, dev))
-        return true;
-    if (code == 8 || code == 24)
-        return a.m >= 5 && a.n <= 64 * dev.cus;
-    return a.n <= 40 * dev.cus && (a.m >= 5 || (a.m >= 3 && a.n >= 2048));
+    const int bits = code == 24 ? 8 : code == 22 ? 6 : code;
+    return wide_format_preferred(a.m, a.n, a.k, bits, mfma_tile_can_run(a, dev), dev.cus, dev.lds_bytes);
 }
 
 // ---- BF16-weight product ----------------------------------------------------------------

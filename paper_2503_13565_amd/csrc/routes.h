@@ -91,4 +91,40 @@ inline bool wide_ragged_preferred(int m, int n, int k, int cus, int lds_bytes)
     return m >= 3;
 }
 
+// The other formats, K % 128 == 0.  `bits` per element; `tiles`: the call's rows fit the LDS whole on the tile kernels (of
+// 6 and 8 bits; the ternary codes run on the vector ALUs).
+inline bool wide_format_preferred(int m, int n, int k, int bits, bool tiles, int cus, int lds_bytes)
+{
+    const int unit = cus;
+    // Beyond 16 rows always (E4M3 12288 x 4096 at 32 rows 33 -> 18, E2M3 28 -> 18).
+    if (m > 16)
+        return true;
+    // The ternary codes went over the weights once per four rows (22016 x 4096 at 8 rows 51 -> 16).  In one such pass, up
+    // to eight weight rows per unit, the vector ALUs are faster from K = 2560 (1000 x 8192 at four rows 1.14 of them) until
+    // a unit has room for one copy of the four rows only (1000 x 12288 0.89); a short K leaves nothing but
+    // the start of the blocks, once per tile of many (24000 x 128 1.28, 24000 x 512 1.07, 24000 x 768 0.52).
+    if (bits == 2) {
+        if (m > 4)
+            return true;
+        if (n <= 8 * unit)
+            return (m == 4 || n >= 4 * unit) && (k <= 2048 || 16 * k > lds_bytes);
+        return m >= 3 && (n <= 16 * unit || k >= 768);
+    }
+    // Rows that do not fit ran as passes of four (E4M3 4096 x 11008 at 16 rows 54 -> 15).
+    if (m >= 5 && !tiles)
+        return true;
+    // Else while a unit has few tiles, the 8-bit elements from five rows on: 8192 x 4096 0.78 of the tiles, 12288 x 4096 0.93,
+    // but 12288 x 3072 1.05 and 9216 x 9216 1.2 (the loop takes two phases of 1024 elements at a time).
+    if (bits == 8)
+        return m >= 5 && (n <= 32 * unit || (n <= 64 * unit && (k <= 2048 || k == 4096)));
+    // 6-bit: 8192 x 4096 0.88 of the tiles, but 9216 x 4096 1.12 and more; three and four rows unless N is small too (896 x 4864
+    // 7.0 -> 7.3) or K is long (3072 x 16384 1.06), where the decode kernel takes passes of two again from
+    // where four rows do not fit (2048 x 24576 0.9, 8192 x 24576 0.6).
+    if (m < 3 || n < 8 * unit)
+        return m >= 5 && n <= 32 * unit;
+    if (m <= 4 && 8 * k > lds_bytes)
+        return n <= 40 * unit;
+    return n <= 32 * unit && (m >= 5 || k <= 12288);
+}
+
 }  // namespace mxfp4

@@ -15,6 +15,10 @@ extern "C" int mx(int m, int n, int k, int fits, int split, int tiled, int fused
 {
     return wide_preferred({m, n, k, 256, fits != 0, split != 0, tiled != 0, fused != 0, pick != 0});
 }
+extern "C" int format(int m, int n, int k, int bits, int tiles)
+{
+    return wide_format_preferred(m, n, k, bits, tiles != 0, 256, 160 * 1024);
+}
 extern "C" int ragged(int m, int n, int k) { return wide_ragged_preferred(m, n, k, 256, 160 * 1024); }
 """
 
@@ -77,3 +81,21 @@ def test_ragged_k(rules):
     assert not rules.ragged(1, 4096, 1376) and not rules.ragged(2, 4096, 1376)
     assert rules.ragged(3, 4096, 1376) and rules.ragged(3, 1, 544) and rules.ragged(3, 1, 65504)
     assert not rules.ragged(3, 1, 8224) and not rules.ragged(3, 4, 28704) and not rules.ragged(3, 256, 28704)
+
+
+@pytest.mark.parametrize("bits,m,n,k,blocks", [
+    (6, 5, 9216, 4096, False), (6, 8, 10240, 8192, False), (6, 16, 10240, 4096, False), (6, 3, 9216, 16384, False),
+    (6, 3, 2048, 16384, False), (6, 4, 3072, 20480, False), (6, 5, 8192, 4096, True), (6, 3, 8192, 4096, True),
+    (6, 3, 2048, 4096, True), (6, 3, 1000, 4096, False), (6, 5, 1000, 4096, True), (6, 5, 32000, 11008, True),
+    (6, 3, 2048, 24576, True), (6, 4, 8192, 24576, True), (6, 17, 32000, 4096, True), (6, 2, 4096, 24576, False),
+    (8, 5, 9216, 9216, False), (8, 8, 12288, 3072, False), (8, 8, 12288, 7168, False), (8, 5, 16384, 8192, False),
+    (8, 8, 12288, 4096, True), (8, 5, 16384, 2048, True), (8, 5, 8192, 9216, True), (8, 4, 8192, 4096, False),
+    (8, 5, 32000, 11008, True), (8, 16, 4096, 5120, True), (8, 24, 64000, 128, True), (8, 8, 22016, 4096, False),
+    (2, 4, 1000, 8192, False), (2, 3, 2048, 10240, False), (2, 4, 24000, 128, False), (2, 3, 18000, 512, False),
+    (2, 4, 1000, 1024, True), (2, 3, 1000, 1024, False), (2, 4, 1000, 12288, True), (2, 3, 24000, 768, True),
+    (2, 4, 4096, 128, True), (2, 5, 1000, 8192, True), (2, 2, 32000, 4096, False),
+])
+def test_other_formats(rules, bits, m, n, k, blocks):
+    width = 4 if m <= 4 else 8 if m <= 8 else 16
+    fits = (k // 128 + 3) // 4 * 1024 * width + 16384 <= 160 * 1024
+    assert bool(rules.format(m, n, k, bits, int(fits))) == blocks
