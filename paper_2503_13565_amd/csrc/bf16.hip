@@ -12,6 +12,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "routes.h"
 #include "../../include/mxfp4.h"
 
 namespace mxfp4 {
@@ -886,11 +887,7 @@ hipError_t launch_rows(const Bf16Args& a, int m0, int r, int nw, int blocks, siz
 
 }  // namespace
 
-// Whether the blocks of gemm_wide.h take a call (us per launch, before -> blocks): always beyond 16 rows (12288 x 4096 at
-// 32 rows 42 -> 27, 4096 x 11008 103 -> 31); nine to 16 rows that the tiles above cannot take (4096 x 11008 at 16
-// rows 53 -> 26, 5001 x 2056 21 -> 9.6) or that leave compute units few of them (4096 x 4096 10.4 -> 9.2, but 12288 x
-// 4096 22.5 -> 24.4); five to eight rows of a matrix of middling size (4096 x 4096 at 8 rows 12.0 -> 8.9, 9728 x 896
-// 10.4 -> 8.2, but 22016 x 4096 37 -> 41, 896 x 4864 9.5 -> 9.5, 4096 x 11008 at five rows 21.6 -> 23.3).
+// Whether the blocks of gemm_wide.h take a call (the lines and their figures: routes.h).
 static bool blocks_preferred(const Bf16Args& a, const DeviceInfo& dev)
 {
     const char* from = knob("MXFP4_WIDE_FROM");                      // measurement only
@@ -898,11 +895,7 @@ static bool blocks_preferred(const Bf16Args& a, const DeviceInfo& dev)
         return false;
     if (from)
         return a.m >= atoi(from);
-    if (a.m > 16)
-        return true;
-    if (a.m > 8)
-        return !bf16_mfma_can_run(a, dev) || (a.n >= 2048 && a.n <= 20 * dev.cus);
-    return a.m >= 5 && a.n >= 2048 && a.n <= 40 * dev.cus && (a.k <= 8192 || a.m > 6);
+    return wide_bf16_preferred(a.m, a.n, a.k, bf16_mfma_can_run(a, dev), dev.cus, dev.lds_bytes);
 }
 
 // Largest K whose activation copy (one row) fits the LDS.

@@ -127,4 +127,27 @@ inline bool wide_format_preferred(int m, int n, int k, int bits, bool tiles, int
     return n <= 32 * unit && (m >= 5 || k <= 12288);
 }
 
+// BF16 weights.  `tiles`: the matrix-core tiles could take a call of nine to 16 rows in one pass.
+inline bool wide_bf16_preferred(int m, int n, int k, bool tiles, int cus, int lds_bytes)
+{
+    const int unit = cus;
+    // Beyond 16 rows always (12288 x 4096 at 32 rows 42 -> 27, 4096 x 11008 103 -> 31).  Nine to 16 rows that the tiles
+    // cannot take (4096 x 11008 at 16 rows 53 -> 26, 5001 x 2056 21 -> 9.6), or that leave the units few of them while K is
+    // whole pairs of phases (4096 x 4096 0.92 of the tiles, 2048 x 2048 1.05, 4096 x 512 1.22, 5120 x 3072 1.09).
+    if (m > 16)
+        return true;
+    if (m > 8)
+        return !tiles || (k % 2048 == 0 && n >= 12 * unit && n <= 20 * unit);
+    // Five to eight rows of a matrix of middling size, against the vector ALUs in one pass: 4096 x 4096 at 8 rows 0.88 of
+    // them, but 2048 x 5120 1.22, 5120 x 2560 1.15, 8192 x 6144 1.09, 10240 x 2048 1.13, 22016 x 4096 37 -> 41.
+    // Rows that just fit the LDS stay (4096 x 10240 at 8 rows 1.03, 8192 x 10240 1.18); those that do not ran in phases
+    // (4096 x 16384 0.74 of them, 8192 x 16384 1.1).
+    if (m < 5 || n <= 8 * unit || n > 40 * unit)
+        return false;
+    const bool phased = m > 6 && 16 * k > lds_bytes;
+    if (n <= 16 * unit)
+        return k <= (m > 6 ? 9216 : 8192) || phased;
+    return n > 32 * unit ? k <= 1024 : k <= 2048 || (phased && n <= 20 * unit);
+}
+
 }  // namespace mxfp4

@@ -19,6 +19,10 @@ extern "C" int format(int m, int n, int k, int bits, int tiles)
 {
     return wide_format_preferred(m, n, k, bits, tiles != 0, 256, 160 * 1024);
 }
+extern "C" int bf16(int m, int n, int k, int tiles)
+{
+    return wide_bf16_preferred(m, n, k, tiles != 0, 256, 160 * 1024);
+}
 extern "C" int ragged(int m, int n, int k) { return wide_ragged_preferred(m, n, k, 256, 160 * 1024); }
 """
 
@@ -99,3 +103,17 @@ def test_other_formats(rules, bits, m, n, k, blocks):
     width = 4 if m <= 4 else 8 if m <= 8 else 16
     fits = (k // 128 + 3) // 4 * 1024 * width + 16384 <= 160 * 1024
     assert bool(rules.format(m, n, k, bits, int(fits))) == blocks
+
+
+@pytest.mark.parametrize("m,n,k,tiles,blocks", [
+    (9, 4096, 512, True, False), (16, 5120, 1024, True, False), (16, 5120, 3072, True, False), (9, 2048, 2048, True, False),
+    (16, 4096, 4096, True, True), (9, 4096, 2048, True, True), (12, 12288, 4096, True, False), (9, 16, 8, False, True),
+    (16, 4096, 11008, False, True), (17, 12288, 4096, True, True),
+    (5, 2048, 5120, False, False), (8, 5120, 2560, False, False), (6, 8192, 6144, False, False), (7, 10240, 2048, False, False),
+    (8, 4096, 10240, False, False), (7, 8192, 10240, False, False), (8, 8192, 16384, False, False), (5, 4096, 11008, False, False),
+    (8, 22016, 4096, False, False), (4, 4096, 4096, False, False), (8, 1000, 4096, False, False),
+    (8, 4096, 4096, False, True), (5, 2050, 8, False, True), (7, 4096, 16384, False, True), (8, 5120, 11008, False, True),
+    (6, 8192, 2048, False, True), (5, 9216, 1024, False, True),
+])
+def test_unquantised_weights(rules, m, n, k, tiles, blocks):
+    assert bool(rules.bf16(m, n, k, int(tiles))) == blocks
