@@ -966,12 +966,7 @@ hipError_t launch_bf16_gemv(const Bf16Args& a, const DeviceInfo& dev, int* parts
         while (mt > 1 && (size_t)mt * a.k * 2 > (size_t)dev.lds_bytes)
             mt = mt > 4 ? 4 : mt >> 1;
         const size_t lds = (size_t)mt * a.k * 2 < 256 ? 256 : (size_t)mt * a.k * 2;   // the argmax combine needs a few bytes
-        int per_cu = (int)((size_t)dev.lds_bytes / lds);
-        per_cu = per_cu < 1 ? 1 : (per_cu > 4 ? 4 : per_cu);
-        // five and more long rows: two workgroups of eight waves (12288 x 4096 at five rows 20.5 us, 21.6 with
-        // three of four; 9728 x 896 8.5 against 8.2)
-        if (mt > 4 && a.k >= 2048 && per_cu > 2)
-            per_cu = 2;
+        const int per_cu = bf16_workgroups_per_unit(mt, a.n, a.k, dev.cus, dev.lds_bytes);
         // 16 waves per CU: larger workgroups when the activation copy leaves room for fewer of them
         const int nw = per_cu >= 3 ? 4 : (per_cu == 2 ? 8 : 16);
         int blocks = (n_groups + nw - 1) / nw;

@@ -150,4 +150,15 @@ inline bool wide_bf16_preferred(int m, int n, int k, bool tiles, int cus, int ld
     return n > 32 * unit ? k <= 1024 : k <= 2048 || (phased && n <= 20 * unit);
 }
 
+// Workgroups per compute unit of a vector-ALU pass of `rows` BF16 rows: as many copies of the rows as the LDS holds, up to
+// four (of four waves each, two of eight, one of 16).  Five rows and more of a long K take two where the
+// matrix is not short (12288 x 4096 at five rows 20.5 us, 21.6 with three; but 1000 x 2048 at eight 7.2, 6.3 with four), three
+// rows that would take three take two, 16 waves instead of 12 (4096 x 7168 12.6 us, 14.8 with three).
+inline int bf16_workgroups_per_unit(int rows, int n, int k, int cus, int lds_bytes)
+{
+    const int bytes = rows * k * 2, fit = lds_bytes / (bytes < 256 ? 256 : bytes);      // (a pick needs a few bytes)
+    const int most = rows > 4 && k > 2048 && n >= 8 * cus ? 2 : rows == 3 && fit == 3 ? 2 : 4;
+    return fit < 1 ? 1 : fit < most ? fit : most;
+}
+
 }  // namespace mxfp4

@@ -23,6 +23,7 @@ extern "C" int bf16(int m, int n, int k, int tiles)
 {
     return wide_bf16_preferred(m, n, k, tiles != 0, 256, 160 * 1024);
 }
+extern "C" int workgroups(int rows, int n, int k) { return bf16_workgroups_per_unit(rows, n, k, 256, 160 * 1024); }
 extern "C" int ragged(int m, int n, int k) { return wide_ragged_preferred(m, n, k, 256, 160 * 1024); }
 """
 
@@ -117,3 +118,24 @@ def test_other_formats(rules, bits, m, n, k, blocks):
 ])
 def test_unquantised_weights(rules, m, n, k, tiles, blocks):
     assert bool(rules.bf16(m, n, k, int(tiles))) == blocks
+
+
+@pytest.mark.parametrize("rows,n,k,want", [
+    (3, 4096, 7168, 2), (3, 4096, 8192, 2), (3, 4096, 6824, 4), (3, 4096, 13104, 2), (3, 4096, 27304, 1),
+    (8, 1000, 2048, 4), (8, 12288, 2048, 4), (8, 2000, 3072, 3), (8, 2048, 3072, 2), (5, 12288, 4096, 2), (8, 12288, 10240, 1),
+    (4, 12288, 6824, 3), (2, 64, 8, 4), (1, 64, 65536, 1), (4, 64, 65536, 1),
+])
+def test_workgroups_of_a_vector_pass(rules, rows, n, k, want):
+    assert rules.workgroups(rows, n, k) == want
+
+
+def test_later_passes_have_no_fewer_workgroups(rules):
+    # a pick reads as many partial winners per row as the first pass has workgroups
+    def blocks(rows, n, k):
+        per_unit = rules.workgroups(rows, n, k)
+        waves = 4 if per_unit >= 3 else 8 if per_unit == 2 else 16
+        return min(-(-n // waves), 256 * per_unit)
+    for n in (1, 300, 2000, 2048, 4096, 20000):
+        for k in range(8, 65537, 488):
+            if 16 * k <= 160 * 1024:
+                assert all(blocks(rows, n, k) >= blocks(8, n, k) for rows in range(1, 8)), (n, k)
