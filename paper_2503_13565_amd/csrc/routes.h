@@ -54,10 +54,11 @@ inline bool wide_preferred(const TileCall& c)
         if (!c.split)
             return m > 4 && (n <= 48 * unit || k <= 14336);
         // K split: 8192 x 11008 at 5 rows 0.87 of it, 12288 x 28672 1.0, 18432 x 11008 1.07; pick 1000 x 20480 1.12;
-        // tile-major pick 1000 x 11008 1.04, 8192 x 20480 0.84, 16384 x 32768 1.06.
+        // tile-major pick 256 x 11008 1.07, 1000 x 11008 1.04 (taken all the same, so that it gives the row-major pick's
+        // bits), 1000 x 14336 1.13, 8192 x 20480 0.84, 16384 x 32768 1.06.
         if (c.tiled)
-            return k <= (n < 16 * unit ? 10240 : n < 24 * unit ? 16384 : 20480);
-        return m > 4 && n <= 64 * unit && (n < 4 * unit ? c.pick && k <= 10240 : k <= 14336);
+            return k <= (n <= unit ? 10240 : n < 16 * unit ? 11264 : n < 24 * unit ? 16384 : 20480);
+        return m > 4 && n <= 64 * unit && k <= 14336 && !(c.fused && n < 4 * unit);
     }
     // No workspace (row-major): narrower passes of eight or four rows, 0.3 to 0.8 of them.
     if (!c.split)

@@ -46,7 +46,7 @@ SLOWER = [                                                  # us per launch on t
     (8, 4096, 65536, "tw"), (5, 1000, 16384, "tw"), (3, 256, 24576, "t"), (8, 6144, 28672, "tw"),
     (9, 16, 28672, "tw"), (16, 1000, 11008, "tw"), (9, 2560, 2048, "t"), (16, 16384, 28672, "tw"),
     (17, 16, 28672, "tw"), (32, 1000, 65536, "tw"), (48, 16, 32768, "tw"), (64, 16, 49152, "tw"),
-    (5, 256, 24576, "wp"), (8, 1000, 20480, "wp"), (5, 1000, 12288, "twp"), (3, 2048, 20480, "wf"),
+    (5, 256, 24576, "wp"), (8, 1000, 20480, "wp"), (5, 1000, 12288, "twp"), (8, 256, 11008, "twp"), (3, 2048, 20480, "wf"),
     (8, 18432, 24576, "f"), (4, 2048, 24576, "f"), (17, 500, 32768, "w"), (32, 3000, 65536, "w"), (16, 5000, 11008, "w"),
 ]
 FASTER = [
@@ -54,7 +54,7 @@ FASTER = [
     (8, 4096, 11008, "w"), (8, 4096, 11008, "t"), (5, 12288, 14336, ""), (5, 24000, 65536, "t"), (8, 8192, 11008, "w"),
     (9, 4096, 11008, "w"), (16, 12288, 14336, "w"), (16, 1000, 11008, ""), (9, 22016, 4096, "f"), (16, 8192, 1024, "t"),
     (16, 24000, 65536, "tw"), (9, 8192, 20480, "tw"), (17, 256, 65536, ""), (96, 16, 49152, "w"), (16, 18432, 4096, "f"),
-    (8, 12288, 11008, "wp"), (8, 8192, 14336, "wf"), (5, 16, 11008, "f"), (16, 32000, 11008, "tw"),
+    (8, 12288, 11008, "wp"), (5, 300, 11008, "wp"), (5, 300, 11008, "twp"), (8, 8192, 14336, "wf"), (5, 16, 11008, "f"), (16, 32000, 11008, "tw"),
 ]
 
 
