@@ -932,8 +932,7 @@ hipError_t launch_bf16_gemv(const Bf16Args& a, const DeviceInfo& dev, int* parts
         // the phased kernel.
         int mt = left > 8 ? 8 : left;
         if ((size_t)mt * a.k * 2 > (size_t)dev.lds_bytes)
-            mt = left > 4 ? (left <= 6 && (size_t)6 * a.k * 2 <= (size_t)dev.lds_bytes ? 6 : 8)
-                          : (left > 2 ? 4 : (left > 1 ? 2 : 1));
+            mt = left > 4 ? 8 : (left > 2 ? 4 : (left > 1 ? 2 : 1));
         // The rows of the pass do not fit the LDS whole: K in phases, still one pass over the weights,
         // when a wave's rows fit its 64 lanes (one workgroup of 16 waves per compute unit).
         if (mt >= 2 && (size_t)mt * a.k * 2 > (size_t)dev.lds_bytes && !general_only) {
@@ -948,11 +947,11 @@ hipError_t launch_bf16_gemv(const Bf16Args& a, const DeviceInfo& dev, int* parts
                 (m0 == 0 || a.part_val == nullptr || pblocks == first_blocks)) {
                 hipError_t e;
                 if (r == 2)
-                    e = mt >= 6   ? launch_phased<8, 2>(a, m0, pblocks, phase_steps, dev.lds_bytes, stream)
+                    e = mt == 8   ? launch_phased<8, 2>(a, m0, pblocks, phase_steps, dev.lds_bytes, stream)
                         : mt == 4 ? launch_phased<4, 2>(a, m0, pblocks, phase_steps, dev.lds_bytes, stream)
                                   : launch_phased<2, 2>(a, m0, pblocks, phase_steps, dev.lds_bytes, stream);
                 else
-                    e = mt >= 6   ? launch_phased<8, 1>(a, m0, pblocks, phase_steps, dev.lds_bytes, stream)
+                    e = mt == 8   ? launch_phased<8, 1>(a, m0, pblocks, phase_steps, dev.lds_bytes, stream)
                         : mt == 4 ? launch_phased<4, 1>(a, m0, pblocks, phase_steps, dev.lds_bytes, stream)
                                   : launch_phased<2, 1>(a, m0, pblocks, phase_steps, dev.lds_bytes, stream);
                 if (e != hipSuccess)
