@@ -81,10 +81,27 @@ def test_matrix_core_passes(n, k, m):
 @pytest.mark.parametrize("n,k,m", [(2100, 28672, 8), (300, 11008, 8), (4100, 11008, 7), (70, 28672, 3),
                                    (2050, 20480, 16)])
 def test_long_k_passes_in_phases(n, k, m):
-    # the rows of a pass do not fit the LDS whole: K in phases, one pass over the weights
+    # the rows of a pass do not fit the LDS whole: K in phases, one pass over the weights, or (beyond 2048 weight rows, and
+    # beyond eight activation rows) the block kernel
     w = synth.weights_student_t(n, k, seed=1100 + n + k)
     x = synth.activations_outlier_channels(m, k, seed=1150 + m + k)
     run_case(w, x, "BF16 phased N=%d K=%d M=%d" % (n, k, m))
+
+
+@pytest.mark.parametrize("n,k,m", [(1030, 28672, 8), (2048, 20480, 7), (9001, 11016, 8)])
+def test_long_k_beyond_the_blocks(n, k, m):
+    # few weight rows, and two of them per group of a wave: K in phases on the vector ALUs
+    w = synth.weights_student_t(n, k, seed=1200 + n + k)
+    x = synth.activations_outlier_channels(m, k, seed=1250 + m + k)
+    run_case(w, x, "BF16 phased N=%d K=%d M=%d" % (n, k, m))
+
+
+@pytest.mark.parametrize("n,k,m", [(4100, 7176, 3), (1000, 2048, 8), (3000, 2056, 7), (1500, 8208, 3)])
+def test_workgroups_per_unit(n, k, m):
+    # both sides of the choice of workgroups per compute unit (checked on the CPU in test_routes.py)
+    w = synth.weights_student_t(n, k, seed=1300 + n + k)
+    x = synth.activations_outlier_channels(m, k, seed=1350 + m + k)
+    run_case(w, x, "BF16 N=%d K=%d M=%d" % (n, k, m))
 
 
 def test_matrix_core_exact_ties_pick_lowest_index():

@@ -93,9 +93,32 @@ def test_fused_on_tile_major_weights(n, k, m):
 
 
 def test_fused_split_in_space_many_tiles():
-    # 16 rows of K = 11008 do not fit the LDS and 12288 weight rows are too many tiles per workgroup
-    # for the in-kernel running sums: with a workspace the finish kernel applies the epilogue
+    # 16 rows of K = 11008 do not fit the LDS; 12288 weight rows go to the block kernel, the next test's are split
     fused_case(12288, 11008, 16, [AUTO], options=[(True, SWIGLU, True), (True, NONE, True)], what="split in space")
+
+
+@pytest.mark.parametrize("n,k,m", [(24832, 5120, 16), (17000, 8192, 9), (18432, 11008, 8)])
+def test_fused_split_in_space_beyond_the_blocks(n, k, m):
+    # rows that do not fit the LDS and too many tiles per workgroup for the in-kernel running sums or the block kernel:
+    # with a workspace K is split and the finish kernel applies the epilogue; checked on sampled pairs of weight rows
+    w = synth.weights_student_t(n, k, seed=9700 + n, device=DEV)
+    x = synth.activations_outlier_channels(m, k, seed=9750 + m, device=DEV)
+    q, s = binding.mxfp4_direct_cast(w)
+    g = torch.Generator().manual_seed(n)
+    even = 2 * torch.unique(torch.cat([torch.arange(10), torch.arange(n // 2 - 10, n // 2), torch.randint(0, n // 2, (50,), generator=g)]))
+    rows = torch.stack([even, even + 1], dim=1).reshape(-1)
+    y_ref, a_ref = oracle.woq_gemm(synth.to_bits(x), q.cpu()[rows].numpy(), s.cpu()[rows].numpy())
+    bias = bf16_randn((n,), 3)
+    ws = torch.empty((binding.mxfp4_woq_gemm_workspace_bytes(m, n, k),), dtype=torch.uint8, device=DEV)
+    for act in (NONE, SWIGLU):
+        cols = even // 2 if act == SWIGLU else rows
+        res = bf16_randn((m, n // 2 if act == SWIGLU else n), 4)
+        out_ref, a_out = oracle.epilogue(y_ref, a_ref, synth.to_bits(bias[rows]), synth.to_bits(res[:, cols].contiguous()), act)
+        for workspace in (None, ws):
+            y = binding.mxfp4_woq_gemm_fused(x, q, s, bias=bias.to(DEV), act=act, residual=res.to(DEV), workspace=workspace)
+            torch.cuda.synchronize()
+            assert_gemm_close(y[:, cols.to(DEV)], out_ref, a_out, "N=%d K=%d M=%d act=%d workspace %r"
+                              % (n, k, m, act, workspace is not None))
 
 
 def test_fused_llama_layer_shapes_auto():

@@ -66,16 +66,15 @@ def test_tiled_product_edge_shapes(n, k, m):
         assert ws_bytes > 0
         ws = torch.empty((ws_bytes,), dtype=torch.uint8, device=DEV)
         if m > 8:
-            # no workspace: refused; with one, K is split over grid rows
+            # no workspace: refused, also where the block kernel, which needs none, takes the call
             with pytest.raises(binding.Mxfp4Error) as e:
                 binding.mxfp4_woq_gemm_tiled(xg, tw)
             assert e.value.code == 6
         else:
-            # up to eight rows walk K in phases inside the workgroup, no workspace needed; with one, the
-            # same kernel where a workgroup has few tiles, else K split over grid rows
+            # up to eight rows need no workspace: K in phases inside the workgroup, or the block kernel
             y0 = binding.mxfp4_woq_gemm_tiled(xg, tw)
             torch.cuda.synchronize()
-            assert_gemm_close(y0, y_ref, a_ref, "tiled, K in phases, N=%d K=%d M=%d" % (n, k, m))
+            assert_gemm_close(y0, y_ref, a_ref, "tiled, no workspace, N=%d K=%d M=%d" % (n, k, m))
         y = binding.mxfp4_woq_gemm_tiled(xg, tw, workspace=ws)
     else:
         y = binding.mxfp4_woq_gemm_tiled(xg, tw)
@@ -87,6 +86,30 @@ def test_tiled_product_edge_shapes(n, k, m):
     idx, val = binding.mxfp4_woq_gemm_tiled_argmax(xg, tw)
     torch.cuda.synchronize()
     assert_argmax_ok(idx, val, y_ref, a_ref, "tiled argmax N=%d K=%d M=%d" % (n, k, m))
+
+
+@pytest.mark.parametrize("n,k,m,phases", [(25000, 12288, 5, True), (25000, 12288, 8, True), (5000, 28928, 3, True),
+                                          (8300, 24576, 16, False), (6000, 20608, 9, False)])
+def test_tiled_long_rows_of_several_tiles_per_workgroup(n, k, m, phases):
+    # what the block kernel does not take: K in phases without a workspace (up to eight rows), split over grid
+    # rows with one; checked on sampled weight rows, the pick on all of them against the product
+    w = synth.weights_student_t(n, k, seed=7300 + n, device=DEV)
+    x = synth.activations_outlier_channels(m, k, seed=8300 + m, device=DEV)
+    q, s = binding.mxfp4_direct_cast(w)
+    tw = binding.mxfp4_tile_repack(q, s)
+    g = torch.Generator().manual_seed(n)
+    rows = torch.unique(torch.cat([torch.arange(20), torch.arange(n - 20, n), torch.randint(0, n, (80,), generator=g)]))
+    y_ref, a_ref = oracle.woq_gemm(synth.to_bits(x), q.cpu()[rows].numpy(), s.cpu()[rows].numpy())
+    ws = torch.empty((binding.mxfp4_woq_gemm_workspace_bytes(m, n, k),), dtype=torch.uint8, device=DEV)
+    for workspace in ([None] if phases else []) + [ws]:
+        y = binding.mxfp4_woq_gemm_tiled(x, tw, workspace=workspace)
+        torch.cuda.synchronize()
+        assert_gemm_close(y[:, rows.to(DEV)], y_ref, a_ref, "N=%d K=%d M=%d workspace %r" % (n, k, m, workspace is not None))
+    idx, val = binding.mxfp4_woq_gemm_tiled_argmax(x, tw)
+    at_pick = y.gather(1, idx.long()[:, None])[:, 0].float()
+    top = y.float().max(dim=1).values                   # (the pick may take another kernel: sums in another order)
+    assert bool(((val - at_pick).abs() <= 2.0 ** -7 * at_pick.abs()).all())
+    assert bool((top - at_pick <= 2.0 ** -7 * top.abs()).all())
 
 
 def test_tiled_llama_lm_head_verify():

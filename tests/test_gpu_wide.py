@@ -1,6 +1,6 @@
 """Parity of the block kernel for many activation rows and for K that is no multiple of 128
-(csrc/gemm_wide.hip; arXiv 2503.13565, section 3.4.3): plain, fused and pick forms against the CPU oracle
-at the edges of its blocks, one case at least per block shape."""
+(csrc/gemm_wide.h; arXiv 2503.13565, section 3.4.3): plain, fused and pick forms against the CPU oracle
+at the edges of its blocks, and every block shape in every weight layout (block_sizes.py)."""
 import functools
 
 import pytest
@@ -11,6 +11,7 @@ from paper_2503_13565_amd import binding, synth
 
 pytestmark = pytest.mark.gpu
 
+from block_sizes import BLOCK_SIZES  # noqa: E402
 from helpers import DEV, assert_argmax_ok, assert_cast_bit_exact, assert_gemm_close  # noqa: E402
 
 
@@ -148,6 +149,46 @@ def test_unquantised_weights(m, n, k):
         assert_argmax_ok(idx, val, y_ref, a_ref, tag)
     wide[:, k:] = float("nan")                              # what lies between the rows is not read into them
     assert torch.equal(binding.mxfp4_bf16_gemm(x, wide[:, :k]), y), tag
+
+
+CASES = [(name, *size) for kind, names in (("mxfp4", ["mxfp4"]), ("tiled", ["tiled"]), (8, ["e4m3", "e5m2"]),
+                                           (6, ["e2m3", "e3m2"]), (2, ["t2"]), ("bf16", ["bf16"]))
+         for name in names for size in BLOCK_SIZES[kind]]
+
+
+@pytest.mark.parametrize("name,m,n,k", CASES)
+def test_every_block_shape_of_every_layout(name, m, n, k):
+    # the product on sampled weight rows, those at the edges of blocks and tiles among them; the pick's value is the
+    # product's sum before its rounding
+    tag = "%s M=%d N=%d K=%d" % (name, m, n, k)
+    print(tag, flush=True)
+    w = synth.weights_student_t(n, k, seed=9200 + n, device=DEV)
+    x = synth.activations_outlier_channels(m, k, seed=9250 + m, device=DEV)
+    g = torch.Generator().manual_seed(n)
+    rows = torch.unique(torch.cat([torch.arange(min(n, 33)), torch.arange(max(0, n - 33), n), torch.randint(0, n, (70,), generator=g)]))
+    if name == "bf16":
+        ref, q = oracle.bf16_gemm, (w,)
+        y, (idx, val) = binding.mxfp4_bf16_gemm(x, w), binding.mxfp4_bf16_gemm_argmax(x, w)
+        ref_args = (synth.to_bits(w[rows.to(DEV)].contiguous()),)
+    elif name in FORMATS:
+        ref, cast, product, pick = FORMATS[name]
+        q = cast(w)
+        y, (idx, val) = product(x, *q), pick(x, *q)
+    else:
+        ref, q = oracle.woq_gemm, binding.mxfp4_direct_cast(w)
+        if name == "tiled":
+            tw = binding.mxfp4_tile_repack(*q)
+            ws = torch.empty((max(8, binding.mxfp4_woq_gemm_workspace_bytes(m, n, k)),), dtype=torch.uint8, device=DEV)
+            y, (idx, val) = binding.mxfp4_woq_gemm_tiled(x, tw, workspace=ws), binding.mxfp4_woq_gemm_tiled_argmax(x, tw)
+        else:
+            y, (idx, val) = binding.mxfp4_woq_gemm(x, *q), binding.mxfp4_woq_gemm_argmax(x, *q)
+    if name != "bf16":
+        ref_args = tuple(t.cpu()[rows].numpy() for t in q)
+    torch.cuda.synchronize()
+    y_ref, a_ref = ref(synth.to_bits(x), *ref_args)
+    assert_gemm_close(y[:, rows.to(DEV)], y_ref, a_ref, tag)
+    at_pick = y.gather(1, idx.long()[:, None])[:, 0]
+    assert torch.equal(val.to(torch.bfloat16), at_pick) and torch.equal(at_pick, y.max(dim=1).values), tag
 
 
 def test_nan_stays_in_its_row_and_block():

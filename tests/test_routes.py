@@ -2,9 +2,12 @@
 the kernels that were measured faster for them (256 compute units, 160 KiB of LDS)."""
 import ctypes
 import os
+import re
 import subprocess
 
 import pytest
+
+from block_sizes import BLOCK_SIZES
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2503_13565_amd", "csrc")
 
@@ -139,3 +142,34 @@ def test_later_passes_have_no_fewer_workgroups(rules):
         for k in range(8, 65537, 488):
             if 16 * k <= 160 * 1024:
                 assert all(blocks(rows, n, k) >= blocks(8, n, k) for rows in range(1, 8)), (n, k)
+
+
+def picked(table, m, n, k):
+    """The block shape that a call takes (pick_shape of csrc/gemm_wide.h), and by how much it is the cheapest."""
+    cost = []
+    for i, (wm, wn, wk, mf, nf, start, step, next_start, next_step) in enumerate(table):
+        bm, bn, wk = int(wm * mf * 16), int(wn * nf * 16), int(wk)
+        rounds = -(-(-(-m // bm) * -(-n // bn)) // 256)
+        steps = -(-(-(-k // 128)) // wk) * wk
+        cost.append((start + step * steps + (rounds - 1) * (next_start + next_step * steps), i))
+    cost.sort()
+    return cost[0][1], cost[1][0] / cost[0][0] - 1
+
+
+@pytest.mark.parametrize("kind,source,name,never", [
+    ("mxfp4", "gemm_wide.hip", "kCosts", []), ("tiled", "gemm_wide.hip", "kCosts", []), (8, "gemm_wide_fmt.hip", "kCosts8", [7]),
+    (6, "gemm_wide_fmt.hip", "kCosts6", []), (2, "gemm_wide_fmt.hip", "kCosts2", []), ("bf16", "gemm_wide_bf16.hip", "kCosts", [7])])
+def test_sizes_that_take_every_block_shape(rules, kind, source, name, never):
+    body = re.search(r"const Cost %s\[\] = \{(.*?)\n\};" % name, open(os.path.join(CSRC, source)).read(), re.S).group(1)
+    table = [[float(v.rstrip("f")) for v in row.split(",")] for row in re.findall(r"\{([^{}]*)\}", body)]
+    assert [picked(table, *size)[0] for size in BLOCK_SIZES[kind]] == [i for i in range(len(table)) if i not in never]
+    for m, n, k in BLOCK_SIZES[kind]:
+        assert picked(table, m, n, k)[1] > 0.005                # (the kernel's sums are in 32 bits)
+        if kind == "mxfp4":
+            assert all(asked(rules, m, n, k, form) for form in ("", "f", "wp"))
+        elif kind == "tiled":
+            assert asked(rules, m, n, k, "tw") and asked(rules, m, n, k, "twp")
+        elif kind == "bf16":
+            assert rules.bf16(m, n, k, int(k % 128 == 0))
+        else:
+            assert rules.format(m, n, k, kind, 1)
