@@ -61,8 +61,9 @@ enum {
 };
 
 /* Kernel families the dispatcher can be forced to (tests and measurements); AUTO picks by M:
- * one or two rows take VALU_REG when the shape allows it, else VALU_CVT; three or more take MFMA or, with many
- * rows or a K that is no multiple of 128, blocks of rows that walk K once (a family that cannot be forced). */
+ * one or two rows take VALU_REG when the shape allows it, else VALU_CVT; three or more take MFMA or, where it is faster
+ * (many rows, rows that do not fit the LDS whole, a K that is no multiple of 128), blocks of rows that walk K once
+ * (a family that cannot be forced). */
 enum {
     MXFP4_PATH_AUTO = 0,
     MXFP4_PATH_VALU_BITS = 1, /* wave-per-row GEMV, nibbles decoded with plain integer/FP32 ops  */
@@ -260,7 +261,8 @@ int mxfp4_woq_gemm_path(const void* x_bf16, int64_t M, int64_t ldx,
  * The same product with a caller-provided scratch buffer.  When the activation rows of a pass do
  * not fit the LDS of a compute unit whole (M * K large), the MFMA path cuts K into phases.  With
  * `workspace` the phases run side by side on different compute units and a second kernel adds
- * their FP32 partial products, which live in the workspace, in a fixed order: the fast form.
+ * their FP32 partial products, which live in the workspace, in a fixed order: the fast form of that path.  (AUTO
+ * takes blocks of rows that walk K once where those are faster, and leaves the workspace alone then.)
  * Without it (NULL, or smaller than mxfp4_woq_gemm_workspace_bytes, which is 0 when no split is
  * needed) the call still works: the phases then run one after the other inside the kernel (up to
  * eight rows: about as fast as the split for matrices with one tile of 16 output rows per compute

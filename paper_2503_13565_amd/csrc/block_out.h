@@ -1,4 +1,4 @@
-// What the block kernels (gemm_wide.hip, gemm_rows.hip) do with a finished 16 x 16 fragment of sums: BF16 store,
+// What the block kernel (gemm_wide.h) does with a finished 16 x 16 fragment of sums: BF16 store,
 // bias / gate / residual behind the product, or the row's best value for the fused pick.
 #pragma once
 

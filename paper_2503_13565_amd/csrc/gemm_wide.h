@@ -24,11 +24,14 @@
 //     unaligned) every byte pulled a cache line, 104 us instead of 130 on the example below.
 //   - Prompts take blocks of 128 rows with all eight waves side by side along the weight rows, so that no
 //     weight is decoded or fetched twice in a block: 92 us against 104 for 2 x 4 waves.
-//   - Bound by the matrix pipe at the clock the power limit leaves (with the loads and the LDS reads taken out
-//     the example takes 69 us, with all-zero operands 80), by the activations' way through the L2 and LDS for some
-//     tens of rows.  Measured, us per call, 16-row passes -> here: 22016 x 4096 with the gate at 509 rows
-//     436 -> 79 (a library product of BF16 weights of that shape: 91), 12288 x 4096 at 32 rows 18.6 -> 12.2
-//     (host time included), 4096 x 1376 at 7 rows (two rows per pass on the vector ALUs before) 18.3 -> 4.7.
+//   - A prompt is bound by the matrix pipe and what feeds it at the clock the power limit leaves: the pipe is busy in 55 % of
+//     the cycles at 2.15 GHz, the LDS in 43 % (with the loads and the LDS reads taken out the example took 69 us, with
+//     all-zero operands 80).  Some tens of rows are bound by the activations' way through the L2 and LDS (at 32 rows
+//     the waves wait in 43 % of their cycles).  Measured, us from launch to launch, passes of 16 rows -> here:
+//     22016 x 4096 with the gate at 509 rows 436 -> 79 to 86 by the box (a library product of BF16 weights of that
+//     shape: 91), 12288 x 4096 at 32 rows 19.9 -> 13.5 with the weights from memory, 18.5 -> 11.0 with three sets
+//     of them in rotation, 4096 x 1376 at 7 rows (two rows per pass on the vector ALUs before) 18.7 -> 5.0 (the
+//     kernel alone 4.9).
 //   - A block past the end of K (K % 128 != 0, the steps that round a phase up) is a load past the
 //     descriptor: zero weights against zero activations.
 #pragma once
@@ -377,7 +380,10 @@ hipError_t launch_block(const Args& a, const DeviceInfo& dev, hipStream_t stream
 
 // A block shape with what it took, in microseconds: the first block of a compute unit and every further one
 // as start + step x (steps of 128 along K, whole phases), measured with 256, 512 and 1024 blocks over K = 1024 and
-// 4096.  (Two blocks share a unit where LDS and registers allow.)
+// 4096 and drawn on beyond.  (Two blocks share a unit where LDS and registers allow.)  The tables of the other formats and
+// of BF16 were measured with a phase's stores behind its matrix instructions, and a difference that the noise hid is 0.
+// The pick against every shape, 42 or 43 sizes each: within 5 % of the best on 35 (row-major), 36 (tile-major), 39 (8-bit), 36
+// (6-bit), 32 (ternary) and 42 (BF16); at worst 1.20, 1.19, 1.45 (57344 x 1024 at 400 rows), 1.13, 1.15 and 1.05 of it.
 struct Cost {
     int wm, wn, wk, mf, nf;
     float first_start, first_step, next_start, next_step;

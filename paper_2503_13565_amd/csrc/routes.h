@@ -28,10 +28,10 @@ inline bool wide_preferred(const TileCall& c)
     if (m < 3)
         return false;
     if (c.fits) {
-        // Beyond 16 rows always: 12288 x 4096 at 32 rows 20.6 -> 12.0, tile-major 18.9 -> 12.2, 22016 x 4096 at 64 59 -> 24.
+        // Beyond 16 rows always: 12288 x 4096 at 32 rows 19.9 -> 13.5, tile-major 18.3 -> 11.7, 22016 x 4096 at 64 57 -> 23.
         // From nine rows on while a unit has one block (9728 x 896 7.3 -> 5.5, but 32000 x 4096 19.1 -> 19.2, 57344 x
         // 8192 61 -> 66): blocks of 96 rows pay for the rows that they lack (18432 x 4096 13.9 -> 14.6, 22016 15.8 ->
-        // 15.4) unless the epilogue's loads are hidden by it (18432 x 4096 with residual 0.9 of the tiles); one tile per
+        // 15.2) unless the epilogue's loads are hidden by it (18432 x 4096 with residual 0.9 of the tiles); one tile per
         // unit starts faster on the tiles (2560 x 2048 tile-major 4.7 -> 5.0) unless K is long enough (4096 x 4096 6.7 -> 6.0).
         if (m > 16)
             return true;
@@ -45,7 +45,7 @@ inline bool wide_preferred(const TileCall& c)
         if (n > 96 * unit)
             return false;
         // Plain products: K in phases inside a tile kernel, which walks one tile per unit as fast as a block and
-        // starts earlier: 4096 x 11008 at 8 rows 12.2 -> 10.8, 4096 x 28672 18.9 -> 22.8 at three; tile-major 1000 x 28672
+        // starts earlier: 4096 x 11008 at 8 rows 12.4 -> 11.7, 4096 x 28672 18.9 -> 22.8 at three; tile-major 1000 x 28672
         // 15.0 -> 19.9.  Every further tile fetches the rows again: 12288 x 14336 at 5 rows 0.74 of it.
         if (plain && (n <= 16 * unit || !c.split))
             return n <= 16 * unit ? m > 4 && k <= (c.tiled ? 11264 : 14336) : c.tiled ? m > 3 || k <= 28672 : m > 4 || k <= 20480;
@@ -83,7 +83,7 @@ inline bool wide_preferred(const TileCall& c)
 }
 
 // K that is no multiple of 128, from three rows on, where the vector ALUs take passes of two rows: 4096 x 1376 at 7 rows
-// 18.3 -> 4.5.  Three rows of a handful of weight rows, or of up to four per unit with a long K, stay there while
+// 18.7 -> 5.0.  Three rows of a handful of weight rows, or of up to four per unit with a long K, stay there while
 // two rows fit the LDS (1 x 8224 6.8 -> 7.6, 256 x 28704 20.3 -> 21.9, 1000 x 40992 0.78 of it).
 inline bool wide_ragged_preferred(int m, int n, int k, int cus, int lds_bytes)
 {
@@ -97,10 +97,10 @@ inline bool wide_ragged_preferred(int m, int n, int k, int cus, int lds_bytes)
 inline bool wide_format_preferred(int m, int n, int k, int bits, bool tiles, int cus, int lds_bytes)
 {
     const int unit = cus;
-    // Beyond 16 rows always (E4M3 12288 x 4096 at 32 rows 33 -> 18, E2M3 28 -> 18).
+    // Beyond 16 rows always (E4M3 12288 x 4096 at 32 rows 33 -> 19, E2M3 27 -> 19).
     if (m > 16)
         return true;
-    // The ternary codes went over the weights once per four rows (22016 x 4096 at 8 rows 51 -> 16).  In one such pass, up
+    // The ternary codes went over the weights once per four rows (22016 x 4096 at 8 rows 51 -> 17).  In one such pass, up
     // to eight weight rows per unit, the vector ALUs are faster from K = 2560 (1000 x 8192 at four rows 1.14 of them) until
     // a unit has room for one copy of the four rows only (1000 x 12288 0.89); a short K leaves nothing but
     // the start of the blocks, once per tile of many (24000 x 128 1.28, 24000 x 512 1.07, 24000 x 768 0.52).
@@ -111,7 +111,7 @@ inline bool wide_format_preferred(int m, int n, int k, int bits, bool tiles, int
             return (m == 4 || n >= 4 * unit) && (k <= 2048 || 16 * k > lds_bytes);
         return m >= 3 && (n <= 16 * unit || k >= 768);
     }
-    // Rows that do not fit ran as passes of four (E4M3 4096 x 11008 at 16 rows 54 -> 15).
+    // Rows that do not fit ran as passes of four (E4M3 4096 x 11008 at 16 rows 55 -> 17).
     if (m >= 5 && !tiles)
         return true;
     // Else while a unit has few tiles, the 8-bit elements from five rows on: 8192 x 4096 0.78 of the tiles, 12288 x 4096 0.93,
@@ -132,8 +132,8 @@ inline bool wide_format_preferred(int m, int n, int k, int bits, bool tiles, int
 inline bool wide_bf16_preferred(int m, int n, int k, bool tiles, int cus, int lds_bytes)
 {
     const int unit = cus;
-    // Beyond 16 rows always (12288 x 4096 at 32 rows 42 -> 27, 4096 x 11008 103 -> 31).  Nine to 16 rows that the tiles
-    // cannot take (4096 x 11008 at 16 rows 53 -> 26, 5001 x 2056 21 -> 9.6), or that leave the units few of them while K is
+    // Beyond 16 rows always (12288 x 4096 at 32 rows 41 -> 26, 4096 x 11008 98 -> 30).  Nine to 16 rows that the tiles
+    // cannot take (4096 x 11008 at 16 rows 49 -> 25, 5001 x 2056 20 -> 11), or that leave the units few of them while K is
     // whole pairs of phases (4096 x 4096 0.92 of the tiles, 2048 x 2048 1.05, 4096 x 512 1.22, 5120 x 3072 1.09).
     if (m > 16)
         return true;
