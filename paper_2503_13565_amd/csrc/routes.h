@@ -100,6 +100,8 @@ inline bool wide_format_preferred(int m, int n, int k, int bits, bool tiles, int
     // Beyond 16 rows always (E4M3 12288 x 4096 at 32 rows 33 -> 19, E2M3 27 -> 19).
     if (m > 16)
         return true;
+    if (m < 3)
+        return false;
     // The ternary codes went over the weights once per four rows (22016 x 4096 at 8 rows 51 -> 17).  In one such pass, up
     // to eight weight rows per unit, the vector ALUs are faster from K = 2560 (1000 x 8192 at four rows 1.14 of them) until
     // a unit has room for one copy of the four rows only (1000 x 12288 0.89); a short K leaves nothing but
@@ -109,7 +111,7 @@ inline bool wide_format_preferred(int m, int n, int k, int bits, bool tiles, int
             return true;
         if (n <= 8 * unit)
             return (m == 4 || n >= 4 * unit) && (k <= 2048 || 16 * k > lds_bytes);
-        return m >= 3 && (n <= 16 * unit || k >= 768);
+        return n <= 16 * unit || k >= 768;
     }
     // Rows that do not fit ran as passes of four (E4M3 4096 x 11008 at 16 rows 55 -> 17).
     if (m >= 5 && !tiles)
@@ -121,8 +123,8 @@ inline bool wide_format_preferred(int m, int n, int k, int bits, bool tiles, int
     // 6-bit: 8192 x 4096 0.88 of the tiles, but 9216 x 4096 1.12 and more; three and four rows unless N is small too (896 x 4864
     // 7.0 -> 7.3) or K is long (3072 x 16384 1.06), where the decode kernel takes passes of two again from
     // where four rows do not fit (2048 x 24576 0.9, 8192 x 24576 0.6).
-    if (m < 3 || n < 8 * unit)
-        return m >= 5 && n <= 32 * unit;
+    if (n < 8 * unit)
+        return m >= 5;
     if (m <= 4 && 8 * k > lds_bytes)
         return n <= 40 * unit;
     return n <= 32 * unit && (m >= 5 || k <= 12288);

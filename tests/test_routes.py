@@ -144,6 +144,16 @@ def test_later_passes_have_no_fewer_workgroups(rules):
                 assert all(blocks(rows, n, k) >= blocks(8, n, k) for rows in range(1, 8)), (n, k)
 
 
+def test_one_and_two_rows_never_take_the_blocks(rules):
+    for m in (1, 2):
+        for n in (1, 16, 1000, 1024, 1500, 2048, 4096, 9000, 32000):
+            for k in (128, 1024, 4096, 11008, 28672, 65536):
+                for split in (0, 1):
+                    assert not any(rules.mx(m, n, k, fits, split, tiled, fused, 0) for fits in (0, 1) for tiled in (0, 1) for fused in (0, 1))
+                assert not any(rules.format(m, n, k, bits, fits) for bits in (2, 6, 8) for fits in (0, 1))
+                assert not any(rules.bf16(m, n, k, tiles) for tiles in (0, 1)) and not rules.ragged(m, n, k + 32)
+
+
 def picked(table, m, n, k):
     """The block shape that a call takes (pick_shape of csrc/gemm_wide.h), and by how much it is the cheapest."""
     cost = []
