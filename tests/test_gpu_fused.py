@@ -63,6 +63,11 @@ def test_fused_register_gemv(n, k, m):
     fused_case(n, k, m, [REG, AUTO], what="register GEMV")
 
 
+@pytest.mark.parametrize("n,k", [(2050, 14336), (2100, 16512), (3000, 22528), (2050, 28672)])
+def test_fused_register_gemv_long_k(n, k):
+    fused_case(n, k, 1, [REG, AUTO], what="register GEMV, eight steps and more")
+
+
 @pytest.mark.parametrize("n,k", [(2, 32), (34, 96), (250, 4096), (1000, 160), (300, 16384)])
 @pytest.mark.parametrize("m", [1, 2, 5])
 def test_fused_general_gemv(n, k, m):
