@@ -105,7 +105,10 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
     u32x4_t xl[MT][XPR];
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
-        const u32x4_t* xp = reinterpret_cast<const u32x4_t*>(a.x + (int64_t)(m0 + m) * a.ldx);    // (a pass has all its rows)
+        // a pass has all its rows; the 8-bit one keeps the clamp, without which it waits longer for its first rows
+        // (6144 x 1024 at two rows 6.8 -> 7.1 us)
+        const int row = kBits == 8 ? min(m0 + m, a.m - 1) : m0 + m;
+        const u32x4_t* xp = reinterpret_cast<const u32x4_t*>(a.x + (int64_t)row * a.ldx);
 #pragma unroll
         for (int i = 0; i < XPR; ++i)
             xl[m][i] = xp[min(tid + i * T, chunks - 1)];
