@@ -1,5 +1,5 @@
-// What the block kernel (gemm_wide.h) does with a finished 16 x 16 fragment of sums: BF16 store,
-// bias / gate / residual behind the product, or the row's best value for the fused pick.
+// What the block kernel (gemm_wide.h) does with the finished sums of a block: BF16 store, bias / gate / residual behind
+// the product, or the row's best value for the fused pick.
 #pragma once
 
 #include "common.h"
@@ -24,78 +24,112 @@ inline BlockOut block_out(const GemmArgs& a, const Epilogue* epi)
             a.parts, epi ? epi->ldr : 0, epi ? epi->act : MXFP4_ACT_NONE};
 }
 
-// Lane (li, lg) holds the sums of weight rows col .. col + 3 for activation row `row`.  Pick: the best of
-// the fragment's 16 weight rows goes to *slot (one per activation row, written by lanes 0 .. 15).
-__device__ __forceinline__ void emit_fragment(const BlockOut& a, const f32x4_t sum, int row, int col, float2* slot)
+// `N` neighbouring 16-bit values at any even address (global accesses need no more than the element's alignment).
+template <int N>
+struct Packed {
+    typedef __attribute__((ext_vector_type(N / 2))) unsigned int type;
+    typedef type anywhere __attribute__((aligned(2)));
+};
+template <int N>
+__device__ __forceinline__ void load_bf16(const uint16_t* from, int count, float* to)
 {
-    const int n = a.n, m = a.m;
-    if (a.part_val != nullptr) {
-        float best = -INFINITY;
-        int idx = 0x7FFFFFFF;
+    if (count >= N) {
+        const typename Packed<N>::type v = *reinterpret_cast<const typename Packed<N>::anywhere*>(from);
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (col + r < n && sum[r] > best) {                     // rows ascend: lowest index wins ties
-                best = sum[r];
-                idx = col + r;
-            }
-#pragma unroll
-        for (int off = 16; off < 64; off <<= 1) {
-            const float v = __shfl_xor(best, off);
-            const int o = __shfl_xor(idx, off);
-            if (v > best || (v == best && o < idx)) {
-                best = v;
-                idx = o;
-            }
-        }
-        if ((threadIdx.x & 63) < 16)
-            *slot = make_float2(best, __int_as_float(idx));
-        return;
-    }
-    if (row >= m || col >= n)
-        return;
-    float z[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-        z[r] = sum[r] + (a.bias && col + r < n ? bf16_bits_to_f32(a.bias[col + r]) : 0.f);
-    uint16_t* y = a.y + (int64_t)row * a.ldy;
-    const uint16_t* res = a.residual ? a.residual + (int64_t)row * a.ldr : nullptr;
-    const bool gated = a.act == MXFP4_ACT_SWIGLU;
-    if (gated) {                                                    // rows (0, 1) and (2, 3) are (gate, up) pairs
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-            if (col + 2 * c < n)
-                y[(col >> 1) + c] = f32_to_bf16_rne(silu_gate(z[2 * c], z[2 * c + 1]) +
-                                                    (res ? bf16_bits_to_f32(res[(col >> 1) + c]) : 0.f));
-        return;
-    }
-    uint16_t o[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-        o[r] = f32_to_bf16_rne(z[r] + (res && col + r < n ? bf16_bits_to_f32(res[col + r]) : 0.f));
-    if ((a.ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(a.y) & 7) == 0 && col + 4 <= n) {
-        *reinterpret_cast<uint2*>(y + col) = make_uint2(o[0] | (uint32_t)o[1] << 16, o[2] | (uint32_t)o[3] << 16);
+        for (int i = 0; i < N; ++i)
+            to[i] = bf16_bits_to_f32(v[i >> 1] >> (16 * (i & 1)) & 0xFFFFu);
     } else {
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (col + r < n)
-                y[col + r] = o[r];
+        for (int i = 0; i < N; ++i)
+            to[i] = i < count ? bf16_bits_to_f32(from[i]) : 0.f;
+    }
+}
+template <int N>
+__device__ __forceinline__ void store_bf16(uint16_t* to, int count, const float* v)
+{
+    if (count >= N) {
+        typename Packed<N>::type o;
+#pragma unroll
+        for (int i = 0; i < N; i += 2)
+            o[i >> 1] = f32_to_bf16_rne(v[i]) | (uint32_t)f32_to_bf16_rne(v[i + 1]) << 16;
+        *reinterpret_cast<typename Packed<N>::anywhere*>(to) = o;
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if (i < count)
+                to[i] = f32_to_bf16_rne(v[i]);
     }
 }
 
-// Pick: the block's winner of one activation row out of its `count` fragments (columns ascend).
-__device__ __forceinline__ void publish_winner(const BlockOut& a, const float2* slots, int count, int row, int part)
+// What becomes of `kRows` rows of kCols finished sums each, which sit in the LDS (kStride floats from row to row).
+// Row r is activation row row_of(r), its first sum weight row n0; `part` is the block column of the pick.
+template <int kRows, int kCols, int kStride, class RowOf>
+__device__ __forceinline__ void emit_rows(const BlockOut& a, const float* tile, int n0, int part, RowOf row_of)
 {
-    float best = -INFINITY;
-    int idx = 0x7FFFFFFF;
-    for (int e = 0; e < count; ++e) {
-        const float2 c = slots[e];
-        if (c.x > best) {
-            best = c.x;
-            idx = __float_as_int(c.y);
+    constexpr int kThreads = 512, kChunks = kCols / 8;
+    const int tid = threadIdx.x;
+    if (a.part_val != nullptr) {                                        // sixteen threads per row
+        for (int r = tid >> 4; r < kRows; r += kThreads / 16) {
+            float best = -INFINITY;
+            int idx = 0x7FFFFFFF;
+            for (int c = tid & 15; c < kCols; c += 16) {                // columns ascend: lowest index wins ties
+                const float v = tile[r * kStride + c];
+                if (n0 + c < a.n && v > best) {
+                    best = v;
+                    idx = n0 + c;
+                }
+            }
+#pragma unroll
+            for (int off = 1; off < 16; off <<= 1) {
+                const float v = __shfl_xor(best, off);
+                const int o = __shfl_xor(idx, off);
+                if (v > best || (v == best && o < idx)) {
+                    best = v;
+                    idx = o;
+                }
+            }
+            const int row = row_of(r);
+            if ((tid & 15) == 0 && row < a.m) {
+                a.part_val[(int64_t)row * a.parts + part] = best;
+                a.part_idx[(int64_t)row * a.parts + part] = idx;
+            }
+        }
+        return;
+    }
+#pragma unroll 1
+    for (int e = tid; e < kRows * kChunks; e += kThreads) {
+        const int r = e / kChunks, c = e % kChunks * 8, row = row_of(r), col = n0 + c;
+        if (row >= a.m || col >= a.n)
+            continue;
+        const f32x4_t low = *reinterpret_cast<const f32x4_t*>(tile + r * kStride + c);
+        const f32x4_t high = *reinterpret_cast<const f32x4_t*>(tile + r * kStride + c + 4);
+        float z[8] = {low[0], low[1], low[2], low[3], high[0], high[1], high[2], high[3]};
+        if (a.bias) {
+            float b[8];
+            load_bf16<8>(a.bias + col, a.n - col, b);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                z[i] += b[i];
+        }
+        uint16_t* y = a.y + (int64_t)row * a.ldy;
+        const uint16_t* res = a.residual ? a.residual + (int64_t)row * a.ldr : nullptr;
+        float add[8] = {};
+        if (a.act == MXFP4_ACT_SWIGLU) {                                // rows (2 i, 2 i + 1) are (gate, up) pairs
+            if (res)
+                load_bf16<4>(res + (col >> 1), (a.n - col + 1) >> 1, add);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                z[i] = silu_gate(z[2 * i], z[2 * i + 1]) + add[i];
+            store_bf16<4>(y + (col >> 1), (a.n - col + 1) >> 1, z);
+        } else {
+            if (res)
+                load_bf16<8>(res + col, a.n - col, add);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                z[i] += add[i];
+            store_bf16<8>(y + col, a.n - col, z);
         }
     }
-    a.part_val[(int64_t)row * a.parts + part] = best;
-    a.part_idx[(int64_t)row * a.parts + part] = idx;
 }
 
 // Workgroups go to the eight dies round robin: a die takes a run of neighbouring blocks, the blocks of one

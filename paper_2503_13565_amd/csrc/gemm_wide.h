@@ -17,8 +17,14 @@
 //     barrier per phase, which waits for LDS traffic only (with the writes behind the matrix instructions, in front
 //     of the barrier: 4096 x 4096 at 128 rows 13.5 us against 12.2, 12288 x 4096 24.0 against 22.5, at 509 rows
 //     58.5 against 55.5).
-//   - LDS layout [step of the phase][row][16 chunks], chunk c of row r at position c ^ (r % 16): the
-//     threads of a store cover whole rows and the 16 rows of an operand read hit different banks.
+//   - LDS layout [step of the phase][row][16 chunks]: the chunk that lane group lg reads for matrix instruction j
+//     sits at position (4 j + lg) ^ (r % 16) of row r.  The threads of a store cover whole rows; a read of 16 bytes per lane
+//     is served in four turns of rows 0-3 and 12-15 of one lane group and rows 4-11 of its neighbour, which this
+//     position sends to different banks (with 4 lg + j in its place they met in pairs: 18 % of a prompt's cycles).
+//   - The finished sums leave through the LDS (block_out.h): whole rows of the block, 16 bytes per thread, in a short loop.
+//     Stored from the accumulators, in 32-byte pieces by code unrolled over every fragment, they took 6 us of a
+//     prompt: 22016 x 128 at 509 rows with the gate 20.2 -> 14.2 us, 22016 x 4096 79.2 -> 75.8, 14000 x 6016 at 399 rows
+//     77.6 -> 73.4, 28500 x 2432 at 95 25.4 -> 23.2.
 //   - The scale bytes of two phases travel together, one dword per step and row, through the LDS: as byte
 //     loads by the lanes that use them (which the kernel does where K % 128 != 0 leaves the dwords
 //     unaligned) every byte pulled a cache line, 104 us instead of 130 on the example below.
@@ -28,7 +34,7 @@
 //     the cycles at 2.15 GHz, the LDS in 43 % (with the loads and the LDS reads taken out the example took 69 us, with
 //     all-zero operands 80).  Some tens of rows are bound by the activations' way through the L2 and LDS (at 32 rows
 //     the waves wait in 43 % of their cycles).  Measured, us from launch to launch, passes of 16 rows -> here:
-//     22016 x 4096 with the gate at 509 rows 436 -> 79 to 86 by the box (a library product of BF16 weights of that
+//     22016 x 4096 with the gate at 509 rows 436 -> 76 to 81 by the box (a library product of BF16 weights of that
 //     shape: 91), 12288 x 4096 at 32 rows 19.9 -> 13.5 with the weights from memory, 18.5 -> 11.0 with three sets
 //     of them in rotation, 4096 x 1376 at 7 rows (two rows per pass on the vector ALUs before) 18.7 -> 5.0 (the
 //     kernel alone 4.9).
@@ -66,14 +72,24 @@ struct Args {
     BlockOut out;
 };
 
+// Finished sums on their way out: floats from row to row, and how many rows of the block take a turn together where the
+// waves do not share K (as many as the activations' buffers hold).
+constexpr int tile_stride(int bn) { return bn + 4; }
+constexpr int tile_rows(int wm, int mf, int bn, int bytes)
+{
+    int pf = mf;
+    while (pf > 1 && wm * pf * 16 * tile_stride(bn) * 4 > bytes)
+        pf /= 2;
+    return wm * pf * 16;
+}
+
 constexpr size_t lds_bytes(Kind w, int wm, int wn, int wk, int mf, int nf)
 {
-    const size_t xs = (size_t)2 * wk * wm * mf * 16 * 256 +             // two buffers of one phase
-                      (w == kBf16 ? 0 : (size_t)2 * wn * nf * 16 * scale_row_bytes(wk));    // and two of the scales
+    const int bm = wm * mf * 16, bn = wn * nf * 16, x = 2 * wk * bm * 256;  // two buffers of one phase
+    const size_t xs = (size_t)x + (w == kBf16 ? 0 : (size_t)2 * bn * scale_row_bytes(wk));      // and two of the scales
     const size_t red = wk > 1 ? (size_t)8 * mf * nf * 1024 : 0;         // the waves' partial sums, afterwards
-    const size_t table = (size_t)wm * wn * mf * nf * 16 * 8;            // pick: a winner per fragment and row
-    const size_t most = xs > red ? xs : red;
-    return wk > 1 ? most + table : most > table ? most : table;         // (WK = 1: the table takes the buffers' place)
+    const size_t tile = (size_t)(wk > 1 ? bm : tile_rows(wm, mf, bn, x)) * tile_stride(bn) * 4;
+    return xs > red + tile ? xs : red + tile;
 }
 
 // Eight codes of the 2-bit format (16 bits of `c`) -> eight MXFP4 nibbles with the same values (+-1.0 or +-0).
@@ -126,6 +142,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
     constexpr int BM = WM * MF * 16, BN = WN * NF * 16;
     constexpr int CA = WK * BM * 16 / kThreads;                         // activation chunks per thread and phase
     static_assert(CA >= 1 && CA * kThreads == WK * BM * 16, "whole chunks");
+    static_assert(lds_bytes(kW, WM, WN, WK, MF, NF) <= 160 * 1024, "the LDS of a compute unit");
     constexpr int kRowChunks = WK * 16;                                 // chunks of one row in a phase
     constexpr int kRowStep = kThreads / kRowChunks;                     // rows between a thread's chunks
     constexpr int kBuf = WK * BM * 16;                                  // chunks of one LDS buffer
@@ -248,11 +265,12 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
         }
         ++ld_q;
     };
+    auto chunk_at = [](int c) { return kW == kBf16 ? c : (c & 3) << 2 | c >> 2; };
     auto x_store = [&](int b) {
 #pragma unroll
         for (int i = 0; i < CA; ++i) {
             const int r = x_row + i * kRowStep;
-            xs[b * kBuf + ((xc >> 4) * BM + r) * 16 + ((xc & 15) ^ (r & 15))] = xr[i];
+            xs[b * kBuf + ((xc >> 4) * BM + r) * 16 + (chunk_at(xc & 15) ^ (r & 15))] = xr[i];
         }
     };
     issue_scales(0);
@@ -311,7 +329,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
                     u32x4_t xf[MF];
 #pragma unroll
                     for (int i = 0; i < MF; ++i)
-                        xf[i] = xb[i * 256 + ((kW == kBf16 ? 4 * j + lg : 4 * lg + j) ^ li)];
+                        xf[i] = xb[i * 256 + ((4 * j + lg) ^ li)];
 #pragma unroll
                     for (int f = 0; f < NF; ++f) {
                         const u32x4_t w = operand<kW>(sl.q[f], six[kBits == 6 ? f : 0], scl[f], j);
@@ -328,22 +346,29 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
     }
 
     // Output fragment (i, f) of block position (wm, wn): lane (li, lg) holds weight rows 4 lg + r for
-    // activation row li.
-    constexpr size_t kXBytes = (size_t)2 * kBuf * 16 + (kScaled ? 2 * kSBuf : 0);
-    constexpr size_t kRedBytes = WK > 1 ? (size_t)8 * MF * NF * 1024 : 0;
-    float2* table = reinterpret_cast<float2*>(smem + (WK == 1 ? 0 : kXBytes > kRedBytes ? kXBytes : kRedBytes));
-    auto emit = [&](const f32x4_t sum, int i, int f) {
-        const int r = (wm * MF + i) * 16 + li, c = wn * NF + f;
-        emit_fragment(out, sum, m0 + r, n0 + c * 16 + 4 * lg, &table[r * (WN * NF) + c]);
-    };
+    // activation row li.  The sums go through the LDS, so that whole rows are stored.
+    constexpr int kStride = tile_stride(BN);
     if constexpr (WK == 1) {
+        float* tile = reinterpret_cast<float*>(smem);
+        constexpr int PF = tile_rows(WM, MF, BN, kBuf * 32) / (WM * 16);                     // fragment rows of a wave per turn
 #pragma unroll
-        for (int i = 0; i < MF; ++i)
+        for (int p = 0; p < MF / PF; ++p) {
+            if (p > 0)
+                lds_barrier();
 #pragma unroll
-            for (int f = 0; f < NF; ++f)
-                emit(acc[i][f], i, f);
+            for (int i = 0; i < PF; ++i)
+#pragma unroll
+                for (int f = 0; f < NF; ++f)
+                    *reinterpret_cast<f32x4_t*>(tile + ((wm * PF + i) * 16 + li) * kStride + (wn * NF + f) * 16 + 4 * lg) =
+                        acc[p * PF + i][f];
+            lds_barrier();
+            emit_rows<WM * PF * 16, BN, kStride>(out, tile, n0, tn, [&](int r) {
+                return m0 + r / (PF * 16) * (MF * 16) + p * (PF * 16) + r % (PF * 16);
+            });
+        }
     } else {
         f32x4_t* red = reinterpret_cast<f32x4_t*>(smem);               // [position][fragment][wk][lane]
+        float* tile = reinterpret_cast<float*>(smem + (size_t)8 * MF * NF * 1024);
         const int base = (wm * WN + wn) * MF * NF;
 #pragma unroll
         for (int i = 0; i < MF; ++i)
@@ -356,13 +381,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
 #pragma unroll
             for (int w = 1; w < WK; ++w)
                 sum += red[((base + e) * WK + w) * 64 + lane];
-            emit(sum, e / NF, e % NF);
+            *reinterpret_cast<f32x4_t*>(tile + ((wm * MF + e / NF) * 16 + li) * kStride + (wn * NF + e % NF) * 16 + 4 * lg) = sum;
         }
-    }
-    if (out.part_val != nullptr) {
         lds_barrier();
-        if (tid < BM && m0 + tid < m)
-            publish_winner(out, &table[tid * (WN * NF)], WN * NF, m0 + tid, tn);
+        emit_rows<BM, BN, kStride>(out, tile, n0, tn, [&](int r) { return m0 + r; });
     }
 }
 
