@@ -61,73 +61,85 @@ __device__ __forceinline__ void store_bf16(uint16_t* to, int count, const float*
     }
 }
 
-// What becomes of `kRows` rows of kCols finished sums each, which sit in the LDS (kStride floats from row to row).
-// Row r is activation row row_of(r), its first sum weight row n0; `part` is the block column of the pick.
-template <int kRows, int kCols, int kStride, class RowOf>
-__device__ __forceinline__ void emit_rows(const BlockOut& a, const float* tile, int n0, int part, RowOf row_of)
+// `N` neighbouring sums of activation row `row`, from weight row `col` on (a multiple of N): bias, gate, residual, store.
+template <int N>
+__device__ __forceinline__ void emit_sums(const BlockOut& a, const float (&sums)[N], int row, int col)
 {
-    constexpr int kThreads = 512, kChunks = kCols / 8;
-    const int tid = threadIdx.x;
-    if (a.part_val != nullptr) {                                        // sixteen threads per row
-        for (int r = tid >> 4; r < kRows; r += kThreads / 16) {
-            float best = -INFINITY;
-            int idx = 0x7FFFFFFF;
-            for (int c = tid & 15; c < kCols; c += 16) {                // columns ascend: lowest index wins ties
-                const float v = tile[r * kStride + c];
-                if (n0 + c < a.n && v > best) {
-                    best = v;
-                    idx = n0 + c;
-                }
-            }
-#pragma unroll
-            for (int off = 1; off < 16; off <<= 1) {
-                const float v = __shfl_xor(best, off);
-                const int o = __shfl_xor(idx, off);
-                if (v > best || (v == best && o < idx)) {
-                    best = v;
-                    idx = o;
-                }
-            }
-            const int row = row_of(r);
-            if ((tid & 15) == 0 && row < a.m) {
-                a.part_val[(int64_t)row * a.parts + part] = best;
-                a.part_idx[(int64_t)row * a.parts + part] = idx;
-            }
-        }
+    if (row >= a.m || col >= a.n)
         return;
+    float z[N], add[N] = {};
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        z[i] = sums[i];
+    if (a.bias) {
+        float b[N];
+        load_bf16<N>(a.bias + col, a.n - col, b);
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            z[i] += b[i];
     }
+    uint16_t* y = a.y + (int64_t)row * a.ldy;
+    const uint16_t* res = a.residual ? a.residual + (int64_t)row * a.ldr : nullptr;
+    if (a.act == MXFP4_ACT_SWIGLU) {                                    // rows (2 i, 2 i + 1) are (gate, up) pairs
+        const int left = (a.n - col + 1) >> 1;
+        if (res)
+            load_bf16<N / 2>(res + (col >> 1), left, add);
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i)
+            z[i] = silu_gate(z[2 * i], z[2 * i + 1]) + add[i];
+        store_bf16<N / 2>(y + (col >> 1), left, z);
+    } else {
+        if (res)
+            load_bf16<N>(res + col, a.n - col, add);
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            z[i] += add[i];
+        store_bf16<N>(y + col, a.n - col, z);
+    }
+}
+
+// Rows of finished sums in the LDS, kStride floats from row to row; row r is activation row row_of(r), its first sum weight
+// row n0.
+template <int kRows, int kCols, int kStride, class RowOf>
+__device__ __forceinline__ void emit_rows(const BlockOut& a, const float* tile, int n0, RowOf row_of)
+{
+    constexpr int kChunks = kCols / 8;
 #pragma unroll 1
-    for (int e = tid; e < kRows * kChunks; e += kThreads) {
-        const int r = e / kChunks, c = e % kChunks * 8, row = row_of(r), col = n0 + c;
-        if (row >= a.m || col >= a.n)
-            continue;
-        const f32x4_t low = *reinterpret_cast<const f32x4_t*>(tile + r * kStride + c);
-        const f32x4_t high = *reinterpret_cast<const f32x4_t*>(tile + r * kStride + c + 4);
-        float z[8] = {low[0], low[1], low[2], low[3], high[0], high[1], high[2], high[3]};
-        if (a.bias) {
-            float b[8];
-            load_bf16<8>(a.bias + col, a.n - col, b);
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                z[i] += b[i];
+    for (int e = threadIdx.x; e < kRows * kChunks; e += 512) {
+        const f32x4_t* at = reinterpret_cast<const f32x4_t*>(tile + e / kChunks * kStride + e % kChunks * 8);
+        const f32x4_t low = at[0], high = at[1];
+        const float sums[8] = {low[0], low[1], low[2], low[3], high[0], high[1], high[2], high[3]};
+        emit_sums(a, sums, row_of(e / kChunks), n0 + e % kChunks * 8);
+    }
+}
+
+// Pick: the best of every such row, by sixteen threads, to column `part` of the partial winners.
+template <int kRows, int kCols, int kStride, class RowOf>
+__device__ __forceinline__ void pick_rows(const BlockOut& a, const float* tile, int n0, int part, RowOf row_of)
+{
+    for (int r = threadIdx.x >> 4; r < kRows; r += 512 / 16) {
+        float best = -INFINITY;
+        int idx = 0x7FFFFFFF;
+        for (int c = threadIdx.x & 15; c < kCols; c += 16) {            // columns ascend: lowest index wins ties
+            const float v = tile[r * kStride + c];
+            if (n0 + c < a.n && v > best) {
+                best = v;
+                idx = n0 + c;
+            }
         }
-        uint16_t* y = a.y + (int64_t)row * a.ldy;
-        const uint16_t* res = a.residual ? a.residual + (int64_t)row * a.ldr : nullptr;
-        float add[8] = {};
-        if (a.act == MXFP4_ACT_SWIGLU) {                                // rows (2 i, 2 i + 1) are (gate, up) pairs
-            if (res)
-                load_bf16<4>(res + (col >> 1), (a.n - col + 1) >> 1, add);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                z[i] = silu_gate(z[2 * i], z[2 * i + 1]) + add[i];
-            store_bf16<4>(y + (col >> 1), (a.n - col + 1) >> 1, z);
-        } else {
-            if (res)
-                load_bf16<8>(res + col, a.n - col, add);
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                z[i] += add[i];
-            store_bf16<8>(y + col, a.n - col, z);
+        for (int off = 1; off < 16; off <<= 1) {
+            const float v = __shfl_xor(best, off);
+            const int o = __shfl_xor(idx, off);
+            if (v > best || (v == best && o < idx)) {
+                best = v;
+                idx = o;
+            }
+        }
+        const int row = row_of(r);
+        if ((threadIdx.x & 15) == 0 && row < a.m) {
+            a.part_val[(int64_t)row * a.parts + part] = best;
+            a.part_idx[(int64_t)row * a.parts + part] = idx;
         }
     }
 }

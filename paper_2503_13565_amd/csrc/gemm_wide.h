@@ -16,15 +16,23 @@
 //     go to the LDS, beside this one's reads and matrix instructions, and the ones after it are asked for: one
 //     barrier per phase, which waits for LDS traffic only (with the writes behind the matrix instructions, in front
 //     of the barrier: 4096 x 4096 at 128 rows 13.5 us against 12.2, 12288 x 4096 24.0 against 22.5, at 509 rows
-//     58.5 against 55.5).
-//   - LDS layout [step of the phase][row][16 chunks]: the chunk that lane group lg reads for matrix instruction j
-//     sits at position (4 j + lg) ^ (r % 16) of row r.  The threads of a store cover whole rows; a read of 16 bytes per lane
-//     is served in four turns of rows 0-3 and 12-15 of one lane group and rows 4-11 of its neighbour, which this
-//     position sends to different banks (with 4 lg + j in its place they met in pairs: 18 % of a prompt's cycles).
+//     58.5 against 55.5).  A third LDS buffer, so that the reads of a phase start before its barrier, and a second set
+//     of registers for the activations were 1 to 10 % slower: the blocks that fit beside each other are worth more.
+//   - Operand reads run one matrix instruction ahead.  From four fragments of activations on the next read goes into the
+//     register that its fragment's instructions have just used, and the converts are spread between them: 64 x 4096
+//     weight rows at K = 4096 (four tiles of 64 rows) 16.6 -> 14.4 us, 192 rows wide 27.6 -> 26.8, prompts 1 %.
+//   - LDS layout [step of the phase][row][16 chunks]: chunk c of row r at position (c ^ (c & 4) * 2) ^ (r % 16).  A store
+//     of 16 bytes per lane is served eight lanes at a time, half a row; a read in turns of rows 0-3 and 12-15 of one lane
+//     group and rows 4-11 of its neighbour (from the counted conflicts): this position sends either to different banks.
+//     Without the middle term the reads met in pairs (18 % of a prompt's cycles), with 4 j + lg in its place the stores (748 x 6528
+//     at 20 rows 7.15 us against 6.85).
 //   - The finished sums leave through the LDS (block_out.h): whole rows of the block, 16 bytes per thread, in a short loop.
 //     Stored from the accumulators, in 32-byte pieces by code unrolled over every fragment, they took 6 us of a
 //     prompt: 22016 x 128 at 509 rows with the gate 20.2 -> 14.2 us, 22016 x 4096 79.2 -> 75.8, 14000 x 6016 at 399 rows
-//     77.6 -> 73.4, 28500 x 2432 at 95 25.4 -> 23.2.
+//     77.6 -> 73.4.  Where the waves share K, a thread adds the partial sums of its outputs and stores them.
+//   - Blocks of few rows keep a phase short (four or two steps instead of eight), so that several of them fit the LDS of a unit and
+//     one works while another waits: 32 weight rows x 1024 at 16 rows, 512 blocks, 6.4 -> 4.6 us, 96 weight rows 11.9 -> 7.7.  The
+//     short phase costs more per step, so the long one stays for a long K.
 //   - The scale bytes of two phases travel together, one dword per step and row, through the LDS: as byte
 //     loads by the lanes that use them (which the kernel does where K % 128 != 0 leaves the dwords
 //     unaligned) every byte pulled a cache line, 104 us instead of 130 on the example below.
@@ -35,9 +43,8 @@
 //     all-zero operands 80).  Some tens of rows are bound by the activations' way through the L2 and LDS (at 32 rows
 //     the waves wait in 43 % of their cycles).  Measured, us from launch to launch, passes of 16 rows -> here:
 //     22016 x 4096 with the gate at 509 rows 436 -> 76 to 81 by the box (a library product of BF16 weights of that
-//     shape: 91), 12288 x 4096 at 32 rows 19.9 -> 13.5 with the weights from memory, 18.5 -> 11.0 with three sets
-//     of them in rotation, 4096 x 1376 at 7 rows (two rows per pass on the vector ALUs before) 18.7 -> 5.0 (the
-//     kernel alone 4.9).
+//     shape: 91), 12288 x 4096 at 32 rows 18.5 -> 10.1 with three sets of weights in rotation, 22016 x 4096 with the
+//     gate 13.0, 28500 x 2432 at 95 rows 20.3, 5418 x 512 at 86 rows 3.9.
 //   - A block past the end of K (K % 128 != 0, the steps that round a phase up) is a load past the
 //     descriptor: zero weights against zero activations.
 #pragma once
@@ -131,9 +138,17 @@ __device__ __forceinline__ u32x4_t operand(const uint32_t* r, const u32x16_t& si
     return w;
 }
 
+// Waves per SIMD to keep registers for.  Two blocks of 128 rows and 128 weight rows, or 64 and 128, of MXFP4 or ternary weights
+// fit a compute unit side by side (one's barriers, start and end are hidden behind the other) if they make do with 128
+// registers, one or two less than the compiler would take: 512 blocks of 128 x 128 at K = 1024 23.2 us, 25.6 without.
+constexpr int block_waves(Kind w, int wm, int wk, int mf, int nf)
+{
+    return kind_bits(w) <= 4 && mf >= 4 && mf * nf == 8 && wk * wm * mf <= 8 ? 4 : 2;
+}
+
 // The leading arguments are scalars that arrive in registers when a wave starts; `out` is for the end.
 template <Kind kW, int WM, int WN, int WK, int MF, int NF>
-__global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* __restrict__ x,
+__global__ __launch_bounds__(kThreads, block_waves(kW, WM, WK, MF, NF)) void gemm_wide_kernel(const uint16_t* __restrict__ x,
                                                                 const uint8_t* __restrict__ q,
                                                                 const uint8_t* __restrict__ s, int n, int k, int m,
                                                                 int ldx, int ldw, int tiles_m, int tiles_n, BlockOut out)
@@ -265,7 +280,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
         }
         ++ld_q;
     };
-    auto chunk_at = [](int c) { return kW == kBf16 ? c : (c & 3) << 2 | c >> 2; };
+    auto chunk_at = [](int c) { return c ^ (c & 4) << 1; };
     auto x_store = [&](int b) {
 #pragma unroll
         for (int i = 0; i < CA; ++i) {
@@ -294,6 +309,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
             acc[i][f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const int x_read = (wk * BM + wm * MF * 16 + li) * 16;
     const int s_read = (wn * NF * 16 + li) * kSRow + wk * 4 + lg;
+    // The operand reads of matrix instructions j + 1 go out beside those of j: into a second set of registers, or, from
+    // four fragments of activations on, each into the register that its fragment's instructions have just read.
+    constexpr bool kRoll = MF >= 4;
+    u32x4_t xf[kRoll ? 1 : 2][MF];
 
     for (int u0 = 0; u0 < phases; u0 += 2) {
 #pragma unroll
@@ -313,6 +332,15 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
                 const uint8_t* sb = ss + ((u0 >> 1) & 1) * kSBuf + s_read + d * (WK * 4);
                 float scl[NF];
                 u32x16_t six[kBits == 6 ? NF : 1] = {};                 // 6-bit: one convert for the whole block
+                auto read_x = [&](int i, int j) { return xb[i * 256 + (chunk_at(kW == kBf16 ? 4 * j + lg : 4 * lg + j) ^ li)]; };
+                auto weights = [&](int f, int j) { return operand<kW>(sl.q[f], six[kBits == 6 ? f : 0], scl[f], j); };
+                auto multiply = [&](int i, int f, u32x4_t w, u32x4_t x) {
+                    acc[i][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w),
+                                                                        __builtin_bit_cast(bf16x8_t, x), acc[i][f], 0, 0, 0);
+                };
+#pragma unroll
+                for (int i = 0; i < MF; ++i)
+                    xf[0][i] = read_x(i, 0);
 #pragma unroll
                 for (int f = 0; f < NF; ++f) {
                     scl[f] = !kScaled ? 1.f : __uint_as_float((kRagged ? sl.s[f] : (uint32_t)sb[f * 16 * kSRow]) << 23);
@@ -324,19 +352,43 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
                             six[f] = __builtin_bit_cast(u32x16_t, __builtin_amdgcn_cvt_scalef32_pk32_bf16_fp6(packed, scl[f]));
                     }
                 }
+                if constexpr (kRoll) {
+                    u32x4_t w[2][NF];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    u32x4_t xf[MF];
+                    for (int f = 0; f < NF; ++f)
+                        w[0][f] = weights(f, 0);
 #pragma unroll
-                    for (int i = 0; i < MF; ++i)
-                        xf[i] = xb[i * 256 + ((4 * j + lg) ^ li)];
+                    for (int j = 0; j < 4; ++j)
 #pragma unroll
-                    for (int f = 0; f < NF; ++f) {
-                        const u32x4_t w = operand<kW>(sl.q[f], six[kBits == 6 ? f : 0], scl[f], j);
+                        for (int i = 0; i < MF; ++i) {
 #pragma unroll
-                        for (int i = 0; i < MF; ++i)
-                            acc[i][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                __builtin_bit_cast(bf16x8_t, w), __builtin_bit_cast(bf16x8_t, xf[i]), acc[i][f], 0, 0, 0);
+                            for (int f = 0; f < NF; ++f)
+                                multiply(i, f, w[j & 1][f], xf[0][i]);
+                            if (j < 3) {
+                                xf[0][i] = read_x(i, j + 1);
+#pragma unroll
+                                for (int f = 0; f < NF; ++f)            // the converts spread over the fragments
+                                    if (f * (MF - 1) / NF + 1 == i)
+                                        w[(j + 1) & 1][f] = weights(f, j + 1);
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if (j < 3)
+#pragma unroll
+                            for (int i = 0; i < MF; ++i)
+                                xf[(j + 1) & 1][i] = read_x(i, j + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int f = 0; f < NF; ++f) {
+                            const u32x4_t w = weights(f, j);
+#pragma unroll
+                            for (int i = 0; i < MF; ++i)
+                                multiply(i, f, w, xf[j & 1][i]);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
                     }
                 }
             }
@@ -362,13 +414,14 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
                     *reinterpret_cast<f32x4_t*>(tile + ((wm * PF + i) * 16 + li) * kStride + (wn * NF + f) * 16 + 4 * lg) =
                         acc[p * PF + i][f];
             lds_barrier();
-            emit_rows<WM * PF * 16, BN, kStride>(out, tile, n0, tn, [&](int r) {
-                return m0 + r / (PF * 16) * (MF * 16) + p * (PF * 16) + r % (PF * 16);
-            });
+            auto row_of = [&](int r) { return m0 + r / (PF * 16) * (MF * 16) + p * (PF * 16) + r % (PF * 16); };
+            if (out.part_val != nullptr)
+                pick_rows<WM * PF * 16, BN, kStride>(out, tile, n0, tn, row_of);
+            else
+                emit_rows<WM * PF * 16, BN, kStride>(out, tile, n0, row_of);
         }
     } else {
         f32x4_t* red = reinterpret_cast<f32x4_t*>(smem);               // [position][fragment][wk][lane]
-        float* tile = reinterpret_cast<float*>(smem + (size_t)8 * MF * NF * 1024);
         const int base = (wm * WN + wn) * MF * NF;
 #pragma unroll
         for (int i = 0; i < MF; ++i)
@@ -376,15 +429,40 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
             for (int f = 0; f < NF; ++f)
                 red[((base + i * NF + f) * WK + wk) * 64 + lane] = acc[i][f];
         lds_barrier();
-        for (int e = wk; e < MF * NF; e += WK) {                        // a fragment's sums, in wave order
-            f32x4_t sum = red[(base + e) * WK * 64 + lane];
+        // the sums of fragment (at / NF, at % NF) of a position, of one lane's place, in wave order
+        auto sum_of = [&](int at, int place) {
+            f32x4_t sum = red[at * WK * 64 + place];
 #pragma unroll
             for (int w = 1; w < WK; ++w)
-                sum += red[((base + e) * WK + w) * 64 + lane];
-            *reinterpret_cast<f32x4_t*>(tile + ((wm * MF + e / NF) * 16 + li) * kStride + (wn * NF + e % NF) * 16 + 4 * lg) = sum;
+                sum += red[(at * WK + w) * 64 + place];
+            return sum;
+        };
+        if (out.part_val != nullptr) {
+            float* tile = reinterpret_cast<float*>(smem + (size_t)8 * MF * NF * 1024);
+            for (int e = wk; e < MF * NF; e += WK)
+                *reinterpret_cast<f32x4_t*>(tile + ((wm * MF + e / NF) * 16 + li) * kStride + (wn * NF + e % NF) * 16 + 4 * lg) =
+                    sum_of(base + e, lane);
+            lds_barrier();
+            pick_rows<BM, BN, kStride>(out, tile, n0, tn, [&](int r) { return m0 + r; });
+        } else {
+            // straight from the partial sums: sixteen rows side by side, then the next columns; four sums per thread where
+            // that takes one turn (748 x 6528 at 20 rows 6.85 us with eight, 6.48), else eight
+            constexpr int kCols = BM * BN <= 4 * kThreads ? 4 : 8, kChunks = BN / kCols, kPerTile = 16 / kCols;
+#pragma unroll 1
+            for (int e = tid; e < BM * kChunks; e += kThreads) {
+                const int row = e & 15, c = (e >> 4) % kChunks, i = (e >> 4) / kChunks, col = c / kPerTile;
+                const int at = ((i / MF * WN + col / NF) * MF + i % MF) * NF + col % NF, place = c % kPerTile * (kCols * 4) + row;
+                float sums[kCols];
+#pragma unroll
+                for (int h = 0; h < kCols / 4; ++h) {
+                    const f32x4_t part = sum_of(at, place + 16 * h);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        sums[4 * h + r] = part[r];
+                }
+                emit_sums(out, sums, m0 + i * 16 + row, n0 + c * kCols);
+            }
         }
-        lds_barrier();
-        emit_rows<BM, BN, kStride>(out, tile, n0, tn, [&](int r) { return m0 + r; });
     }
 }
 
@@ -401,11 +479,12 @@ hipError_t launch_block(const Args& a, const DeviceInfo& dev, hipStream_t stream
 }
 
 // A block shape with what it took, in microseconds: the first block of a compute unit and every further one
-// as start + step x (steps of 128 along K, whole phases), measured with 256, 512 and 1024 blocks over K = 1024 and
-// 4096 and drawn on beyond.  (Two blocks share a unit where LDS and registers allow.)  The tables of the other formats and
-// of BF16 were measured with a phase's stores behind its matrix instructions, and a difference that the noise hid is 0.
-// The pick against every shape, 42 or 43 sizes each: within 5 % of the best on 35 (row-major), 36 (tile-major), 39 (8-bit), 36
-// (6-bit), 32 (ternary) and 42 (BF16); at worst 1.20, 1.19, 1.45 (57344 x 1024 at 400 rows), 1.13, 1.15 and 1.05 of it.
+// as start + step x (steps of 128 along K, whole phases).  MXFP4: the fit to 256, 512 and 1024 blocks, four and more of them
+// over the same weights, at K = 1024, 4096 and 10240 (within 1 to 4 %; several blocks share a unit where LDS and registers
+// allow); the pick against every shape at 50 sizes of 5 to 512 rows: within 5 % of the best on 34, at worst 1.16.  The tables
+// of the other formats and of BF16 were measured with a phase's stores behind its matrix instructions, with 256 to 1024 blocks
+// at K = 1024 and 4096, and a difference that the noise hid is 0; their pick is within 5 % on 39 of 43 (8-bit), 36 of 42 (6-bit), 32
+// (ternary) and 42 (BF16), at worst 1.45 (57344 x 1024 at 400 rows), 1.13, 1.15 and 1.05 of it.
 struct Cost {
     int wm, wn, wk, mf, nf;
     float first_start, first_step, next_start, next_step;

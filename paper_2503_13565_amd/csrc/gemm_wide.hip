@@ -8,29 +8,45 @@ namespace {
 using namespace wide;
 
 const Cost kCosts[] = {
-    {1, 1, 8, 1, 1, 4.23f, 0.055f, 1.16f, 0.049f},
-    {1, 1, 8, 1, 2, 4.51f, 0.075f, 1.40f, 0.073f},
-    {1, 1, 8, 1, 3, 4.66f, 0.112f, 1.62f, 0.096f},
-    {1, 1, 8, 1, 4, 4.67f, 0.155f, 1.73f, 0.123f},
-    {1, 1, 8, 1, 6, 5.29f, 0.211f, 3.88f, 0.179f},
-    {1, 1, 8, 1, 8, 5.86f, 0.276f, 4.65f, 0.240f},
-    {1, 1, 8, 2, 1, 5.10f, 0.099f, 3.34f, 0.103f},
-    {1, 1, 8, 2, 2, 5.59f, 0.129f, 3.95f, 0.108f},
-    {1, 1, 8, 2, 3, 5.68f, 0.175f, 4.01f, 0.155f},
-    {1, 1, 8, 2, 4, 6.05f, 0.192f, 4.71f, 0.156f},
-    {1, 1, 8, 2, 6, 7.21f, 0.287f, 5.86f, 0.240f},
-    {1, 2, 4, 4, 1, 4.45f, 0.304f, 2.94f, 0.259f},
-    {1, 2, 4, 4, 2, 5.60f, 0.346f, 4.50f, 0.296f},
-    {1, 2, 4, 4, 3, 6.92f, 0.426f, 5.63f, 0.365f},
-    {2, 2, 2, 4, 2, 7.68f, 0.609f, 5.36f, 0.601f},
-    {2, 2, 2, 4, 3, 9.76f, 0.749f, 7.03f, 0.718f},
-    {2, 4, 1, 4, 2, 9.24f, 0.924f, 0.75f, 0.972f},
-    {2, 4, 1, 4, 3, 11.60f, 1.275f, 5.75f, 1.423f},
-    {1, 8, 1, 8, 2, 14.14f, 1.536f, 10.05f, 1.691f},
-    {1, 8, 1, 8, 3, 17.04f, 2.171f, 14.60f, 2.183f},
-    {1, 4, 2, 4, 1, 4.45f, 0.401f, 1.63f, 0.305f},
-    {1, 4, 2, 4, 2, 6.68f, 0.500f, 2.07f, 0.422f},
-    {1, 4, 2, 4, 3, 8.60f, 0.643f, 4.77f, 0.792f},
+    {1, 1, 8, 1, 1, 3.46f, 0.068f, 0.92f, 0.051f},
+    {1, 1, 8, 1, 2, 3.83f, 0.089f, 1.10f, 0.079f},
+    {1, 1, 8, 1, 3, 4.19f, 0.117f, 1.39f, 0.103f},
+    {1, 1, 8, 1, 4, 4.44f, 0.144f, 1.71f, 0.127f},
+    {1, 1, 8, 1, 6, 5.12f, 0.198f, 3.73f, 0.189f},
+    {1, 2, 4, 1, 1, 2.92f, 0.100f, 0.28f, 0.088f},
+    {1, 2, 4, 1, 2, 3.15f, 0.159f, 0.63f, 0.138f},
+    {1, 2, 4, 1, 3, 3.44f, 0.218f, 1.06f, 0.191f},
+    {1, 4, 2, 1, 1, 2.73f, 0.185f, 0.30f, 0.139f},
+    {1, 4, 2, 1, 2, 2.90f, 0.300f, 0.55f, 0.265f},
+    {1, 4, 2, 1, 3, 3.26f, 0.423f, 0.82f, 0.379f},
+    {1, 1, 8, 2, 3, 5.54f, 0.151f, 3.95f, 0.142f},
+    {1, 2, 4, 2, 1, 3.23f, 0.142f, 0.70f, 0.120f},
+    {1, 2, 4, 2, 2, 3.68f, 0.196f, 1.08f, 0.172f},
+    {1, 2, 4, 2, 3, 4.20f, 0.258f, 1.47f, 0.228f},
+    {1, 2, 4, 2, 4, 4.64f, 0.311f, 3.14f, 0.304f},
+    {1, 4, 2, 2, 1, 3.20f, 0.220f, 0.49f, 0.188f},
+    {1, 4, 2, 2, 2, 3.61f, 0.329f, 0.97f, 0.306f},
+    {1, 4, 2, 2, 3, 4.61f, 0.451f, 0.98f, 0.452f},
+    {1, 4, 2, 2, 4, 5.03f, 0.574f, 2.87f, 0.615f},
+    {1, 8, 1, 2, 2, 4.08f, 0.653f, 0.37f, 0.681f},
+    {1, 2, 4, 3, 3, 5.43f, 0.298f, 3.67f, 0.312f},
+    {1, 4, 2, 3, 1, 3.35f, 0.272f, 0.72f, 0.243f},
+    {1, 4, 2, 3, 2, 4.89f, 0.381f, 0.80f, 0.395f},
+    {1, 4, 2, 3, 3, 5.92f, 0.535f, 2.68f, 0.605f},
+    {1, 2, 4, 4, 2, 4.71f, 0.289f, 3.35f, 0.271f},
+    {1, 2, 4, 4, 3, 5.79f, 0.358f, 4.14f, 0.371f},
+    {1, 4, 2, 4, 1, 3.44f, 0.327f, 0.99f, 0.296f},
+    {1, 8, 1, 4, 1, 4.63f, 0.552f, 0.62f, 0.534f},
+    {1, 4, 2, 4, 2, 5.59f, 0.452f, 2.59f, 0.488f},
+    {1, 4, 2, 4, 3, 5.84f, 0.655f, 3.00f, 0.697f},
+    {1, 8, 1, 4, 2, 6.37f, 0.863f, 0.55f, 0.964f},
+    {1, 8, 1, 6, 2, 8.95f, 1.145f, 2.96f, 1.343f},
+    {1, 8, 1, 6, 3, 11.31f, 1.690f, 7.65f, 1.784f},
+    {2, 4, 1, 4, 2, 7.33f, 0.903f, 0.35f, 1.004f},
+    {2, 4, 1, 4, 3, 8.79f, 1.244f, 2.56f, 1.413f},
+    {2, 2, 2, 4, 3, 7.10f, 0.688f, 3.33f, 0.775f},
+    {1, 8, 1, 8, 2, 9.90f, 1.478f, 5.53f, 1.669f},
+    {1, 8, 1, 8, 3, 12.04f, 2.153f, 7.99f, 2.292f},
 };
 
 #define MXFP4_WIDE(...)                                                                             \
@@ -41,24 +57,40 @@ hipError_t (*const kLaunch[][3])(const Args&, const DeviceInfo&, hipStream_t) = 
     MXFP4_WIDE(1, 1, 8, 1, 3),
     MXFP4_WIDE(1, 1, 8, 1, 4),
     MXFP4_WIDE(1, 1, 8, 1, 6),
-    MXFP4_WIDE(1, 1, 8, 1, 8),
-    MXFP4_WIDE(1, 1, 8, 2, 1),
-    MXFP4_WIDE(1, 1, 8, 2, 2),
+    MXFP4_WIDE(1, 2, 4, 1, 1),
+    MXFP4_WIDE(1, 2, 4, 1, 2),
+    MXFP4_WIDE(1, 2, 4, 1, 3),
+    MXFP4_WIDE(1, 4, 2, 1, 1),
+    MXFP4_WIDE(1, 4, 2, 1, 2),
+    MXFP4_WIDE(1, 4, 2, 1, 3),
     MXFP4_WIDE(1, 1, 8, 2, 3),
-    MXFP4_WIDE(1, 1, 8, 2, 4),
-    MXFP4_WIDE(1, 1, 8, 2, 6),
-    MXFP4_WIDE(1, 2, 4, 4, 1),
+    MXFP4_WIDE(1, 2, 4, 2, 1),
+    MXFP4_WIDE(1, 2, 4, 2, 2),
+    MXFP4_WIDE(1, 2, 4, 2, 3),
+    MXFP4_WIDE(1, 2, 4, 2, 4),
+    MXFP4_WIDE(1, 4, 2, 2, 1),
+    MXFP4_WIDE(1, 4, 2, 2, 2),
+    MXFP4_WIDE(1, 4, 2, 2, 3),
+    MXFP4_WIDE(1, 4, 2, 2, 4),
+    MXFP4_WIDE(1, 8, 1, 2, 2),
+    MXFP4_WIDE(1, 2, 4, 3, 3),
+    MXFP4_WIDE(1, 4, 2, 3, 1),
+    MXFP4_WIDE(1, 4, 2, 3, 2),
+    MXFP4_WIDE(1, 4, 2, 3, 3),
     MXFP4_WIDE(1, 2, 4, 4, 2),
     MXFP4_WIDE(1, 2, 4, 4, 3),
-    MXFP4_WIDE(2, 2, 2, 4, 2),
-    MXFP4_WIDE(2, 2, 2, 4, 3),
-    MXFP4_WIDE(2, 4, 1, 4, 2),
-    MXFP4_WIDE(2, 4, 1, 4, 3),
-    MXFP4_WIDE(1, 8, 1, 8, 2),
-    MXFP4_WIDE(1, 8, 1, 8, 3),
     MXFP4_WIDE(1, 4, 2, 4, 1),
+    MXFP4_WIDE(1, 8, 1, 4, 1),
     MXFP4_WIDE(1, 4, 2, 4, 2),
     MXFP4_WIDE(1, 4, 2, 4, 3),
+    MXFP4_WIDE(1, 8, 1, 4, 2),
+    MXFP4_WIDE(1, 8, 1, 6, 2),
+    MXFP4_WIDE(1, 8, 1, 6, 3),
+    MXFP4_WIDE(2, 4, 1, 4, 2),
+    MXFP4_WIDE(2, 4, 1, 4, 3),
+    MXFP4_WIDE(2, 2, 2, 4, 3),
+    MXFP4_WIDE(1, 8, 1, 8, 2),
+    MXFP4_WIDE(1, 8, 1, 8, 3),
 };
 #undef MXFP4_WIDE
 constexpr int kShapes = sizeof kCosts / sizeof kCosts[0];
