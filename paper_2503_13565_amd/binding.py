@@ -1,4 +1,5 @@
-"""Thin ctypes binding of ``include/mxfp4.h``: argument marshalling only.
+"""Thin ctypes binding of ``include/mxfp4.h``: argument marshalling only, for the common call of a product through the
+extension module ``_host``.
 
 Every step of the path runs in the HIP kernels of ``libmxfp4_hip.so``; torch supplies device
 memory and the current stream.  There is no fallback: if the library has not been built
@@ -41,6 +42,20 @@ EXPORTS = [
 
 _lib = None
 
+# What ``_host`` takes (csrc/host.cpp): plain tensors on the current device that pass every check below, outputs
+# allocated by the call.  It answers None to everything else, and the checks here take the call.
+_MX, _E4M3, _E2M3, _BF16, _TILED, _FMT = 0, 1, 2, 3, 4, 16
+
+
+def _product(*args):
+    load()                                          # (puts the extension's functions in the place of these two)
+    return _product(*args)
+
+
+def _verify(*args):
+    load()
+    return _verify(*args)
+
 
 class GemmDesc(ctypes.Structure):
     """``mxfp4_gemm_desc`` of the header, field for field."""
@@ -69,7 +84,7 @@ class Mxfp4Error(RuntimeError):
 
 def load() -> ctypes.CDLL:
     """Load the HIP library (torch first, so that both share one HIP runtime)."""
-    global _lib
+    global _lib, _product, _verify
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -176,6 +191,9 @@ def load() -> ctypes.CDLL:
         getattr(lib, name).restype = i32
     lib.mxfp4_last_error.restype = ctypes.c_char_p
     lib.mxfp4_version.restype = ctypes.c_char_p
+    from . import _host
+    _host.on_failure(_check)
+    _product, _verify = _host.product, _host.verify
     _lib = lib
     return lib
 
@@ -188,7 +206,7 @@ def _check(rc: int) -> None:
 # What surrounds a call costs more host time than the call's checks and as much as its launch, and most of the
 # products here are shorter on the device than that.  So addresses go to ctypes as plain integers, the stream is
 # asked for as the integer it is, and the device is switched only where another one is current (one product
-# 10.9 -> 7.1 us of host time; the launch itself is 3.5 of them).
+# 10.9 -> 6.9 us of host time; through the extension module 3.5).
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
 _stay = contextlib.nullcontext()
@@ -265,6 +283,10 @@ def mxfp4_woq_gemm(x: torch.Tensor, q: torch.Tensor, s: torch.Tensor, y: Optiona
                    path: int = PATH_AUTO, workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """y ``[M,N]`` BF16 = x ``[M,K]`` BF16 times dequant(q, s)^T.  With ``workspace`` (uint8, at least
     ``mxfp4_woq_gemm_workspace_bytes``) the call goes through ``mxfp4_woq_gemm_ws``."""
+    if y is None:
+        y = _product(_MX, x, q, s, 0, 0, False, None, 0, None, path, workspace)
+        if y is not None:
+            return y
     m, n, k, ldx = _gemm_shapes(x, q, s)
     if y is None:
         y = torch.empty((m, n), dtype=torch.bfloat16, device=x.device)
@@ -338,6 +360,10 @@ def _bf16_shapes(x, w):
 
 def mxfp4_bf16_gemm(x: torch.Tensor, w: torch.Tensor, y: Optional[torch.Tensor] = None) -> torch.Tensor:
     """y ``[M,N]`` BF16 = x ``[M,K]`` BF16 times w ``[N,K]``^T with unquantised BF16 weights."""
+    if y is None:
+        y = _product(_BF16, x, w, None, 0, 0, False, None, 0, None, 0, None)
+        if y is not None:
+            return y
     m, n, k, ldx, ldw = _bf16_shapes(x, w)
     if y is None:
         y = torch.empty((m, n), dtype=torch.bfloat16, device=x.device)
@@ -385,6 +411,9 @@ def _verify_buffers(x, m, draft, need, workspace):
 def mxfp4_woq_gemm_verify(x: torch.Tensor, q: torch.Tensor, s: torch.Tensor, draft: Optional[torch.Tensor],
                           workspace: Optional[torch.Tensor] = None):
     """(accept int32 ``[2]`` = (G, next token), argmax int32 ``[M]``, max float32 ``[M]``)."""
+    got = _verify(_MX, x, q, s, 0, 0, draft, workspace)
+    if got is not None:
+        return got
     m, n, k, ldx = _gemm_shapes(x, q, s)
     workspace, accept, idx, val = _verify_buffers(x, m, draft, mxfp4_woq_gemm_argmax_workspace_bytes(m, n, k),
                                                   workspace)
@@ -433,6 +462,10 @@ def _e4m3_shapes(x, q8, s):
 
 def mxfp4_e4m3_woq_gemm(x: torch.Tensor, q8: torch.Tensor, s: torch.Tensor,
                         y: Optional[torch.Tensor] = None) -> torch.Tensor:
+    if y is None:
+        y = _product(_E4M3, x, q8, s, 0, 0, False, None, 0, None, 0, None)
+        if y is not None:
+            return y
     m, n, k, ldx = _e4m3_shapes(x, q8, s)
     if y is None:
         y = torch.empty((m, n), dtype=torch.bfloat16, device=x.device)
@@ -500,6 +533,10 @@ def _e2m3_shapes(x, q6, s):
 
 def mxfp4_e2m3_woq_gemm(x: torch.Tensor, q6: torch.Tensor, s: torch.Tensor,
                         y: Optional[torch.Tensor] = None) -> torch.Tensor:
+    if y is None:
+        y = _product(_E2M3, x, q6, s, 0, 0, False, None, 0, None, 0, None)
+        if y is not None:
+            return y
     m, n, k, ldx = _e2m3_shapes(x, q6, s)
     if y is None:
         y = torch.empty((m, n), dtype=torch.bfloat16, device=x.device)
@@ -604,6 +641,10 @@ def _fmt_shapes(fmt, x, q, s):
 
 def mxfp4_fmt_woq_gemm(fmt: int, x: torch.Tensor, q: torch.Tensor, s: torch.Tensor,
                        y: Optional[torch.Tensor] = None) -> torch.Tensor:
+    if y is None and type(fmt) is int and FMT_E5M2 <= fmt <= FMT_T2:
+        y = _product(_FMT + fmt, x, q, s, 0, 0, False, None, 0, None, 0, None)
+        if y is not None:
+            return y
     m, n, k, ldx = _fmt_shapes(fmt, x, q, s)
     if y is None:
         y = torch.empty((m, n), dtype=torch.bfloat16, device=x.device)
@@ -641,6 +682,10 @@ def mxfp4_woq_gemm_fused(x: torch.Tensor, q: torch.Tensor, s: torch.Tensor, bias
                          y: Optional[torch.Tensor] = None, path: int = PATH_AUTO,
                          workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """The product with bias, gate and residual add fused; ``residual`` may be ``y`` itself."""
+    if y is None:
+        y = _product(_MX, x, q, s, 0, 0, True, bias, act, residual, path, workspace)
+        if y is not None:
+            return y
     m, n, k, ldx = _gemm_shapes(x, q, s)
     c = n // 2 if act == ACT_SWIGLU else n
     if bias is not None and (bias.dtype != torch.bfloat16 or bias.dim() != 1 or bias.shape[0] != n
@@ -796,6 +841,10 @@ def mxfp4_woq_gemm_tiled(x: torch.Tensor, w: TiledWeights, y: Optional[torch.Ten
                          workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """The product on the tile-major copy; with ``workspace`` (uint8, ``mxfp4_woq_gemm_workspace_bytes``)
     through ``mxfp4_woq_gemm_tiled_ws``, which also takes the shapes that need K split."""
+    if y is None:
+        y = _product(_TILED, x, w.q, w.s, w.n, w.k, False, None, 0, None, 0, workspace)
+        if y is not None:
+            return y
     m, n, k, ldx = _tiled_shapes(x, w)
     if y is None:
         y = torch.empty((m, n), dtype=torch.bfloat16, device=x.device)
@@ -813,6 +862,10 @@ def mxfp4_woq_gemm_tiled(x: torch.Tensor, w: TiledWeights, y: Optional[torch.Ten
 def mxfp4_woq_gemm_tiled_fused(x: torch.Tensor, w: TiledWeights, bias: Optional[torch.Tensor] = None,
                                act: int = ACT_NONE, residual: Optional[torch.Tensor] = None,
                                y: Optional[torch.Tensor] = None) -> torch.Tensor:
+    if y is None:
+        y = _product(_TILED, x, w.q, w.s, w.n, w.k, True, bias, act, residual, 0, None)
+        if y is not None:
+            return y
     m, n, k, ldx = _tiled_shapes(x, w)
     c = n // 2 if act == ACT_SWIGLU else n
     if bias is not None and (bias.dtype != torch.bfloat16 or bias.dim() != 1 or bias.shape[0] != n
@@ -853,6 +906,9 @@ def mxfp4_woq_gemm_tiled_argmax(x: torch.Tensor, w: TiledWeights, workspace: Opt
 
 def mxfp4_woq_gemm_tiled_verify(x: torch.Tensor, w: TiledWeights, draft: Optional[torch.Tensor],
                                 workspace: Optional[torch.Tensor] = None):
+    got = _verify(_TILED, x, w.q, w.s, w.n, w.k, draft, workspace)
+    if got is not None:
+        return got
     m, n, k, ldx = _tiled_shapes(x, w)
     workspace, accept, idx, val = _verify_buffers(x, m, draft, mxfp4_woq_gemm_argmax_workspace_bytes(m, n, k),
                                                   workspace)
@@ -866,6 +922,9 @@ def mxfp4_woq_gemm_tiled_verify(x: torch.Tensor, w: TiledWeights, draft: Optiona
 def mxfp4_bf16_gemm_verify(x: torch.Tensor, w: torch.Tensor, draft: Optional[torch.Tensor],
                            workspace: Optional[torch.Tensor] = None):
     """The same with unquantised BF16 weights."""
+    got = _verify(_BF16, x, w, None, 0, 0, draft, workspace)
+    if got is not None:
+        return got
     m, n, k, ldx, ldw = _bf16_shapes(x, w)
     workspace, accept, idx, val = _verify_buffers(x, m, draft, mxfp4_bf16_gemm_argmax_workspace_bytes(m, n, k),
                                                   workspace)
