@@ -20,6 +20,58 @@ struct TileCall {
     bool pick;      // the pick instead of the product
 };
 
+// Three to eight rows that the tiles take in one pass.  Figures: blocks as a part of what the tiles take, over 64 to 57344
+// weight rows, K = 128 to 10240 and 3 to 8 rows, with and without gate and pick.  A tile per unit and a short K are nothing but start
+// and end, where the blocks are the faster (4096 x 512 0.89, 0.95 tile-major; 8192 x 512 0.73; 32000 x 512 0.54, 0.58; K = 128 0.4
+// to 0.87, left where it was).  From there on either side wins where the weight rows and the phases of its loop come
+// out even, within a tenth mostly: blocks in rounds of 256, phases of 256 to 1024 elements, against tiles of 16 rows per unit in
+// groups of 512 elements.
+inline bool wide_one_pass_preferred(const TileCall& c)
+{
+    const int m = c.m, n = c.n, k = c.k, unit = c.cus;
+    const bool wide = m > 4;                        // the tiles stage eight rows instead of four
+    if (k <= 128)
+        return false;
+    // One tile per unit: 4096 x 1280 1.01, x 4096 0.98, x 5120 1.02, 1632 x 5632 0.93, 4096 x 8192 0.81, x 9216 0.90; at four rows 1.0 or more; tile-major
+    // from K = 1280 on 1.02 to 1.2.
+    if (n <= 16 * unit)
+        return k <= 1024 || (!c.tiled && wide && k > 5120);
+    if (c.tiled) {
+        // Just past a whole number of the tiles' groups: 27262 x 4224 0.73, 18268 x 4608 0.80, 13822 x 4352 0.85.
+        if (k > 4096 && k <= 4608)
+            return true;
+        // 8192 x 3072 0.88, x 4096 0.93 (0.95 at four rows, x 3584 0.97 to 1.02), x 5120 0.91 (0.99), x 8192 1.07.
+        if (n <= 32 * unit)
+            return k <= (wide ? 5120 : 3072);
+        // 12288 x 1536 0.97, x 2048 1.02, x 3584 1.1, x 5120 0.89 (1.05), x 7168 0.99 (1.06), x 9216 0.90.
+        if (n <= 48 * unit)
+            return k <= 1536 || (wide && k > 4096 && k <= 6144) || k > 8704;
+        // 22016 x 4096 0.91, 24576 x 2048 0.87, x 4096 0.96, x 5120 0.75 (0.89), x 8192 0.95; 33924 x 7808 1.13; 57344 x 3584 0.97,
+        // x 10240 1.0.
+        return k <= 3072 || (wide && k > 4096 && k <= 7680) || (k > 7936 && (wide || k <= 9728)) ||
+               (n > 80 * unit && n < 96 * unit && k <= 4096);
+    }
+    // Just past a whole number of the tiles' groups: 20530 x 4352 at four rows 0.85, 32490 x 4480 0.76, 45178 x 4480 0.87.
+    if (k > 4096 && k <= 4864)
+        return true;
+    // 8192 x 2048 0.80, x 4096 0.85, x 7168 0.82 (0.90 at four rows), x 11008 0.75 (0.91).
+    if (n <= 32 * unit)
+        return k <= 11520;
+    // 12288 x 3072 0.97, x 3584 1.05, x 4096 0.98, x 5120 0.91 (1.03), x 8192 0.78, x 10240 0.76 (0.98).
+    if (n <= 48 * unit)
+        return k <= 3072 || (wide && k > 4096) || (k > 7680 && k <= 11264);
+    // 16384 x 4096 0.91, x 9216 0.92, x 10240 1.11 at four rows.
+    if (n <= 64 * unit)
+        return k <= 9728;
+    // 20480 x 3072 0.97, x 4096 1.03, x 5120 0.86 (0.99), x 7168 0.9 (1.07); 22016 x 4096 0.94; 24576 x 4096 0.98, x 6144 0.93;
+    // 28672 x 5120 0.95 (1.17), x 6144 1.05; 32000 x 2048 0.87, x 3584 0.94, x 4096 1.0, x 8192 1.1.
+    if (n <= 128 * unit)
+        return k <= (n <= 80 * unit ? 3072 : n < 96 * unit ? 4096 : 3584) ||
+               (wide && k > 4096 && k <= (n <= 96 * unit ? 7680 : 5632));
+    // 34174 x 2944 0.84, 40960 x 2560 0.88, x 3072 1.03; 53574 x 2304 0.76, 54536 x 2688 0.87, 57344 x 2560 0.99, x 3072 1.07.
+    return k <= (n <= 160 * unit ? 2944 : 2688);
+}
+
 // From three rows on, K % 128 == 0.  Figures: us per launch, tiles -> blocks, or blocks as a part of what the tiles take.
 inline bool wide_preferred(const TileCall& c)
 {
@@ -28,22 +80,26 @@ inline bool wide_preferred(const TileCall& c)
     if (m < 3)
         return false;
     if (c.fits) {
-        // Beyond 16 rows always: 12288 x 4096 at 32 rows 19.9 -> 13.5, tile-major 18.3 -> 11.7, 22016 x 4096 at 64 57 -> 23.
-        // From nine rows on while a unit has one block (9728 x 896 7.3 -> 5.5, but 32000 x 4096 19.1 -> 19.2, 57344 x
-        // 8192 61 -> 66): blocks of 96 rows pay for the rows that they lack (18432 x 4096 13.9 -> 14.6, 22016 15.8 ->
-        // 15.2) unless the epilogue's loads are hidden by it (18432 x 4096 with residual 0.9 of the tiles); one tile per
-        // unit starts faster on the tiles (2560 x 2048 tile-major 4.7 -> 5.0) unless K is long enough (4096 x 4096 6.7 -> 6.0).
+        // Beyond 16 rows always: 12288 x 4096 at 32 rows 19.9 -> 10.1, 22016 x 4096 at 64 57 -> 19.
         if (m > 16)
             return true;
-        if (m <= 8 || n > 96 * unit)
-            return false;
+        if (m <= 8)
+            return wide_one_pass_preferred(c);
+        // Nine to 16: the tiles' passes of 16 rows have fewer waves in flight.  One tile per unit: 1024 x 1024 0.91, x 2048 1.02,
+        // x 3072 0.92, x 4096 0.86, tile-major 0.95, 1.12, 0.96, 0.98.
         if (n <= 16 * unit)
-            return k > 3072 && !(c.tiled && c.fused);
-        return c.fused || n <= 64 * unit || n >= 84 * unit || k <= 2560;
+            return (n < 16 * unit && k <= 1024) || (k > 2560 && !(c.tiled && c.fused));
+        // Many rows and K past the short phases: 32000 x 4096 0.92 (19.4 -> 17.8 with the pick), 32930 x 3712 0.79, 40960 x 3584
+        // 0.93 to 1.01, x 4096 1.03 to 1.1, 47416 x 4224 0.83, 57344 x 3072 0.93, x 3584 1.0 to 1.06; tile-major 0.96.
+        // (18432 x 4096 was 1.05 in blocks before their short phases and is 0.86 now: the plain product stays with the tiles there.)
+        if (n > 128 * unit)
+            return c.tiled || k <= (n < 208 * unit ? 3840 : 3072) || k > 4096;
+        return !plain || c.tiled || n <= 64 * unit || n > 72 * unit || k <= 3584;
     }
     if (m <= 8) {
+        // (57344 x 10240 and 32000 x 11008 tile-major at five and eight rows 0.76 of K split; row-major 1.04)
         if (n > 96 * unit)
-            return false;
+            return c.tiled && c.split && m > 4 && k <= 11264;
         // Plain products: K in phases inside a tile kernel, which walks one tile per unit as fast as a block and
         // starts earlier: 4096 x 11008 at 8 rows 12.4 -> 11.7, 4096 x 28672 18.9 -> 22.8 at three; tile-major 1000 x 28672
         // 15.0 -> 19.9.  Every further tile fetches the rows again: 12288 x 14336 at 5 rows 0.74 of it.
@@ -64,13 +120,17 @@ inline bool wide_preferred(const TileCall& c)
     if (!c.split)
         return m > 16 || (n <= 96 * unit && k <= 16384);
     // One pass of K split over the units: at 16 rows 4096 x 11008 0.83 of it, 256 x 14336 1.13, 5000 x 11008 1.05, 18432 x 12288
-    // 1.05; tile-major 1000 x 10240 1.07, 2048 x 14336 1.08, 4096 x 20480 1.03, 16384 x 28672 1.09, 24000 x 65536 0.94.
+    // 1.05, 1414 x 10880 0.80, 5782 x 11264 0.74, 32000 x 5120 0.70, x 7168 0.81, x 8192 1.0, x 10240 0.91, 31892 x 11392 0.89, 29836 x 8448 0.74; tile-major 1000 x 10240 1.07, 2048 x 14336 1.08, 4096 x 20480 1.03, 16384 x 28672 1.09, 24000 x 65536 0.94.
     if (passes == 1 && c.tiled)
         return n > 64 * unit ||
-               k <= (n < 8 * unit ? 8192 : n < 16 * unit ? 12288 : n < 32 * unit ? 16384 : 20480);
+               k <= (n < 5 * unit ? 8192 : n < 8 * unit ? 10240 : n < 16 * unit ? 12288 : n < 32 * unit ? 16384 : 20480);
     if (passes == 1)
-        return n <= 96 * unit && (n <= 64 * unit || n >= 84 * unit) &&
-               k <= (n < 8 * unit || (n > 16 * unit && n < 32 * unit) ? 10240 : 14336);
+        return (n <= 96 * unit && (n <= 64 * unit || n >= 84 * unit) &&
+                k <= (n < 5 * unit || (n > 16 * unit && n <= 20 * unit) ? 10240
+                      : n < 8 * unit                                    ? 12288
+                      : n > 16 * unit && n < 32 * unit                  ? 11520
+                                                                        : 14336)) ||
+               (n > 64 * unit && (k <= 7680 || (k > 8192 && k <= (n > 84 * unit ? 11520 : 10240))));
     // Several passes: each of them streams the weights again, so the line moves with their number.  At 17 to 32
     // rows 256 x 24576 1.0 of them, 256 x 65536 1.9, 500 x 32768 1.19, 1500 x 49152 1.14, 3000 x 65536 1.09, 4096 x 65536 0.84;
     // tile-major 64 x 20480 1.14, 64 x 65536 2.5, 1000 x 28672 1.05, 1500 x 49152 1.14; at 64 rows 16 x 65536 1.2, 1.6.

@@ -84,6 +84,23 @@ def test_rows_that_the_other_kernels_take_in_one_pass_stay(rules):
                 assert not asked(rules, m, n, k, "") and not asked(rules, m, n, k, "tw")
 
 
+@pytest.mark.parametrize("m,n,k,form,blocks", [
+    # one pass of the tiles, three to eight rows
+    (3, 4096, 1024, "", True), (8, 4096, 1152, "", False), (5, 1000, 5248, "", True), (4, 1000, 5248, "", False),
+    (5, 1000, 5248, "tw", False), (3, 8192, 4096, "", True), (8, 12288, 3584, "f", False), (5, 12288, 4224, "f", True),
+    (4, 20480, 4352, "", True), (4, 20480, 5120, "", False), (5, 22016, 4096, "f", True), (8, 28672, 4096, "p", False),
+    (8, 32000, 5120, "p", True), (8, 57344, 2048, "", True), (8, 57344, 3072, "", False), (4, 64, 128, "", False),
+    (6, 8192, 5120, "tw", True), (4, 8192, 5120, "tw", False), (8, 12288, 2048, "tw", False), (5, 12288, 9216, "tw", True),
+    (8, 22016, 4096, "tw", True), (8, 33924, 7808, "tf", False), (8, 57344, 8192, "tw", True),
+    # nine to sixteen, and K split over the units
+    (9, 1000, 512, "", True), (9, 1000, 2048, "", False), (16, 32000, 4096, "wp", True), (16, 57344, 4096, "", False),
+    (9, 57344, 4096, "tw", True), (16, 32000, 7168, "w", True), (16, 32000, 8192, "w", False), (9, 32000, 10240, "w", True),
+    (8, 57344, 11008, "tw", True), (8, 57344, 10240, "w", False), (12, 1400, 10880, "w", True),
+])
+def test_lines_of_the_rows_of_one_pass(rules, m, n, k, form, blocks):
+    assert asked(rules, m, n, k, form) == blocks
+
+
 def test_ragged_k(rules):
     assert all(rules.ragged(m, n, k) for m in (4, 7, 16, 500) for n in (1, 300, 32000) for k in (32, 1376, 65504))
     assert not rules.ragged(1, 4096, 1376) and not rules.ragged(2, 4096, 1376)
