@@ -481,10 +481,10 @@ hipError_t launch_block(const Args& a, const DeviceInfo& dev, hipStream_t stream
 // A block shape with what it took, in microseconds: the first block of a compute unit and every further one
 // as start + step x (steps of 128 along K, whole phases).  MXFP4: the fit to 256, 512 and 1024 blocks, four and more of them
 // over the same weights, at K = 1024, 4096 and 10240 (within 1 to 4 %; several blocks share a unit where LDS and registers
-// allow); the pick against every shape at 50 sizes of 5 to 512 rows: within 5 % of the best on 34, at worst 1.16.  The tables
-// of the other formats and of BF16 were measured with a phase's stores behind its matrix instructions, with 256 to 1024 blocks
-// at K = 1024 and 4096, and a difference that the noise hid is 0; their pick is within 5 % on 39 of 43 (8-bit), 36 of 42 (6-bit), 32
-// (ternary) and 42 (BF16), at worst 1.45 (57344 x 1024 at 400 rows), 1.13, 1.15 and 1.05 of it.
+// allow); the pick against every shape at 50 sizes of 5 to 512 rows: within 5 % of the best on 34, at worst 1.16.  The other
+// formats and BF16: the fit to 256, 512 and 1024 blocks, four over the same weights, at K = 1024 to 10240 and to 120 sizes of 3 to 270
+// rows; the pick against 24 shapes at those sizes within 5 % of the best on 111 (8-bit, at worst 1.07), 107 (6-bit, 1.11), 117
+// (ternary, 1.07) and 118 (BF16, 1.07).  Each table has the shapes that are the cheapest somewhere.
 struct Cost {
     int wm, wn, wk, mf, nf;
     float first_start, first_step, next_start, next_step;

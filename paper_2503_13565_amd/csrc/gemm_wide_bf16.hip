@@ -8,33 +8,39 @@ namespace {
 using namespace wide;
 
 const Cost kCosts[] = {
-    {1, 1, 8, 1, 1, 4.46f, 0.113f, 1.37f, 0.124f},
-    {1, 1, 8, 1, 2, 5.27f, 0.228f, 2.39f, 0.209f},
-    {1, 1, 8, 1, 4, 7.30f, 0.417f, 5.55f, 0.427f},
-    {1, 1, 8, 2, 1, 5.65f, 0.147f, 3.59f, 0.161f},
-    {1, 1, 8, 2, 2, 6.94f, 0.256f, 5.42f, 0.230f},
-    {1, 1, 8, 2, 4, 8.58f, 0.472f, 6.54f, 0.515f},
-    {1, 2, 4, 4, 1, 4.88f, 0.409f, 3.63f, 0.363f},
-    {1, 2, 4, 4, 2, 6.27f, 0.618f, 4.04f, 0.684f},
-    {1, 4, 2, 4, 1, 4.57f, 0.594f, 0.77f, 0.647f},
-    {1, 4, 2, 4, 2, 7.79f, 0.987f, 2.73f, 1.275f},
-    {2, 4, 1, 4, 2, 9.68f, 1.937f, 3.04f, 2.291f},
-    {1, 8, 1, 8, 2, 12.47f, 2.422f, 13.42f, 2.361f},
+    {1, 1, 8, 1, 1, 3.45f, 0.135f, 0.663f, 0.177f},
+    {1, 2, 4, 1, 1, 3.05f, 0.257f, 0.552f, 0.307f},
+    {1, 4, 2, 1, 1, 2.64f, 0.541f, 1.11f, 0.476f},
+    {1, 4, 2, 1, 2, 3.53f, 0.981f, 0.692f, 0.962f},
+    {1, 1, 8, 2, 1, 4.18f, 0.175f, 2.43f, 0.209f},
+    {1, 2, 4, 2, 1, 3.14f, 0.307f, 0.717f, 0.336f},
+    {1, 4, 2, 2, 1, 2.91f, 0.567f, 1.14f, 0.515f},
+    {1, 4, 2, 2, 2, 4.04f, 1.01f, 1.79f, 1.02f},
+    {1, 4, 2, 3, 1, 3.35f, 0.587f, 0.722f, 0.606f},
+    {1, 4, 2, 3, 2, 4.47f, 1.06f, 1.97f, 1.14f},
+    {1, 2, 4, 4, 1, 4.04f, 0.395f, 1.63f, 0.438f},
+    {1, 4, 2, 4, 1, 3.57f, 0.631f, 0.781f, 0.636f},
+    {1, 8, 1, 4, 1, 4.02f, 1.08f, 0.884f, 1.12f},
+    {1, 8, 1, 4, 2, 5.77f, 1.99f, 4.28f, 2.13f},
+    {1, 8, 1, 8, 2, 9.26f, 2.38f, 9.86f, 2.34f},
 };
 
 #define MXFP4_WIDE(...) launch_block<kBf16, __VA_ARGS__>
 hipError_t (*const kLaunch[])(const Args&, const DeviceInfo&, hipStream_t) = {
     MXFP4_WIDE(1, 1, 8, 1, 1),
-    MXFP4_WIDE(1, 1, 8, 1, 2),
-    MXFP4_WIDE(1, 1, 8, 1, 4),
+    MXFP4_WIDE(1, 2, 4, 1, 1),
+    MXFP4_WIDE(1, 4, 2, 1, 1),
+    MXFP4_WIDE(1, 4, 2, 1, 2),
     MXFP4_WIDE(1, 1, 8, 2, 1),
-    MXFP4_WIDE(1, 1, 8, 2, 2),
-    MXFP4_WIDE(1, 1, 8, 2, 4),
+    MXFP4_WIDE(1, 2, 4, 2, 1),
+    MXFP4_WIDE(1, 4, 2, 2, 1),
+    MXFP4_WIDE(1, 4, 2, 2, 2),
+    MXFP4_WIDE(1, 4, 2, 3, 1),
+    MXFP4_WIDE(1, 4, 2, 3, 2),
     MXFP4_WIDE(1, 2, 4, 4, 1),
-    MXFP4_WIDE(1, 2, 4, 4, 2),
     MXFP4_WIDE(1, 4, 2, 4, 1),
-    MXFP4_WIDE(1, 4, 2, 4, 2),
-    MXFP4_WIDE(2, 4, 1, 4, 2),
+    MXFP4_WIDE(1, 8, 1, 4, 1),
+    MXFP4_WIDE(1, 8, 1, 4, 2),
     MXFP4_WIDE(1, 8, 1, 8, 2),
 };
 #undef MXFP4_WIDE
