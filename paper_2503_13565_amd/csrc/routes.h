@@ -163,31 +163,38 @@ inline bool wide_format_preferred(int m, int n, int k, int bits, bool tiles, int
     if (m < 3)
         return false;
     // The ternary codes went over the weights once per four rows (22016 x 4096 at 8 rows 51 -> 17).  In one such pass, up
-    // to eight weight rows per unit, the vector ALUs are faster from K = 2560 (1000 x 8192 at four rows 1.14 of them) until
+    // to eight weight rows per unit, the vector ALUs are faster from K = 4224 (1024 x 4096 0.95, 1000 x 8192 at four rows 1.14 of them) until
     // a unit has room for one copy of the four rows only (1000 x 12288 0.89); a short K leaves nothing but
     // the start of the blocks, once per tile of many (24000 x 128 1.28, 24000 x 512 1.07, 24000 x 768 0.52).
     if (bits == 2) {
         if (m > 4)
             return true;
         if (n <= 8 * unit)
-            return (m == 4 || n >= 4 * unit) && (k <= 2048 || 16 * k > lds_bytes);
+            return ((m == 4 || n >= 4 * unit) && (k <= 2048 || 16 * k > lds_bytes)) || (n >= 4 * unit && k <= 4096);
         return n <= 16 * unit || k >= 768;
     }
     // Rows that do not fit ran as passes of four (E4M3 4096 x 11008 at 16 rows 55 -> 17).
     if (m >= 5 && !tiles)
         return true;
-    // Else while a unit has few tiles, the 8-bit elements from five rows on: 8192 x 4096 0.78 of the tiles, 12288 x 4096 0.93,
-    // but 12288 x 3072 1.05 and 9216 x 9216 1.2 (the loop takes two phases of 1024 elements at a time).
+    // Else while a unit has few tiles, the 8-bit elements from five rows on: 8192 x 4096 0.57 to 0.78 of the tiles, 12288 x 2560
+    // 0.87, x 3072 0.94 to 1.05, x 4096 0.83; many weight rows with a short K: 20480 x 2048 0.80, x 3072 1.09, 57344 x 2048 0.95.  Three
+    // and four rows: 1024 x 3072 1.14, 2048 x 1024 0.86, x 4096 0.96, 4096 x 8192 0.75, 8192 x 3072 0.79, x 11008 1.10, 9216 x 2048
+    // 0.85, x 3072 1.11, 20480 x 2048 0.90, 57344 x 2048 0.97.
+    if (bits == 8 && m <= 4)
+        return n > 4 * unit && k <= (n <= 8 * unit ? 1024 : n < 32 * unit ? 7168 : n == 32 * unit ? 3072 : 2048);
     if (bits == 8)
-        return m >= 5 && (n <= 32 * unit || (n <= 64 * unit && (k <= 2048 || k == 4096)));
-    // 6-bit: 8192 x 4096 0.88 of the tiles, but 9216 x 4096 1.12 and more; three and four rows unless N is small too (896 x 4864
-    // 7.0 -> 7.3) or K is long (3072 x 16384 1.06), where the decode kernel takes passes of two again from
-    // where four rows do not fit (2048 x 24576 0.9, 8192 x 24576 0.6).
+        return n <= 32 * unit || k <= 2048 || (n <= 64 * unit && (k <= 2560 || k == 4096));
+    // 6-bit: 8192 x 4096 0.75 of the tiles, 9216 x 3072 0.83, x 7168 1.2, 12288 x 6144 0.96, 20480 x 3072 0.93, x 4096 1.05, 57344 x 2048
+    // 0.85, x 2560 1.1; three and four rows not where N is small and K is not (1024 x 1024 0.87, 896 x 4864 1.04) or K is
+    // long (3072 x 16384 1.06), where the decode kernel takes passes of two again from where four rows do not fit (2048 x
+    // 24576 0.9, 8192 x 24576 0.6).
     if (n < 8 * unit)
-        return m >= 5;
+        return m >= 5 || k <= 1024;
     if (m <= 4 && 8 * k > lds_bytes)
         return n <= 40 * unit;
-    return n <= 32 * unit && (m >= 5 || k <= 12288);
+    if (n <= 32 * unit)
+        return m >= 5 || k <= 12288;
+    return k <= (n <= 40 * unit ? 3072 : n <= 64 * unit ? 6144 : n <= 128 * unit ? 3072 : 2048);
 }
 
 // BF16 weights.  `tiles`: the matrix-core tiles could take a call of nine to 16 rows in one pass.
@@ -196,21 +203,31 @@ inline bool wide_bf16_preferred(int m, int n, int k, bool tiles, int cus, int ld
     const int unit = cus;
     // Beyond 16 rows always (12288 x 4096 at 32 rows 41 -> 26, 4096 x 11008 98 -> 30).  Nine to 16 rows that the tiles
     // cannot take (4096 x 11008 at 16 rows 49 -> 25, 5001 x 2056 20 -> 11), or that leave the units few of them while K is
-    // whole pairs of phases (4096 x 4096 0.92 of the tiles, 2048 x 2048 1.05, 4096 x 512 1.22, 5120 x 3072 1.09).
+    // whole pairs of phases (4096 x 4096 0.86 of the tiles, 2048 x 2048 1.04, 4096 x 512 1.14), or 21 to 32 rows per unit (8192 x 512
+    // 0.90, x 2048 0.70, x 3072 0.92), or a short K (12288 x 512 0.92, x 1536 1.15, x 2048 0.85, 20480 x 512 1.06).
     if (m > 16)
         return true;
     if (m > 8)
-        return !tiles || (k % 2048 == 0 && n >= 12 * unit && n <= 20 * unit);
+        return !tiles || (k % 2048 == 0 && n >= 12 * unit && n <= 32 * unit) || (n > 20 * unit && n <= 32 * unit) ||
+               (n > 32 * unit && n <= 64 * unit && (k <= 512 || k == 2048));
     // Five to eight rows of a matrix of middling size, against the vector ALUs in one pass: 4096 x 4096 at 8 rows 0.88 of
-    // them, but 2048 x 5120 1.22, 5120 x 2560 1.15, 8192 x 6144 1.09, 10240 x 2048 1.13, 22016 x 4096 37 -> 41.
+    // them, 8192 x 4096 0.77, x 5120 0.97, but 2048 x 5120 1.0 to 1.22, 8192 x 6144 1.09, 10240 x 2048 1.13, 22016 x 4096 37 -> 41.
     // Rows that just fit the LDS stay (4096 x 10240 at 8 rows 1.03, 8192 x 10240 1.18); those that do not ran in phases
     // (4096 x 16384 0.74 of them, 8192 x 16384 1.1).
-    if (m < 5 || n <= 8 * unit || n > 40 * unit)
+    // A short K, where the start of a pass is most of it: three rows 4096 x 512 0.84, 12288 x 512 0.82, 57344 x 512 0.97; four 4096 x
+    // 1536 0.84, 12288 x 1024 0.87, 57344 x 512 0.79; five to eight 2048 x 2048 0.85, 12288 x 1024 0.74, 32000 x 1024 0.73.
+    if (m < 3)
         return false;
+    if (m < 5)
+        return n > 12 * unit && k <= (m == 3 || n > 64 * unit ? 512 : n > 32 * unit ? 1024 : 1536);
+    if (n <= 8 * unit)
+        return n >= 6 * unit && k <= 2048;
+    if (n > 40 * unit)
+        return k <= 1024;
     const bool phased = m > 6 && 16 * k > lds_bytes;
     if (n <= 16 * unit)
         return k <= (m > 6 ? 9216 : 8192) || phased;
-    return n > 32 * unit ? k <= 1024 : k <= 2048 || (phased && n <= 20 * unit);
+    return k <= (n > 32 * unit ? 1024 : n > 20 * unit ? 5120 : 2048) || (phased && n <= 20 * unit);
 }
 
 // Workgroups per compute unit of a vector-ALU pass of `rows` BF16 rows: as many copies of the rows as the LDS holds, up to

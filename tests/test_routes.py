@@ -140,6 +140,27 @@ def test_unquantised_weights(rules, m, n, k, tiles, blocks):
     assert bool(rules.bf16(m, n, k, int(tiles))) == blocks
 
 
+@pytest.mark.parametrize("bits,m,n,k,blocks", [
+    (8, 4, 1024, 512, False), (8, 4, 2048, 1024, True), (8, 3, 2048, 1152, False), (8, 3, 4096, 7168, True), (8, 4, 8192, 3072, True),
+    (8, 4, 9216, 2048, True), (8, 4, 9216, 2560, False), (8, 8, 12288, 2560, True), (8, 16, 32000, 2048, True),
+    (8, 16, 32000, 2560, False), (6, 3, 1000, 1024, True), (6, 4, 10240, 3072, True), (6, 16, 10240, 3200, False),
+    (6, 16, 12288, 6144, True), (6, 5, 12288, 7168, False), (6, 8, 32000, 3072, True), (6, 8, 57344, 3072, False),
+    (6, 4, 57344, 2048, True), (2, 3, 1024, 4096, True), (2, 3, 1024, 4224, False), (2, 4, 1000, 2560, False),
+])
+def test_other_formats_with_a_short_k(rules, bits, m, n, k, blocks):
+    assert bool(rules.format(m, n, k, bits, 1)) == blocks
+
+
+@pytest.mark.parametrize("m,n,k,tiles,blocks", [
+    (3, 4096, 512, False, True), (3, 4096, 1024, False, False), (4, 4096, 1536, False, True), (4, 12288, 1024, False, True),
+    (4, 12288, 1536, False, False), (4, 32000, 512, False, True), (4, 2048, 512, False, False), (5, 2048, 2048, False, True),
+    (5, 1024, 2048, False, False), (8, 32000, 1024, False, True), (8, 32000, 1152, False, False), (8, 8192, 5120, False, True),
+    (16, 8192, 3072, True, True), (16, 12288, 2048, True, True), (16, 12288, 512, True, True), (16, 12288, 1024, True, False),
+])
+def test_unquantised_weights_with_a_short_k(rules, m, n, k, tiles, blocks):
+    assert bool(rules.bf16(m, n, k, int(tiles))) == blocks
+
+
 @pytest.mark.parametrize("rows,n,k,want", [
     (3, 4096, 7168, 2), (3, 4096, 8192, 2), (3, 4096, 6824, 4), (3, 4096, 13104, 2), (3, 4096, 27304, 1),
     (8, 1000, 2048, 4), (8, 12288, 2048, 4), (8, 2000, 3072, 3), (8, 2048, 3072, 2), (5, 12288, 4096, 2), (8, 12288, 10240, 1),
