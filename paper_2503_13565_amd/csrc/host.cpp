@@ -104,6 +104,21 @@ bool operands(PyObject* const* args, int* kind, Operands* o)
     return true;
 }
 
+// What the binding's own checks take over: also a number that is none or too large, whose error they raise in their words.
+PyObject* left()
+{
+    PyErr_Clear();
+    Py_RETURN_NONE;
+}
+
+bool small(PyObject* o, int* v)                     // an int of the C interface as it stands
+{
+    int over = 0;
+    const long long wide = PyLong_Check(o) ? PyLong_AsLongLongAndOverflow(o, &over) : 0;
+    *v = (int)wide;
+    return PyLong_Check(o) && over == 0 && wide == *v;
+}
+
 struct Scratch {
     void* at = nullptr;
     size_t bytes = 0;
@@ -161,30 +176,28 @@ PyObject* product(PyObject*, PyObject* const* args, Py_ssize_t count)
     int kind;
     Operands o;
     Scratch ws;
-    if (!PyLong_Check(args[8]) || !PyLong_Check(args[10]) || !operands(args, &kind, &o) || !scratch(args[11], o.device, &ws))
-        Py_RETURN_NONE;
+    int act, path;
+    if (!small(args[8], &act) || !small(args[10], &path) || !operands(args, &kind, &o) || !scratch(args[11], o.device, &ws))
+        return left();
     const bool fused = args[6] == Py_True, spare = args[11] != Py_None;
-    const int act = (int)PyLong_AsLong(args[8]), path = (int)PyLong_AsLong(args[10]);
     const int64_t c = act == 1 ? o.n / 2 : o.n;
     const void *bias = nullptr, *residual = nullptr;
     int64_t ldr = 0;
     if (args[7] != Py_None) {
         const at::Tensor* b = plain(args[7], at::kBFloat16, o.device);
         if (!b || b->dim() != 1 || b->size(0) != o.n || !b->is_contiguous())
-            Py_RETURN_NONE;
+            return left();
         bias = b->data_ptr();
     }
     if (args[9] != Py_None) {
         const at::Tensor* r = rows_of(args[9], o.device);
         if (!r || r->size(0) != o.m || r->size(1) != c)
-            Py_RETURN_NONE;
+            return left();
         residual = r->data_ptr();
         ldr = o.m > 1 ? r->stride(0) : c;
     }
-    if (PyErr_Occurred()) {                         // a number that is none: the binding says so
-        PyErr_Clear();
-        Py_RETURN_NONE;
-    }
+    if (PyErr_Occurred())
+        return left();
     at::Tensor y;
     int rc;
     {
@@ -226,18 +239,16 @@ PyObject* verify(PyObject*, PyObject* const* args, Py_ssize_t count)
     Scratch ws;
     if (args[7] == Py_None || !operands(args, &kind, &o) || !scratch(args[7], o.device, &ws) ||
         (kind != kMx && kind != kBf16 && kind != kTiled))
-        Py_RETURN_NONE;
+        return left();
     const void* draft = nullptr;
     if (args[6] != Py_None) {
         const at::Tensor* d = plain(args[6], at::kInt, o.device);
         if (!d || d->numel() != o.m - 1 || !d->is_contiguous())
-            Py_RETURN_NONE;
+            return left();
         draft = d->data_ptr();
     }
-    if (PyErr_Occurred()) {
-        PyErr_Clear();
-        Py_RETURN_NONE;
-    }
+    if (PyErr_Occurred())
+        return left();
     at::Tensor out[3];
     int rc;
     {

@@ -129,6 +129,15 @@ def test_what_does_not_fit_is_answered_as_before(what, monkeypatch):
     assert torch.equal(got, want) if isinstance(want, torch.Tensor) else got == want
 
 
+def test_numbers_that_do_not_fit_are_answered_as_before():
+    x, _, q, s = _inputs(4, 2048, 512)
+    tiles = B.mxfp4_tile_repack(q, s)
+    with pytest.raises(ValueError, match="BF16 tensor"):
+        B.mxfp4_woq_gemm_tiled(x, B.TiledWeights(tiles.q, tiles.s, 2048, 2 ** 70))
+    for act in (2 ** 70, 2 ** 32 + 1):              # (marshalled to what an int of the C interface keeps of it)
+        assert B._product(0, x, q, s, 0, 0, True, None, act, None, 0, None) is None
+
+
 def test_a_status_raises_the_error_of_the_library():
     x, _, q, s = _inputs(4, 2048, 512)
     with pytest.raises(B.Mxfp4Error) as e:
