@@ -146,6 +146,12 @@ constexpr int block_waves(Kind w, int wm, int wk, int mf, int nf)
     return kind_bits(w) <= 4 && mf >= 4 && mf * nf == 8 && wk * wm * mf <= 8 ? 4 : 2;
 }
 
+// Chains of sums per output and wave.  With a short phase a wave has more of K to itself, and its chain of roundings grows:
+// 32000 x 4096 at nine rows, the picks' values against 64 bits, 1.6e-7 of them with two waves along K against 0.8e-7 with
+// eight.  So the matrix instructions of a step take turns on as many sums as make it eight chains of K (0.9e-7; the tiles
+// 1.0e-7) in the blocks that have the registers for it; the others have one, and a pick does not take them (sums_deep_enough).
+constexpr int sum_sets(int wk, int mf) { return mf == 1 || (mf <= 3 && wk == 4) ? 8 / wk : 1; }
+
 // The leading arguments are scalars that arrive in registers when a wave starts; `out` is for the end.
 template <Kind kW, int WM, int WN, int WK, int MF, int NF>
 __global__ __launch_bounds__(kThreads, block_waves(kW, WM, WK, MF, NF)) void gemm_wide_kernel(const uint16_t* __restrict__ x,
@@ -301,12 +307,17 @@ __global__ __launch_bounds__(kThreads, block_waves(kW, WM, WK, MF, NF)) void gem
     __builtin_amdgcn_sched_barrier(0);
     lds_barrier();
 
-    f32x4_t acc[MF][NF];
+    constexpr int kSets = sum_sets(WK, MF);
+    static_assert(kSets <= 4, "one of a step's four instructions each");
+    f32x4_t sums_of[kSets][MF][NF];
+    auto& acc = sums_of[0];
 #pragma unroll
-    for (int i = 0; i < MF; ++i)
+    for (int c = 0; c < kSets; ++c)
 #pragma unroll
-        for (int f = 0; f < NF; ++f)
-            acc[i][f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < MF; ++i)
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+                sums_of[c][i][f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const int x_read = (wk * BM + wm * MF * 16 + li) * 16;
     const int s_read = (wn * NF * 16 + li) * kSRow + wk * 4 + lg;
     // The operand reads of matrix instructions j + 1 go out beside those of j: into a second set of registers, or, from
@@ -334,9 +345,10 @@ __global__ __launch_bounds__(kThreads, block_waves(kW, WM, WK, MF, NF)) void gem
                 u32x16_t six[kBits == 6 ? NF : 1] = {};                 // 6-bit: one convert for the whole block
                 auto read_x = [&](int i, int j) { return xb[i * 256 + (chunk_at(kW == kBf16 ? 4 * j + lg : 4 * lg + j) ^ li)]; };
                 auto weights = [&](int f, int j) { return operand<kW>(sl.q[f], six[kBits == 6 ? f : 0], scl[f], j); };
-                auto multiply = [&](int i, int f, u32x4_t w, u32x4_t x) {
-                    acc[i][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w),
-                                                                        __builtin_bit_cast(bf16x8_t, x), acc[i][f], 0, 0, 0);
+                auto multiply = [&](int i, int f, int j, u32x4_t w, u32x4_t x) {
+                    f32x4_t& sum = sums_of[j % kSets][i][f];
+                    sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w),
+                                                                  __builtin_bit_cast(bf16x8_t, x), sum, 0, 0, 0);
                 };
 #pragma unroll
                 for (int i = 0; i < MF; ++i)
@@ -363,7 +375,7 @@ __global__ __launch_bounds__(kThreads, block_waves(kW, WM, WK, MF, NF)) void gem
                         for (int i = 0; i < MF; ++i) {
 #pragma unroll
                             for (int f = 0; f < NF; ++f)
-                                multiply(i, f, w[j & 1][f], xf[0][i]);
+                                multiply(i, f, j, w[j & 1][f], xf[0][i]);
                             if (j < 3) {
                                 xf[0][i] = read_x(i, j + 1);
 #pragma unroll
@@ -386,7 +398,7 @@ __global__ __launch_bounds__(kThreads, block_waves(kW, WM, WK, MF, NF)) void gem
                             const u32x4_t w = weights(f, j);
 #pragma unroll
                             for (int i = 0; i < MF; ++i)
-                                multiply(i, f, w, xf[j & 1][i]);
+                                multiply(i, f, j, w, xf[j & 1][i]);
                         }
                         __builtin_amdgcn_sched_barrier(0);
                     }
@@ -396,6 +408,14 @@ __global__ __launch_bounds__(kThreads, block_waves(kW, WM, WK, MF, NF)) void gem
             lds_barrier();
         }
     }
+
+#pragma unroll
+    for (int c = 1; c < kSets; ++c)
+#pragma unroll
+        for (int i = 0; i < MF; ++i)
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+                acc[i][f] += sums_of[c][i][f];
 
     // Output fragment (i, f) of block position (wm, wn): lane (li, lg) holds weight rows 4 lg + r for
     // activation row li.  The sums go through the LDS, so that whole rows are stored.
@@ -490,8 +510,16 @@ struct Cost {
     float first_start, first_step, next_start, next_step;
 };
 
+// Whether a shape's sums are split as far as a pick's float32 values need: no longer chains than the shapes of up to 48, of 64 to
+// 96 and of 128 rows had before the short phases.  (Products are rounded to BF16, four orders above the difference.)
+inline bool sums_deep_enough(const Cost& c)
+{
+    const int rows = c.wm * c.mf * 16;
+    return c.wk * sum_sets(c.wk, c.mf) >= (rows <= 48 ? 8 : rows <= 96 ? 2 : 1);
+}
+
 // The cheapest of `count` shapes for a call (-1: none with at most `max_cols` block columns).
-inline int pick_shape(const Cost* costs, int count, int m, int n, int k, int cus, int max_cols, Args* a)
+inline int pick_shape(const Cost* costs, int count, int m, int n, int k, int cus, int max_cols, bool pick, Args* a)
 {
     const char* forced_shape = knob("MXFP4_WIDE_SHAPE");            // measurement only
     const int forced = forced_shape ? atoi(forced_shape) : -1;
@@ -505,7 +533,7 @@ inline int pick_shape(const Cost* costs, int count, int m, int n, int k, int cus
         const int steps = ((k + 127) / 128 + c.wk - 1) / c.wk * c.wk;
         const float time = i == forced ? -1.f
                                        : c.first_start + c.first_step * steps + (rounds - 1) * (c.next_start + c.next_step * steps);
-        if (tiles_n <= max_cols && (best < 0 || time < best_time)) {
+        if (tiles_n <= max_cols && (!pick || sums_deep_enough(c)) && (best < 0 || time < best_time)) {
             best = i;
             best_time = time;
             a->tiles_m = tiles_m;
