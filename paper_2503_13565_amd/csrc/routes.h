@@ -89,7 +89,7 @@ inline bool wide_preferred(const TileCall& c)
         // x 3072 0.92, x 4096 0.86, tile-major 0.95, 1.12, 0.96, 0.98.
         if (n <= 16 * unit)
             return (n < 16 * unit && k <= 1024) || (k > 2560 && !(c.tiled && c.fused));
-        // Many rows and K past the short phases: 32000 x 4096 0.92 (19.4 -> 17.8 with the pick), 32930 x 3712 0.79, 40960 x 3584
+        // Many rows and K past the short phases: 32000 x 4096 0.94 (19.5 -> 18.2 us with the pick), 32930 x 3712 0.79, 40960 x 3584
         // 0.93 to 1.01, x 4096 1.03 to 1.1, 47416 x 4224 0.83, 57344 x 3072 0.93, x 3584 1.0 to 1.06; tile-major 0.96.
         // (18432 x 4096 was 1.05 in blocks before their short phases and is 0.86 now: the plain product stays with the tiles there.)
         if (n > 128 * unit)
