@@ -53,6 +53,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "scale_stage.h"
+#include "sum_chains.h"
 
 namespace mxfp4 {
 namespace wide {
@@ -76,6 +77,7 @@ struct Args {
     const uint8_t* q;
     const uint8_t* s;
     int n, k, m, ldx, ldw, tiles_m, tiles_n;    // ldw: BF16 weights only
+    int chains;                                 // into how many an output's sum is cut (sum_chains.h)
     BlockOut out;
 };
 
@@ -138,26 +140,25 @@ __device__ __forceinline__ u32x4_t operand(const uint32_t* r, const u32x16_t& si
     return w;
 }
 
-// Waves per SIMD to keep registers for.  Two blocks of 128 rows and 128 weight rows, or 64 and 128, of MXFP4 or ternary weights
-// fit a compute unit side by side (one's barriers, start and end are hidden behind the other) if they make do with 128
-// registers, one or two less than the compiler would take: 512 blocks of 128 x 128 at K = 1024 23.2 us, 25.6 without.
-constexpr int block_waves(Kind w, int wm, int wk, int mf, int nf)
+// How the sums of a wave are cut into chains (what for: sum_chains.h).  kChains: a chain of whole pairs of phases is added to the
+// output's sum at its end, in a second set of registers, K / chains long.  kSteps: so is every step's, which is also more exact than
+// eight long chains for elements of 6 bits and more (a BF16 pick's values at K = 4096, against 64 bits: 0.9e-7 to 1.2e-7, 1.5e-7 in
+// eight chains, 4.2e-7 in one); blocks of many rows then go through one row of fragments after the other, for which two
+// rows' sums are enough.  The largest 8-bit block has the registers for kChains and not the time for kSteps (22016 x 4096 at 509
+// rows: 15 % of it).
+enum Cut { kWhole, kChains, kSteps };
+constexpr Cut sum_cut(Kind w, int wk, int mf, int nf)
 {
-    return kind_bits(w) <= 4 && mf >= 4 && mf * nf == 8 && wk * wm * mf <= 8 ? 4 : 2;
+    return wk == 8 || uncut(mf, nf) ? kWhole : kind_bits(w) > 4 && !(kind_bits(w) == 8 && mf * nf == 16) ? kSteps : kChains;
 }
-
-// Chains of sums per output and wave.  With a short phase a wave has more of K to itself, and its chain of roundings grows:
-// 32000 x 4096 at nine rows, the picks' values against 64 bits, 1.6e-7 of them with two waves along K against 0.8e-7 with
-// eight.  So the matrix instructions of a step take turns on as many sums as make it eight chains of K (0.9e-7; the tiles
-// 1.0e-7) in the blocks that have the registers for it; the others have one, and a pick does not take them (sums_deep_enough).
-constexpr int sum_sets(int wk, int mf) { return mf == 1 || (mf <= 3 && wk == 4) ? 8 / wk : 1; }
 
 // The leading arguments are scalars that arrive in registers when a wave starts; `out` is for the end.
 template <Kind kW, int WM, int WN, int WK, int MF, int NF>
-__global__ __launch_bounds__(kThreads, block_waves(kW, WM, WK, MF, NF)) void gemm_wide_kernel(const uint16_t* __restrict__ x,
+__global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* __restrict__ x,
                                                                 const uint8_t* __restrict__ q,
                                                                 const uint8_t* __restrict__ s, int n, int k, int m,
-                                                                int ldx, int ldw, int tiles_m, int tiles_n, BlockOut out)
+                                                                int ldx, int ldw, int tiles_m, int tiles_n, int chains,
+                                                                BlockOut out)
 {
     static_assert(WM * WN * WK == 8, "eight waves");
     constexpr int BM = WM * MF * 16, BN = WN * NF * 16;
@@ -307,22 +308,35 @@ __global__ __launch_bounds__(kThreads, block_waves(kW, WM, WK, MF, NF)) void gem
     __builtin_amdgcn_sched_barrier(0);
     lds_barrier();
 
-    constexpr int kSets = sum_sets(WK, MF);
-    static_assert(kSets <= 4, "one of a step's four instructions each");
-    f32x4_t sums_of[kSets][MF][NF];
-    auto& acc = sums_of[0];
+    constexpr Cut kCut = sum_cut(kW, WK, MF, NF);
+    constexpr bool kRoll = MF >= 4;                                     // (below)
+    constexpr bool kApart = kCut == kChains || (kCut == kSteps && !kRoll);
+    f32x4_t acc[MF][NF], chain[kApart ? MF : 1][NF];
 #pragma unroll
-    for (int c = 0; c < kSets; ++c)
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            acc[i][f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            chain[kApart ? i : 0][f] = acc[i][f];
+        }
+    const int chain_all = chain_pairs(phases, WK, chains);
+    int chain_left = chain_all;
+    auto end_chain = [&]() {
 #pragma unroll
         for (int i = 0; i < MF; ++i)
 #pragma unroll
-            for (int f = 0; f < NF; ++f)
-                sums_of[c][i][f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            for (int f = 0; f < NF; ++f) {
+                acc[i][f] += chain[kApart ? i : 0][f];
+                if (kCut == kChains)
+                    chain[kApart ? i : 0][f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                else                                                    // (kSteps starts from zero; the sum stays here)
+                    asm volatile("" : "+v"(acc[i][f]));
+            }
+    };
     const int x_read = (wk * BM + wm * MF * 16 + li) * 16;
     const int s_read = (wn * NF * 16 + li) * kSRow + wk * 4 + lg;
     // The operand reads of matrix instructions j + 1 go out beside those of j: into a second set of registers, or, from
     // four fragments of activations on, each into the register that its fragment's instructions have just read.
-    constexpr bool kRoll = MF >= 4;
     u32x4_t xf[kRoll ? 1 : 2][MF];
 
     for (int u0 = 0; u0 < phases; u0 += 2) {
@@ -346,12 +360,13 @@ __global__ __launch_bounds__(kThreads, block_waves(kW, WM, WK, MF, NF)) void gem
                 auto read_x = [&](int i, int j) { return xb[i * 256 + (chunk_at(kW == kBf16 ? 4 * j + lg : 4 * lg + j) ^ li)]; };
                 auto weights = [&](int f, int j) { return operand<kW>(sl.q[f], six[kBits == 6 ? f : 0], scl[f], j); };
                 auto multiply = [&](int i, int f, int j, u32x4_t w, u32x4_t x) {
-                    f32x4_t& sum = sums_of[j % kSets][i][f];
-                    sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w),
-                                                                  __builtin_bit_cast(bf16x8_t, x), sum, 0, 0, 0);
+                    f32x4_t& sum = kApart ? chain[kApart ? i : 0][f] : acc[i][f];
+                    sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8_t, w), __builtin_bit_cast(bf16x8_t, x),
+                        kCut == kSteps && j == 0 ? f32x4_t{0.f, 0.f, 0.f, 0.f} : sum, 0, 0, 0);
                 };
 #pragma unroll
-                for (int i = 0; i < MF; ++i)
+                for (int i = 0; i < (kCut == kSteps && kRoll ? 1 : MF); ++i)
                     xf[0][i] = read_x(i, 0);
 #pragma unroll
                 for (int f = 0; f < NF; ++f) {
@@ -364,7 +379,36 @@ __global__ __launch_bounds__(kThreads, block_waves(kW, WM, WK, MF, NF)) void gem
                             six[f] = __builtin_bit_cast(u32x16_t, __builtin_amdgcn_cvt_scalef32_pk32_bf16_fp6(packed, scl[f]));
                     }
                 }
-                if constexpr (kRoll) {
+                if constexpr (kCut == kSteps && kRoll) {
+                    // one fragment's four instructions behind each other; its sums are added beside the next one's
+                    u32x4_t w[4][NF], xj[4] = {xf[0][0], read_x(0, 1), read_x(0, 2), read_x(0, 3)};
+                    f32x4_t part[2][NF];
+#pragma unroll
+                    for (int f = 0; f < NF; ++f)
+                        w[0][f] = weights(f, 0);
+#pragma unroll
+                    for (int i = 0; i <= MF; ++i)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+#pragma unroll
+                            for (int f = 0; f < NF; ++f) {
+                                f32x4_t& sum = part[i & 1][f];
+                                if (i < MF)
+                                    sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                        __builtin_bit_cast(bf16x8_t, w[j][f]), __builtin_bit_cast(bf16x8_t, xj[j]),
+                                        j == 0 ? f32x4_t{0.f, 0.f, 0.f, 0.f} : sum, 0, 0, 0);
+                                if (i == 0 && j < 3)
+                                    w[j + 1][f] = weights(f, j + 1);
+                                if (i > 0 && j == 1) {
+                                    acc[i - 1][f] += part[(i - 1) & 1][f];
+                                    asm volatile("" : "+v"(acc[i - 1][f]));     // (the sum stays here)
+                                }
+                            }
+                            if (i + 1 < MF)
+                                xj[j] = read_x(i + 1, j);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                } else if constexpr (kRoll) {
                     u32x4_t w[2][NF];
 #pragma unroll
                     for (int f = 0; f < NF; ++f)
@@ -402,20 +446,22 @@ __global__ __launch_bounds__(kThreads, block_waves(kW, WM, WK, MF, NF)) void gem
                         }
                         __builtin_amdgcn_sched_barrier(0);
                     }
+                    if constexpr (kCut == kSteps)
+                        end_chain();
                 }
+            }
+            if constexpr (kCut == kChains) {
+                if (d == 1 && (--chain_left == 0 || u0 + 2 >= phases)) {
+                    chain_left = chain_all;
+                    end_chain();
+                }
+                if (d == 0 && cuts_phases(WK, MF) && phases <= 2)       // a single pair
+                    end_chain();
             }
             issue_q(buf[d]);
             lds_barrier();
         }
     }
-
-#pragma unroll
-    for (int c = 1; c < kSets; ++c)
-#pragma unroll
-        for (int i = 0; i < MF; ++i)
-#pragma unroll
-            for (int f = 0; f < NF; ++f)
-                acc[i][f] += sums_of[c][i][f];
 
     // Output fragment (i, f) of block position (wm, wn): lane (li, lg) holds weight rows 4 lg + r for
     // activation row li.  The sums go through the LDS, so that whole rows are stored.
@@ -494,7 +540,7 @@ hipError_t launch_block(const Args& a, const DeviceInfo& dev, hipStream_t stream
     if (hipError_t e = lds_limit.raise(reinterpret_cast<const void*>(kern), dev.lds_bytes); e != hipSuccess)
         return e;
     hipLaunchKernelGGL(kern, dim3(a.tiles_m * a.tiles_n), dim3(kThreads), lds_bytes(kW, WM, WN, WK, MF, NF), stream, a.x, a.q,
-                       a.s, a.n, a.k, a.m, a.ldx, a.ldw, a.tiles_m, a.tiles_n, a.out);
+                       a.s, a.n, a.k, a.m, a.ldx, a.ldw, a.tiles_m, a.tiles_n, a.chains, a.out);
     return hipGetLastError();
 }
 
@@ -510,16 +556,9 @@ struct Cost {
     float first_start, first_step, next_start, next_step;
 };
 
-// Whether a shape's sums are split as far as a pick's float32 values need: no longer chains than the shapes of up to 48, of 64 to
-// 96 and of 128 rows had before the short phases.  (Products are rounded to BF16, four orders above the difference.)
-inline bool sums_deep_enough(const Cost& c)
-{
-    const int rows = c.wm * c.mf * 16;
-    return c.wk * sum_sets(c.wk, c.mf) >= (rows <= 48 ? 8 : rows <= 96 ? 2 : 1);
-}
-
-// The cheapest of `count` shapes for a call (-1: none with at most `max_cols` block columns).
-inline int pick_shape(const Cost* costs, int count, int m, int n, int k, int cus, int max_cols, bool pick, Args* a)
+// The cheapest of `count` shapes for a call, of those that cut its sums as far as it wants (-1: none with at most `max_cols` block
+// columns); `bits` per weight.  Products and picks take the same one, but for picks with little room for partial winners.
+inline int pick_shape(const Cost* costs, int count, int m, int n, int k, int cus, int max_cols, int bits, Args* a)
 {
     const char* forced_shape = knob("MXFP4_WIDE_SHAPE");            // measurement only
     const int forced = forced_shape ? atoi(forced_shape) : -1;
@@ -533,13 +572,15 @@ inline int pick_shape(const Cost* costs, int count, int m, int n, int k, int cus
         const int steps = ((k + 127) / 128 + c.wk - 1) / c.wk * c.wk;
         const float time = i == forced ? -1.f
                                        : c.first_start + c.first_step * steps + (rounds - 1) * (c.next_start + c.next_step * steps);
-        if (tiles_n <= max_cols && (!pick || sums_deep_enough(c)) && (best < 0 || time < best_time)) {
+        if (tiles_n <= max_cols && (best < 0 || time < best_time) &&
+            (i == forced || cuts_enough(bits, c.wm, c.wn, c.wk, c.mf, c.nf, m, n, k, cus))) {
             best = i;
             best_time = time;
             a->tiles_m = tiles_m;
             a->tiles_n = tiles_n;
         }
     }
+    a->chains = chains_wanted(m, n, k, cus);
     return best;
 }
 

@@ -147,11 +147,11 @@ hipError_t launch_gemm_wide_fmt(int code, const GemmArgs& a, const DeviceInfo& d
     const int kind = code == 8 ? 0 : code == 24 ? 1 : code == 6 ? 2 : code == 22 ? 3 : code == 2 ? 4 : -1;
     if (kind < 0)
         return hipErrorInvalidValue;
-    Args w{a.x, a.q, a.s, a.n, a.k, a.m, (int)a.ldx, 0, 0, 0, block_out(a, nullptr)};
+    Args w{a.x, a.q, a.s, a.n, a.k, a.m, (int)a.ldx, 0, 0, 0, 0, block_out(a, nullptr)};
     const Cost* costs = kind < 2 ? kCosts8 : kind < 4 ? kCosts6 : kCosts2;
     const size_t bytes = kind < 2 ? sizeof kCosts8 : kind < 4 ? sizeof kCosts6 : sizeof kCosts2;
     const int c = pick_shape(costs, (int)(bytes / sizeof costs[0]), a.m, a.n, a.k, dev.cus, a.part_val ? a.parts : 0x7FFFFFFF,
-                             a.part_val != nullptr, &w);
+                             kind < 2 ? 8 : kind < 4 ? 6 : 2, &w);
     if (c < 0)
         return hipErrorInvalidValue;
     if (parts_used)

@@ -158,8 +158,8 @@ CASES = [(name, *size) for kind, names in (("mxfp4", ["mxfp4"]), ("tiled", ["til
 
 @pytest.mark.parametrize("name,m,n,k", CASES)
 def test_every_block_shape_of_every_layout(name, m, n, k):
-    # the product on sampled weight rows, those at the edges of blocks and tiles among them; the pick's value is the
-    # product's sum before its rounding
+    # the product on sampled weight rows, those at the edges of blocks and tiles among them; product and pick take the same
+    # block shape, so the pick's value is the product's sum before its rounding
     tag = "%s M=%d N=%d K=%d" % (name, m, n, k)
     print(tag, flush=True)
     w = synth.weights_student_t(n, k, seed=9200 + n, device=DEV)
@@ -189,6 +189,31 @@ def test_every_block_shape_of_every_layout(name, m, n, k):
     assert_gemm_close(y[:, rows.to(DEV)], y_ref, a_ref, tag)
     at_pick = y.gather(1, idx.long()[:, None])[:, 0]
     assert torch.equal(val.to(torch.bfloat16), at_pick) and torch.equal(at_pick, y.max(dim=1).values), tag
+
+
+@pytest.mark.parametrize("name,m,n,k,bound", [("mxfp4", 100, 6656, 4096, 1.0e-7), ("e4m3", 40, 8448, 4096, 1.8e-7),
+                                              ("bf16", 40, 8448, 4096, 2.0e-7), ("bf16", 32, 12288, 8192, 2.5e-7)])
+def test_picks_values_are_sums_of_eight_chains(name, m, n, k, bound):
+    # against 64 bits, as a part of them: between what eight chains of K leave (0.8e-7, 1.3e-7, 1.5e-7, 1.9e-7, by the format's
+    # digits and K) and what two do (1.3e-7, 2.7e-7, 2.8e-7, 3.6e-7)
+    off = size = 0.0
+    for seed in range(4):
+        w = synth.weights_student_t(n, k, seed=9600 + seed, device=DEV)
+        x = synth.activations_outlier_channels(m, k, seed=9650 + seed, device=DEV)
+        if name == "bf16":
+            wide, (idx, val) = w, binding.mxfp4_bf16_gemm_argmax(x, w)
+        elif name == "e4m3":
+            q = binding.mxfp4_e4m3_direct_cast(w)
+            wide, (idx, val) = binding.mxfp4_e4m3_dequant(*q), binding.mxfp4_e4m3_woq_gemm_argmax(x, *q)
+        else:
+            q = binding.mxfp4_direct_cast(w)
+            wide, (idx, val) = binding.mxfp4_dequant(*q), binding.mxfp4_woq_gemm_argmax(x, *q)
+        exact = (x.double() * wide[idx.long()].double()).sum(dim=1)
+        off += float((val.double() - exact).square().sum())
+        size += float(exact.square().sum())
+    error = (off / size) ** 0.5
+    print("%s M=%d N=%d K=%d: %.2e" % (name, m, n, k, error), flush=True)
+    assert error <= bound
 
 
 def test_nan_stays_in_its_row_and_block():

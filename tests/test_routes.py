@@ -13,6 +13,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 
 RULES = r"""
 #include "routes.h"
+#include "sum_chains.h"
 using namespace mxfp4;
 extern "C" int mx(int m, int n, int k, int fits, int split, int tiled, int fused, int pick)
 {
@@ -25,6 +26,10 @@ extern "C" int format(int m, int n, int k, int bits, int tiles)
 extern "C" int bf16(int m, int n, int k, int tiles)
 {
     return wide_bf16_preferred(m, n, k, tiles != 0, 256, 160 * 1024);
+}
+extern "C" int cuts(int bits, int wm, int wn, int wk, int mf, int nf, int m, int n, int k)
+{
+    return wide::cuts_enough(bits, wm, wn, wk, mf, nf, m, n, k, 256);
 }
 extern "C" int workgroups(int rows, int n, int k) { return bf16_workgroups_per_unit(rows, n, k, 256, 160 * 1024); }
 extern "C" int ragged(int m, int n, int k) { return wide_ragged_preferred(m, n, k, 256, 160 * 1024); }
@@ -192,10 +197,12 @@ def test_one_and_two_rows_never_take_the_blocks(rules):
                 assert not any(rules.bf16(m, n, k, tiles) for tiles in (0, 1)) and not rules.ragged(m, n, k + 32)
 
 
-def picked(table, m, n, k):
+def picked(rules, bits, table, m, n, k):
     """The block shape that a call takes (pick_shape of csrc/gemm_wide.h), and by how much it is the cheapest."""
     cost = []
     for i, (wm, wn, wk, mf, nf, start, step, next_start, next_step) in enumerate(table):
+        if not rules.cuts(bits, *(int(v) for v in (wm, wn, wk, mf, nf)), m, n, k):
+            continue
         bm, bn, wk = int(wm * mf * 16), int(wn * nf * 16), int(wk)
         rounds = -(-(-(-m // bm) * -(-n // bn)) // 256)
         steps = -(-(-(-k // 128)) // wk) * wk
@@ -210,9 +217,10 @@ def picked(table, m, n, k):
 def test_sizes_that_take_every_block_shape(rules, kind, source, name, never):
     body = re.search(r"const Cost %s\[\] = \{(.*?)\n\};" % name, open(os.path.join(CSRC, source)).read(), re.S).group(1)
     table = [[float(v.rstrip("f")) for v in row.split(",")] for row in re.findall(r"\{([^{}]*)\}", body)]
-    assert [picked(table, *size)[0] for size in BLOCK_SIZES[kind]] == [i for i in range(len(table)) if i not in never]
+    bits = {"mxfp4": 4, "tiled": 4, "bf16": 16}.get(kind, kind)
+    assert [picked(rules, bits, table, *size)[0] for size in BLOCK_SIZES[kind]] == [i for i in range(len(table)) if i not in never]
     for m, n, k in BLOCK_SIZES[kind]:
-        assert picked(table, m, n, k)[1] > 0.005                # (the kernel's sums are in 32 bits)
+        assert picked(rules, bits, table, m, n, k)[1] > 0.005                # (the kernel's sums are in 32 bits)
         if kind == "mxfp4":
             assert all(asked(rules, m, n, k, form) for form in ("", "f", "wp"))
         elif kind == "tiled":
