@@ -5,7 +5,7 @@
 // its length: the picks' values at 64 rows and K = 4096 are off by 0.84e-7 of them in eight chains, 0.98e-7 in four, 1.3e-7 in two
 // and 1.9e-7 in one (MXFP4; BF16 1.5e-7, 2.0e-7, 2.8e-7, 4.2e-7).  The waves that share K make a chain each, so how far a
 // sum is cut would change with the block shape, that is with what is fastest at a size.  It does not: a call is cut
-// as far as blocks of eight (few outputs), four and two waves along K cut it, and a shape with fewer waves along K cuts its
+// as far as blocks of eight (few outputs, or a long K), four and two waves along K cut it, and a shape with fewer waves along K cuts its
 // waves' sums further.
 #pragma once
 
@@ -20,12 +20,16 @@ constexpr bool uncut(int mf, int nf) { return mf * nf > 16; }
 // Whether a block whose sums are cut at pairs of phases also cuts the only pair there is.
 constexpr bool cuts_phases(int wk, int mf) { return wk > 1 && mf <= 3; }
 
-// Chains of a call's outputs: eight up to 32 rows or 12 tiles of 16 x 16 outputs per compute unit, four up to 24, else two; never
-// more than steps of 128 along K.
+constexpr int64_t tiles_of(int m, int n) { return (int64_t)((m + 15) / 16) * ((n + 15) / 16); }
+
+// Chains of a call's outputs: eight up to 32 rows or 12 tiles of 16 x 16 outputs per compute unit, four up to 24, else two; twice
+// that, and eight at most, where K is longer than 8192 (blocks of four waves along K went there too, and a further cut of
+// so long a sum takes no time that could be measured); never more than steps of 128 along K.
 constexpr int chains_wanted(int m, int n, int k, int cus)
 {
-    const int64_t tiles = (int64_t)((m + 15) / 16) * ((n + 15) / 16);
-    const int most = m <= 32 || tiles <= 12 * (int64_t)cus ? 8 : tiles <= 24 * (int64_t)cus ? 4 : 2, steps = (k + 127) / 128;
+    const int64_t tiles = tiles_of(m, n);
+    const int few = m <= 32 || tiles <= 12 * (int64_t)cus ? 8 : tiles <= 24 * (int64_t)cus ? 4 : 2, steps = (k + 127) / 128;
+    const int most = k > 8192 && few < 8 ? 2 * few : few;
     return steps < most ? steps : most;
 }
 
@@ -55,7 +59,8 @@ constexpr bool cuts_enough(int bits, int wm, int wn, int wk, int mf, int nf, int
     if (chains_of(bits, wk, mf, nf, (k + 127) / 128) >= wanted)
         return true;
     const int64_t bm = 16 * wm * mf, bn = 16 * wn * nf, blocks = ((m + bm - 1) / bm) * ((n + bn - 1) / bn);
-    return uncut(mf, nf) && wanted <= 2 && (int64_t)m * n * 100 >= 85 * bm * bn * ((blocks + cus - 1) / cus * cus);
+    return uncut(mf, nf) && m > 32 && tiles_of(m, n) > 24 * (int64_t)cus &&
+           (int64_t)m * n * 100 >= 85 * bm * bn * ((blocks + cus - 1) / cus * cus);
 }
 
 }  // namespace wide
