@@ -8,21 +8,22 @@ namespace {
 using namespace wide;
 
 const Cost kCosts[] = {
-    {1, 1, 8, 1, 1, 3.45f, 0.135f, 0.663f, 0.177f},
-    {1, 2, 4, 1, 1, 3.05f, 0.257f, 0.552f, 0.307f},
-    {1, 4, 2, 1, 1, 2.64f, 0.541f, 1.11f, 0.476f},
-    {1, 4, 2, 1, 2, 3.53f, 0.981f, 0.692f, 0.962f},
-    {1, 1, 8, 2, 1, 4.18f, 0.175f, 2.43f, 0.209f},
-    {1, 2, 4, 2, 1, 3.14f, 0.307f, 0.717f, 0.336f},
-    {1, 4, 2, 2, 1, 2.91f, 0.567f, 1.14f, 0.515f},
-    {1, 4, 2, 2, 2, 4.04f, 1.01f, 1.79f, 1.02f},
-    {1, 4, 2, 3, 1, 3.35f, 0.587f, 0.722f, 0.606f},
-    {1, 4, 2, 3, 2, 4.47f, 1.06f, 1.97f, 1.14f},
-    {1, 2, 4, 4, 1, 4.04f, 0.395f, 1.63f, 0.438f},
-    {1, 4, 2, 4, 1, 3.57f, 0.631f, 0.781f, 0.636f},
-    {1, 8, 1, 4, 1, 4.02f, 1.08f, 0.884f, 1.12f},
-    {1, 8, 1, 4, 2, 5.77f, 1.99f, 4.28f, 2.13f},
-    {1, 8, 1, 8, 2, 9.26f, 2.38f, 9.86f, 2.34f},
+    {1, 1, 8, 1, 1, 3.780f, 0.142f, 0.573f, 0.199f},
+    {1, 2, 4, 1, 1, 3.296f, 0.260f, 0.f, 0.370f},
+    {1, 4, 2, 1, 1, 3.324f, 0.520f, 0.176f, 0.657f},
+    {1, 4, 2, 1, 2, 2.938f, 1.046f, 1.549f, 0.816f},
+    {1, 1, 8, 2, 1, 4.155f, 0.185f, 2.585f, 0.203f},
+    {1, 2, 4, 2, 1, 3.402f, 0.292f, 0.628f, 0.360f},
+    {1, 4, 2, 2, 1, 3.349f, 0.531f, 0.350f, 0.636f},
+    {1, 4, 2, 2, 2, 3.464f, 1.060f, 2.887f, 0.857f},
+    {1, 4, 2, 3, 1, 3.626f, 0.573f, 0.815f, 0.588f},
+    {1, 4, 2, 3, 2, 4.446f, 1.069f, 3.219f, 1.005f},
+    {1, 2, 4, 4, 1, 4.317f, 0.396f, 2.696f, 0.428f},
+    {1, 4, 2, 4, 1, 3.946f, 0.615f, 1.062f, 0.615f},
+    {1, 4, 2, 4, 2, 4.794f, 1.082f, 3.729f, 1.075f},
+    {1, 8, 1, 4, 1, 4.210f, 1.080f, 1.242f, 1.019f},
+    {1, 8, 1, 4, 2, 6.305f, 1.961f, 4.235f, 1.883f},
+    {1, 8, 1, 8, 2, 9.855f, 2.460f, 6.286f, 2.506f},
 };
 
 #define MXFP4_WIDE(...) launch_block<kBf16, __VA_ARGS__>
@@ -39,6 +40,7 @@ hipError_t (*const kLaunch[])(const Args&, const DeviceInfo&, hipStream_t) = {
     MXFP4_WIDE(1, 4, 2, 3, 2),
     MXFP4_WIDE(1, 2, 4, 4, 1),
     MXFP4_WIDE(1, 4, 2, 4, 1),
+    MXFP4_WIDE(1, 4, 2, 4, 2),
     MXFP4_WIDE(1, 8, 1, 4, 1),
     MXFP4_WIDE(1, 8, 1, 4, 2),
     MXFP4_WIDE(1, 8, 1, 8, 2),

@@ -9,22 +9,22 @@ namespace {
 using namespace wide;
 
 const Cost kCosts8[] = {
-    {1, 1, 8, 1, 1, 3.52f, 0.081f, 0.664f, 0.104f},
-    {1, 2, 4, 1, 1, 3.20f, 0.142f, 0.f, 0.194f},
-    {1, 4, 2, 1, 1, 2.92f, 0.284f, 0.f, 0.322f},
-    {1, 4, 2, 1, 2, 2.67f, 0.583f, 0.f, 0.566f},
-    {1, 1, 8, 2, 1, 4.48f, 0.117f, 2.94f, 0.124f},
-    {1, 2, 4, 2, 1, 3.45f, 0.181f, 0.164f, 0.228f},
-    {1, 4, 2, 2, 1, 3.17f, 0.316f, 0.268f, 0.358f},
-    {1, 4, 2, 2, 2, 3.13f, 0.653f, 0.826f, 0.556f},
-    {1, 4, 2, 3, 1, 3.67f, 0.345f, 0.416f, 0.389f},
-    {1, 4, 2, 3, 2, 3.60f, 0.686f, 0.540f, 0.616f},
-    {1, 2, 4, 4, 1, 4.42f, 0.255f, 1.95f, 0.322f},
-    {1, 4, 2, 4, 1, 3.74f, 0.420f, 0.f, 0.456f},
-    {1, 4, 2, 4, 2, 3.60f, 0.756f, 2.26f, 0.734f},
-    {1, 8, 1, 4, 1, 2.50f, 0.819f, 0.192f, 0.682f},
-    {1, 8, 1, 4, 2, 4.06f, 1.30f, 3.54f, 1.35f},
-    {1, 8, 1, 8, 2, 7.16f, 1.68f, 8.49f, 1.82f},
+    {1, 1, 8, 1, 1, 3.509f, 0.081f, 0.581f, 0.108f},
+    {1, 2, 4, 1, 1, 3.322f, 0.139f, 0.f, 0.198f},
+    {1, 4, 2, 1, 1, 3.185f, 0.264f, 0.182f, 0.336f},
+    {1, 4, 2, 1, 2, 3.126f, 0.520f, 0.652f, 0.432f},
+    {1, 1, 8, 2, 1, 4.293f, 0.122f, 2.731f, 0.128f},
+    {1, 2, 4, 2, 1, 3.669f, 0.185f, 0.574f, 0.221f},
+    {1, 4, 2, 2, 1, 3.321f, 0.304f, 0.409f, 0.339f},
+    {1, 4, 2, 2, 2, 3.546f, 0.622f, 1.128f, 0.463f},
+    {1, 4, 2, 3, 1, 3.785f, 0.353f, 0.631f, 0.358f},
+    {1, 4, 2, 3, 2, 4.234f, 0.640f, 2.298f, 0.577f},
+    {1, 2, 4, 4, 1, 4.716f, 0.276f, 2.966f, 0.302f},
+    {1, 4, 2, 4, 1, 4.227f, 0.427f, 1.002f, 0.411f},
+    {1, 4, 2, 4, 2, 4.551f, 0.659f, 3.207f, 0.607f},
+    {1, 8, 1, 4, 1, 4.073f, 0.678f, 1.394f, 0.597f},
+    {1, 8, 1, 4, 2, 5.530f, 1.265f, 4.935f, 1.075f},
+    {1, 8, 1, 8, 2, 10.39f, 1.487f, 7.528f, 1.611f},
 };
 #define MXFP4_WIDE(...) {launch_block<kE4m3, __VA_ARGS__>, launch_block<kE5m2, __VA_ARGS__>}
 hipError_t (*const kLaunch8[][2])(const Args&, const DeviceInfo&, hipStream_t) = {
@@ -49,21 +49,23 @@ hipError_t (*const kLaunch8[][2])(const Args&, const DeviceInfo&, hipStream_t) =
 static_assert(sizeof kCosts8 / sizeof kCosts8[0] == sizeof kLaunch8 / sizeof kLaunch8[0], "one cost per shape");
 
 const Cost kCosts6[] = {
-    {1, 1, 8, 1, 1, 3.64f, 0.068f, 0.764f, 0.095f},
-    {1, 2, 4, 1, 1, 3.37f, 0.108f, 0.f, 0.165f},
-    {1, 2, 4, 1, 2, 3.42f, 0.212f, 0.f, 0.319f},
-    {1, 4, 2, 1, 1, 3.10f, 0.225f, 0.f, 0.294f},
-    {1, 4, 2, 1, 2, 2.76f, 0.476f, 0.f, 0.582f},
-    {1, 2, 4, 2, 1, 3.53f, 0.168f, 0.593f, 0.187f},
-    {1, 4, 2, 2, 1, 3.27f, 0.278f, 0.208f, 0.346f},
-    {1, 4, 2, 2, 2, 3.48f, 0.510f, 0.983f, 0.553f},
-    {1, 4, 2, 3, 1, 3.68f, 0.323f, 0.726f, 0.346f},
-    {1, 4, 2, 3, 2, 4.36f, 0.596f, 2.16f, 0.569f},
-    {1, 2, 4, 4, 1, 4.61f, 0.243f, 1.92f, 0.311f},
-    {1, 4, 2, 4, 1, 3.84f, 0.372f, 0.798f, 0.408f},
-    {1, 8, 1, 4, 1, 3.79f, 0.675f, 1.10f, 0.679f},
-    {1, 8, 1, 4, 2, 4.63f, 1.22f, 1.70f, 1.56f},
-    {1, 8, 1, 8, 2, 9.77f, 1.65f, 7.25f, 1.91f},
+    {1, 1, 8, 1, 1, 3.806f, 0.072f, 0.723f, 0.093f},
+    {1, 2, 4, 1, 1, 3.416f, 0.116f, 0.f, 0.160f},
+    {1, 2, 4, 1, 2, 3.426f, 0.206f, 0.f, 0.283f},
+    {1, 4, 2, 1, 1, 3.254f, 0.224f, 0.212f, 0.224f},
+    {1, 4, 2, 1, 2, 3.206f, 0.418f, 0.913f, 0.307f},
+    {1, 1, 8, 2, 1, 4.446f, 0.118f, 2.857f, 0.121f},
+    {1, 2, 4, 2, 1, 3.754f, 0.156f, 0.547f, 0.180f},
+    {1, 4, 2, 2, 1, 3.445f, 0.270f, 0.420f, 0.261f},
+    {1, 4, 2, 2, 2, 3.745f, 0.529f, 0.882f, 0.374f},
+    {1, 4, 2, 3, 1, 3.956f, 0.331f, 0.839f, 0.295f},
+    {1, 4, 2, 3, 2, 4.294f, 0.539f, 2.276f, 0.508f},
+    {1, 2, 4, 4, 1, 4.419f, 0.244f, 2.794f, 0.252f},
+    {1, 4, 2, 4, 1, 3.900f, 0.373f, 1.094f, 0.322f},
+    {1, 4, 2, 4, 2, 4.507f, 0.608f, 3.006f, 0.568f},
+    {1, 8, 1, 4, 1, 4.186f, 0.652f, 1.435f, 0.551f},
+    {1, 8, 1, 4, 2, 5.960f, 1.163f, 5.081f, 1.119f},
+    {1, 8, 1, 8, 2, 8.990f, 1.600f, 5.428f, 1.698f},
 };
 #define MXFP4_WIDE(...) {launch_block<kE2m3, __VA_ARGS__>, launch_block<kE3m2, __VA_ARGS__>}
 hipError_t (*const kLaunch6[][2])(const Args&, const DeviceInfo&, hipStream_t) = {
@@ -72,6 +74,7 @@ hipError_t (*const kLaunch6[][2])(const Args&, const DeviceInfo&, hipStream_t) =
     MXFP4_WIDE(1, 2, 4, 1, 2),
     MXFP4_WIDE(1, 4, 2, 1, 1),
     MXFP4_WIDE(1, 4, 2, 1, 2),
+    MXFP4_WIDE(1, 1, 8, 2, 1),
     MXFP4_WIDE(1, 2, 4, 2, 1),
     MXFP4_WIDE(1, 4, 2, 2, 1),
     MXFP4_WIDE(1, 4, 2, 2, 2),
@@ -79,6 +82,7 @@ hipError_t (*const kLaunch6[][2])(const Args&, const DeviceInfo&, hipStream_t) =
     MXFP4_WIDE(1, 4, 2, 3, 2),
     MXFP4_WIDE(1, 2, 4, 4, 1),
     MXFP4_WIDE(1, 4, 2, 4, 1),
+    MXFP4_WIDE(1, 4, 2, 4, 2),
     MXFP4_WIDE(1, 8, 1, 4, 1),
     MXFP4_WIDE(1, 8, 1, 4, 2),
     MXFP4_WIDE(1, 8, 1, 8, 2),
@@ -87,35 +91,35 @@ hipError_t (*const kLaunch6[][2])(const Args&, const DeviceInfo&, hipStream_t) =
 static_assert(sizeof kCosts6 / sizeof kCosts6[0] == sizeof kLaunch6 / sizeof kLaunch6[0], "one cost per shape");
 
 const Cost kCosts2[] = {
-    {1, 1, 8, 1, 1, 3.63f, 0.064f, 0.902f, 0.054f},
-    {1, 1, 8, 1, 2, 3.82f, 0.094f, 1.24f, 0.078f},
-    {1, 1, 8, 1, 4, 4.43f, 0.160f, 1.80f, 0.137f},
-    {1, 2, 4, 1, 1, 3.37f, 0.117f, 0.432f, 0.075f},
-    {1, 2, 4, 1, 2, 3.69f, 0.178f, 0.738f, 0.126f},
-    {1, 4, 2, 1, 1, 3.25f, 0.213f, 0.540f, 0.128f},
-    {1, 4, 2, 1, 2, 3.63f, 0.333f, 0.525f, 0.277f},
-    {1, 2, 4, 2, 1, 3.66f, 0.151f, 0.774f, 0.118f},
-    {1, 2, 4, 2, 2, 4.11f, 0.221f, 1.18f, 0.177f},
-    {1, 4, 2, 2, 1, 3.40f, 0.274f, 0.756f, 0.170f},
-    {1, 4, 2, 2, 2, 4.03f, 0.408f, 1.27f, 0.306f},
-    {1, 4, 2, 3, 1, 3.71f, 0.333f, 0.916f, 0.227f},
-    {1, 4, 2, 3, 2, 4.52f, 0.469f, 1.81f, 0.387f},
-    {1, 2, 4, 4, 2, 5.17f, 0.328f, 3.28f, 0.329f},
-    {1, 4, 2, 4, 1, 3.86f, 0.372f, 1.36f, 0.279f},
-    {1, 4, 2, 4, 2, 5.61f, 0.509f, 3.21f, 0.557f},
-    {1, 8, 1, 4, 1, 4.26f, 0.642f, 1.23f, 0.531f},
-    {1, 8, 1, 4, 2, 6.83f, 1.00f, 0.580f, 0.946f},
-    {1, 8, 1, 8, 2, 11.01f, 1.60f, 5.68f, 1.71f},
+    {1, 1, 8, 1, 1, 3.652f, 0.065f, 0.757f, 0.055f},
+    {1, 1, 8, 1, 2, 3.807f, 0.097f, 0.848f, 0.085f},
+    {1, 2, 4, 1, 1, 3.538f, 0.122f, 0.447f, 0.082f},
+    {1, 2, 4, 1, 2, 3.768f, 0.174f, 0.800f, 0.126f},
+    {1, 4, 2, 1, 1, 3.405f, 0.229f, 0.569f, 0.136f},
+    {1, 4, 2, 1, 2, 3.735f, 0.361f, 0.934f, 0.235f},
+    {1, 1, 8, 2, 2, 4.722f, 0.145f, 3.242f, 0.135f},
+    {1, 2, 4, 2, 1, 3.833f, 0.165f, 0.954f, 0.110f},
+    {1, 2, 4, 2, 2, 4.255f, 0.233f, 1.416f, 0.161f},
+    {1, 4, 2, 2, 1, 3.610f, 0.281f, 0.762f, 0.165f},
+    {1, 4, 2, 2, 2, 4.214f, 0.410f, 1.422f, 0.287f},
+    {1, 4, 2, 3, 1, 4.010f, 0.324f, 1.060f, 0.222f},
+    {1, 4, 2, 3, 2, 4.944f, 0.475f, 1.896f, 0.341f},
+    {1, 2, 4, 4, 2, 6.097f, 0.331f, 3.870f, 0.329f},
+    {1, 4, 2, 4, 1, 4.368f, 0.380f, 1.407f, 0.281f},
+    {1, 4, 2, 4, 2, 5.323f, 0.510f, 3.631f, 0.498f},
+    {1, 8, 1, 4, 1, 4.324f, 0.667f, 1.617f, 0.464f},
+    {1, 8, 1, 4, 2, 6.954f, 0.987f, 4.795f, 0.988f},
+    {1, 8, 1, 8, 2, 10.50f, 1.487f, 6.196f, 1.604f},
 };
 #define MXFP4_WIDE(...) {launch_block<kT2, __VA_ARGS__>}
 hipError_t (*const kLaunch2[][1])(const Args&, const DeviceInfo&, hipStream_t) = {
     MXFP4_WIDE(1, 1, 8, 1, 1),
     MXFP4_WIDE(1, 1, 8, 1, 2),
-    MXFP4_WIDE(1, 1, 8, 1, 4),
     MXFP4_WIDE(1, 2, 4, 1, 1),
     MXFP4_WIDE(1, 2, 4, 1, 2),
     MXFP4_WIDE(1, 4, 2, 1, 1),
     MXFP4_WIDE(1, 4, 2, 1, 2),
+    MXFP4_WIDE(1, 1, 8, 2, 2),
     MXFP4_WIDE(1, 2, 4, 2, 1),
     MXFP4_WIDE(1, 2, 4, 2, 2),
     MXFP4_WIDE(1, 4, 2, 2, 1),

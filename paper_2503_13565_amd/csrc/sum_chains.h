@@ -22,14 +22,14 @@ constexpr bool cuts_phases(int wk, int mf) { return wk > 1 && mf <= 3; }
 
 constexpr int64_t tiles_of(int m, int n) { return (int64_t)((m + 15) / 16) * ((n + 15) / 16); }
 
-// Chains of a call's outputs: eight up to 32 rows or 12 tiles of 16 x 16 outputs per compute unit, four up to 24, else two; twice
-// that, and eight at most, where K is longer than 8192 (blocks of four waves along K went there too, and a further cut of
+// Chains of a call's outputs: eight up to 32 rows or 12 tiles of 16 x 16 outputs per compute unit, four up to 28, else two; twice
+// that, and eight at most, where K is longer than 4096 (blocks of four waves along K went there too, and a further cut of
 // so long a sum takes no time that could be measured); never more than steps of 128 along K.
 constexpr int chains_wanted(int m, int n, int k, int cus)
 {
     const int64_t tiles = tiles_of(m, n);
-    const int few = m <= 32 || tiles <= 12 * (int64_t)cus ? 8 : tiles <= 24 * (int64_t)cus ? 4 : 2, steps = (k + 127) / 128;
-    const int most = k > 8192 && few < 8 ? 2 * few : few;
+    const int few = m <= 32 || tiles <= 12 * (int64_t)cus ? 8 : tiles <= 28 * (int64_t)cus ? 4 : 2, steps = (k + 127) / 128;
+    const int most = k > 4096 && few < 8 ? 2 * few : few;
     return steps < most ? steps : most;
 }
 
@@ -51,15 +51,15 @@ constexpr int chain_pairs(int phases, int wk, int chains)
 }
 
 // Whether a call may take a shape.  A block that cannot cut its sums is there for the largest products alone, where its outputs
-// fill their rounds over the units to 85 %: there it is the fastest by a tenth (22016 x 4096 with the gate at 509 rows 76 us,
-// 84 in blocks that do).
+// fill their rounds over the units to 85 %: there it is the fastest by a tenth (22016 x 4096 at 509 rows 78 us,
+// 89 in blocks that do).
 constexpr bool cuts_enough(int bits, int wm, int wn, int wk, int mf, int nf, int m, int n, int k, int cus)
 {
     const int wanted = chains_wanted(m, n, k, cus);
     if (chains_of(bits, wk, mf, nf, (k + 127) / 128) >= wanted)
         return true;
     const int64_t bm = 16 * wm * mf, bn = 16 * wn * nf, blocks = ((m + bm - 1) / bm) * ((n + bn - 1) / bn);
-    return uncut(mf, nf) && m > 32 && tiles_of(m, n) > 24 * (int64_t)cus &&
+    return uncut(mf, nf) && m > 32 && tiles_of(m, n) > 28 * (int64_t)cus &&
            (int64_t)m * n * 100 >= 85 * bm * bn * ((blocks + cus - 1) / cus * cus);
 }
 

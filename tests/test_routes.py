@@ -229,3 +229,23 @@ def test_sizes_that_take_every_block_shape(rules, kind, source, name, never):
             assert rules.bf16(m, n, k, int(k % 128 == 0))
         else:
             assert rules.format(m, n, k, kind, 1)
+
+
+@pytest.mark.parametrize("kind,m,n,k,fast", [
+    # us by shape, four sets of weights in rotation; those within 5 % of the fastest
+    ("bf16", 39, 21924, 4224, [(1, 4, 2, 3, 2), (1, 4, 2, 4, 2)]),      # 47.3, 48.4; one column of tiles instead of two 54.7
+    ("bf16", 33, 254, 1408, [(1, 1, 8, 1, 1)]),                         # 7.7; 8.8
+    ("mxfp4", 46, 2986, 5504, [(1, 1, 8, 1, 3)]),                       # 11.7; 12.3
+    ("mxfp4", 5, 8162, 11392, [(1, 1, 8, 1, 2)]),                       # 12.6; 13.9
+    (6, 54, 22740, 10752, [(1, 4, 2, 4, 2)]),                           # 70; 90
+    ("mxfp4", 48, 32000, 4096, [(1, 4, 2, 3, 2)]),                      # 23.0; 24.4
+    ("mxfp4", 64, 12000, 4096, [(1, 2, 4, 2, 3)]),                      # 15.4; 17.0
+    ("mxfp4", 128, 4096, 4096, [(1, 2, 4, 2, 2)]),                      # 9.9; 10.5
+    ("mxfp4", 509, 22016, 4096, [(1, 8, 1, 8, 3)]),                     # 78; 89
+])
+def test_shapes_that_were_measured_the_fastest(rules, kind, m, n, k, fast):
+    source, name, bits = {"bf16": ("gemm_wide_bf16.hip", "kCosts", 16), "mxfp4": ("gemm_wide.hip", "kCosts", 4),
+                          6: ("gemm_wide_fmt.hip", "kCosts6", 6)}[kind]
+    body = re.search(r"const Cost %s\[\] = \{(.*?)\n\};" % name, open(os.path.join(CSRC, source)).read(), re.S).group(1)
+    table = [[float(v.rstrip("f")) for v in row.split(",")] for row in re.findall(r"\{([^{}]*)\}", body)]
+    assert tuple(int(v) for v in table[picked(rules, bits, table, m, n, k)[0]][:5]) in fast
