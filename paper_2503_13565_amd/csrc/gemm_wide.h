@@ -140,17 +140,26 @@ __device__ __forceinline__ u32x4_t operand(const uint32_t* r, const u32x16_t& si
     return w;
 }
 
-// How the sums of a wave are cut into chains (what for: sum_chains.h).  kChains: a chain of whole pairs of phases is added to the
-// output's sum at its end, in a second set of registers, K / chains long.  kSteps: so is every step's, which is also more exact than
-// eight long chains for elements of 6 bits and more (a BF16 pick's values at K = 4096, against 64 bits: 0.9e-7 to 1.2e-7, 1.5e-7 in
-// eight chains, 4.2e-7 in one); blocks of many rows then go through one row of fragments after the other, for which two
-// rows' sums are enough.  The largest 8-bit block has the registers for kChains and not the time for kSteps (22016 x 4096 at 509
-// rows: 15 % of it).
-enum Cut { kWhole, kChains, kSteps };
+// How the sums of a wave are cut into chains (what for: sum_chains.h).
+//   - kSets: the matrix instructions of a step take turns on two or four sums.  Takes registers only, for one row of fragments (and
+//     two or three where four waves share K).
+//   - kChains: a chain of whole pairs of phases is added to the output's sum at its end, K / chains long.  (One row of fragments
+//     like that: 4096 x 1024 at 5 rows 3.8 us, 3.6 with sets.)
+//   - kSteps: so is every step's, which is more exact than long chains for elements of 6 bits and more (a pick's BF16 values at
+//     K = 4096, against 64 bits: 0.9e-7 to 1.2e-7, 1.5e-7 in eight chains, 4.2e-7 in one).  Blocks of many rows then go through
+//     one row of fragments after the other, for which two rows' sums are enough.  The largest 8-bit block has the registers for
+//     kChains and not the time for this (22016 x 4096 at 509 rows: 15 % of it).
+// A step's four instructions on BF16 weights make a sum each at one row of fragments, added in pairs: as exact as the vector ALUs, which
+// take the shorter of these calls' neighbours (0.98 of their error at K = 512, 0.79 at 4096; 1.13 and 0.88 in one chain), and no slower.
+enum Cut { kWhole, kSets, kChains, kSteps };
 constexpr Cut sum_cut(Kind w, int wk, int mf, int nf)
 {
-    return wk == 8 || uncut(mf, nf) ? kWhole : kind_bits(w) > 4 && !(kind_bits(w) == 8 && mf * nf == 16) ? kSteps : kChains;
+    return uncut(mf, nf) || (wk == 8 && mf > 1)                              ? kWhole
+           : kind_bits(w) > 4 && !(kind_bits(w) == 8 && mf * nf == 16)       ? kSteps
+           : sum_sets(wk, mf) > 1 && kind_bits(w) <= 4                       ? kSets
+                                                                             : kChains;
 }
+constexpr bool each_apart(Kind w, int mf) { return w == kBf16 && mf == 1; }
 
 // The leading arguments are scalars that arrive in registers when a wave starts; `out` is for the end.
 template <Kind kW, int WM, int WN, int WK, int MF, int NF>
@@ -310,15 +319,17 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
 
     constexpr Cut kCut = sum_cut(kW, WK, MF, NF);
     constexpr bool kRoll = MF >= 4;                                     // (below)
-    constexpr bool kApart = kCut == kChains || (kCut == kSteps && !kRoll);
-    f32x4_t acc[MF][NF], chain[kApart ? MF : 1][NF];
+    constexpr bool kEach = each_apart(kW, MF), kStepSums = kCut == kSteps && !kRoll;
+    constexpr int kCopies = kCut == kSets ? sum_sets(WK, MF) : kCut == kChains ? 2 : kStepSums ? (kEach ? 5 : 2) : 1;
+    f32x4_t sums_of[kCopies][MF][NF];                                   // [0]: the outputs' sums; kSteps, kChains: what is added to them
+    auto& acc = sums_of[0];
 #pragma unroll
-    for (int i = 0; i < MF; ++i)
+    for (int c = 0; c < kCopies; ++c)
 #pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            acc[i][f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            chain[kApart ? i : 0][f] = acc[i][f];
-        }
+        for (int i = 0; i < MF; ++i)
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+                sums_of[c][i][f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const int chain_all = chain_pairs(phases, WK, chains);
     int chain_left = chain_all;
     auto end_chain = [&]() {
@@ -326,10 +337,13 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
         for (int i = 0; i < MF; ++i)
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
-                acc[i][f] += chain[kApart ? i : 0][f];
-                if (kCut == kChains)
-                    chain[kApart ? i : 0][f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-                else                                                    // (kSteps starts from zero; the sum stays here)
+                if constexpr (kEach)
+                    acc[i][f] += (sums_of[1][i][f] + sums_of[2][i][f]) + (sums_of[3][i][f] + sums_of[4][i][f]);
+                else
+                    acc[i][f] += sums_of[1][i][f];
+                if constexpr (kCut == kChains)
+                    sums_of[1][i][f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                else                                                    // (a step starts from zero; the sum stays here)
                     asm volatile("" : "+v"(acc[i][f]));
             }
     };
@@ -360,10 +374,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
                 auto read_x = [&](int i, int j) { return xb[i * 256 + (chunk_at(kW == kBf16 ? 4 * j + lg : 4 * lg + j) ^ li)]; };
                 auto weights = [&](int f, int j) { return operand<kW>(sl.q[f], six[kBits == 6 ? f : 0], scl[f], j); };
                 auto multiply = [&](int i, int f, int j, u32x4_t w, u32x4_t x) {
-                    f32x4_t& sum = kApart ? chain[kApart ? i : 0][f] : acc[i][f];
+                    f32x4_t& sum = sums_of[kCut == kSets ? j % kCopies : kCut == kChains ? 1 : kStepSums ? (kEach ? 1 + j : 1) : 0][i][f];
                     sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                         __builtin_bit_cast(bf16x8_t, w), __builtin_bit_cast(bf16x8_t, x),
-                        kCut == kSteps && j == 0 ? f32x4_t{0.f, 0.f, 0.f, 0.f} : sum, 0, 0, 0);
+                        kStepSums && (kEach || j == 0) ? f32x4_t{0.f, 0.f, 0.f, 0.f} : sum, 0, 0, 0);
                 };
 #pragma unroll
                 for (int i = 0; i < (kCut == kSteps && kRoll ? 1 : MF); ++i)
@@ -446,7 +460,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
                         }
                         __builtin_amdgcn_sched_barrier(0);
                     }
-                    if constexpr (kCut == kSteps)
+                    if constexpr (kStepSums)
                         end_chain();
                 }
             }
@@ -462,6 +476,15 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
             lds_barrier();
         }
     }
+
+    if constexpr (kCut == kSets)
+#pragma unroll
+        for (int c = 1; c < kCopies; ++c)
+#pragma unroll
+            for (int i = 0; i < MF; ++i)
+#pragma unroll
+                for (int f = 0; f < NF; ++f)
+                    acc[i][f] += sums_of[c][i][f];
 
     // Output fragment (i, f) of block position (wm, wn): lane (li, lg) holds weight rows 4 lg + r for
     // activation row li.  The sums go through the LDS, so that whole rows are stored.
@@ -548,8 +571,8 @@ hipError_t launch_block(const Args& a, const DeviceInfo& dev, hipStream_t stream
 // as start + step x (steps of 128 along K, whole phases).  Fitted to every shape at 2000 sizes (MXFP4; 1100 each of the 8-bit,
 // 6-bit, ternary and BF16 elements) of 3 to 520 rows, 128 to 34000 weight rows and K = 256 to 12288, four sets of weights in
 // rotation, those near the fastest shape of a size weighing most, and to 256, 512 and 1024 blocks at K = 512 to 10240.  At a quarter of
-// the sizes that was left out of the fit the choice is within 5 % of the fastest shape that cuts the sums far enough on 488 of 500,
-// 256, 265, 274 and 273 of 275, on average 1.006, 1.007, 1.006, 1.003 and 1.002 of it, at worst 1.25, 1.09, 1.13, 1.08 and 1.10.
+// the sizes that was left out of the fit the choice is within 5 % of the fastest shape that cuts the sums far enough on 481 of 500,
+// 256, 268, 268 and 271 of 275, on average 1.006, 1.006, 1.004, 1.004 and 1.002 of it, at worst 1.11, 1.07, 1.09, 1.08 and 1.16.
 // A shape is in a table if the choice would be 6e-5 slower on average without it.
 struct Cost {
     int wm, wn, wk, mf, nf;

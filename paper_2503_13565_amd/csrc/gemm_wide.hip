@@ -8,34 +8,34 @@ namespace {
 using namespace wide;
 
 const Cost kCosts[] = {
-    {1, 1, 8, 1, 1, 3.622f, 0.058f, 0.686f, 0.058f},
-    {1, 1, 8, 1, 2, 3.841f, 0.077f, 0.785f, 0.090f},
-    {1, 1, 8, 1, 3, 3.946f, 0.113f, 0.966f, 0.119f},
-    {1, 2, 4, 1, 1, 3.510f, 0.100f, 0.362f, 0.079f},
-    {1, 2, 4, 1, 2, 3.827f, 0.137f, 0.594f, 0.134f},
-    {1, 2, 4, 1, 3, 3.980f, 0.194f, 1.082f, 0.149f},
-    {1, 4, 2, 1, 1, 3.386f, 0.174f, 0.478f, 0.113f},
-    {1, 4, 2, 1, 2, 3.641f, 0.251f, 0.778f, 0.163f},
-    {1, 1, 8, 2, 3, 4.658f, 0.156f, 3.111f, 0.161f},
-    {1, 2, 4, 2, 2, 4.246f, 0.183f, 1.079f, 0.166f},
-    {1, 2, 4, 2, 3, 4.785f, 0.239f, 3.122f, 0.221f},
-    {1, 4, 2, 2, 1, 3.644f, 0.217f, 0.685f, 0.152f},
-    {1, 4, 2, 2, 2, 4.146f, 0.323f, 1.194f, 0.242f},
-    {1, 4, 2, 2, 3, 5.014f, 0.429f, 3.059f, 0.425f},
-    {1, 8, 1, 2, 2, 4.324f, 0.616f, 1.823f, 0.444f},
-    {1, 2, 4, 3, 3, 6.123f, 0.313f, 4.433f, 0.310f},
-    {1, 4, 2, 3, 1, 4.140f, 0.280f, 0.978f, 0.202f},
-    {1, 4, 2, 3, 2, 4.752f, 0.395f, 2.816f, 0.383f},
-    {1, 4, 2, 3, 3, 5.950f, 0.516f, 4.163f, 0.507f},
-    {1, 2, 4, 4, 3, 6.346f, 0.368f, 4.390f, 0.393f},
-    {1, 4, 2, 4, 2, 5.225f, 0.433f, 3.313f, 0.450f},
-    {1, 4, 2, 4, 3, 6.753f, 0.585f, 4.280f, 0.638f},
-    {1, 8, 1, 4, 1, 4.147f, 0.606f, 1.668f, 0.414f},
-    {1, 8, 1, 4, 2, 6.889f, 0.863f, 5.098f, 0.832f},
-    {1, 8, 1, 6, 2, 9.250f, 1.074f, 5.661f, 1.178f},
-    {2, 4, 1, 4, 3, 9.174f, 1.204f, 6.128f, 1.224f},
-    {1, 8, 1, 8, 2, 11.32f, 1.383f, 8.953f, 1.413f},
-    {1, 8, 1, 8, 3, 12.40f, 2.021f, 9.467f, 2.519f},
+    {1, 1, 8, 1, 1, 3.724f, 0.062f, 0.883f, 0.059f},
+    {1, 1, 8, 1, 2, 3.948f, 0.079f, 0.931f, 0.089f},
+    {1, 1, 8, 1, 3, 4.205f, 0.097f, 1.050f, 0.122f},
+    {1, 2, 4, 1, 1, 3.459f, 0.090f, 0.386f, 0.078f},
+    {1, 2, 4, 1, 2, 3.644f, 0.131f, 0.535f, 0.136f},
+    {1, 2, 4, 1, 3, 4.023f, 0.189f, 2.250f, 0.181f},
+    {1, 4, 2, 1, 1, 3.370f, 0.157f, 0.414f, 0.110f},
+    {1, 4, 2, 1, 2, 3.747f, 0.254f, 0.879f, 0.177f},
+    {1, 2, 4, 2, 2, 4.234f, 0.178f, 1.074f, 0.164f},
+    {1, 2, 4, 2, 3, 4.761f, 0.228f, 2.994f, 0.210f},
+    {1, 2, 4, 2, 4, 5.022f, 0.300f, 3.412f, 0.287f},
+    {1, 4, 2, 2, 1, 3.673f, 0.218f, 0.703f, 0.151f},
+    {1, 4, 2, 2, 2, 4.190f, 0.327f, 1.291f, 0.260f},
+    {1, 4, 2, 2, 3, 5.069f, 0.428f, 3.034f, 0.422f},
+    {1, 8, 1, 2, 2, 4.412f, 0.648f, 1.956f, 0.464f},
+    {1, 2, 4, 3, 3, 5.448f, 0.304f, 3.990f, 0.307f},
+    {1, 4, 2, 3, 1, 4.257f, 0.290f, 1.007f, 0.215f},
+    {1, 4, 2, 3, 2, 4.798f, 0.422f, 2.933f, 0.393f},
+    {1, 4, 2, 3, 3, 6.242f, 0.537f, 4.725f, 0.528f},
+    {1, 2, 4, 4, 3, 6.690f, 0.391f, 4.652f, 0.405f},
+    {1, 4, 2, 4, 2, 5.218f, 0.429f, 3.278f, 0.428f},
+    {1, 4, 2, 4, 3, 6.762f, 0.586f, 4.044f, 0.634f},
+    {1, 8, 1, 4, 1, 4.124f, 0.586f, 1.650f, 0.412f},
+    {1, 8, 1, 4, 2, 6.822f, 0.837f, 5.039f, 0.785f},
+    {1, 8, 1, 6, 2, 8.877f, 1.034f, 5.601f, 1.103f},
+    {2, 4, 1, 4, 3, 9.003f, 1.219f, 6.400f, 1.175f},
+    {1, 8, 1, 8, 2, 11.10f, 1.346f, 9.165f, 1.309f},
+    {1, 8, 1, 8, 3, 12.85f, 1.957f, 8.726f, 2.422f},
 };
 
 #define MXFP4_WIDE(...)                                                                             \
@@ -49,9 +49,9 @@ hipError_t (*const kLaunch[][3])(const Args&, const DeviceInfo&, hipStream_t) = 
     MXFP4_WIDE(1, 2, 4, 1, 3),
     MXFP4_WIDE(1, 4, 2, 1, 1),
     MXFP4_WIDE(1, 4, 2, 1, 2),
-    MXFP4_WIDE(1, 1, 8, 2, 3),
     MXFP4_WIDE(1, 2, 4, 2, 2),
     MXFP4_WIDE(1, 2, 4, 2, 3),
+    MXFP4_WIDE(1, 2, 4, 2, 4),
     MXFP4_WIDE(1, 4, 2, 2, 1),
     MXFP4_WIDE(1, 4, 2, 2, 2),
     MXFP4_WIDE(1, 4, 2, 2, 3),

@@ -8,22 +8,22 @@ namespace {
 using namespace wide;
 
 const Cost kCosts[] = {
-    {1, 1, 8, 1, 1, 3.780f, 0.142f, 0.573f, 0.199f},
-    {1, 2, 4, 1, 1, 3.296f, 0.260f, 0.f, 0.370f},
-    {1, 4, 2, 1, 1, 3.324f, 0.520f, 0.176f, 0.657f},
-    {1, 4, 2, 1, 2, 2.938f, 1.046f, 1.549f, 0.816f},
-    {1, 1, 8, 2, 1, 4.155f, 0.185f, 2.585f, 0.203f},
-    {1, 2, 4, 2, 1, 3.402f, 0.292f, 0.628f, 0.360f},
-    {1, 4, 2, 2, 1, 3.349f, 0.531f, 0.350f, 0.636f},
-    {1, 4, 2, 2, 2, 3.464f, 1.060f, 2.887f, 0.857f},
-    {1, 4, 2, 3, 1, 3.626f, 0.573f, 0.815f, 0.588f},
-    {1, 4, 2, 3, 2, 4.446f, 1.069f, 3.219f, 1.005f},
-    {1, 2, 4, 4, 1, 4.317f, 0.396f, 2.696f, 0.428f},
-    {1, 4, 2, 4, 1, 3.946f, 0.615f, 1.062f, 0.615f},
-    {1, 4, 2, 4, 2, 4.794f, 1.082f, 3.729f, 1.075f},
-    {1, 8, 1, 4, 1, 4.210f, 1.080f, 1.242f, 1.019f},
-    {1, 8, 1, 4, 2, 6.305f, 1.961f, 4.235f, 1.883f},
-    {1, 8, 1, 8, 2, 9.855f, 2.460f, 6.286f, 2.506f},
+    {1, 1, 8, 1, 1, 3.341f, 0.138f, 0.497f, 0.196f},
+    {1, 2, 4, 1, 1, 3.187f, 0.250f, 0.f, 0.361f},
+    {1, 4, 2, 1, 1, 3.209f, 0.501f, 0.203f, 0.631f},
+    {1, 4, 2, 1, 2, 2.594f, 1.011f, 1.528f, 0.794f},
+    {1, 1, 8, 2, 1, 3.994f, 0.176f, 2.514f, 0.196f},
+    {1, 2, 4, 2, 1, 3.422f, 0.294f, 0.623f, 0.361f},
+    {1, 4, 2, 2, 1, 3.360f, 0.533f, 0.345f, 0.636f},
+    {1, 4, 2, 2, 2, 3.541f, 1.050f, 2.797f, 0.867f},
+    {1, 4, 2, 3, 1, 3.645f, 0.576f, 0.838f, 0.590f},
+    {1, 4, 2, 3, 2, 4.413f, 1.069f, 3.155f, 1.010f},
+    {1, 2, 4, 4, 1, 4.212f, 0.389f, 2.693f, 0.416f},
+    {1, 4, 2, 4, 1, 3.914f, 0.682f, 1.088f, 0.617f},
+    {1, 4, 2, 4, 2, 4.770f, 1.086f, 3.754f, 1.074f},
+    {1, 8, 1, 4, 1, 4.237f, 1.081f, 1.268f, 1.024f},
+    {1, 8, 1, 4, 2, 6.103f, 2.006f, 4.303f, 1.929f},
+    {1, 8, 1, 8, 2, 9.309f, 2.480f, 6.431f, 2.503f},
 };
 
 #define MXFP4_WIDE(...) launch_block<kBf16, __VA_ARGS__>

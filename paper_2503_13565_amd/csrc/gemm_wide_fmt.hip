@@ -9,22 +9,22 @@ namespace {
 using namespace wide;
 
 const Cost kCosts8[] = {
-    {1, 1, 8, 1, 1, 3.509f, 0.081f, 0.581f, 0.108f},
-    {1, 2, 4, 1, 1, 3.322f, 0.139f, 0.f, 0.198f},
-    {1, 4, 2, 1, 1, 3.185f, 0.264f, 0.182f, 0.336f},
-    {1, 4, 2, 1, 2, 3.126f, 0.520f, 0.652f, 0.432f},
-    {1, 1, 8, 2, 1, 4.293f, 0.122f, 2.731f, 0.128f},
-    {1, 2, 4, 2, 1, 3.669f, 0.185f, 0.574f, 0.221f},
-    {1, 4, 2, 2, 1, 3.321f, 0.304f, 0.409f, 0.339f},
-    {1, 4, 2, 2, 2, 3.546f, 0.622f, 1.128f, 0.463f},
-    {1, 4, 2, 3, 1, 3.785f, 0.353f, 0.631f, 0.358f},
-    {1, 4, 2, 3, 2, 4.234f, 0.640f, 2.298f, 0.577f},
-    {1, 2, 4, 4, 1, 4.716f, 0.276f, 2.966f, 0.302f},
-    {1, 4, 2, 4, 1, 4.227f, 0.427f, 1.002f, 0.411f},
-    {1, 4, 2, 4, 2, 4.551f, 0.659f, 3.207f, 0.607f},
-    {1, 8, 1, 4, 1, 4.073f, 0.678f, 1.394f, 0.597f},
-    {1, 8, 1, 4, 2, 5.530f, 1.265f, 4.935f, 1.075f},
-    {1, 8, 1, 8, 2, 10.39f, 1.487f, 7.528f, 1.611f},
+    {1, 1, 8, 1, 1, 3.509f, 0.082f, 0.606f, 0.109f},
+    {1, 2, 4, 1, 1, 3.503f, 0.132f, 0.f, 0.208f},
+    {1, 4, 2, 1, 1, 3.130f, 0.260f, 0.217f, 0.360f},
+    {1, 4, 2, 1, 2, 3.316f, 0.558f, 0.724f, 0.459f},
+    {1, 1, 8, 2, 1, 4.468f, 0.115f, 2.588f, 0.122f},
+    {1, 2, 4, 2, 1, 3.609f, 0.182f, 0.596f, 0.216f},
+    {1, 4, 2, 2, 1, 3.406f, 0.310f, 0.424f, 0.345f},
+    {1, 4, 2, 2, 2, 3.629f, 0.560f, 1.118f, 0.464f},
+    {1, 4, 2, 3, 1, 3.730f, 0.346f, 0.614f, 0.349f},
+    {1, 4, 2, 3, 2, 4.328f, 0.600f, 2.334f, 0.618f},
+    {1, 2, 4, 4, 1, 4.841f, 0.271f, 2.916f, 0.296f},
+    {1, 4, 2, 4, 1, 3.876f, 0.430f, 0.989f, 0.415f},
+    {1, 4, 2, 4, 2, 4.871f, 0.658f, 3.342f, 0.619f},
+    {1, 8, 1, 4, 1, 4.135f, 0.678f, 1.336f, 0.613f},
+    {1, 8, 1, 4, 2, 5.680f, 1.250f, 4.844f, 1.080f},
+    {1, 8, 1, 8, 2, 10.67f, 1.570f, 7.428f, 1.646f},
 };
 #define MXFP4_WIDE(...) {launch_block<kE4m3, __VA_ARGS__>, launch_block<kE5m2, __VA_ARGS__>}
 hipError_t (*const kLaunch8[][2])(const Args&, const DeviceInfo&, hipStream_t) = {
@@ -49,23 +49,23 @@ hipError_t (*const kLaunch8[][2])(const Args&, const DeviceInfo&, hipStream_t) =
 static_assert(sizeof kCosts8 / sizeof kCosts8[0] == sizeof kLaunch8 / sizeof kLaunch8[0], "one cost per shape");
 
 const Cost kCosts6[] = {
-    {1, 1, 8, 1, 1, 3.806f, 0.072f, 0.723f, 0.093f},
-    {1, 2, 4, 1, 1, 3.416f, 0.116f, 0.f, 0.160f},
-    {1, 2, 4, 1, 2, 3.426f, 0.206f, 0.f, 0.283f},
-    {1, 4, 2, 1, 1, 3.254f, 0.224f, 0.212f, 0.224f},
-    {1, 4, 2, 1, 2, 3.206f, 0.418f, 0.913f, 0.307f},
-    {1, 1, 8, 2, 1, 4.446f, 0.118f, 2.857f, 0.121f},
-    {1, 2, 4, 2, 1, 3.754f, 0.156f, 0.547f, 0.180f},
-    {1, 4, 2, 2, 1, 3.445f, 0.270f, 0.420f, 0.261f},
-    {1, 4, 2, 2, 2, 3.745f, 0.529f, 0.882f, 0.374f},
-    {1, 4, 2, 3, 1, 3.956f, 0.331f, 0.839f, 0.295f},
-    {1, 4, 2, 3, 2, 4.294f, 0.539f, 2.276f, 0.508f},
-    {1, 2, 4, 4, 1, 4.419f, 0.244f, 2.794f, 0.252f},
-    {1, 4, 2, 4, 1, 3.900f, 0.373f, 1.094f, 0.322f},
-    {1, 4, 2, 4, 2, 4.507f, 0.608f, 3.006f, 0.568f},
-    {1, 8, 1, 4, 1, 4.186f, 0.652f, 1.435f, 0.551f},
-    {1, 8, 1, 4, 2, 5.960f, 1.163f, 5.081f, 1.119f},
-    {1, 8, 1, 8, 2, 8.990f, 1.600f, 5.428f, 1.698f},
+    {1, 1, 8, 1, 1, 3.854f, 0.073f, 0.728f, 0.094f},
+    {1, 2, 4, 1, 1, 3.426f, 0.116f, 0.f, 0.160f},
+    {1, 2, 4, 1, 2, 3.828f, 0.199f, 0.f, 0.283f},
+    {1, 4, 2, 1, 1, 3.256f, 0.226f, 0.264f, 0.215f},
+    {1, 4, 2, 1, 2, 3.348f, 0.439f, 0.999f, 0.315f},
+    {1, 1, 8, 2, 1, 4.469f, 0.117f, 2.857f, 0.121f},
+    {1, 2, 4, 2, 1, 3.765f, 0.158f, 0.571f, 0.180f},
+    {1, 4, 2, 2, 1, 3.472f, 0.267f, 0.424f, 0.262f},
+    {1, 4, 2, 2, 2, 3.832f, 0.529f, 0.810f, 0.385f},
+    {1, 4, 2, 3, 1, 4.021f, 0.334f, 0.847f, 0.295f},
+    {1, 4, 2, 3, 2, 4.646f, 0.537f, 2.144f, 0.514f},
+    {1, 2, 4, 4, 1, 4.303f, 0.248f, 2.904f, 0.258f},
+    {1, 4, 2, 4, 1, 4.035f, 0.397f, 1.145f, 0.353f},
+    {1, 4, 2, 4, 2, 5.005f, 0.616f, 3.021f, 0.518f},
+    {1, 8, 1, 4, 1, 4.170f, 0.657f, 1.407f, 0.533f},
+    {1, 8, 1, 4, 2, 6.538f, 1.119f, 4.837f, 0.973f},
+    {1, 8, 1, 8, 2, 9.933f, 1.600f, 6.196f, 1.840f},
 };
 #define MXFP4_WIDE(...) {launch_block<kE2m3, __VA_ARGS__>, launch_block<kE3m2, __VA_ARGS__>}
 hipError_t (*const kLaunch6[][2])(const Args&, const DeviceInfo&, hipStream_t) = {
@@ -91,25 +91,24 @@ hipError_t (*const kLaunch6[][2])(const Args&, const DeviceInfo&, hipStream_t) =
 static_assert(sizeof kCosts6 / sizeof kCosts6[0] == sizeof kLaunch6 / sizeof kLaunch6[0], "one cost per shape");
 
 const Cost kCosts2[] = {
-    {1, 1, 8, 1, 1, 3.652f, 0.065f, 0.757f, 0.055f},
-    {1, 1, 8, 1, 2, 3.807f, 0.097f, 0.848f, 0.085f},
-    {1, 2, 4, 1, 1, 3.538f, 0.122f, 0.447f, 0.082f},
-    {1, 2, 4, 1, 2, 3.768f, 0.174f, 0.800f, 0.126f},
-    {1, 4, 2, 1, 1, 3.405f, 0.229f, 0.569f, 0.136f},
-    {1, 4, 2, 1, 2, 3.735f, 0.361f, 0.934f, 0.235f},
-    {1, 1, 8, 2, 2, 4.722f, 0.145f, 3.242f, 0.135f},
-    {1, 2, 4, 2, 1, 3.833f, 0.165f, 0.954f, 0.110f},
-    {1, 2, 4, 2, 2, 4.255f, 0.233f, 1.416f, 0.161f},
-    {1, 4, 2, 2, 1, 3.610f, 0.281f, 0.762f, 0.165f},
-    {1, 4, 2, 2, 2, 4.214f, 0.410f, 1.422f, 0.287f},
-    {1, 4, 2, 3, 1, 4.010f, 0.324f, 1.060f, 0.222f},
-    {1, 4, 2, 3, 2, 4.944f, 0.475f, 1.896f, 0.341f},
-    {1, 2, 4, 4, 2, 6.097f, 0.331f, 3.870f, 0.329f},
-    {1, 4, 2, 4, 1, 4.368f, 0.380f, 1.407f, 0.281f},
-    {1, 4, 2, 4, 2, 5.323f, 0.510f, 3.631f, 0.498f},
-    {1, 8, 1, 4, 1, 4.324f, 0.667f, 1.617f, 0.464f},
-    {1, 8, 1, 4, 2, 6.954f, 0.987f, 4.795f, 0.988f},
-    {1, 8, 1, 8, 2, 10.50f, 1.487f, 6.196f, 1.604f},
+    {1, 1, 8, 1, 1, 3.666f, 0.065f, 0.796f, 0.054f},
+    {1, 1, 8, 1, 2, 3.943f, 0.098f, 1.084f, 0.082f},
+    {1, 2, 4, 1, 1, 3.480f, 0.115f, 0.389f, 0.078f},
+    {1, 2, 4, 1, 2, 3.663f, 0.176f, 0.863f, 0.138f},
+    {1, 4, 2, 1, 1, 3.355f, 0.211f, 0.488f, 0.128f},
+    {1, 4, 2, 1, 2, 3.570f, 0.344f, 0.868f, 0.247f},
+    {1, 2, 4, 2, 1, 3.653f, 0.152f, 0.863f, 0.121f},
+    {1, 2, 4, 2, 2, 4.383f, 0.221f, 1.336f, 0.167f},
+    {1, 4, 2, 2, 1, 3.635f, 0.278f, 0.759f, 0.166f},
+    {1, 4, 2, 2, 2, 4.241f, 0.408f, 1.407f, 0.289f},
+    {1, 4, 2, 3, 1, 3.816f, 0.325f, 1.052f, 0.221f},
+    {1, 4, 2, 3, 2, 5.182f, 0.477f, 1.819f, 0.337f},
+    {1, 2, 4, 4, 2, 5.925f, 0.318f, 3.849f, 0.324f},
+    {1, 4, 2, 4, 1, 4.318f, 0.373f, 1.350f, 0.276f},
+    {1, 4, 2, 4, 2, 5.455f, 0.523f, 3.705f, 0.504f},
+    {1, 8, 1, 4, 1, 4.416f, 0.662f, 1.429f, 0.483f},
+    {1, 8, 1, 4, 2, 6.932f, 0.982f, 4.741f, 0.984f},
+    {1, 8, 1, 8, 2, 10.81f, 1.485f, 6.768f, 1.621f},
 };
 #define MXFP4_WIDE(...) {launch_block<kT2, __VA_ARGS__>}
 hipError_t (*const kLaunch2[][1])(const Args&, const DeviceInfo&, hipStream_t) = {
@@ -119,7 +118,6 @@ hipError_t (*const kLaunch2[][1])(const Args&, const DeviceInfo&, hipStream_t) =
     MXFP4_WIDE(1, 2, 4, 1, 2),
     MXFP4_WIDE(1, 4, 2, 1, 1),
     MXFP4_WIDE(1, 4, 2, 1, 2),
-    MXFP4_WIDE(1, 1, 8, 2, 2),
     MXFP4_WIDE(1, 2, 4, 2, 1),
     MXFP4_WIDE(1, 2, 4, 2, 2),
     MXFP4_WIDE(1, 4, 2, 2, 1),

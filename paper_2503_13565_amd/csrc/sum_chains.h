@@ -17,8 +17,12 @@ namespace wide {
 // Blocks without registers for a second set of sums: one chain per wave.
 constexpr bool uncut(int mf, int nf) { return mf * nf > 16; }
 
+// Sums that the matrix instructions of a step take turns on, where there are registers for them: sixteen chains of K for blocks of
+// sixteen rows, as many as the tile kernels make (eight with two waves along K), eight for the others.
+constexpr int sum_sets(int wk, int mf) { return mf == 1 ? (wk == 8 ? 2 : 4) : mf <= 3 && wk == 4 ? 2 : 1; }
+
 // Whether a block whose sums are cut at pairs of phases also cuts the only pair there is.
-constexpr bool cuts_phases(int wk, int mf) { return wk > 1 && mf <= 3; }
+constexpr bool cuts_phases(int wk, int mf) { return wk == 2 && mf <= 3; }
 
 constexpr int64_t tiles_of(int m, int n) { return (int64_t)((m + 15) / 16) * ((n + 15) / 16); }
 
@@ -37,10 +41,10 @@ constexpr int chains_wanted(int m, int n, int k, int cus)
 constexpr int chains_of(int bits, int wk, int mf, int nf, int steps)
 {
     if (wk == 8 || uncut(mf, nf))
-        return wk;
+        return wk;                                                      // (and more at one row of fragments)
     if (wk == 1)
         return steps > 4 ? 4 : 2;
-    return bits <= 4 && !cuts_phases(wk, mf) && steps <= 2 * wk ? wk : 8;    // (6 bits and more: every step is a chain)
+    return bits <= 4 && mf > 3 && steps <= 2 * wk ? wk : 8;             // (6 bits and more: every step is a chain)
 }
 
 // Pairs of phases in a chain of a wave whose sums are cut at pairs: an eighth (a quarter, a half) of K at most, or one pair.

@@ -24,7 +24,8 @@ extern "C" int cuts(int bits, int wm, int wn, int wk, int mf, int nf, int m, int
 extern "C" int longest(int bits, int wk, int mf, int nf, int k, int chains)
 {
     const int steps = (k + 127) / 128, phases = (steps + wk - 1) / wk, pairs = chain_pairs(phases, wk, chains);
-    const bool whole = wk == 8 || uncut(mf, nf), each = !whole && bits > 4 && !(bits == 8 && mf * nf == 16);
+    const bool whole = (wk == 8 && mf > 1) || uncut(mf, nf), each = !whole && bits > 4 && !(bits == 8 && mf * nf == 16);
+    const int sets = whole || each || bits > 4 ? 1 : sum_sets(wk, mf);
     int most = 0;
     for (int w = 0; w < wk; ++w) {
         int at = 0, left = pairs;
@@ -32,13 +33,13 @@ extern "C" int longest(int bits, int wk, int mf, int nf, int k, int chains)
             at += u * wk + w < steps;
             most = at > most ? at : most;
             const bool ends = u % 2 == 1 ? --left == 0 : cuts_phases(wk, mf) && phases <= 2;
-            if (each || (!whole && ends)) {
+            if (each || (!whole && sets == 1 && ends)) {
                 at = 0;
                 left = left > 0 ? left : pairs;
             }
         }
     }
-    return most;
+    return (most + sets - 1) / sets;                            // (a step's instructions take turns)
 }
 """
 
