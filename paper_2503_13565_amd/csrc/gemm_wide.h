@@ -49,6 +49,10 @@
 //     descriptor: zero weights against zero activations.
 #pragma once
 
+#include <array>
+#include <iterator>
+#include <utility>
+
 #include "block_out.h"
 #include "common.h"
 #include "kernels.h"
@@ -578,6 +582,19 @@ struct Cost {
     int wm, wn, wk, mf, nf;
     float first_start, first_step, next_start, next_step;
 };
+
+// The launches of a table's shapes, in its order.
+using Launch = hipError_t (*)(const Args&, const DeviceInfo&, hipStream_t);
+template <Kind kW, auto& kTable, size_t... kAt>
+constexpr std::array<Launch, sizeof...(kAt)> launches(std::index_sequence<kAt...>)
+{
+    return {launch_block<kW, kTable[kAt].wm, kTable[kAt].wn, kTable[kAt].wk, kTable[kAt].mf, kTable[kAt].nf>...};
+}
+template <Kind kW, auto& kTable>
+constexpr auto launches()
+{
+    return launches<kW, kTable>(std::make_index_sequence<std::size(kTable)>{});
+}
 
 // The cheapest of `count` shapes for a call, of those that cut its sums as far as it wants (-1: none with at most `max_cols` block
 // columns); `bits` per weight.  Products and picks take the same one, but for picks with little room for partial winners.

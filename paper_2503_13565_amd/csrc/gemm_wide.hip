@@ -7,7 +7,7 @@ namespace {
 
 using namespace wide;
 
-const Cost kCosts[] = {
+constexpr Cost kCosts[] = {
     {1, 1, 8, 1, 1, 3.724f, 0.062f, 0.883f, 0.059f},
     {1, 1, 8, 1, 2, 3.948f, 0.079f, 0.931f, 0.089f},
     {1, 1, 8, 1, 3, 4.205f, 0.097f, 1.050f, 0.122f},
@@ -38,41 +38,7 @@ const Cost kCosts[] = {
     {1, 8, 1, 8, 3, 12.85f, 1.957f, 8.726f, 2.422f},
 };
 
-#define MXFP4_WIDE(...)                                                                             \
-    {launch_block<kMx, __VA_ARGS__>, launch_block<kMxTiled, __VA_ARGS__>, launch_block<kMxRagged, __VA_ARGS__>}
-hipError_t (*const kLaunch[][3])(const Args&, const DeviceInfo&, hipStream_t) = {
-    MXFP4_WIDE(1, 1, 8, 1, 1),
-    MXFP4_WIDE(1, 1, 8, 1, 2),
-    MXFP4_WIDE(1, 1, 8, 1, 3),
-    MXFP4_WIDE(1, 2, 4, 1, 1),
-    MXFP4_WIDE(1, 2, 4, 1, 2),
-    MXFP4_WIDE(1, 2, 4, 1, 3),
-    MXFP4_WIDE(1, 4, 2, 1, 1),
-    MXFP4_WIDE(1, 4, 2, 1, 2),
-    MXFP4_WIDE(1, 2, 4, 2, 2),
-    MXFP4_WIDE(1, 2, 4, 2, 3),
-    MXFP4_WIDE(1, 2, 4, 2, 4),
-    MXFP4_WIDE(1, 4, 2, 2, 1),
-    MXFP4_WIDE(1, 4, 2, 2, 2),
-    MXFP4_WIDE(1, 4, 2, 2, 3),
-    MXFP4_WIDE(1, 8, 1, 2, 2),
-    MXFP4_WIDE(1, 2, 4, 3, 3),
-    MXFP4_WIDE(1, 4, 2, 3, 1),
-    MXFP4_WIDE(1, 4, 2, 3, 2),
-    MXFP4_WIDE(1, 4, 2, 3, 3),
-    MXFP4_WIDE(1, 2, 4, 4, 3),
-    MXFP4_WIDE(1, 4, 2, 4, 2),
-    MXFP4_WIDE(1, 4, 2, 4, 3),
-    MXFP4_WIDE(1, 8, 1, 4, 1),
-    MXFP4_WIDE(1, 8, 1, 4, 2),
-    MXFP4_WIDE(1, 8, 1, 6, 2),
-    MXFP4_WIDE(2, 4, 1, 4, 3),
-    MXFP4_WIDE(1, 8, 1, 8, 2),
-    MXFP4_WIDE(1, 8, 1, 8, 3),
-};
-#undef MXFP4_WIDE
-constexpr int kShapes = sizeof kCosts / sizeof kCosts[0];
-static_assert(kShapes == sizeof kLaunch / sizeof kLaunch[0], "one cost per shape");
+constexpr auto kLaunch = launches<kMx, kCosts>(), kLaunchTiled = launches<kMxTiled, kCosts>(), kLaunchRagged = launches<kMxRagged, kCosts>();
 
 }  // namespace
 
@@ -91,12 +57,12 @@ hipError_t launch_gemm_wide(const GemmArgs& a, const DeviceInfo& dev, int* parts
     if (!gemm_wide_can_run(a, dev) || (tiled && a.k % 128 != 0))
         return hipErrorInvalidValue;
     Args w{a.x, a.q, a.s, a.n, a.k, a.m, (int)a.ldx, 0, 0, 0, 0, block_out(a, epi)};
-    const int c = pick_shape(kCosts, kShapes, a.m, a.n, a.k, dev.cus, a.part_val ? a.parts : 0x7FFFFFFF, 4, &w);
+    const int c = pick_shape(kCosts, std::size(kCosts), a.m, a.n, a.k, dev.cus, a.part_val ? a.parts : 0x7FFFFFFF, 4, &w);
     if (c < 0)
         return hipErrorInvalidValue;
     if (parts_used)
         *parts_used = w.tiles_n;
-    return kLaunch[c][tiled ? 1 : a.k % 128 != 0 ? 2 : 0](w, dev, stream);
+    return (tiled ? kLaunchTiled : a.k % 128 != 0 ? kLaunchRagged : kLaunch)[c](w, dev, stream);
 }
 
 }  // namespace mxfp4

@@ -7,7 +7,7 @@ namespace {
 
 using namespace wide;
 
-const Cost kCosts[] = {
+constexpr Cost kCosts[] = {
     {1, 1, 8, 1, 1, 3.341f, 0.138f, 0.497f, 0.196f},
     {1, 2, 4, 1, 1, 3.187f, 0.250f, 0.f, 0.361f},
     {1, 4, 2, 1, 1, 3.209f, 0.501f, 0.203f, 0.631f},
@@ -26,28 +26,7 @@ const Cost kCosts[] = {
     {1, 8, 1, 8, 2, 9.309f, 2.480f, 6.431f, 2.503f},
 };
 
-#define MXFP4_WIDE(...) launch_block<kBf16, __VA_ARGS__>
-hipError_t (*const kLaunch[])(const Args&, const DeviceInfo&, hipStream_t) = {
-    MXFP4_WIDE(1, 1, 8, 1, 1),
-    MXFP4_WIDE(1, 2, 4, 1, 1),
-    MXFP4_WIDE(1, 4, 2, 1, 1),
-    MXFP4_WIDE(1, 4, 2, 1, 2),
-    MXFP4_WIDE(1, 1, 8, 2, 1),
-    MXFP4_WIDE(1, 2, 4, 2, 1),
-    MXFP4_WIDE(1, 4, 2, 2, 1),
-    MXFP4_WIDE(1, 4, 2, 2, 2),
-    MXFP4_WIDE(1, 4, 2, 3, 1),
-    MXFP4_WIDE(1, 4, 2, 3, 2),
-    MXFP4_WIDE(1, 2, 4, 4, 1),
-    MXFP4_WIDE(1, 4, 2, 4, 1),
-    MXFP4_WIDE(1, 4, 2, 4, 2),
-    MXFP4_WIDE(1, 8, 1, 4, 1),
-    MXFP4_WIDE(1, 8, 1, 4, 2),
-    MXFP4_WIDE(1, 8, 1, 8, 2),
-};
-#undef MXFP4_WIDE
-constexpr int kShapes = sizeof kCosts / sizeof kCosts[0];
-static_assert(kShapes == sizeof kLaunch / sizeof kLaunch[0], "one cost per shape");
+constexpr auto kLaunch = launches<kBf16, kCosts>();
 
 }  // namespace
 
@@ -66,7 +45,7 @@ hipError_t launch_gemm_wide_bf16(const Bf16Args& a, const DeviceInfo& dev, int* 
         return hipErrorInvalidValue;
     Args w{a.x, reinterpret_cast<const uint8_t*>(a.w), nullptr, a.n, a.k, a.m, (int)a.ldx, (int)a.ldw, 0, 0, 0,
            BlockOut{a.y, a.ldy, a.part_val, a.part_idx, nullptr, nullptr, a.n, a.m, a.parts, 0, 0}};
-    const int c = pick_shape(kCosts, kShapes, a.m, a.n, a.k, dev.cus, a.part_val ? a.parts : 0x7FFFFFFF, 16, &w);
+    const int c = pick_shape(kCosts, std::size(kCosts), a.m, a.n, a.k, dev.cus, a.part_val ? a.parts : 0x7FFFFFFF, 16, &w);
     if (c < 0)
         return hipErrorInvalidValue;
     if (parts_used)

@@ -8,7 +8,7 @@ namespace {
 
 using namespace wide;
 
-const Cost kCosts8[] = {
+constexpr Cost kCosts8[] = {
     {1, 1, 8, 1, 1, 3.509f, 0.082f, 0.606f, 0.109f},
     {1, 2, 4, 1, 1, 3.503f, 0.132f, 0.f, 0.208f},
     {1, 4, 2, 1, 1, 3.130f, 0.260f, 0.217f, 0.360f},
@@ -26,29 +26,9 @@ const Cost kCosts8[] = {
     {1, 8, 1, 4, 2, 5.680f, 1.250f, 4.844f, 1.080f},
     {1, 8, 1, 8, 2, 10.67f, 1.570f, 7.428f, 1.646f},
 };
-#define MXFP4_WIDE(...) {launch_block<kE4m3, __VA_ARGS__>, launch_block<kE5m2, __VA_ARGS__>}
-hipError_t (*const kLaunch8[][2])(const Args&, const DeviceInfo&, hipStream_t) = {
-    MXFP4_WIDE(1, 1, 8, 1, 1),
-    MXFP4_WIDE(1, 2, 4, 1, 1),
-    MXFP4_WIDE(1, 4, 2, 1, 1),
-    MXFP4_WIDE(1, 4, 2, 1, 2),
-    MXFP4_WIDE(1, 1, 8, 2, 1),
-    MXFP4_WIDE(1, 2, 4, 2, 1),
-    MXFP4_WIDE(1, 4, 2, 2, 1),
-    MXFP4_WIDE(1, 4, 2, 2, 2),
-    MXFP4_WIDE(1, 4, 2, 3, 1),
-    MXFP4_WIDE(1, 4, 2, 3, 2),
-    MXFP4_WIDE(1, 2, 4, 4, 1),
-    MXFP4_WIDE(1, 4, 2, 4, 1),
-    MXFP4_WIDE(1, 4, 2, 4, 2),
-    MXFP4_WIDE(1, 8, 1, 4, 1),
-    MXFP4_WIDE(1, 8, 1, 4, 2),
-    MXFP4_WIDE(1, 8, 1, 8, 2),
-};
-#undef MXFP4_WIDE
-static_assert(sizeof kCosts8 / sizeof kCosts8[0] == sizeof kLaunch8 / sizeof kLaunch8[0], "one cost per shape");
+constexpr auto kLaunchE4m3 = launches<kE4m3, kCosts8>(), kLaunchE5m2 = launches<kE5m2, kCosts8>();
 
-const Cost kCosts6[] = {
+constexpr Cost kCosts6[] = {
     {1, 1, 8, 1, 1, 3.854f, 0.073f, 0.728f, 0.094f},
     {1, 2, 4, 1, 1, 3.426f, 0.116f, 0.f, 0.160f},
     {1, 2, 4, 1, 2, 3.828f, 0.199f, 0.f, 0.283f},
@@ -67,30 +47,9 @@ const Cost kCosts6[] = {
     {1, 8, 1, 4, 2, 6.538f, 1.119f, 4.837f, 0.973f},
     {1, 8, 1, 8, 2, 9.933f, 1.600f, 6.196f, 1.840f},
 };
-#define MXFP4_WIDE(...) {launch_block<kE2m3, __VA_ARGS__>, launch_block<kE3m2, __VA_ARGS__>}
-hipError_t (*const kLaunch6[][2])(const Args&, const DeviceInfo&, hipStream_t) = {
-    MXFP4_WIDE(1, 1, 8, 1, 1),
-    MXFP4_WIDE(1, 2, 4, 1, 1),
-    MXFP4_WIDE(1, 2, 4, 1, 2),
-    MXFP4_WIDE(1, 4, 2, 1, 1),
-    MXFP4_WIDE(1, 4, 2, 1, 2),
-    MXFP4_WIDE(1, 1, 8, 2, 1),
-    MXFP4_WIDE(1, 2, 4, 2, 1),
-    MXFP4_WIDE(1, 4, 2, 2, 1),
-    MXFP4_WIDE(1, 4, 2, 2, 2),
-    MXFP4_WIDE(1, 4, 2, 3, 1),
-    MXFP4_WIDE(1, 4, 2, 3, 2),
-    MXFP4_WIDE(1, 2, 4, 4, 1),
-    MXFP4_WIDE(1, 4, 2, 4, 1),
-    MXFP4_WIDE(1, 4, 2, 4, 2),
-    MXFP4_WIDE(1, 8, 1, 4, 1),
-    MXFP4_WIDE(1, 8, 1, 4, 2),
-    MXFP4_WIDE(1, 8, 1, 8, 2),
-};
-#undef MXFP4_WIDE
-static_assert(sizeof kCosts6 / sizeof kCosts6[0] == sizeof kLaunch6 / sizeof kLaunch6[0], "one cost per shape");
+constexpr auto kLaunchE2m3 = launches<kE2m3, kCosts6>(), kLaunchE3m2 = launches<kE3m2, kCosts6>();
 
-const Cost kCosts2[] = {
+constexpr Cost kCosts2[] = {
     {1, 1, 8, 1, 1, 3.666f, 0.065f, 0.796f, 0.054f},
     {1, 1, 8, 1, 2, 3.943f, 0.098f, 1.084f, 0.082f},
     {1, 2, 4, 1, 1, 3.480f, 0.115f, 0.389f, 0.078f},
@@ -110,29 +69,7 @@ const Cost kCosts2[] = {
     {1, 8, 1, 4, 2, 6.932f, 0.982f, 4.741f, 0.984f},
     {1, 8, 1, 8, 2, 10.81f, 1.485f, 6.768f, 1.621f},
 };
-#define MXFP4_WIDE(...) {launch_block<kT2, __VA_ARGS__>}
-hipError_t (*const kLaunch2[][1])(const Args&, const DeviceInfo&, hipStream_t) = {
-    MXFP4_WIDE(1, 1, 8, 1, 1),
-    MXFP4_WIDE(1, 1, 8, 1, 2),
-    MXFP4_WIDE(1, 2, 4, 1, 1),
-    MXFP4_WIDE(1, 2, 4, 1, 2),
-    MXFP4_WIDE(1, 4, 2, 1, 1),
-    MXFP4_WIDE(1, 4, 2, 1, 2),
-    MXFP4_WIDE(1, 2, 4, 2, 1),
-    MXFP4_WIDE(1, 2, 4, 2, 2),
-    MXFP4_WIDE(1, 4, 2, 2, 1),
-    MXFP4_WIDE(1, 4, 2, 2, 2),
-    MXFP4_WIDE(1, 4, 2, 3, 1),
-    MXFP4_WIDE(1, 4, 2, 3, 2),
-    MXFP4_WIDE(1, 2, 4, 4, 2),
-    MXFP4_WIDE(1, 4, 2, 4, 1),
-    MXFP4_WIDE(1, 4, 2, 4, 2),
-    MXFP4_WIDE(1, 8, 1, 4, 1),
-    MXFP4_WIDE(1, 8, 1, 4, 2),
-    MXFP4_WIDE(1, 8, 1, 8, 2),
-};
-#undef MXFP4_WIDE
-static_assert(sizeof kCosts2 / sizeof kCosts2[0] == sizeof kLaunch2 / sizeof kLaunch2[0], "one cost per shape");
+constexpr auto kLaunchT2 = launches<kT2, kCosts2>();
 
 }  // namespace
 
@@ -151,14 +88,15 @@ hipError_t launch_gemm_wide_fmt(int code, const GemmArgs& a, const DeviceInfo& d
         return hipErrorInvalidValue;
     Args w{a.x, a.q, a.s, a.n, a.k, a.m, (int)a.ldx, 0, 0, 0, 0, block_out(a, nullptr)};
     const Cost* costs = kind < 2 ? kCosts8 : kind < 4 ? kCosts6 : kCosts2;
-    const size_t bytes = kind < 2 ? sizeof kCosts8 : kind < 4 ? sizeof kCosts6 : sizeof kCosts2;
-    const int c = pick_shape(costs, (int)(bytes / sizeof costs[0]), a.m, a.n, a.k, dev.cus, a.part_val ? a.parts : 0x7FFFFFFF,
+    const size_t count = kind < 2 ? std::size(kCosts8) : kind < 4 ? std::size(kCosts6) : std::size(kCosts2);
+    const int c = pick_shape(costs, count, a.m, a.n, a.k, dev.cus, a.part_val ? a.parts : 0x7FFFFFFF,
                              kind < 2 ? 8 : kind < 4 ? 6 : 2, &w);
     if (c < 0)
         return hipErrorInvalidValue;
     if (parts_used)
         *parts_used = w.tiles_n;
-    return (kind < 2 ? kLaunch8[c][kind] : kind < 4 ? kLaunch6[c][kind - 2] : kLaunch2[c][0])(w, dev, stream);
+    const Launch* const launch[] = {kLaunchE4m3.data(), kLaunchE5m2.data(), kLaunchE2m3.data(), kLaunchE3m2.data(), kLaunchT2.data()};
+    return launch[kind][c](w, dev, stream);
 }
 
 }  // namespace mxfp4

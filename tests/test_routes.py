@@ -215,7 +215,7 @@ def picked(rules, bits, table, m, n, k):
     ("mxfp4", "gemm_wide.hip", "kCosts", []), ("tiled", "gemm_wide.hip", "kCosts", []), (8, "gemm_wide_fmt.hip", "kCosts8", []),
     (6, "gemm_wide_fmt.hip", "kCosts6", []), (2, "gemm_wide_fmt.hip", "kCosts2", []), ("bf16", "gemm_wide_bf16.hip", "kCosts", [])])
 def test_sizes_that_take_every_block_shape(rules, kind, source, name, never):
-    body = re.search(r"const Cost %s\[\] = \{(.*?)\n\};" % name, open(os.path.join(CSRC, source)).read(), re.S).group(1)
+    body = re.search(r"constexpr Cost %s\[\] = \{(.*?)\n\};" % name, open(os.path.join(CSRC, source)).read(), re.S).group(1)
     table = [[float(v.rstrip("f")) for v in row.split(",")] for row in re.findall(r"\{([^{}]*)\}", body)]
     bits = {"mxfp4": 4, "tiled": 4, "bf16": 16}.get(kind, kind)
     assert [picked(rules, bits, table, *size)[0] for size in BLOCK_SIZES[kind]] == [i for i in range(len(table)) if i not in never]
@@ -246,6 +246,6 @@ def test_sizes_that_take_every_block_shape(rules, kind, source, name, never):
 def test_shapes_that_were_measured_the_fastest(rules, kind, m, n, k, fast):
     source, name, bits = {"bf16": ("gemm_wide_bf16.hip", "kCosts", 16), "mxfp4": ("gemm_wide.hip", "kCosts", 4),
                           6: ("gemm_wide_fmt.hip", "kCosts6", 6)}[kind]
-    body = re.search(r"const Cost %s\[\] = \{(.*?)\n\};" % name, open(os.path.join(CSRC, source)).read(), re.S).group(1)
+    body = re.search(r"constexpr Cost %s\[\] = \{(.*?)\n\};" % name, open(os.path.join(CSRC, source)).read(), re.S).group(1)
     table = [[float(v.rstrip("f")) for v in row.split(",")] for row in re.findall(r"\{([^{}]*)\}", body)]
     assert tuple(int(v) for v in table[picked(rules, bits, table, m, n, k)[0]][:5]) in fast

@@ -54,7 +54,7 @@ def walk(tmp_path_factory):
 
 
 def shapes(source, name):
-    body = re.search(r"const Cost %s\[\] = \{(.*?)\n\};" % name, open(os.path.join(CSRC, source)).read(), re.S).group(1)
+    body = re.search(r"constexpr Cost %s\[\] = \{(.*?)\n\};" % name, open(os.path.join(CSRC, source)).read(), re.S).group(1)
     return [tuple(int(v) for v in row.split(",")[:5]) for row in re.findall(r"\{([^{}]*)\}", body)]
 
 
