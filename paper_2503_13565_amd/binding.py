@@ -10,6 +10,7 @@ from __future__ import annotations
 import contextlib
 import ctypes
 import os
+import warnings
 from typing import Optional, Tuple
 
 import torch
@@ -191,11 +192,24 @@ def load() -> ctypes.CDLL:
         getattr(lib, name).restype = i32
     lib.mxfp4_last_error.restype = ctypes.c_char_p
     lib.mxfp4_version.restype = ctypes.c_char_p
-    from . import _host
-    _host.on_failure(_check)
-    _product, _verify = _host.product, _host.verify
+    _product, _verify = _host_calls()
     _lib = lib
     return lib
+
+
+def _host_calls():
+    """The two calls of the extension module.  Without it, or with one that was built for another torch, every call takes
+    the checks here, which reach the same kernels with more host time."""
+    try:
+        from . import _host
+        if _host.torch_version != str(torch.__version__):
+            raise ImportError("built for torch %s" % _host.torch_version)
+    except ImportError as e:
+        warnings.warn("the extension module _host cannot be used (%s): calls go through ctypes, which takes more host time; "
+                      "build it with `python -m paper_2503_13565_amd.build`" % e, RuntimeWarning, stacklevel=3)
+        return (lambda *args: None,) * 2
+    _host.on_failure(_check)
+    return _host.product, _host.verify
 
 
 def _check(rc: int) -> None:

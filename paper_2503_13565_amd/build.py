@@ -54,7 +54,8 @@ def _compile_host(verbose: bool) -> str:
     """The extension module behind the binding: host code against torch's headers."""
     obj, at = os.path.join(BUILD, "host.o"), os.path.join(os.path.dirname(torch.__file__), "include")
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-isystem", at, "-isystem",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DMXFP4_TORCH_VERSION="%s"' % torch.__version__,
+           "-isystem", at, "-isystem",
            os.path.join(at, "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include", "-isystem",
            sysconfig.get_paths()["include"], "-c", os.path.join(CSRC, "host.cpp"), "-o", obj]
     if verbose:

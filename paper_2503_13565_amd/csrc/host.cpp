@@ -289,4 +289,12 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_host", nullptr, -1, kMethods, nu
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__host() { return PyModule_Create(&kModule); }
+PyMODINIT_FUNC PyInit__host()
+{
+    PyObject* module = PyModule_Create(&kModule);
+    if (module && PyModule_AddStringConstant(module, "torch_version", MXFP4_TORCH_VERSION) < 0) {
+        Py_DECREF(module);
+        return nullptr;
+    }
+    return module;
+}

@@ -3,6 +3,8 @@ and its host-side argument checks return error codes (never abort) before any GP
 import ctypes
 import os
 import re
+import sys
+import types
 
 import pytest
 
@@ -17,6 +19,20 @@ def declared_functions():
     text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
     names = re.findall(r"\b(mxfp4_[a-z0-9_]+)\s*\(", text)
     return sorted(set(names))
+
+
+@pytest.mark.parametrize("module", [None, types.SimpleNamespace(torch_version="1.0", product=len, verify=len)])
+def test_without_a_usable_extension_module_the_binding_takes_the_calls(module, monkeypatch):
+    import paper_2503_13565_amd as package
+    monkeypatch.setattr(package, "_host", module, raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2503_13565_amd._host", module)      # (None: the import fails)
+    if module is None:
+        monkeypatch.delattr(package, "_host")
+    for name in ("_lib", "_product", "_verify"):
+        monkeypatch.setattr(binding, name, None)
+    with pytest.warns(RuntimeWarning, match="_host"):
+        assert binding.load() is not None
+    assert binding._product(0) is None and binding._verify(0) is None
 
 
 def test_library_exports_every_declared_symbol():
