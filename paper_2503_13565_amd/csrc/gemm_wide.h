@@ -572,12 +572,12 @@ hipError_t launch_block(const Args& a, const DeviceInfo& dev, hipStream_t stream
 }
 
 // A block shape with what it took, in microseconds: the first block of a compute unit and every further one
-// as start + step x (steps of 128 along K, whole phases).  Fitted to every shape at 2000 sizes (MXFP4; 1100 each of the 8-bit,
-// 6-bit, ternary and BF16 elements) of 3 to 520 rows, 128 to 34000 weight rows and K = 256 to 12288, four sets of weights in
-// rotation, those near the fastest shape of a size weighing most, and to 256, 512 and 1024 blocks at K = 512 to 10240.  At a quarter of
-// the sizes that was left out of the fit the choice is within 5 % of the fastest shape that cuts the sums far enough on 481 of 500,
-// 256, 268, 268 and 271 of 275, on average 1.006, 1.006, 1.004, 1.004 and 1.002 of it, at worst 1.11, 1.07, 1.09, 1.08 and 1.16.
-// A shape is in a table if the choice would be 6e-5 slower on average without it.
+// as start + step x (steps of 128 along K, whole phases).  Fitted to every shape at 3300 sizes (MXFP4; 1550 each of the 8-bit,
+// 6-bit, ternary and BF16 elements) of 3 to 520 rows, 128 to 65536 weight rows and K = 128 to 12288, six sets of weights in
+// rotation, those near the fastest shape of a size weighing most.  (Fitted up to 34000 weight rows alone: 1.018 of the fastest on average
+// beyond them, 1.004 now.)  At a quarter of the sizes that was left out of the fit the choice is within 5 % of the fastest shape that
+// cuts the sums far enough on 799 of 825, 369 of 389, 379 of 397, 391 of 408 and 353 of 358, on average 1.006, 1.006, 1.007, 1.006 and
+// 1.003 of it, at worst (K of 128 to 512) 1.24, 1.14, 1.18, 1.21 and 1.10.
 struct Cost {
     int wm, wn, wk, mf, nf;
     float first_start, first_step, next_start, next_step;

@@ -8,34 +8,39 @@ namespace {
 using namespace wide;
 
 constexpr Cost kCosts[] = {
-    {1, 1, 8, 1, 1, 3.724f, 0.062f, 0.883f, 0.059f},
-    {1, 1, 8, 1, 2, 3.948f, 0.079f, 0.931f, 0.089f},
-    {1, 1, 8, 1, 3, 4.205f, 0.097f, 1.050f, 0.122f},
-    {1, 2, 4, 1, 1, 3.459f, 0.090f, 0.386f, 0.078f},
-    {1, 2, 4, 1, 2, 3.644f, 0.131f, 0.535f, 0.136f},
-    {1, 2, 4, 1, 3, 4.023f, 0.189f, 2.250f, 0.181f},
-    {1, 4, 2, 1, 1, 3.370f, 0.157f, 0.414f, 0.110f},
-    {1, 4, 2, 1, 2, 3.747f, 0.254f, 0.879f, 0.177f},
-    {1, 2, 4, 2, 2, 4.234f, 0.178f, 1.074f, 0.164f},
-    {1, 2, 4, 2, 3, 4.761f, 0.228f, 2.994f, 0.210f},
-    {1, 2, 4, 2, 4, 5.022f, 0.300f, 3.412f, 0.287f},
-    {1, 4, 2, 2, 1, 3.673f, 0.218f, 0.703f, 0.151f},
-    {1, 4, 2, 2, 2, 4.190f, 0.327f, 1.291f, 0.260f},
-    {1, 4, 2, 2, 3, 5.069f, 0.428f, 3.034f, 0.422f},
-    {1, 8, 1, 2, 2, 4.412f, 0.648f, 1.956f, 0.464f},
-    {1, 2, 4, 3, 3, 5.448f, 0.304f, 3.990f, 0.307f},
-    {1, 4, 2, 3, 1, 4.257f, 0.290f, 1.007f, 0.215f},
-    {1, 4, 2, 3, 2, 4.798f, 0.422f, 2.933f, 0.393f},
-    {1, 4, 2, 3, 3, 6.242f, 0.537f, 4.725f, 0.528f},
-    {1, 2, 4, 4, 3, 6.690f, 0.391f, 4.652f, 0.405f},
-    {1, 4, 2, 4, 2, 5.218f, 0.429f, 3.278f, 0.428f},
-    {1, 4, 2, 4, 3, 6.762f, 0.586f, 4.044f, 0.634f},
-    {1, 8, 1, 4, 1, 4.124f, 0.586f, 1.650f, 0.412f},
-    {1, 8, 1, 4, 2, 6.822f, 0.837f, 5.039f, 0.785f},
-    {1, 8, 1, 6, 2, 8.877f, 1.034f, 5.601f, 1.103f},
-    {2, 4, 1, 4, 3, 9.003f, 1.219f, 6.400f, 1.175f},
-    {1, 8, 1, 8, 2, 11.10f, 1.346f, 9.165f, 1.309f},
-    {1, 8, 1, 8, 3, 12.85f, 1.957f, 8.726f, 2.422f},
+    {1, 1, 8, 1, 1, 4.509f, 0.038f, 0.747f, 0.068f},
+    {1, 1, 8, 1, 2, 4.480f, 0.081f, 0.551f, 0.119f},
+    {1, 1, 8, 1, 3, 4.556f, 0.112f, 0.470f, 0.181f},
+    {1, 2, 4, 1, 1, 4.061f, 0.092f, 0.223f, 0.115f},
+    {1, 2, 4, 1, 2, 4.308f, 0.140f, 0.238f, 0.210f},
+    {1, 2, 4, 1, 3, 4.350f, 0.229f, 1.507f, 0.268f},
+    {1, 4, 2, 1, 1, 4.040f, 0.161f, 0.185f, 0.179f},
+    {1, 4, 2, 1, 2, 4.103f, 0.286f, 0.466f, 0.308f},
+    {1, 4, 2, 1, 3, 4.420f, 0.517f, 0.846f, 0.297f},
+    {1, 1, 8, 2, 3, 5.723f, 0.173f, 2.857f, 0.204f},
+    {1, 2, 4, 2, 1, 4.501f, 0.146f, 0.733f, 0.145f},
+    {1, 2, 4, 2, 2, 4.643f, 0.198f, 0.760f, 0.225f},
+    {1, 2, 4, 2, 3, 5.668f, 0.264f, 2.385f, 0.311f},
+    {1, 2, 4, 2, 4, 5.399f, 0.389f, 2.964f, 0.380f},
+    {1, 4, 2, 2, 1, 4.215f, 0.226f, 0.547f, 0.213f},
+    {1, 4, 2, 2, 2, 4.659f, 0.410f, 1.045f, 0.353f},
+    {1, 4, 2, 2, 3, 5.774f, 0.558f, 3.035f, 0.468f},
+    {1, 4, 2, 2, 4, 6.199f, 0.715f, 3.685f, 0.454f},
+    {1, 8, 1, 2, 2, 4.013f, 0.807f, 2.124f, 0.480f},
+    {1, 2, 4, 3, 3, 5.825f, 0.317f, 3.639f, 0.426f},
+    {1, 4, 2, 3, 1, 4.631f, 0.318f, 0.971f, 0.224f},
+    {1, 4, 2, 3, 2, 5.257f, 0.431f, 3.466f, 0.518f},
+    {1, 4, 2, 3, 3, 7.025f, 0.643f, 5.014f, 0.565f},
+    {1, 2, 4, 4, 3, 6.550f, 0.431f, 4.432f, 0.431f},
+    {1, 4, 2, 4, 2, 5.104f, 0.546f, 3.955f, 0.452f},
+    {1, 4, 2, 4, 3, 7.130f, 0.668f, 4.921f, 0.637f},
+    {1, 8, 1, 4, 1, 4.073f, 0.621f, 1.305f, 0.500f},
+    {1, 8, 1, 4, 2, 6.249f, 1.031f, 5.105f, 0.841f},
+    {1, 8, 1, 6, 2, 9.337f, 1.136f, 7.388f, 1.129f},
+    {1, 8, 1, 6, 3, 12.12f, 1.520f, 10.37f, 1.933f},
+    {1, 8, 1, 8, 2, 11.95f, 1.524f, 10.22f, 1.239f},
+    {1, 8, 1, 8, 3, 10.88f, 2.061f, 12.51f, 1.498f},
+    {2, 4, 1, 4, 3, 7.673f, 1.316f, 7.349f, 1.250f},
 };
 
 constexpr auto kLaunch = launches<kMx, kCosts>(), kLaunchTiled = launches<kMxTiled, kCosts>(), kLaunchRagged = launches<kMxRagged, kCosts>();

@@ -8,22 +8,22 @@ namespace {
 using namespace wide;
 
 constexpr Cost kCosts[] = {
-    {1, 1, 8, 1, 1, 3.341f, 0.138f, 0.497f, 0.196f},
-    {1, 2, 4, 1, 1, 3.187f, 0.250f, 0.f, 0.361f},
-    {1, 4, 2, 1, 1, 3.209f, 0.501f, 0.203f, 0.631f},
-    {1, 4, 2, 1, 2, 2.594f, 1.011f, 1.528f, 0.794f},
-    {1, 1, 8, 2, 1, 3.994f, 0.176f, 2.514f, 0.196f},
-    {1, 2, 4, 2, 1, 3.422f, 0.294f, 0.623f, 0.361f},
-    {1, 4, 2, 2, 1, 3.360f, 0.533f, 0.345f, 0.636f},
-    {1, 4, 2, 2, 2, 3.541f, 1.050f, 2.797f, 0.867f},
-    {1, 4, 2, 3, 1, 3.645f, 0.576f, 0.838f, 0.590f},
-    {1, 4, 2, 3, 2, 4.413f, 1.069f, 3.155f, 1.010f},
-    {1, 2, 4, 4, 1, 4.212f, 0.389f, 2.693f, 0.416f},
-    {1, 4, 2, 4, 1, 3.914f, 0.682f, 1.088f, 0.617f},
-    {1, 4, 2, 4, 2, 4.770f, 1.086f, 3.754f, 1.074f},
-    {1, 8, 1, 4, 1, 4.237f, 1.081f, 1.268f, 1.024f},
-    {1, 8, 1, 4, 2, 6.103f, 2.006f, 4.303f, 1.929f},
-    {1, 8, 1, 8, 2, 9.309f, 2.480f, 6.431f, 2.503f},
+    {1, 1, 8, 1, 1, 3.685f, 0.146f, 0.354f, 0.209f},
+    {1, 2, 4, 1, 1, 3.667f, 0.267f, 0.263f, 0.400f},
+    {1, 4, 2, 1, 1, 3.895f, 0.532f, 0.341f, 0.671f},
+    {1, 4, 2, 1, 2, 3.947f, 1.087f, 0.848f, 1.462f},
+    {1, 1, 8, 2, 1, 4.711f, 0.189f, 2.284f, 0.222f},
+    {1, 2, 4, 2, 1, 4.709f, 0.294f, 0.488f, 0.411f},
+    {1, 4, 2, 2, 1, 3.750f, 0.605f, 0.608f, 0.659f},
+    {1, 4, 2, 2, 2, 4.623f, 1.131f, 2.094f, 1.258f},
+    {1, 4, 2, 3, 1, 4.145f, 0.602f, 1.143f, 0.641f},
+    {1, 4, 2, 3, 2, 4.737f, 1.131f, 2.982f, 1.232f},
+    {1, 2, 4, 4, 1, 5.172f, 0.386f, 2.825f, 0.418f},
+    {1, 4, 2, 4, 1, 4.191f, 0.634f, 1.198f, 0.666f},
+    {1, 4, 2, 4, 2, 5.115f, 1.182f, 3.670f, 1.136f},
+    {1, 8, 1, 4, 1, 3.984f, 1.050f, 1.644f, 1.081f},
+    {1, 8, 1, 4, 2, 6.368f, 2.068f, 5.338f, 2.093f},
+    {1, 8, 1, 8, 2, 9.822f, 2.675f, 11.51f, 2.267f},
 };
 
 constexpr auto kLaunch = launches<kBf16, kCosts>();

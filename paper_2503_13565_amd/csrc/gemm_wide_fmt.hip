@@ -9,65 +9,65 @@ namespace {
 using namespace wide;
 
 constexpr Cost kCosts8[] = {
-    {1, 1, 8, 1, 1, 3.509f, 0.082f, 0.606f, 0.109f},
-    {1, 2, 4, 1, 1, 3.503f, 0.132f, 0.f, 0.208f},
-    {1, 4, 2, 1, 1, 3.130f, 0.260f, 0.217f, 0.360f},
-    {1, 4, 2, 1, 2, 3.316f, 0.558f, 0.724f, 0.459f},
-    {1, 1, 8, 2, 1, 4.468f, 0.115f, 2.588f, 0.122f},
+    {1, 1, 8, 1, 1, 3.509f, 0.082f, 0.606f, 0.102f},
+    {1, 2, 4, 1, 1, 3.621f, 0.132f, 0.f, 0.208f},
+    {1, 4, 2, 1, 1, 3.130f, 0.260f, 0.211f, 0.353f},
+    {1, 4, 2, 1, 2, 3.593f, 0.551f, 0.724f, 0.459f},
+    {1, 1, 8, 2, 1, 6.056f, 0.119f, 2.588f, 0.122f},
     {1, 2, 4, 2, 1, 3.609f, 0.182f, 0.596f, 0.216f},
-    {1, 4, 2, 2, 1, 3.406f, 0.310f, 0.424f, 0.345f},
-    {1, 4, 2, 2, 2, 3.629f, 0.560f, 1.118f, 0.464f},
-    {1, 4, 2, 3, 1, 3.730f, 0.346f, 0.614f, 0.349f},
-    {1, 4, 2, 3, 2, 4.328f, 0.600f, 2.334f, 0.618f},
-    {1, 2, 4, 4, 1, 4.841f, 0.271f, 2.916f, 0.296f},
-    {1, 4, 2, 4, 1, 3.876f, 0.430f, 0.989f, 0.415f},
-    {1, 4, 2, 4, 2, 4.871f, 0.658f, 3.342f, 0.619f},
-    {1, 8, 1, 4, 1, 4.135f, 0.678f, 1.336f, 0.613f},
-    {1, 8, 1, 4, 2, 5.680f, 1.250f, 4.844f, 1.080f},
-    {1, 8, 1, 8, 2, 10.67f, 1.570f, 7.428f, 1.646f},
+    {1, 4, 2, 2, 1, 3.508f, 0.343f, 0.424f, 0.345f},
+    {1, 4, 2, 2, 2, 4.131f, 0.560f, 1.118f, 0.464f},
+    {1, 4, 2, 3, 1, 3.512f, 0.404f, 1.013f, 0.416f},
+    {1, 4, 2, 3, 2, 4.241f, 0.612f, 1.767f, 0.623f},
+    {1, 2, 4, 4, 1, 4.841f, 0.285f, 2.916f, 0.296f},
+    {1, 4, 2, 4, 1, 3.876f, 0.430f, 0.989f, 0.407f},
+    {1, 4, 2, 4, 2, 4.678f, 0.618f, 3.342f, 0.619f},
+    {1, 8, 1, 4, 1, 3.804f, 0.678f, 1.323f, 0.613f},
+    {1, 8, 1, 4, 2, 5.405f, 1.250f, 4.562f, 1.081f},
+    {1, 8, 1, 8, 2, 10.58f, 1.503f, 7.428f, 1.356f},
 };
 constexpr auto kLaunchE4m3 = launches<kE4m3, kCosts8>(), kLaunchE5m2 = launches<kE5m2, kCosts8>();
 
 constexpr Cost kCosts6[] = {
-    {1, 1, 8, 1, 1, 3.854f, 0.073f, 0.728f, 0.094f},
-    {1, 2, 4, 1, 1, 3.426f, 0.116f, 0.f, 0.160f},
-    {1, 2, 4, 1, 2, 3.828f, 0.199f, 0.f, 0.283f},
-    {1, 4, 2, 1, 1, 3.256f, 0.226f, 0.264f, 0.215f},
-    {1, 4, 2, 1, 2, 3.348f, 0.439f, 0.999f, 0.315f},
-    {1, 1, 8, 2, 1, 4.469f, 0.117f, 2.857f, 0.121f},
-    {1, 2, 4, 2, 1, 3.765f, 0.158f, 0.571f, 0.180f},
-    {1, 4, 2, 2, 1, 3.472f, 0.267f, 0.424f, 0.262f},
-    {1, 4, 2, 2, 2, 3.832f, 0.529f, 0.810f, 0.385f},
-    {1, 4, 2, 3, 1, 4.021f, 0.334f, 0.847f, 0.295f},
-    {1, 4, 2, 3, 2, 4.646f, 0.537f, 2.144f, 0.514f},
-    {1, 2, 4, 4, 1, 4.303f, 0.248f, 2.904f, 0.258f},
-    {1, 4, 2, 4, 1, 4.035f, 0.397f, 1.145f, 0.353f},
-    {1, 4, 2, 4, 2, 5.005f, 0.616f, 3.021f, 0.518f},
-    {1, 8, 1, 4, 1, 4.170f, 0.657f, 1.407f, 0.533f},
-    {1, 8, 1, 4, 2, 6.538f, 1.119f, 4.837f, 0.973f},
-    {1, 8, 1, 8, 2, 9.933f, 1.600f, 6.196f, 1.840f},
+    {1, 1, 8, 1, 1, 4.692f, 0.036f, 0.578f, 0.103f},
+    {1, 2, 4, 1, 1, 4.035f, 0.114f, 0.002f, 0.179f},
+    {1, 2, 4, 1, 2, 4.075f, 0.214f, 0.091f, 0.295f},
+    {1, 4, 2, 1, 1, 3.939f, 0.217f, 0.075f, 0.299f},
+    {1, 4, 2, 1, 2, 3.865f, 0.486f, 0.396f, 0.530f},
+    {1, 1, 8, 2, 1, 4.962f, 0.121f, 2.689f, 0.130f},
+    {1, 2, 4, 2, 1, 4.282f, 0.189f, 0.503f, 0.208f},
+    {1, 4, 2, 2, 1, 4.163f, 0.303f, 0.295f, 0.333f},
+    {1, 4, 2, 2, 2, 4.535f, 0.591f, 0.977f, 0.449f},
+    {1, 4, 2, 3, 1, 4.245f, 0.310f, 0.848f, 0.375f},
+    {1, 4, 2, 3, 2, 4.544f, 0.633f, 3.744f, 0.528f},
+    {1, 2, 4, 4, 1, 4.691f, 0.284f, 3.009f, 0.278f},
+    {1, 4, 2, 4, 1, 4.767f, 0.424f, 1.145f, 0.391f},
+    {1, 4, 2, 4, 2, 5.100f, 0.718f, 3.740f, 0.605f},
+    {1, 8, 1, 4, 1, 4.097f, 0.783f, 1.104f, 0.622f},
+    {1, 8, 1, 4, 2, 5.320f, 1.393f, 4.533f, 1.113f},
+    {1, 8, 1, 8, 2, 10.22f, 1.806f, 7.852f, 1.758f},
 };
 constexpr auto kLaunchE2m3 = launches<kE2m3, kCosts6>(), kLaunchE3m2 = launches<kE3m2, kCosts6>();
 
 constexpr Cost kCosts2[] = {
     {1, 1, 8, 1, 1, 3.666f, 0.065f, 0.796f, 0.054f},
-    {1, 1, 8, 1, 2, 3.943f, 0.098f, 1.084f, 0.082f},
-    {1, 2, 4, 1, 1, 3.480f, 0.115f, 0.389f, 0.078f},
-    {1, 2, 4, 1, 2, 3.663f, 0.176f, 0.863f, 0.138f},
-    {1, 4, 2, 1, 1, 3.355f, 0.211f, 0.488f, 0.128f},
-    {1, 4, 2, 1, 2, 3.570f, 0.344f, 0.868f, 0.247f},
+    {1, 1, 8, 1, 2, 3.943f, 0.098f, 1.084f, 0.078f},
+    {1, 2, 4, 1, 1, 3.480f, 0.117f, 0.496f, 0.078f},
+    {1, 2, 4, 1, 2, 3.663f, 0.178f, 0.863f, 0.134f},
+    {1, 4, 2, 1, 1, 3.251f, 0.220f, 0.586f, 0.128f},
+    {1, 4, 2, 1, 2, 3.515f, 0.351f, 0.868f, 0.251f},
     {1, 2, 4, 2, 1, 3.653f, 0.152f, 0.863f, 0.121f},
-    {1, 2, 4, 2, 2, 4.383f, 0.221f, 1.336f, 0.167f},
-    {1, 4, 2, 2, 1, 3.635f, 0.278f, 0.759f, 0.166f},
+    {1, 2, 4, 2, 2, 4.383f, 0.230f, 1.336f, 0.167f},
+    {1, 4, 2, 2, 1, 3.635f, 0.278f, 0.835f, 0.177f},
     {1, 4, 2, 2, 2, 4.241f, 0.408f, 1.407f, 0.289f},
-    {1, 4, 2, 3, 1, 3.816f, 0.325f, 1.052f, 0.221f},
-    {1, 4, 2, 3, 2, 5.182f, 0.477f, 1.819f, 0.337f},
-    {1, 2, 4, 4, 2, 5.925f, 0.318f, 3.849f, 0.324f},
-    {1, 4, 2, 4, 1, 4.318f, 0.373f, 1.350f, 0.276f},
-    {1, 4, 2, 4, 2, 5.455f, 0.523f, 3.705f, 0.504f},
-    {1, 8, 1, 4, 1, 4.416f, 0.662f, 1.429f, 0.483f},
-    {1, 8, 1, 4, 2, 6.932f, 0.982f, 4.741f, 0.984f},
-    {1, 8, 1, 8, 2, 10.81f, 1.485f, 6.768f, 1.621f},
+    {1, 4, 2, 3, 1, 3.713f, 0.307f, 1.285f, 0.221f},
+    {1, 4, 2, 3, 2, 4.882f, 0.411f, 1.769f, 0.329f},
+    {1, 2, 4, 4, 2, 4.932f, 0.318f, 3.849f, 0.324f},
+    {1, 4, 2, 4, 1, 4.318f, 0.355f, 1.377f, 0.319f},
+    {1, 4, 2, 4, 2, 5.310f, 0.492f, 3.705f, 0.504f},
+    {1, 8, 1, 4, 1, 3.718f, 0.662f, 1.038f, 0.468f},
+    {1, 8, 1, 4, 2, 6.932f, 0.982f, 5.225f, 0.844f},
+    {1, 8, 1, 8, 2, 9.837f, 1.296f, 7.270f, 1.385f},
 };
 constexpr auto kLaunchT2 = launches<kT2, kCosts2>();
 
