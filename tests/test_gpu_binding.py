@@ -77,13 +77,14 @@ def test_same_bits_as_the_binding_itself(m, monkeypatch):
 def test_the_current_stream_and_the_device_of_a_mode():
     x, _, q, s = _inputs(4, 2048, 512)
     want = B.mxfp4_woq_gemm(x, q, s)
-    side = torch.cuda.Stream()
-    side.wait_stream(torch.cuda.current_stream())
+    side, busy = torch.cuda.Stream(), torch.ones((8192, 8192), device=DEV)
+    late = torch.zeros_like(x)                      # what a product on another stream would read
+    torch.cuda.synchronize()
     with torch.cuda.stream(side):
-        slow = x.clone()
-        for _ in range(64):
-            slow = slow * 1                         # the product has to wait for this
-        got = B.mxfp4_woq_gemm(slow, q, s)
+        for _ in range(8):
+            busy = busy @ busy                      # (some tens of ms: the call returns long before its input is there)
+        late.copy_(x)
+        got = B.mxfp4_woq_gemm(late, q, s)
     side.synchronize()
     assert torch.equal(got, want)
     with torch.device("cpu"):                       # an active mode: the binding's own way
