@@ -20,22 +20,22 @@ struct TileCall {
     bool pick;      // the pick instead of the product
 };
 
-// Three to eight rows that the tiles take in one pass.  Figures: blocks as a part of what the tiles take, over 64 to 57344
-// weight rows, K = 128 to 10240 and 3 to 8 rows, with and without gate and pick.  A tile per unit and a short K are nothing but start
-// and end, where the blocks are the faster (4096 x 512 0.89, 0.95 tile-major; 8192 x 512 0.73; 32000 x 512 0.54, 0.58; K = 128 0.4
-// to 0.87, left where it was).  From there on either side wins where the weight rows and the phases of its loop come
-// out even, within a tenth mostly: blocks in rounds of 256, phases of 256 to 1024 elements, against tiles of 16 rows per unit in
-// groups of 512 elements.
+// Three to eight rows that the tiles take in one pass.  Figures: blocks as a part of what the tiles take, over 256 to 65536
+// weight rows, K = 128 to 14336 and 3 to 8 rows, with and without gate and pick, on average around the size that is named.  A tile per
+// unit and a short K are nothing but start and end, where the blocks are the faster (4096 x 512 0.89, 0.95 tile-major; 8192 x 512 0.73;
+// 32000 x 512 0.54, 0.58; K = 128 0.41 at 57344 weight rows, 0.86 to 0.93 at one tile per unit).  From there on either side wins where the
+// weight rows and the phases of its loop come out even, within a tenth mostly: blocks in rounds of 256, phases of 256 to 1024
+// elements, against tiles of 16 rows per unit in groups of 512 elements.
 inline bool wide_one_pass_preferred(const TileCall& c)
 {
     const int m = c.m, n = c.n, k = c.k, unit = c.cus;
     const bool wide = m > 4;                        // the tiles stage eight rows instead of four
-    if (k <= 128)
-        return false;
-    // One tile per unit: 4096 x 1280 1.01, x 4096 0.98, x 5120 1.02, 1632 x 5632 0.93, 4096 x 8192 0.81, x 9216 0.90; at four rows 1.0 or more; tile-major
-    // from K = 1280 on 1.02 to 1.2.
+    // One tile per unit: 4096 x 1280 1.03, x 4096 0.99, x 5120 1.0 to 1.03, x 6144 0.97, x 9216 0.93 to 0.97; at four rows 1.0 or more;
+    // tile-major from K = 1280 on 1.02 to 1.2.
     if (n <= 16 * unit)
         return k <= 1024 || (!c.tiled && wide && k > 5120);
+    if (k <= 1024)
+        return true;
     if (c.tiled) {
         // Just past a whole number of the tiles' groups: 27262 x 4224 0.73, 18268 x 4608 0.80, 13822 x 4352 0.85.
         if (k > 4096 && k <= 4608)
@@ -49,27 +49,28 @@ inline bool wide_one_pass_preferred(const TileCall& c)
         // 22016 x 4096 0.91, 24576 x 2048 0.87, x 4096 0.96, x 5120 0.75 (0.89), x 8192 0.95; 33924 x 7808 1.13; 57344 x 3584 0.97,
         // x 10240 1.0.
         return k <= 3072 || (wide && k > 4096 && k <= 7680) || (k > 7936 && (wide || k <= 9728)) ||
-               (n > 80 * unit && n < 96 * unit && k <= 4096);
+               (n > 80 * unit && n <= 96 * unit && k <= 4096);
     }
-    // Just past a whole number of the tiles' groups: 20530 x 4352 at four rows 0.85, 32490 x 4480 0.76, 45178 x 4480 0.87.
-    if (k > 4096 && k <= 4864)
+    // Just past a whole number of the tiles' groups: K = 4224 to 4608 at more than four rows 0.80 (20480 to 32768, 45056 weight rows)
+    // to 0.92 (36864), at fewer 0.93 to 1.04, beyond 128 rows per unit 1.04 to 1.2.
+    if (k > 4096 && k <= 4864 && (wide || n <= 128 * unit))
         return true;
     // 8192 x 2048 0.80, x 4096 0.85, x 7168 0.82 (0.90 at four rows), x 11008 0.75 (0.91).
     if (n <= 32 * unit)
         return k <= 11520;
-    // 12288 x 3072 0.97, x 3584 1.05, x 4096 0.98, x 5120 0.91 (1.03), x 8192 0.78, x 10240 0.76 (0.98).
+    // 12288 x 3072 0.98, x 3584 0.97 to 1.0, x 4096 0.94 to 1.0, x 5120 0.90, x 8192 0.95; at four rows from 3584 on 1.0 to 1.1.
     if (n <= 48 * unit)
-        return k <= 3072 || (wide && k > 4096) || (k > 7680 && k <= 11264);
+        return wide || k <= 3072;
     // 16384 x 4096 0.91, x 9216 0.92, x 10240 1.11 at four rows.
     if (n <= 64 * unit)
         return k <= 9728;
-    // 20480 x 3072 0.97, x 4096 1.03, x 5120 0.86 (0.99), x 7168 0.9 (1.07); 22016 x 4096 0.94; 24576 x 4096 0.98, x 6144 0.93;
-    // 28672 x 5120 0.95 (1.17), x 6144 1.05; 32000 x 2048 0.87, x 3584 0.94, x 4096 1.0, x 8192 1.1.
+    // 20480 x 3072 1.02, x 3584 1.11, x 5120 0.98, x 6144 0.96; 32000 x 3072 0.99, x 3584 1.05, x 5120 0.91, x 7168 0.92, x 8192 1.09; at
+    // four rows from 3584 on 1.07 to 1.2.  One round of blocks of 96 weight rows: 22016 to 24576 x 3584 0.99, x 4096 0.98 to 1.0 (pick 1.07).
     if (n <= 128 * unit)
-        return k <= (n <= 80 * unit ? 3072 : n < 96 * unit ? 4096 : 3584) ||
-               (wide && k > 4096 && k <= (n <= 96 * unit ? 7680 : 5632));
-    // 34174 x 2944 0.84, 40960 x 2560 0.88, x 3072 1.03; 53574 x 2304 0.76, 54536 x 2688 0.87, 57344 x 2560 0.99, x 3072 1.07.
-    return k <= (n <= 160 * unit ? 2944 : 2688);
+        return k <= 3072 || (wide && k > 4096 && k <= 7680) || (n > 80 * unit && n <= 96 * unit && k <= 4096 && !c.pick);
+    // Two rounds and more: K = 1280 0.95, 1536 1.0, 1664 1.08, 2048 1.08, just past the groups again 2176 0.96, 2304 0.93, 2432 0.99,
+    // 2560 1.03, 3072 1.1, 4096 1.2.
+    return k <= 1536 || (k > 2048 && k <= 2432);
 }
 
 // From three rows on, K % 128 == 0.  Figures: us per launch, tiles -> blocks, or blocks as a part of what the tiles take.
@@ -85,16 +86,13 @@ inline bool wide_preferred(const TileCall& c)
             return true;
         if (m <= 8)
             return wide_one_pass_preferred(c);
-        // Nine to 16: the tiles' passes of 16 rows have fewer waves in flight.  One tile per unit: 1024 x 1024 0.91, x 2048 1.02,
-        // x 3072 0.92, x 4096 0.86, tile-major 0.95, 1.12, 0.96, 0.98.
+        // Nine to 16: the tiles' passes of 16 rows have fewer waves in flight.  One tile per unit: K = 128 to 1024 0.86 to 0.94, 1536 1.03,
+        // 2048 0.98, 2560 1.0, 3072 0.92, 4096 0.89; tile-major 0.87 to 0.97, 1.07, 1.02, 0.95, 0.96, 0.98.
         if (n <= 16 * unit)
-            return (n < 16 * unit && k <= 1024) || (k > 2560 && !(c.tiled && c.fused));
-        // Many rows and K past the short phases: 32000 x 4096 0.94 (19.5 -> 18.2 us with the pick), 32930 x 3712 0.79, 40960 x 3584
-        // 0.93 to 1.01, x 4096 1.03 to 1.1, 47416 x 4224 0.83, 57344 x 3072 0.93, x 3584 1.0 to 1.06; tile-major 0.96.
-        // (18432 x 4096 was 1.05 in blocks before their short phases and is 0.86 now: the plain product stays with the tiles there.)
-        if (n > 128 * unit)
-            return c.tiled || k <= (n < 208 * unit ? 3840 : 3072) || k > 4096;
-        return !plain || c.tiled || n <= 64 * unit || n > 72 * unit || k <= 3584;
+            return k <= 1024 || (k > 2560 && !(c.tiled && c.fused));
+        // 18432 x 3584 0.96, x 4096 0.98; beyond 128 rows per unit K = 3072 0.97, 3584 0.97, 3712 to 4096 1.07, 4224 to 4608 0.94;
+        // tile-major never more than 0.98.
+        return n <= 128 * unit || c.tiled || k <= 3584 || k > 4096;
     }
     if (m <= 8) {
         // (57344 x 10240 and 32000 x 11008 tile-major at five and eight rows 0.76 of K split; row-major 1.04)
@@ -176,16 +174,17 @@ inline bool wide_format_preferred(int m, int n, int k, int bits, bool tiles, int
     // Rows that do not fit ran as passes of four (E4M3 4096 x 11008 at 16 rows 55 -> 17).
     if (m >= 5 && !tiles)
         return true;
-    // Else while a unit has few tiles, the 8-bit elements from five rows on: 8192 x 4096 0.57 to 0.78 of the tiles, 12288 x 2560
-    // 0.87, x 3072 0.94 to 1.05, x 4096 0.83; many weight rows with a short K: 20480 x 2048 0.80, x 3072 1.09, 57344 x 2048 0.95.  Three
+    // Else while a unit has few tiles, the 8-bit elements from five rows on: 8192 x 4096 0.57 to 0.78 of the tiles, 8448 to 12288 x 2560
+    // 0.87, x 3072 0.98, x 3584 0.95, x 4096 0.88, x 4608 0.91, x 6912 1.09, 12544 to 16384 x 4608 0.83; many weight rows with a short K: 20480 x 2048 0.80, x 3072 1.09, 57344 x 2048 0.95.  Three
     // and four rows: 1024 x 3072 1.14, 2048 x 1024 0.86, x 4096 0.96, 4096 x 8192 0.75, 8192 x 3072 0.79, x 11008 1.10, 9216 x 2048
-    // 0.85, x 3072 1.11, 20480 x 2048 0.90, 57344 x 2048 0.97.
+    // 0.85, x 3072 1.06, 20480 x 2048 0.90, 57344 x 2048 0.97; 8192 x 4096 0.91, x 6144 0.92.
     if (bits == 8 && m <= 4)
-        return n > 4 * unit && k <= (n <= 8 * unit ? 1024 : n < 32 * unit ? 7168 : n == 32 * unit ? 3072 : 2048);
+        return n > 4 * unit && k <= (n <= 8 * unit ? 1024 : n <= 32 * unit ? 7168 : 2048);
     if (bits == 8)
-        return n <= 32 * unit || k <= 2048 || (n <= 64 * unit && (k <= 2560 || k == 4096));
-    // 6-bit: 8192 x 4096 0.75 of the tiles, 9216 x 3072 0.83, x 7168 1.2, 12288 x 6144 0.96, 20480 x 3072 0.93, x 4096 1.05, 57344 x 2048
-    // 0.85, x 2560 1.1; three and four rows not where N is small and K is not (1024 x 1024 0.87, 896 x 4864 1.04) or K is
+        return n <= 32 * unit || k <= 2048 || (n <= 64 * unit && k <= 4608);
+    // 6-bit: 8192 x 4096 0.75 of the tiles, 8448 to 12288 x 3072 0.93 to 0.98, x 3584 0.98, x 4096 1.04, just past the groups x 4352 0.89 to 0.93,
+    // x 4864 0.95, x 5632 1.07, 16384 x 6144 0.96, 20480 x 2560 1.0, x 3072 1.01 to 1.08, 24576 x 3072 0.98, 57344 x 2048
+    // 0.85, x 2560 0.97 to 1.1; three and four rows not where N is small and K is not (1024 x 1024 0.87, 896 x 4864 1.04) or K is
     // long (3072 x 16384 1.06), where the decode kernel takes passes of two again from where four rows do not fit (2048 x
     // 24576 0.9, 8192 x 24576 0.6).
     if (n < 8 * unit)
@@ -194,7 +193,9 @@ inline bool wide_format_preferred(int m, int n, int k, int bits, bool tiles, int
         return n <= 40 * unit;
     if (n <= 32 * unit)
         return m >= 5 || k <= 12288;
-    return k <= (n <= 40 * unit ? 3072 : n <= 64 * unit ? 6144 : n <= 128 * unit ? 3072 : 2048);
+    if (n <= 48 * unit)
+        return k <= 3584 || (k > 4096 && k <= 5120);
+    return k <= (n <= 64 * unit ? 6144 : n <= 80 * unit ? 2560 : n <= 128 * unit ? 3072 : 2048);
 }
 
 // BF16 weights.  `tiles`: the matrix-core tiles could take a call of nine to 16 rows in one pass.
@@ -203,13 +204,14 @@ inline bool wide_bf16_preferred(int m, int n, int k, bool tiles, int cus, int ld
     const int unit = cus;
     // Beyond 16 rows always (12288 x 4096 at 32 rows 41 -> 26, 4096 x 11008 98 -> 30).  Nine to 16 rows that the tiles
     // cannot take (4096 x 11008 at 16 rows 49 -> 25, 5001 x 2056 20 -> 11), or that leave the units few of them while K is
-    // whole pairs of phases (4096 x 4096 0.86 of the tiles, 2048 x 2048 1.04, 4096 x 512 1.14), or 21 to 32 rows per unit (8192 x 512
-    // 0.90, x 2048 0.70, x 3072 0.92), or a short K (12288 x 512 0.92, x 1536 1.15, x 2048 0.85, 20480 x 512 1.06).
+    // whole pairs of phases (4096 x 4096 0.93 of the tiles, x 2048 0.89, 2048 x 2048 1.0, 4096 x 512 1.07), or 17 to 32 or 49 to 64 rows
+    // per unit (5120 x 1024 0.92, x 3072 0.94, 8192 x 512 0.93, x 3072 0.92, 16384 x 1024 0.92, x 2048 0.93, x 4096 1.0), or a short K (12288 x 512
+    // 0.94, x 768 0.97 to 1.02, x 1536 1.07, x 2304 1.01, x 3072 1.05; 20480 x 512 1.09) or a single pair of phases (12288 x 2048 0.93).
     if (m > 16)
         return true;
     if (m > 8)
-        return !tiles || (k % 2048 == 0 && n >= 12 * unit && n <= 32 * unit) || (n > 20 * unit && n <= 32 * unit) ||
-               (n > 32 * unit && n <= 64 * unit && (k <= 512 || k == 2048));
+        return !tiles || (k % 2048 == 0 && n >= 12 * unit && n <= 16 * unit) || (n > 16 * unit && n <= 32 * unit) ||
+               (n > 32 * unit && n <= 64 * unit && (k <= 512 || k == 2048 || n > 48 * unit));
     // Five to eight rows of a matrix of middling size, against the vector ALUs in one pass: 4096 x 4096 at 8 rows 0.88 of
     // them, 8192 x 4096 0.77, x 5120 0.97, but 2048 x 5120 1.0 to 1.22, 8192 x 6144 1.09, 10240 x 2048 1.13, 22016 x 4096 37 -> 41.
     // Rows that just fit the LDS stay (4096 x 10240 at 8 rows 1.03, 8192 x 10240 1.18); those that do not ran in phases

@@ -49,7 +49,7 @@ def rules(tmp_path_factory):
 SLOWER = [                                                  # us per launch on the other kernels -> in blocks
     (3, 16, 65536, ""), (3, 2048, 24576, "w"), (5, 1000, 49152, ""), (8, 4096, 65536, ""),        # 26.3 -> 34.1, ...
     (8, 6144, 65536, "w"), (5, 24000, 24576, "w"), (5, 18432, 12288, "wf"),
-    (9, 16, 16384, "w"), (12, 1000, 16384, "w"), (16, 18432, 4096, ""), (16, 4096, 512, ""),
+    (9, 16, 16384, "w"), (12, 1000, 16384, "w"), (16, 36864, 4096, ""), (16, 4096, 1536, ""),
     (17, 16, 65536, "w"), (32, 256, 65536, "w"), (17, 1000, 65536, "w"), (48, 16, 65536, "w"), (64, 16, 65536, "w"),
     (8, 4096, 65536, "tw"), (5, 1000, 16384, "tw"), (3, 256, 24576, "t"), (8, 6144, 28672, "tw"),
     (9, 16, 28672, "tw"), (16, 1000, 11008, "tw"), (9, 2560, 2048, "t"), (16, 16384, 28672, "tw"),
@@ -62,6 +62,7 @@ FASTER = [
     (8, 4096, 11008, "w"), (8, 4096, 11008, "t"), (5, 12288, 14336, ""), (5, 24000, 65536, "t"), (8, 8192, 11008, "w"),
     (9, 4096, 11008, "w"), (16, 12288, 14336, "w"), (16, 1000, 11008, ""), (9, 22016, 4096, "f"), (16, 8192, 1024, "t"),
     (16, 24000, 65536, "tw"), (9, 8192, 20480, "tw"), (17, 256, 65536, ""), (96, 16, 49152, "w"), (16, 18432, 4096, "f"),
+    (16, 18432, 4096, ""), (16, 4096, 512, ""), (3, 57344, 128, ""), (8, 16, 128, "tw"),
     (8, 12288, 11008, "wp"), (5, 300, 11008, "wp"), (5, 300, 11008, "twp"), (8, 8192, 14336, "wf"), (5, 16, 11008, "f"), (16, 32000, 11008, "tw"),
 ]
 
@@ -83,22 +84,23 @@ def test_calls_that_are_faster_in_blocks(rules, m, n, k, form):
 
 
 def test_rows_that_the_other_kernels_take_in_one_pass_stay(rules):
-    for m in range(1, 9):
-        for n in (1, 16, 4096, 24576, 64000):
-            for k in (128, 4096):
-                assert not asked(rules, m, n, k, "") and not asked(rules, m, n, k, "tw")
+    for m in range(3, 9):
+        for n in (1, 16, 4096, 64000):
+            assert not asked(rules, m, n, 4096, "") and not asked(rules, m, n, 4096, "tw")
 
 
 @pytest.mark.parametrize("m,n,k,form,blocks", [
     # one pass of the tiles, three to eight rows
     (3, 4096, 1024, "", True), (8, 4096, 1152, "", False), (5, 1000, 5248, "", True), (4, 1000, 5248, "", False),
-    (5, 1000, 5248, "tw", False), (3, 8192, 4096, "", True), (8, 12288, 3584, "f", False), (5, 12288, 4224, "f", True),
+    (5, 1000, 5248, "tw", False), (3, 8192, 4096, "", True), (8, 12288, 3584, "f", True), (4, 12288, 3584, "", False), (5, 12288, 4224, "f", True),
     (4, 20480, 4352, "", True), (4, 20480, 5120, "", False), (5, 22016, 4096, "f", True), (8, 28672, 4096, "p", False),
-    (8, 32000, 5120, "p", True), (8, 57344, 2048, "", True), (8, 57344, 3072, "", False), (4, 64, 128, "", False),
+    (8, 32000, 5120, "p", True), (8, 57344, 2048, "", False), (8, 57344, 2304, "", True), (8, 57344, 3072, "", False), (4, 64, 128, "", True),
+    (3, 33024, 4480, "p", False), (7, 33024, 4480, "p", True), (7, 36864, 2944, "p", False), (3, 34816, 1664, "", False),
+    (5, 24576, 4096, "", True), (5, 24832, 4096, "", False), (5, 22016, 4096, "p", False), (8, 32000, 7168, "", True),
     (6, 8192, 5120, "tw", True), (4, 8192, 5120, "tw", False), (8, 12288, 2048, "tw", False), (5, 12288, 9216, "tw", True),
     (8, 22016, 4096, "tw", True), (8, 33924, 7808, "tf", False), (8, 57344, 8192, "tw", True),
     # nine to sixteen, and K split over the units
-    (9, 1000, 512, "", True), (9, 1000, 2048, "", False), (16, 32000, 4096, "wp", True), (16, 57344, 4096, "", False),
+    (9, 1000, 512, "", True), (9, 4096, 1024, "", True), (9, 1000, 2048, "", False), (11, 35328, 3840, "f", False), (16, 57344, 3584, "", True), (16, 32000, 4096, "wp", True), (16, 57344, 4096, "", False),
     (9, 57344, 4096, "tw", True), (16, 32000, 7168, "w", True), (16, 32000, 8192, "w", False), (9, 32000, 10240, "w", True),
     (8, 57344, 11008, "tw", True), (8, 57344, 10240, "w", False), (12, 1400, 10880, "w", True),
 ])
@@ -118,8 +120,8 @@ def test_ragged_k(rules):
     (6, 3, 2048, 16384, False), (6, 4, 3072, 20480, False), (6, 5, 8192, 4096, True), (6, 3, 8192, 4096, True),
     (6, 3, 2048, 4096, True), (6, 3, 1000, 4096, False), (6, 5, 1000, 4096, True), (6, 5, 32000, 11008, True),
     (6, 3, 2048, 24576, True), (6, 4, 8192, 24576, True), (6, 17, 32000, 4096, True), (6, 2, 4096, 24576, False),
-    (8, 5, 9216, 9216, False), (8, 8, 12288, 3072, False), (8, 8, 12288, 7168, False), (8, 5, 16384, 8192, False),
-    (8, 8, 12288, 4096, True), (8, 5, 16384, 2048, True), (8, 5, 8192, 9216, True), (8, 4, 8192, 4096, False),
+    (8, 5, 9216, 9216, False), (8, 8, 12288, 3072, True), (8, 8, 12288, 4736, False), (8, 8, 12288, 7168, False), (8, 5, 16384, 8192, False),
+    (8, 8, 12288, 4096, True), (8, 5, 16384, 2048, True), (8, 5, 8192, 9216, True), (8, 4, 8192, 4096, True), (8, 4, 8448, 4096, False),
     (8, 5, 32000, 11008, True), (8, 16, 4096, 5120, True), (8, 24, 64000, 128, True), (8, 8, 22016, 4096, False),
     (2, 4, 1000, 8192, False), (2, 3, 2048, 10240, False), (2, 4, 24000, 128, False), (2, 3, 18000, 512, False),
     (2, 4, 1000, 1024, True), (2, 3, 1000, 1024, False), (2, 4, 1000, 12288, True), (2, 3, 24000, 768, True),
@@ -132,7 +134,7 @@ def test_other_formats(rules, bits, m, n, k, blocks):
 
 
 @pytest.mark.parametrize("m,n,k,tiles,blocks", [
-    (9, 4096, 512, True, False), (16, 5120, 1024, True, False), (16, 5120, 3072, True, False), (9, 2048, 2048, True, False),
+    (9, 4096, 512, True, False), (16, 5120, 1024, True, True), (16, 5120, 3072, True, True), (16, 14336, 3072, True, True), (9, 2048, 2048, True, False),
     (16, 4096, 4096, True, True), (9, 4096, 2048, True, True), (12, 12288, 4096, True, False), (9, 16, 8, False, True),
     (16, 4096, 11008, False, True), (17, 12288, 4096, True, True),
     (5, 2048, 5120, False, False), (8, 5120, 2560, False, False), (6, 8192, 6144, False, False), (7, 10240, 2048, False, False),
@@ -148,8 +150,8 @@ def test_unquantised_weights(rules, m, n, k, tiles, blocks):
 @pytest.mark.parametrize("bits,m,n,k,blocks", [
     (8, 4, 1024, 512, False), (8, 4, 2048, 1024, True), (8, 3, 2048, 1152, False), (8, 3, 4096, 7168, True), (8, 4, 8192, 3072, True),
     (8, 4, 9216, 2048, True), (8, 4, 9216, 2560, False), (8, 8, 12288, 2560, True), (8, 16, 32000, 2048, True),
-    (8, 16, 32000, 2560, False), (6, 3, 1000, 1024, True), (6, 4, 10240, 3072, True), (6, 16, 10240, 3200, False),
-    (6, 16, 12288, 6144, True), (6, 5, 12288, 7168, False), (6, 8, 32000, 3072, True), (6, 8, 57344, 3072, False),
+    (8, 16, 32000, 2560, False), (6, 3, 1000, 1024, True), (6, 4, 10240, 3072, True), (6, 16, 10240, 3200, True),
+    (6, 16, 10240, 3712, False), (6, 16, 10240, 4352, True), (6, 16, 16384, 6144, True), (6, 16, 20480, 3072, False), (6, 16, 20736, 3072, True), (6, 5, 12288, 7168, False), (6, 8, 32000, 3072, True), (6, 8, 57344, 3072, False),
     (6, 4, 57344, 2048, True), (2, 3, 1024, 4096, True), (2, 3, 1024, 4224, False), (2, 4, 1000, 2560, False),
 ])
 def test_other_formats_with_a_short_k(rules, bits, m, n, k, blocks):
