@@ -1,6 +1,7 @@
 // The product for more activation rows than one matrix-core tile column holds (a prompt, several
-// sequences verified together) and, at any row count from three on, for MXFP4 weights whose K is no multiple of
-// 128 (arXiv 2503.13565, section 3.4.3, Eq. 2 for the arithmetic; every weight is read once per block of rows).
+// sequences verified together), and from three rows on wherever it is faster than the kernels that hold their rows in the LDS (routes.h):
+// nearly always for MXFP4 weights whose K is no multiple of 128 (arXiv 2503.13565, section 3.4.3, Eq. 2 for the arithmetic; every
+// weight is read once per block of rows).
 //
 // The tile kernels keep all of K of at most 16 activation rows in the LDS, so more rows take more
 // passes, and every pass streams and decodes the weights again.  Here a workgroup of eight waves
@@ -38,13 +39,13 @@
 //     unaligned) every byte pulled a cache line, 104 us instead of 130 on the example below.
 //   - Prompts take blocks of 128 rows with all eight waves side by side along the weight rows, so that no
 //     weight is decoded or fetched twice in a block: 92 us against 104 for 2 x 4 waves.
-//   - A prompt is bound by the matrix pipe and what feeds it at the clock the power limit leaves: the pipe is busy in 55 % of
-//     the cycles at 2.15 GHz, the LDS in 43 % (with the loads and the LDS reads taken out the example took 69 us, with
-//     all-zero operands 80).  Some tens of rows are bound by the activations' way through the L2 and LDS (at 32 rows
-//     the waves wait in 43 % of their cycles).  Measured, us from launch to launch, passes of 16 rows -> here:
+//   - A prompt is bound by the matrix pipe and what feeds it at the clock the power limit leaves: the pipe is busy in 60 % of
+//     the cycles at 2.15 GHz, the LDS in 28 %.  (When it took 86 us: 69 with the loads and the LDS reads taken out, 80 with
+//     all-zero operands.)  Some tens of rows are bound by the activations' way through the L2 and LDS (at 32 rows
+//     the waves wait in 45 % of their cycles).  Measured, us from launch to launch, passes of 16 rows -> here:
 //     22016 x 4096 with the gate at 509 rows 436 -> 76 to 81 by the box (a library product of BF16 weights of that
-//     shape: 91), 12288 x 4096 at 32 rows 18.5 -> 10.1 with three sets of weights in rotation, 22016 x 4096 with the
-//     gate 13.0, 28500 x 2432 at 95 rows 20.3, 5418 x 512 at 86 rows 3.9.
+//     shape: 91), 12288 x 4096 at 32 rows 18.5 -> 10.2 with three sets of weights in rotation, 22016 x 4096 with the
+//     gate at 5 rows 11.1, 32000 x 4096 with the pick at 9 rows 17.7 (two launches).
 //   - A block past the end of K (K % 128 != 0, the steps that round a phase up) is a load past the
 //     descriptor: zero weights against zero activations.
 #pragma once
