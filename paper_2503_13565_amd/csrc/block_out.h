@@ -51,7 +51,7 @@ __device__ __forceinline__ void store_bf16(uint16_t* to, int count, const float*
         typename Packed<N>::type o;
 #pragma unroll
         for (int i = 0; i < N; i += 2)
-            o[i >> 1] = f32_to_bf16_rne(v[i]) | (uint32_t)f32_to_bf16_rne(v[i + 1]) << 16;
+            o[i >> 1] = f32_to_bf16_rne2(v[i], v[i + 1]);
         *reinterpret_cast<typename Packed<N>::anywhere*>(to) = o;
     } else {
 #pragma unroll
@@ -98,18 +98,132 @@ __device__ __forceinline__ void emit_sums(const BlockOut& a, const float (&sums)
     }
 }
 
-// Rows of finished sums in the LDS, kStride floats from row to row; row r is activation row row_of(r), its first sum weight
-// row n0.
-template <int kRows, int kCols, int kStride, class RowOf>
-__device__ __forceinline__ void emit_rows(const BlockOut& a, const float* tile, int n0, RowOf row_of)
+// Four neighbouring values of the bias, from weight row `col` on (rows past the last one: the last one's again, not stored).
+__device__ __forceinline__ f32x4_t bias_of(const BlockOut& a, int col)
 {
-    constexpr int kChunks = kCols / 8;
+    f32x4_t b;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        b[i] = bf16_bits_to_f32(a.bias[min(col + i, a.n - 1)]);
+    return b;
+}
+
+// Whether 16 bytes of `p`'s rows lie on 16-byte boundaries, from a multiple of eight columns on.
+__device__ __forceinline__ bool rows_aligned(const uint16_t* p, int64_t ld)
+{
+    return ((reinterpret_cast<uintptr_t>(p) >> 1 | (uint64_t)ld) & 7) == 0;
+}
+
+// kN floats of a row in the LDS from column `at` on.  Where that is no multiple of four, or not inside the row's kCols columns (what
+// lies outside is not used): whole 16-byte reads, shifted into place.
+template <int kN, int kCols>
+__device__ __forceinline__ void row_floats(const float* row, int at, bool aligned, float* to)
+{
+    f32x4_t v[kN / 4 + 1];
+    if (aligned) {
+#pragma unroll
+        for (int i = 0; i < kN / 4; ++i)
+            v[i] = *reinterpret_cast<const f32x4_t*>(row + at + 4 * i);
+    } else {
+#pragma unroll
+        for (int i = 0; i <= kN / 4; ++i)
+            v[i] = *reinterpret_cast<const f32x4_t*>(row + min(max((at & ~3) + 4 * i, 0), kCols - 4));
+#pragma unroll
+        for (int i = 0; i < kN / 4; ++i) {                              // (shuffles: selects of elements became indexed memory)
+            const f32x4_t next = v[i + 1];
+            const f32x4_t one = __builtin_shufflevector(v[i], next, 1, 2, 3, 4), two = __builtin_shufflevector(v[i], next, 2, 3, 4, 5),
+                          three = __builtin_shufflevector(v[i], next, 3, 4, 5, 6);
+            const f32x4_t even = at & 2 ? two : v[i], odd = at & 2 ? three : one;
+            v[i] = at & 1 ? odd : even;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kN; ++i)
+        to[i] = v[i / 4][i % 4];
+}
+
+// Rows of finished sums (bias included) on their way out through the LDS, kStride floats from row to row; row r is activation
+// row row_of(r), its first sum weight row n0.  `fill` puts them there.
+//   - A thread takes eight neighbouring outputs that lie on a 16-byte boundary of the residual.  A load of 16 bytes on another
+//     boundary takes the texture unit several times as long: with pieces that began at multiples of eight columns, 12967 x 512 with
+//     residual at 327 rows took 22.1 us where 12960 took 15.2; now 15.5 and 12.9.  (Stores do not care: without a residual the pieces
+//     begin at multiples of eight columns, 12967 x 512 14.0 us; 14.4 on y's boundaries, with the ends of its rows apart.)
+//   - The residual of up to four pieces is asked for together, the first ones in front of `fill`.  A piece is read
+//     whole, also where only a part of it belongs to the row: what is read beside it lies in the same 16 bytes.
+template <int kRows, int kCols, int kStride, class RowOf, class Fill>
+__device__ __forceinline__ void emit_rows(const BlockOut& a, const float* tile, int n0, RowOf row_of, Fill fill)
+{
+    constexpr int kBatch = 4;
+    const bool gate = a.act == MXFP4_ACT_SWIGLU;                        // rows (2 i, 2 i + 1) are (gate, up) pairs
+    const bool aligned = !a.residual || rows_aligned(a.residual, a.ldr);   // (n0 is a multiple of 16)
+    const int col0 = gate ? n0 >> 1 : n0, width = gate ? kCols / 2 : kCols;
+    const int left = min(width, (gate ? a.n >> 1 : a.n) - col0);        // outputs of the block in a row
+    const int units = (width >> 3) + (aligned ? 0 : 1), total = kRows * units;
+    const uint32_t inverse = ((1u << 20) + units - 1) / units;          // exact up to 2^20 / (units - 1) pieces
+    static_assert(kRows * (kCols / 8 + 1) * (kCols / 8) < 1 << 20, "piece / units by multiplication");
+    // the piece `e` of the block: its row in the LDS, activation row, first output in the row's part of the block
+    struct Piece {
+        int r, row, c;
+        bool some;
+    };
+    auto piece = [&](int e) {
+        Piece p;
+        p.r = (int)((uint32_t)e * inverse >> 20);
+        p.row = row_of(p.r);
+        p.c = (e - p.r * units) * 8;
+        if (!aligned)
+            p.c -= (int)((reinterpret_cast<uintptr_t>(a.residual + (int64_t)p.row * a.ldr + col0) >> 1) & 7);
+        p.some = e < total && p.row < a.m && p.c < left && p.c > -8;
+        return p;
+    };
+    u32x4_t res[kBatch];
+    auto ask = [&](int e0) {
+        const uintptr_t any = reinterpret_cast<uintptr_t>(a.residual) & ~(uintptr_t)15;
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            const Piece p = piece(e0 + j * 512);
+            res[j] = *reinterpret_cast<const u32x4_t*>(
+                p.some ? reinterpret_cast<uintptr_t>(a.residual + (int64_t)p.row * a.ldr + col0 + p.c) : any);
+        }
+    };
+    if (a.residual)
+        ask(threadIdx.x);
+    fill();
 #pragma unroll 1
-    for (int e = threadIdx.x; e < kRows * kChunks; e += 512) {
-        const f32x4_t* at = reinterpret_cast<const f32x4_t*>(tile + e / kChunks * kStride + e % kChunks * 8);
-        const f32x4_t low = at[0], high = at[1];
-        const float sums[8] = {low[0], low[1], low[2], low[3], high[0], high[1], high[2], high[3]};
-        emit_sums(a, sums, row_of(e / kChunks), n0 + e % kChunks * 8);
+    for (int e0 = threadIdx.x; e0 < total; e0 += kBatch * 512) {
+        if (a.residual && e0 >= 512)
+            ask(e0);
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            const Piece p = piece(e0 + j * 512);
+            if (!p.some)
+                continue;
+            const float* row = tile + p.r * kStride;
+            float z[8];
+            if (gate) {
+                float v[16];
+                row_floats<16, kCols>(row, 2 * p.c, aligned, v);
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    z[i] = silu_gate(v[2 * i], v[2 * i + 1]);
+            } else {
+                row_floats<8, kCols>(row, p.c, aligned, z);
+            }
+            if (a.residual) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    z[i] += bf16_bits_to_f32(res[j][i >> 1] >> (16 * (i & 1)) & 0xFFFFu);
+            }
+            uint16_t* to = a.y + (int64_t)p.row * a.ldy + col0 + p.c;
+            if (p.c >= 0 && p.c + 8 <= left) {
+                store_bf16<8>(to, 8, z);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (p.c + i >= 0 && p.c + i < left)
+                        to[i] = f32_to_bf16_rne(z[i]);
+            }
+        }
     }
 }
 

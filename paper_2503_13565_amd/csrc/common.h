@@ -29,14 +29,12 @@ __device__ __forceinline__ float e8m0_to_f32(uint32_t byte)
     return __uint_as_float(bits);
 }
 
-// FP32 -> BF16 bit pattern, round to nearest even; NaN stays NaN.
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
+// FP32 -> BF16 bit pattern, round to nearest even; NaN stays NaN (one convert instruction; the same bits as the integer rule
+// u + 0x7FFF + (u >> 16 & 1) for every other number).
+__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+__device__ __forceinline__ uint32_t f32_to_bf16_rne2(float low, float high)
 {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u)
-        return (uint16_t)((u >> 16) | 0x0040u);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{low, high}), bf16x2_t));
 }
 
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }

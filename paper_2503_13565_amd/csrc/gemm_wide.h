@@ -87,12 +87,13 @@ struct Args {
 };
 
 // Finished sums on their way out: floats from row to row, and how many rows of the block take a turn together where the
-// waves do not share K (as many as the activations' buffers hold).
+// waves do not share K: all of them as far as the LDS goes, which a block of eight fragments and more has to itself (its registers leave
+// no room for a second one on the unit).
 constexpr int tile_stride(int bn) { return bn + 4; }
-constexpr int tile_rows(int wm, int mf, int bn, int bytes)
+constexpr int tile_rows(int wm, int mf, int nf, int bn)
 {
     int pf = mf;
-    while (pf > 1 && wm * pf * 16 * tile_stride(bn) * 4 > bytes)
+    while (pf > 1 && wm * pf * 16 * tile_stride(bn) * 4 > (mf * nf >= 8 ? 160 : 40) * 1024)
         pf /= 2;
     return wm * pf * 16;
 }
@@ -102,7 +103,7 @@ constexpr size_t lds_bytes(Kind w, int wm, int wn, int wk, int mf, int nf)
     const int bm = wm * mf * 16, bn = wn * nf * 16, x = 2 * wk * bm * 256;  // two buffers of one phase
     const size_t xs = (size_t)x + (w == kBf16 ? 0 : (size_t)2 * bn * scale_row_bytes(wk));      // and two of the scales
     const size_t red = wk > 1 ? (size_t)8 * mf * nf * 1024 : 0;         // the waves' partial sums, afterwards
-    const size_t tile = (size_t)(wk > 1 ? bm : tile_rows(wm, mf, bn, x)) * tile_stride(bn) * 4;
+    const size_t tile = (size_t)(wk > 1 ? bm : tile_rows(wm, mf, nf, bn)) * tile_stride(bn) * 4;
     return xs > red + tile ? xs : red + tile;
 }
 
@@ -495,24 +496,37 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
     // activation row li.  The sums go through the LDS, so that whole rows are stored.
     constexpr int kStride = tile_stride(BN);
     if constexpr (WK == 1) {
+        if (out.bias) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                const f32x4_t bias = bias_of(out, n0 + (wn * NF + f) * 16 + 4 * lg);
+#pragma unroll
+                for (int i = 0; i < MF; ++i)
+                    acc[i][f] += bias;
+            }
+        }
         float* tile = reinterpret_cast<float*>(smem);
-        constexpr int PF = tile_rows(WM, MF, BN, kBuf * 32) / (WM * 16);                     // fragment rows of a wave per turn
+        constexpr int PF = tile_rows(WM, MF, NF, BN) / (WM * 16);                            // fragment rows of a wave per turn
 #pragma unroll
         for (int p = 0; p < MF / PF; ++p) {
-            if (p > 0)
-                lds_barrier();
-#pragma unroll
-            for (int i = 0; i < PF; ++i)
-#pragma unroll
-                for (int f = 0; f < NF; ++f)
-                    *reinterpret_cast<f32x4_t*>(tile + ((wm * PF + i) * 16 + li) * kStride + (wn * NF + f) * 16 + 4 * lg) =
-                        acc[p * PF + i][f];
-            lds_barrier();
             auto row_of = [&](int r) { return m0 + r / (PF * 16) * (MF * 16) + p * (PF * 16) + r % (PF * 16); };
-            if (out.part_val != nullptr)
+            auto fill = [&]() {
+                if (p > 0)
+                    lds_barrier();
+#pragma unroll
+                for (int i = 0; i < PF; ++i)
+#pragma unroll
+                    for (int f = 0; f < NF; ++f)
+                        *reinterpret_cast<f32x4_t*>(tile + ((wm * PF + i) * 16 + li) * kStride + (wn * NF + f) * 16 + 4 * lg) =
+                            acc[p * PF + i][f];
+                lds_barrier();
+            };
+            if (out.part_val != nullptr) {
+                fill();
                 pick_rows<WM * PF * 16, BN, kStride>(out, tile, n0, tn, row_of);
-            else
-                emit_rows<WM * PF * 16, BN, kStride>(out, tile, n0, row_of);
+            } else {
+                emit_rows<WM * PF * 16, BN, kStride>(out, tile, n0, row_of, fill);
+            }
         }
     } else {
         f32x4_t* red = reinterpret_cast<f32x4_t*>(smem);               // [position][fragment][wk][lane]
@@ -531,13 +545,24 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
                 sum += red[(at * WK + w) * 64 + place];
             return sum;
         };
-        if (out.part_val != nullptr) {
+        auto rows_at = [&](int r) { return m0 + r; };
+        if (out.part_val != nullptr || (BM * BN >= 4096 && out.residual && !rows_aligned(out.residual, out.ldr))) {
             float* tile = reinterpret_cast<float*>(smem + (size_t)8 * MF * NF * 1024);
-            for (int e = wk; e < MF * NF; e += WK)
-                *reinterpret_cast<f32x4_t*>(tile + ((wm * MF + e / NF) * 16 + li) * kStride + (wn * NF + e % NF) * 16 + 4 * lg) =
-                    sum_of(base + e, lane);
-            lds_barrier();
-            pick_rows<BM, BN, kStride>(out, tile, n0, tn, [&](int r) { return m0 + r; });
+            auto fill = [&]() {
+                for (int e = wk; e < MF * NF; e += WK) {
+                    f32x4_t sum = sum_of(base + e, lane);
+                    if (out.bias)
+                        sum += bias_of(out, n0 + (wn * NF + e % NF) * 16 + 4 * lg);
+                    *reinterpret_cast<f32x4_t*>(tile + ((wm * MF + e / NF) * 16 + li) * kStride + (wn * NF + e % NF) * 16 + 4 * lg) = sum;
+                }
+                lds_barrier();
+            };
+            if (out.part_val != nullptr) {
+                fill();
+                pick_rows<BM, BN, kStride>(out, tile, n0, tn, rows_at);
+            } else {
+                emit_rows<BM, BN, kStride>(out, tile, n0, rows_at, fill);
+            }
         } else {
             // straight from the partial sums: sixteen rows side by side, then the next columns; four sums per thread where
             // that takes one turn (748 x 6528 at 20 rows 6.85 us with eight, 6.48), else eight

@@ -87,6 +87,37 @@ def test_largest_blocks(m, n, k):
     assert_gemm_close(gated[:, even.to(DEV) // 2], out_ref, a_out, tag)
 
 
+@pytest.mark.parametrize("m,n,k,act", [(20, 131, 160, 0), (75, 17661, 128, 0), (75, 9002, 128, 1), (327, 12967, 128, 0), (130, 9002, 256, 1),
+                                       (509, 22015, 1024, 0), (509, 22018, 1024, 1)])
+@pytest.mark.parametrize("shift,pad", [(0, 0), (1, 0), (6, 3), (3, 8)])
+def test_residual_rows_on_any_boundary(m, n, k, act, shift, pad):
+    # blocks of a few and of many outputs, whose waves share K or not, in one and two turns; the residual's rows begin `shift`
+    # elements behind a 16-byte boundary and lie C + pad apart, the outputs are written over it or elsewhere
+    print("M=%d N=%d K=%d act %d shift %d pad %d" % (m, n, k, act, shift, pad), flush=True)
+    w = synth.weights_student_t(n, k, seed=9150 + n, device=DEV)
+    x = synth.activations_outlier_channels(m, k, seed=9160 + m, device=DEV)
+    q, s = binding.mxfp4_direct_cast(w)
+    c, g = n // (1 + act), torch.Generator().manual_seed(n + shift)
+    edges = torch.cat([torch.arange(max(0, at - 9), min(c, at + 9)) for at in (0, 64, 128, 192, 256, 384, c) if at <= c])
+    cols = torch.unique(torch.cat([edges, torch.randint(0, c, (40,), generator=g)]))
+    rows = torch.stack([2 * cols, 2 * cols + 1], dim=1).reshape(-1) if act else cols
+    y_ref, a_ref = oracle.woq_gemm(synth.to_bits(x), q.cpu()[rows].numpy(), s.cpu()[rows].numpy())
+    bias = (torch.randn(n, generator=g) * 0.3).to(torch.bfloat16)
+    room = torch.zeros((m * (c + pad) + 32,), dtype=torch.bfloat16, device=DEV)
+    res = room[shift:shift + m * (c + pad)].view(m, c + pad)
+    res.copy_((torch.randn((m, c + pad), generator=g) * 0.3).to(torch.bfloat16))
+    before = room.clone()
+    out_ref, a_out = oracle.epilogue(y_ref, a_ref, synth.to_bits(bias[rows]), synth.to_bits(res[:, cols.to(DEV)].contiguous()), act)
+    y = binding.mxfp4_woq_gemm_fused(x, q, s, bias=bias.to(DEV), act=act, residual=res[:, :c])
+    assert torch.equal(room.view(torch.int16), before.view(torch.int16))
+    binding.mxfp4_woq_gemm_fused(x, q, s, bias=bias.to(DEV), act=act, residual=res[:, :c], y=res[:, :c])
+    torch.cuda.synchronize()
+    assert_gemm_close(y[:, cols.to(DEV)], out_ref, a_out)
+    assert torch.equal(res[:, :c].contiguous().view(torch.int16), y.view(torch.int16))
+    res[:, :c] = before[shift:shift + m * (c + pad)].view(m, c + pad)[:, :c]       # nothing else was written
+    assert torch.equal(room.view(torch.int16), before.view(torch.int16))
+
+
 @pytest.mark.parametrize("m,n,k", [(9, 4100, 4096), (16, 2050, 896), (5, 300, 11008), (17, 17, 128), (33, 1000, 1152),
                                    (48, 11000, 640), (130, 259, 2048), (300, 5001, 384)])
 def test_tile_major_copy_gives_the_same_bits(m, n, k):
