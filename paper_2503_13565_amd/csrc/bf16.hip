@@ -895,6 +895,8 @@ static bool blocks_preferred(const Bf16Args& a, const DeviceInfo& dev)
         return false;
     if (from)
         return a.m >= atoi(from);
+    if (a.m < 3)
+        return wide_decode_bf16_preferred(a.m, a.n, a.k, dev.cus);
     return wide_bf16_preferred(a.m, a.n, a.k, bf16_mfma_can_run(a, dev), dev.cus, dev.lds_bytes);
 }
 
@@ -907,10 +909,10 @@ hipError_t launch_bf16_gemv(const Bf16Args& a, const DeviceInfo& dev, int* parts
         const char* e = knob("MXFP4_BF16_GENERAL");                // measurement only
         return e && atoi(e) != 0;
     }();
-    if (!general_only && bf16_reg_can_run(a, dev))
-        return launch_bf16_reg(a, dev, parts_used, stream);
     if (!general_only && blocks_preferred(a, dev))
         return launch_gemm_wide_bf16(a, dev, parts_used, stream);
+    if (!general_only && bf16_reg_can_run(a, dev))
+        return launch_bf16_reg(a, dev, parts_used, stream);
     // Up to eight rows the vector-ALU kernel below is as fast or faster in one pass (7B shapes, µs:
     // 20.1 / 33.0 / 46.3 against 21.2 / 36.8 / 48.6 at four rows, equal at eight); from nine rows on
     // it needs two passes and the matrix cores one.

@@ -73,6 +73,78 @@ inline bool wide_one_pass_preferred(const TileCall& c)
     return k <= 1536 || (k > 2048 && k <= 2432);
 }
 
+// One and two rows.  The decode kernels give a wave a step of 2048 elements of one weight row, in pairs: a short K leaves most of its
+// lanes idle, a K just past 4096 half of its steps, and the row's way through the lanes costs the same.  A block walks such a K in
+// as many lanes as it has.  For products only: a pick's value leaves in 32 bits, and the blocks' longer chains are off by
+// 1.0 to 1.7 of what the decode kernels' lanes leave there (5e-8 to 9e-8; below the BF16 rounding of a product by four digits; BF16
+// weights 0.7 to 1.05, so their picks go too).  One row of MXFP4 weights stays with the decode kernel, whose bits the chained and
+// the merged launches give.  Figures: blocks as a part of the decode kernels' time over 12 numbers of weight rows from 256 to 57344 and
+// 16 K from 128 to 16384.
+//
+// MXFP4.  Two rows: 256 x 384 0.93, 1500 x 2048 0.91, 4096 x 512 0.75, 8192 x 2048 0.75, x 3072 0.97, x 5120 0.85, 28000 x 512
+// 0.33, x 2048 0.66, x 3072 0.88, x 4096 1.09, x 5120 0.85, x 6144 1.04, 16000 x 11008 0.91; with gate or residual the same.
+// Tile-major, one row: 16000 x 640 0.82, 28000 x 1280 0.84, 57344 x 1024 0.62; two rows (and one with gate or residual, which the tiles
+// take too): 256 x 1024 0.94, 5000 x 2048 0.93, 28000 x 1024 0.75, x 2560 0.89, 22016 x 6144 0.93.
+inline bool wide_decode_preferred(const TileCall& c)
+{
+    const int m = c.m, n = c.n, k = c.k, unit = c.cus;
+    if (c.pick)
+        return false;
+    if (c.tiled && m == 1 && !c.fused)
+        return n >= 48 * unit && k <= (n >= 80 * unit ? 1280 : 640);
+    if (c.tiled)
+        return k <= 1024 || (n >= 16 * unit && n <= 36 * unit && k <= 2048) || (n >= 56 * unit && n <= 100 * unit && k <= 6144) ||
+               (n > 100 * unit && k <= 1280);
+    if (m == 1)
+        return false;
+    if (n <= 24 * unit)
+        return k <= (n < 4 * unit ? 384 : 2048);
+    if (n <= 64 * unit)
+        return k <= 2560 || (k > 4096 && k <= 11264);
+    return k <= 2560 || (k <= 3072 && n <= 128 * unit) || (k > 4096 && k <= 5120 && n <= 128 * unit);
+}
+
+// MXFP4 with K % 128 != 0, one and two rows against the general vector ALU kernel: one row 3000 x 672 0.87, 5000 x 1056 0.90, 28000 x 416
+// 0.51, x 1056 0.82, 22016 x 1312 1.04; two rows 1500 x 672 0.85, 3000 x 1568 0.89, 8192 x 11040 0.73, 12288 x 5152 0.95,
+// 28000 x 2592 0.73, x 4064 0.96, x 6176 1.25.
+inline bool wide_decode_ragged_preferred(int m, int n, int k, int cus)
+{
+    const int unit = cus;
+    if (n < 4 * unit)
+        return false;
+    if (m == 1)
+        return k <= (n < 8 * unit ? 160 : n < 16 * unit ? 672 : 1088);
+    if (n >= 28 * unit && n <= 36 * unit)
+        return k <= 11264;
+    return k <= (n < 8 * unit ? 672 : n < 16 * unit ? 1568 : 2592);
+}
+
+// The other formats, K % 128 == 0, one and two rows.  8-bit: one row 3000 x 384 0.85, 8192 x 1024 0.69, 28000 x 512 0.43, x 1280
+// 0.74, 22016 x 1536 1.01; two rows 3000 x 2048 0.77, 28000 x 2048 0.77, 57344 x 2048 0.92.  6-bit: few weight rows, where the tiles ran for E2M3,
+// 256 x 128 to 8192 0.74 to 0.93 (of E3M2's vector ALUs 1.2 to 1.4); one row 8192 x 1024 0.69, 28000 x 1280 0.69; two rows 28000 x 2048 0.76, and beyond K = 4096, where
+// E2M3 took a pass of the decode kernel per row, 8192 x 8192 0.62, 28000 x 5120 0.69 (E3M2, in one pass of the vector ALUs, 18175 x 9088 1.17).  Ternary: one row 8192 x 1024 0.67, 28000 x 2048
+// 0.76, x 5120 0.76; two rows 28000 x 512 0.26, x 3072 0.76, x 8192 0.74, 12288 x 16384 0.95.
+inline bool wide_decode_format_preferred(int m, int n, int k, int bits, bool e2m3, int cus)
+{
+    const int unit = cus;
+    if (n < 8 * unit)
+        return e2m3 && k <= 8192;
+    if (m == 1)
+        return k <= (n < 16 * unit && bits != 6 ? 384 : n < 32 * unit ? 1024 : bits == 2 ? 2048 : 1280) ||
+               (bits == 2 && n >= 48 * unit && k > 4096 && k <= 5120);
+    return k <= (bits == 2 && n >= 32 * unit ? 3072 : 2048) || (k > 4096 && k <= 16384 && (e2m3 || (bits == 2 && n >= 32 * unit)));
+}
+
+// BF16 weights, one and two rows, products and picks: one row 5000 x 384 0.84, 8192 x 1024 0.84, 28000 x 1024 0.65, 12288 x 1280 0.85,
+// 28000 x 2048 1.22; two rows 3000 x 384 0.88, 8192 x 1024 0.88, 28000 x 384 0.83, x 640 0.98.
+inline bool wide_decode_bf16_preferred(int m, int n, int k, int cus)
+{
+    const int unit = cus;
+    if (m == 1)
+        return n >= 16 * unit && k <= (n < 32 * unit ? 384 : n < 48 * unit ? 1024 : 1280);
+    return n >= 8 * unit && k <= (n >= 16 * unit && n <= 36 * unit ? 1024 : n <= 128 * unit ? 384 : 128);
+}
+
 // From three rows on, K % 128 == 0.  Figures: us per launch, tiles -> blocks, or blocks as a part of what the tiles take.
 inline bool wide_preferred(const TileCall& c)
 {

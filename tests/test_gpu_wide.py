@@ -134,6 +134,26 @@ def test_tile_major_copy_gives_the_same_bits(m, n, k):
     assert torch.equal(idx, idx_t) and torch.equal(val, val_t)
 
 
+@pytest.mark.parametrize("n,k", [(1000, 384), (2049, 128), (4099, 1408), (8200, 5120), (8201, 672), (24577, 640), (16384, 1024)])
+@pytest.mark.parametrize("m", [1, 2])
+def test_one_and_two_rows(m, n, k):
+    # row-major, tile-major and ragged K, with everything behind the product; sampled weight rows, the last ones among them
+    w = synth.weights_student_t(n, k, seed=9170 + n, device=DEV)
+    x = synth.activations_outlier_channels(m, k, seed=9180 + m, device=DEV)
+    q, s = binding.mxfp4_direct_cast(w)
+    cols = torch.unique(torch.cat([torch.arange(20), torch.arange(n - 40, n), torch.randint(0, n, (60,), generator=torch.Generator().manual_seed(n))]))
+    y_ref, a_ref = oracle.woq_gemm(synth.to_bits(x), q.cpu()[cols].numpy(), s.cpu()[cols].numpy())
+    bias, res = (synth.activations_gaussian(r, n, seed=9190 + r).to(DEV) for r in (1, m))
+    out_ref, a_out = oracle.epilogue(y_ref, a_ref, synth.to_bits(bias[0][cols.to(DEV)].contiguous()), synth.to_bits(res[:, cols.to(DEV)].contiguous()), 0)
+    y = [binding.mxfp4_woq_gemm(x, q, s), binding.mxfp4_woq_gemm_fused(x, q, s, bias=bias[0], residual=res)]
+    if k % 128 == 0:
+        tw = binding.mxfp4_tile_repack(q, s)
+        y += [binding.mxfp4_woq_gemm_tiled(x, tw), binding.mxfp4_woq_gemm_tiled_fused(x, tw, bias=bias[0], residual=res)]
+    torch.cuda.synchronize()
+    for i, t in enumerate(y):
+        assert_gemm_close(t[:, cols.to(DEV)], *((out_ref, a_out) if i % 2 else (y_ref, a_ref)), "form %d" % i)
+
+
 FORMATS = {"e4m3": (oracle.e4m3_woq_gemm, binding.mxfp4_e4m3_direct_cast, binding.mxfp4_e4m3_woq_gemm,
                     binding.mxfp4_e4m3_woq_gemm_argmax),
            "e2m3": (oracle.e2m3_woq_gemm, binding.mxfp4_e2m3_direct_cast, binding.mxfp4_e2m3_woq_gemm,
@@ -141,6 +161,30 @@ FORMATS = {"e4m3": (oracle.e4m3_woq_gemm, binding.mxfp4_e4m3_direct_cast, bindin
 for _name, _id in (("e5m2", binding.FMT_E5M2), ("e3m2", binding.FMT_E3M2), ("t2", binding.FMT_T2)):
     FORMATS[_name] = tuple(functools.partial(f, _id) for f in (
         oracle.mx_woq_gemm, binding.mxfp4_fmt_direct_cast, binding.mxfp4_fmt_woq_gemm, binding.mxfp4_fmt_woq_gemm_argmax))
+
+
+@pytest.mark.parametrize("fmt", sorted(FORMATS))
+@pytest.mark.parametrize("m,n,k", [(1, 2049, 384), (1, 900, 2176), (1, 8200, 1024), (1, 16003, 4224), (2, 2049, 2048), (2, 8200, 128), (2, 8201, 5120)])
+def test_one_and_two_rows_of_other_formats(fmt, m, n, k):
+    ref, cast, product, _ = FORMATS[fmt]
+    w = synth.weights_student_t(n, k, seed=9710 + n, device=DEV)
+    x = synth.activations_outlier_channels(m, k, seed=9810 + m, device=DEV)
+    q, s = cast(w)
+    cols = torch.unique(torch.cat([torch.arange(20), torch.arange(n - 40, n), torch.randint(0, n, (60,), generator=torch.Generator().manual_seed(n))]))
+    y = product(x, q, s)
+    torch.cuda.synchronize()
+    assert_gemm_close(y[:, cols.to(DEV)], *ref(synth.to_bits(x), q.cpu()[cols].numpy(), s.cpu()[cols].numpy()), "%s M=%d N=%d K=%d" % (fmt, m, n, k))
+
+
+@pytest.mark.parametrize("m,n,k", [(1, 4097, 8), (1, 8200, 1000), (1, 16003, 1280), (2, 2049, 384), (2, 8200, 1024), (2, 33000, 128)])
+def test_one_and_two_rows_of_unquantised_weights(m, n, k):
+    w = synth.weights_student_t(n, k, seed=9920 + n, device=DEV)
+    x = synth.activations_outlier_channels(m, k, seed=9960 + m, device=DEV)
+    y_ref, a_ref = oracle.bf16_gemm(synth.to_bits(x), synth.to_bits(w))
+    y, (idx, val) = binding.mxfp4_bf16_gemm(x, w), binding.mxfp4_bf16_gemm_argmax(x, w)
+    torch.cuda.synchronize()
+    assert_gemm_close(y, y_ref, a_ref)
+    assert_argmax_ok(idx, val, y_ref, a_ref)
 
 
 @pytest.mark.parametrize("fmt", sorted(FORMATS))
