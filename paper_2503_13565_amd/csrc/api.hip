@@ -299,7 +299,8 @@ static int run_gemm(const void* x, int64_t M, int64_t ldx, const void* q, const 
             return fail(MXFP4_ERR_ARG, "the register-resident GEMV needs K %% 128 == 0, K <= 12288 and N >= %d",
                         dev.cus * 8);
         if (go)
-            e = launch_gemv_reg(a, dev, &parts_used, st, epi);
+            e = gemv_short_can_run(a, dev) ? launch_gemv_short(a, dev, &parts_used, st, epi)
+                                           : launch_gemv_reg(a, dev, &parts_used, st, epi);
         break;
     case MXFP4_PATH_MFMA:
     case MXFP4_PATH_MFMA_GENERAL:

@@ -76,6 +76,11 @@ hipError_t launch_gemv_multi(const GemmArgs* items, int count, const DeviceInfo&
 hipError_t launch_gemv_reg(const GemmArgs& a, const DeviceInfo& dev, int* parts_used, hipStream_t stream,
                            const Epilogue* epi = nullptr, int bits = 4);
 
+// One or two rows with K <= 2048 on MXFP4 weights: the same results, bit for bit, for the shapes of the decode-step form; gemv_short.hip.
+bool gemv_short_can_run(const GemmArgs& a, const DeviceInfo& dev);
+hipError_t launch_gemv_short(const GemmArgs& a, const DeviceInfo& dev, int* parts_used, hipStream_t stream,
+                             const Epilogue* epi = nullptr);
+
 // The 6-bit draft format (E2M3 codes as a 192-bit string per block: a.q is q6 [N, K/32 * 24]); e2m3.hip.
 hipError_t launch_e2m3_cast(const void* w, int64_t n_rows, int64_t k, int64_t ldw, void* q6, void* s,
                             bool integer_rule, hipStream_t stream);

@@ -97,6 +97,10 @@ inline bool wide_decode_preferred(const TileCall& c)
                (n > 100 * unit && k <= 1280);
     if (m == 1)
         return false;
+    // the decode step's form for K <= 2048 (gemv_short.hip): 4096 x 512 2.28 us, 3.08 in blocks, 8192 x 1024 3.19, 3.36, 6000 x 1536 3.82, 3.83,
+    // 8192 x 1536 4.16, 3.93, 16000 x 512 3.57, 3.19
+    if (n >= 8 * unit && n <= (k <= 1024 ? 32 : k <= 2048 ? 24 : 0) * unit)
+        return false;
     if (n <= 24 * unit)
         return k <= (n < 4 * unit ? 384 : 2048);
     if (n <= 64 * unit)

@@ -304,3 +304,51 @@ def test_errors_are_reported_not_fatal():
     with pytest.raises(binding.Mxfp4Error) as e:
         binding.mxfp4_woq_gemm_argmax(x, q, s, workspace=torch.zeros(8, dtype=torch.uint8, device=DEV))
     assert e.value.code == 4
+
+
+@pytest.mark.parametrize("k", [128, 512, 640, 1024, 1152, 2048])
+@pytest.mark.parametrize("n,m", [(2049, 1), (12003, 1), (58001, 1), (2050, 2), (9999, 2), (28001, 2)])
+def test_short_rows_with_everything_behind_them(n, k, m):
+    # one, two and four rows side by side in a wave, one to four times as many at once, the last wave's rows not whole
+    print("N=%d K=%d M=%d" % (n, k, m), flush=True)
+    w = synth.weights_student_t(n, k, seed=3000 + n + k, device=DEV)
+    xb = synth.activations_outlier_channels(m, k + 8, seed=3100 + m + k, device=DEV)
+    xb[:, k:] = float("nan")                                # rows farther apart than K: what lies between is not read
+    x = xb[:, :k]
+    q, s = binding.mxfp4_direct_cast(w)
+    s[n // 2] = 255                                         # a NaN row, and none of its neighbours
+    g = torch.Generator().manual_seed(n + k)
+    keep = torch.cat([torch.arange(24), torch.randint(0, n, (60,), generator=g), torch.arange(n - 25, n - n % 2)])
+    even = torch.unique(keep // 2 * 2)
+    rows = torch.stack([even, even + 1], dim=1).reshape(-1)
+    rows = rows[(rows // 2 != n // 4) & (rows < n)]
+    y_ref, a_ref = oracle.woq_gemm(synth.to_bits(x.contiguous()), q.cpu()[rows].numpy(), s.cpu()[rows].numpy())
+    y = binding.mxfp4_woq_gemm(x, q, s, path=REG)
+    assert_gemm_close(y[:, rows.to(DEV)], y_ref, a_ref)
+    bad = torch.isnan(y)
+    assert bool(bad[:, n // 2].all()) and int(bad.sum()) == m
+    s[n // 2] = 0
+    y_ref, a_ref = oracle.woq_gemm(synth.to_bits(x.contiguous()), q.cpu().numpy()[:2049], s.cpu().numpy()[:2049])
+    idx, val = binding.mxfp4_woq_gemm_argmax(x, q[:2049], s[:2049], path=REG)
+    assert_argmax_ok(idx, val, y_ref, a_ref)
+    idx, val = binding.mxfp4_woq_gemm_argmax(x, q, s, path=REG)
+    y = binding.mxfp4_woq_gemm(x, q, s, path=REG)
+    at = y.gather(1, idx.long()[:, None])[:, 0]
+    assert torch.equal(at, val.to(torch.bfloat16)) and torch.equal(at, y.max(dim=1).values)
+    if m == 1:                                              # the persistent launch walks the same rows with the same bits
+        out = torch.empty((1, n), dtype=torch.bfloat16, device=DEV)
+        binding.GemmGroup([dict(x=x.contiguous(), q=q, s=s, y=out)], chained=True, mode=binding.CHAIN_PERSISTENT).run()
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), y.view(torch.int16))
+    pairs = n - n % 2
+    bias = (torch.randn(pairs, generator=g) * 0.3).to(torch.bfloat16)
+    sub = rows[rows < pairs]
+    for act in (0, 1):
+        c = pairs // 2 if act else pairs
+        res = (torch.randn((m, c + 3), generator=g) * 0.3).to(torch.bfloat16)
+        cols = sub[::2] // 2 if act else sub
+        y_ref, a_ref = oracle.woq_gemm(synth.to_bits(x.contiguous()), q.cpu()[sub].numpy(), s.cpu()[sub].numpy())
+        out_ref, a_out = oracle.epilogue(y_ref, a_ref, synth.to_bits(bias[sub]), synth.to_bits(res[:, cols].contiguous()), act)
+        t = binding.mxfp4_woq_gemm_fused(x, q[:pairs], s[:pairs], bias=bias.to(DEV), act=act, residual=res.to(DEV)[:, :c], path=REG)
+        torch.cuda.synchronize()
+        assert_gemm_close(t[:, cols.to(DEV)], out_ref, a_out, "act %d" % act)

@@ -273,13 +273,13 @@ def test_one_and_two_rows_of_a_short_k(tmp_path):
     # one row of canonical MXFP4 weights (its bits are those of the chained launch) and picks (32 bits leave) stay
     assert not any(rules.mx(1, n, k, 0, f, 0) for n in (16, 4096, 57344) for k in (128, 1024, 4224) for f in (0, 1))
     assert not any(rules.mx(m, n, k, t, 0, 1) for m in (1, 2) for n in (16, 32000) for k in (128, 1024) for t in (0, 1))
-    for form, calls in (("mx", [(2, 28000, 512, 0, 0), (2, 4096, 2048, 0, 1), (2, 8192, 5120, 0, 0), (1, 57344, 1024, 1, 0), (1, 1000, 1024, 1, 1)]),
+    for form, calls in (("mx", [(2, 28000, 512, 0, 0), (2, 1500, 2048, 0, 1), (2, 8192, 2048, 0, 1), (2, 8192, 5120, 0, 0), (1, 57344, 1024, 1, 0), (1, 1000, 1024, 1, 1)]),
                         ("ragged", [(1, 28000, 416), (2, 8192, 11040), (2, 1500, 672)]),
                         ("format", [(2, 28000, 512, 2, 0), (1, 8192, 1024, 8, 0), (2, 8192, 8192, 6, 1), (1, 1000, 4096, 6, 1)]),
                         ("bf16", [(1, 28000, 1024), (2, 8192, 1024), (2, 3000, 384)])):
         for c in calls:
             assert getattr(rules, form)(*c, 0), (form, c)
-    for form, calls in (("mx", [(2, 28000, 4096, 0, 0), (2, 57344, 6144, 0, 0), (2, 4096, 4224, 0, 1), (1, 8192, 640, 1, 0), (2, 57344, 65536, 0, 0)]),
+    for form, calls in (("mx", [(2, 28000, 4096, 0, 0), (2, 57344, 6144, 0, 0), (2, 4096, 4224, 0, 1), (2, 4096, 2048, 0, 1), (2, 8192, 1024, 0, 0), (1, 8192, 640, 1, 0), (2, 57344, 65536, 0, 0)]),
                         ("ragged", [(1, 1000, 416), (2, 28000, 6176), (1, 22016, 1312), (2, 8192, 65504)]),
                         ("format", [(2, 2047, 11008, 2, 0), (2, 2048, 11008, 2, 0), (1, 2048, 65536, 2, 0), (1, 22016, 4096, 8, 0), (1, 976, 4096, 6, 0),
                                     (2, 4096, 24576, 6, 1), (2, 18175, 9088, 6, 0)]),
