@@ -167,8 +167,23 @@ constexpr Cut sum_cut(Kind w, int wk, int mf, int nf)
 }
 constexpr bool each_apart(Kind w, int mf) { return w == kBf16 && mf == 1; }
 
+// The activations' way into the LDS: through registers (asked for two phases ahead, written a phase ahead), or by loads that put
+// them there (kDirect: asked for a phase ahead, into the buffer that the phase before read).  The direct way saves the registers, the
+// writes and their waits, but its loads leave only when the phase's weights have arrived: the compiler counts the weights'
+// loads exactly as long as nothing younger is in flight that it does not know, and a wait too many is a whole latency.  So it is for
+// blocks whose waves all lie along the weight rows (long phases: 22016 x 4096 with the gate at 509 rows 79.1 -> 75.3 us, 13999 x 6016 at
+// 399 rows 0.93), and for calls of few phases, which are mostly start and end: 1016 x 2016 at three rows 3.72 -> 3.42, 14234 x
+// 768 at 17 4.26 -> 4.02, E3M2 1875 x 1152 at 24 3.85 -> 3.57; with nine phases and more 1.05 to 1.15 of the other way, and so are
+// many rows of blocks over few weight rows (302 x 4352 at 173 rows, five phases, 1.09; 542 x 2048 at 475 1.07) and picks (1.00 to 1.02).
+constexpr bool direct_only(Kind w, int wk) { return w != kBf16 && wk == 1; }
+constexpr bool has_direct(Kind w) { return w != kBf16; }
+inline bool takes_direct(Kind w, int wk, const Args& a)
+{
+    return a.out.part_val == nullptr && (a.k + 127) / 128 <= (w == kMxTiled ? 3 : a.tiles_m > 6 ? 2 : 6) * wk;
+}
+
 // The leading arguments are scalars that arrive in registers when a wave starts; `out` is for the end.
-template <Kind kW, int WM, int WN, int WK, int MF, int NF>
+template <Kind kW, int WM, int WN, int WK, int MF, int NF, bool kDirect>
 __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* __restrict__ x,
                                                                 const uint8_t* __restrict__ q,
                                                                 const uint8_t* __restrict__ s, int n, int k, int m,
@@ -203,19 +218,30 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
     const int m0 = tm * BM, n0 = tn * BN;
 
     const int row_bytes = kW == kBf16 ? ldw * 2 : nblk * kBlock;
-    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t*>(x + (int64_t)m0 * ldx), 0, ((min(BM, m - m0) - 1) * ldx + k) * 2, 0x00020000);
+    const uint16_t* x0 = x + (int64_t)m0 * ldx;
+    const int x_bytes = ((min(BM, m - m0) - 1) * ldx + k) * 2;
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(x0), 0, x_bytes, 0x00020000);
+    auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };     // (for inline assembly)
+    const uint64_t x_at = reinterpret_cast<uint64_t>(x0);
+    const u32x4_t rx_words = {uniform((uint32_t)x_at), uniform((uint32_t)(x_at >> 32) & 0xFFFFu), uniform((uint32_t)x_bytes), 0x00020000u};
     const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint8_t*>(q), 0, kTiled ? n_tiles * 16 * row_bytes : kW == kBf16 ? ((n - 1) * ldw + k) * 2 : n * row_bytes,
         0x00020000);
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint8_t*>(s), 0, !kScaled ? 0 : kTiled ? n_tiles * n_items * 256 : n * nblk, 0x00020000);
 
-    const int xc = tid % kRowChunks, x_row = tid / kRowChunks;             // this thread's chunk of a row, first row
+    // Through registers: this thread's chunk of a row and its first row.  Direct: load i of wave w is the (8 i + w)th KiB of a
+    // phase's buffer, four rows of one step, and a lane asks for the chunk whose place there it fills.
+    auto chunk_at = [](int c) { return c ^ (c & 4) << 1; };
+    constexpr int kRowGroups = BM / 4;
+    const int xc = kDirect ? chunk_at(li ^ ((wave & 3) * 4 + lg)) : tid % kRowChunks, x_row = tid / kRowChunks;
     int x_off[CA];
 #pragma unroll
-    for (int i = 0; i < CA; ++i)
-        x_off[i] = (min(m0 + x_row + i * kRowStep, m - 1) - m0) * ldx * 2 + xc * 16;       // ragged M: repeat the last row
+    for (int i = 0; i < CA; ++i) {
+        const int row = kDirect ? (i * 8 + wave) % kRowGroups * 4 + lg : x_row + i * kRowStep;
+        x_off[i] = (min(m0 + row, m - 1) - m0) * ldx * 2 + xc * 16;                     // ragged M: repeat the last row
+    }
+    const uint32_t lds_at = (uint32_t)reinterpret_cast<uint64_t>((__attribute__((address_space(3))) uint8_t*)smem) + wave * 1024;
     int q_off[NF], s_off[NF];
 #pragma unroll
     for (int f = 0; f < NF; ++f) {                                      // ragged N: repeat the last row (or tile)
@@ -264,6 +290,17 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
             xr[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, x_off[i] | x_past, x_at, 0);
         ++ld_x;
     };
+    auto issue_direct = [&](int u, int b) {
+#pragma unroll
+        for (int i = 0; i < CA; ++i) {
+            const int T = u * WK + (i * 8 + wave) / kRowGroups;
+            const int off = x_off[i] | (kRagged ? past((k >> 3) - 1, T * 16 + xc) : T < steps ? 0 : kOob);
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(
+                             lds_at + (b * kBuf * 16 + i * 8192)),
+                         "v"(off), "s"(rx_words), "s"(T < steps ? T * 256 : 0)
+                         : "memory");
+        }
+    };
     auto issue_q = [&](Slot& sl) {
         const int step = ld_q * WK + wk, T = step < steps ? step : 0;
         const int q_past = past(nblk - 1, 4 * step + lg);
@@ -302,7 +339,6 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
         }
         ++ld_q;
     };
-    auto chunk_at = [](int c) { return c ^ (c & 4) << 1; };
     auto x_store = [&](int b) {
 #pragma unroll
         for (int i = 0; i < CA; ++i) {
@@ -310,17 +346,26 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
             xs[b * kBuf + ((xc >> 4) * BM + r) * 16 + (chunk_at(xc & 15) ^ (r & 15))] = xr[i];
         }
     };
+    // The loads of one phase's weights: direct, the only ones that stay in flight across a barrier.
+    constexpr int kQueued = NF * (kRagged ? 2 : kW == kBf16 ? 4 : kBits == 8 || kBits == 6 ? 2 : 1);
     issue_scales(0);
-    issue_x();
+    if constexpr (kDirect)
+        issue_direct(0, 0);
+    else
+        issue_x();
     __builtin_amdgcn_sched_barrier(0);                                  // keep the loads in this order
     issue_q(buf[0]);
     __builtin_amdgcn_sched_barrier(0);
     store_scales(0);
-    x_store(0);
-    issue_x();
+    if constexpr (!kDirect) {
+        x_store(0);
+        issue_x();
+    }
     __builtin_amdgcn_sched_barrier(0);
     issue_q(buf[1]);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kDirect)                                              // at most the weights of both phases are younger
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kQueued) : "memory");
     lds_barrier();
 
     constexpr Cut kCut = sum_cut(kW, WK, MF, NF);
@@ -364,13 +409,22 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
         for (int d = 0; d < 2; ++d) {
             const Slot& sl = buf[d];
             // the next phase's activations go to the buffer that the phase before this one read, beside this
-            // phase's reads and matrix instructions; the ones after them are asked for
-            x_store(1 - d);
+            // phase's reads and matrix instructions; the ones after them are asked for (or the next phase's, directly)
+            if constexpr (kDirect) {
+#pragma unroll
+                for (int f = 0; f < NF; ++f)                            // this phase's weights are waited for first
+                    asm volatile("" : "+v"(buf[d].q[f][kBits - 1]));
+            } else {
+                x_store(1 - d);
+            }
             if (d == 1)
                 store_scales(((u0 >> 1) + 1) & 1);
             if (d == 0)
                 issue_scales((u0 >> 1) + 1);
-            issue_x();
+            if constexpr (kDirect)
+                issue_direct(u0 + d + 1, 1 - d);
+            else
+                issue_x();
             __builtin_amdgcn_sched_barrier(0);
             if ((u0 + d) * WK + wk < steps) {
                 const u32x4_t* xb = xs + d * kBuf + x_read;
@@ -479,6 +533,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
                     end_chain();
             }
             issue_q(buf[d]);
+            if constexpr (kDirect) {
+                __builtin_amdgcn_sched_barrier(0);
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kQueued) : "memory");      // the activations; younger are the weights just asked for
+            }
             lds_barrier();
         }
     }
@@ -585,16 +643,28 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
     }
 }
 
-template <Kind kW, int WM, int WN, int WK, int MF, int NF>
-hipError_t launch_block(const Args& a, const DeviceInfo& dev, hipStream_t stream)
+template <Kind kW, int WM, int WN, int WK, int MF, int NF, bool kDirect>
+hipError_t launch_way(const Args& a, const DeviceInfo& dev, hipStream_t stream)
 {
-    auto kern = gemm_wide_kernel<kW, WM, WN, WK, MF, NF>;
+    auto kern = gemm_wide_kernel<kW, WM, WN, WK, MF, NF, kDirect>;
     static LdsLimit lds_limit;                      // of this kernel instance
     if (hipError_t e = lds_limit.raise(reinterpret_cast<const void*>(kern), dev.lds_bytes); e != hipSuccess)
         return e;
     hipLaunchKernelGGL(kern, dim3(a.tiles_m * a.tiles_n), dim3(kThreads), lds_bytes(kW, WM, WN, WK, MF, NF), stream, a.x, a.q,
                        a.s, a.n, a.k, a.m, a.ldx, a.ldw, a.tiles_m, a.tiles_n, a.chains, a.out);
     return hipGetLastError();
+}
+template <Kind kW, int WM, int WN, int WK, int MF, int NF>
+hipError_t launch_block(const Args& a, const DeviceInfo& dev, hipStream_t stream)
+{
+    if constexpr (direct_only(kW, WK)) {
+        return launch_way<kW, WM, WN, WK, MF, NF, true>(a, dev, stream);
+    } else {
+        if constexpr (has_direct(kW))
+            if (takes_direct(kW, WK, a))
+                return launch_way<kW, WM, WN, WK, MF, NF, true>(a, dev, stream);
+        return launch_way<kW, WM, WN, WK, MF, NF, false>(a, dev, stream);
+    }
 }
 
 // A block shape with what it took, in microseconds: the first block of a compute unit and every further one
