@@ -49,13 +49,18 @@ _MX, _E4M3, _E2M3, _BF16, _TILED, _FMT = 0, 1, 2, 3, 4, 16
 
 
 def _product(*args):
-    load()                                          # (puts the extension's functions in the place of these two)
+    load()                                          # (puts the extension's functions in the place of these three)
     return _product(*args)
 
 
 def _verify(*args):
     load()
     return _verify(*args)
+
+
+def _cast(w):
+    load()
+    return _cast(w)
 
 
 class GemmDesc(ctypes.Structure):
@@ -85,7 +90,7 @@ class Mxfp4Error(RuntimeError):
 
 def load() -> ctypes.CDLL:
     """Load the HIP library (torch first, so that both share one HIP runtime)."""
-    global _lib, _product, _verify
+    global _lib, _product, _verify, _cast
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -192,13 +197,13 @@ def load() -> ctypes.CDLL:
         getattr(lib, name).restype = i32
     lib.mxfp4_last_error.restype = ctypes.c_char_p
     lib.mxfp4_version.restype = ctypes.c_char_p
-    _product, _verify = _host_calls()
+    _product, _verify, _cast = _host_calls()
     _lib = lib
     return lib
 
 
 def _host_calls():
-    """The two calls of the extension module.  Without it, or with one that was built for another torch, every call takes
+    """The calls of the extension module.  Without it, or with one that was built for another torch, every call takes
     the checks here, which reach the same kernels with more host time."""
     try:
         from . import _host
@@ -207,9 +212,9 @@ def _host_calls():
     except ImportError as e:
         warnings.warn("the extension module _host cannot be used (%s): calls go through ctypes, which takes more host time; "
                       "build it with `python -m paper_2503_13565_amd.build`" % e, RuntimeWarning, stacklevel=3)
-        return (lambda *args: None,) * 2
+        return (lambda *args: None,) * 3
     _host.on_failure(_check)
-    return _host.product, _host.verify
+    return _host.product, _host.verify, _host.cast
 
 
 def _check(rc: int) -> None:
@@ -220,7 +225,7 @@ def _check(rc: int) -> None:
 # What surrounds a call costs more host time than the call's checks and as much as its launch, and most of the
 # products here are shorter on the device than that.  So addresses go to ctypes as plain integers, the stream is
 # asked for as the integer it is, and the device is switched only where another one is current (one product
-# 10.9 -> 6.9 us of host time; through the extension module 3.5).
+# 10.9 -> 6.9 us of host time; through the extension module 3.4).
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
 _stay = contextlib.nullcontext()
@@ -254,6 +259,10 @@ def mxfp4_direct_cast(w: torch.Tensor, q: Optional[torch.Tensor] = None,
                       ) -> Tuple[torch.Tensor, torch.Tensor]:
     """BF16 ``[N,K]`` (last dim contiguous) -> (q uint8 ``[N,K/2]``, s uint8 ``[N,K/32]``).
     ``integer_rule`` calls ``mxfp4_direct_cast_bits``."""
+    if q is None and s is None and not integer_rule:
+        pair = _cast(w)
+        if pair is not None:
+            return pair
     _dev(w)
     if w.dtype != torch.bfloat16 or w.dim() != 2 or w.stride(1) != 1:
         raise ValueError("w must be a 2-D BF16 tensor with a contiguous last dimension")

@@ -70,7 +70,7 @@ def _link_host(obj: str, verbose: bool) -> None:
     """Linked against the library beside it, which the binding has loaded by then."""
     tmp, at = HOST + ".tmp.%d" % os.getpid(), os.path.join(os.path.dirname(torch.__file__), "lib")
     cmd = ["g++", "-shared", "-o", tmp, obj, "-L" + HERE, "-l:" + os.path.basename(LIB), "-L" + at, "-ltorch_python",
-           "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+           "-ltorch_cpu", "-ltorch_hip", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)

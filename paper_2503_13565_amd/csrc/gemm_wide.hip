@@ -62,7 +62,7 @@ hipError_t launch_gemm_wide(const GemmArgs& a, const DeviceInfo& dev, int* parts
     if (!gemm_wide_can_run(a, dev) || (tiled && a.k % 128 != 0))
         return hipErrorInvalidValue;
     Args w{a.x, a.q, a.s, a.n, a.k, a.m, (int)a.ldx, 0, 0, 0, 0, block_out(a, epi)};
-    const int c = pick_shape(kCosts, std::size(kCosts), a.m, a.n, a.k, dev.cus, a.part_val ? a.parts : 0x7FFFFFFF, 4, &w);
+    const int c = pick_shape<kCosts, 4>(a.m, a.n, a.k, dev.cus, a.part_val ? a.parts : 0x7FFFFFFF, &w);
     if (c < 0)
         return hipErrorInvalidValue;
     if (parts_used)

@@ -45,7 +45,7 @@ hipError_t launch_gemm_wide_bf16(const Bf16Args& a, const DeviceInfo& dev, int* 
         return hipErrorInvalidValue;
     Args w{a.x, reinterpret_cast<const uint8_t*>(a.w), nullptr, a.n, a.k, a.m, (int)a.ldx, (int)a.ldw, 0, 0, 0,
            BlockOut{a.y, a.ldy, a.part_val, a.part_idx, nullptr, nullptr, a.n, a.m, a.parts, 0, 0}};
-    const int c = pick_shape(kCosts, std::size(kCosts), a.m, a.n, a.k, dev.cus, a.part_val ? a.parts : 0x7FFFFFFF, 16, &w);
+    const int c = pick_shape<kCosts, 16>(a.m, a.n, a.k, dev.cus, a.part_val ? a.parts : 0x7FFFFFFF, &w);
     if (c < 0)
         return hipErrorInvalidValue;
     if (parts_used)

@@ -87,10 +87,10 @@ hipError_t launch_gemm_wide_fmt(int code, const GemmArgs& a, const DeviceInfo& d
     if (kind < 0)
         return hipErrorInvalidValue;
     Args w{a.x, a.q, a.s, a.n, a.k, a.m, (int)a.ldx, 0, 0, 0, 0, block_out(a, nullptr)};
-    const Cost* costs = kind < 2 ? kCosts8 : kind < 4 ? kCosts6 : kCosts2;
-    const size_t count = kind < 2 ? std::size(kCosts8) : kind < 4 ? std::size(kCosts6) : std::size(kCosts2);
-    const int c = pick_shape(costs, count, a.m, a.n, a.k, dev.cus, a.part_val ? a.parts : 0x7FFFFFFF,
-                             kind < 2 ? 8 : kind < 4 ? 6 : 2, &w);
+    const int cols = a.part_val ? a.parts : 0x7FFFFFFF;
+    const int c = kind < 2   ? pick_shape<kCosts8, 8>(a.m, a.n, a.k, dev.cus, cols, &w)
+                  : kind < 4 ? pick_shape<kCosts6, 6>(a.m, a.n, a.k, dev.cus, cols, &w)
+                             : pick_shape<kCosts2, 2>(a.m, a.n, a.k, dev.cus, cols, &w);
     if (c < 0)
         return hipErrorInvalidValue;
     if (parts_used)

@@ -2,14 +2,17 @@
 // device that pass every check of binding.py.  Anything else (another device, a subclass, an active mode, a shape or a type that does
 // not fit) returns None, and the binding's own checks and messages take the call.
 //
-// What bounds it: products of one to eight rows of a matrix of 2 to 30 MB run 3.5 to 11 us on the device, and the checks, the allocation and the
-// marshalling of the Python form took longer than the launch.  us of host time per call, Python form -> here: one row 6.9 ->
-// 3.5, fused 7.7 -> 3.7, BF16 weights 7.0 -> 4.0, tile-major 6.9 -> 3.6, verification (two launches) 14.2 -> 7.3.
+// What bounds it: products of one to eight rows of a matrix of 2 to 30 MB run 3.5 to 11 us on the device, and the checks, the
+// allocation and the marshalling of the Python form took longer than the launch (2.4 us of a call's host time here).  us of host
+// time per call, Python form -> here: one row 6.9 -> 3.5, fused 7.7 -> 3.8, BF16 weights 7.0 -> 3.7, tile-major 6.9 -> 3.6,
+// verification (two launches) 14.2 -> 7.6, a cast (two outputs) 7.5 -> 4.4.
 #include <ATen/ATen.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <ATen/PythonTorchFunctionTLS.h>
+#include <ATen/hip/EmptyTensor.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -104,6 +107,17 @@ bool operands(PyObject* const* args, int* kind, Operands* o)
     return true;
 }
 
+// A new tensor on the device: from the allocator behind torch.empty, without the way through the dispatcher, unless something on this
+// thread wants to see it there (a transform; autocast and the keys that every thread has do not).  One row of
+// 4096 x 4096, which the host bounds: 4.35 -> 4.17 us from call to call.
+at::Tensor fresh(at::IntArrayRef size, at::ScalarType type, c10::Device device)
+{
+    static const uint64_t usual = (c10::default_included_set | c10::autocast_dispatch_keyset).raw_repr();
+    if ((c10::impl::tls_local_dispatch_key_set().included_.raw_repr() & ~usual) != 0)
+        return at::empty(size, at::TensorOptions().dtype(type).device(device));
+    return at::Tensor(at::detail::empty_cuda(size, type, device, std::nullopt));
+}
+
 // What the binding's own checks take over: also a number that is none or too large, whose error they raise in their words.
 PyObject* left()
 {
@@ -164,6 +178,7 @@ PyObject* wrap_list(const at::Tensor* t, int count)
 }
 
 PyObject* wrap_three(const at::Tensor* t) { return wrap_list(t, 3); }
+PyObject* wrap_two(const at::Tensor* t) { return wrap_list(t, 2); }
 
 // product(kind, x, q, s, n, k, fused, bias, act, residual, path, workspace) -> y, or None
 PyObject* product(PyObject*, PyObject* const* args, Py_ssize_t count)
@@ -202,7 +217,7 @@ PyObject* product(PyObject*, PyObject* const* args, Py_ssize_t count)
     int rc;
     {
         pybind11::gil_scoped_release no_gil;
-        y = at::empty({o.m, c}, at::TensorOptions().dtype(at::kBFloat16).device(o.device));
+        y = fresh({o.m, c}, at::kBFloat16, o.device);
         void* out = y.data_ptr();
         if (kind == kTiled)
             rc = fused ? mxfp4_woq_gemm_tiled_fused(o.x, o.m, o.ldx, o.q, o.s, o.n, o.k, bias, act, residual, ldr, out, c, o.stream)
@@ -253,10 +268,9 @@ PyObject* verify(PyObject*, PyObject* const* args, Py_ssize_t count)
     int rc;
     {
         pybind11::gil_scoped_release no_gil;
-        const auto ints = at::TensorOptions().dtype(at::kInt).device(o.device);
-        out[0] = at::empty({2}, ints);
-        out[1] = at::empty({o.m}, ints);
-        out[2] = at::empty({o.m}, ints.dtype(at::kFloat));
+        out[0] = fresh({2}, at::kInt, o.device);
+        out[1] = fresh({o.m}, at::kInt, o.device);
+        out[2] = fresh({o.m}, at::kFloat, o.device);
         void *accept = out[0].data_ptr(), *index = out[1].data_ptr(), *value = out[2].data_ptr();
         if (kind == kBf16)
             rc = mxfp4_bf16_gemm_verify(o.x, o.m, o.ldx, o.q, o.n, o.k, o.ldw, (const int32_t*)draft, (int32_t*)accept,
@@ -267,6 +281,32 @@ PyObject* verify(PyObject*, PyObject* const* args, Py_ssize_t count)
                 ws.at, ws.bytes, o.stream);
     }
     return finish(rc, wrap_three, out);
+    END_HANDLE_TH_ERRORS
+}
+
+// cast(w) -> (q, s), or None: BF16 weights to MXFP4
+PyObject* cast(PyObject*, PyObject* w_object)
+{
+    HANDLE_TH_ERRORS
+    if (at::impl::torch_function_mode_enabled() || c10::impl::TorchDispatchModeTLS::any_modes_set() ||
+        !THPVariable_CheckExact(w_object) || !THPVariable_Unpack(w_object).is_cuda())
+        return left();
+    const c10::DeviceIndex at = c10::hip::current_device();
+    const c10::Device device(c10::kCUDA, at);
+    const at::Tensor* w = rows_of(w_object, device);
+    if (!w || w->size(0) < 1 || w->size(1) < 32 || w->size(1) % 32 != 0)
+        return left();
+    const int64_t n = w->size(0), k = w->size(1);
+    at::Tensor out[2];
+    int rc;
+    {
+        pybind11::gil_scoped_release no_gil;
+        out[0] = fresh({n, k / 2}, at::kByte, device);
+        out[1] = fresh({n, k / 32}, at::kByte, device);
+        rc = mxfp4_direct_cast(w->data_ptr(), n, k, n > 1 ? w->stride(0) : k, out[0].data_ptr(), out[1].data_ptr(),
+                               c10::hip::getCurrentHIPStream(at).stream());
+    }
+    return finish(rc, wrap_two, out);
     END_HANDLE_TH_ERRORS
 }
 
@@ -281,6 +321,7 @@ PyObject* on_failure(PyObject*, PyObject* f)
 PyMethodDef kMethods[] = {
     {"product", (PyCFunction)(void (*)(void))product, METH_FASTCALL, nullptr},
     {"verify", (PyCFunction)(void (*)(void))verify, METH_FASTCALL, nullptr},
+    {"cast", cast, METH_O, nullptr},
     {"on_failure", on_failure, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };

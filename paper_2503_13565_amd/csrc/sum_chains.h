@@ -57,14 +57,18 @@ constexpr int chain_pairs(int phases, int wk, int chains)
 // Whether a call may take a shape.  A block that cannot cut its sums is there for the largest products alone, where its outputs
 // fill their rounds over the units to 85 %: there it is the fastest by a tenth (22016 x 4096 at 509 rows 78 us,
 // 89 in blocks that do).
-constexpr bool cuts_enough(int bits, int wm, int wn, int wk, int mf, int nf, int m, int n, int k, int cus)
+constexpr bool cuts_enough(int bits, int wm, int wn, int wk, int mf, int nf, int m, int n, int k, int cus, int wanted)
 {
-    const int wanted = chains_wanted(m, n, k, cus);
     if (chains_of(bits, wk, mf, nf, (k + 127) / 128) >= wanted)
         return true;
+    if (!uncut(mf, nf) || m <= 32 || tiles_of(m, n) <= 28 * (int64_t)cus)
+        return false;
     const int64_t bm = 16 * wm * mf, bn = 16 * wn * nf, blocks = ((m + bm - 1) / bm) * ((n + bn - 1) / bn);
-    return uncut(mf, nf) && m > 32 && tiles_of(m, n) > 28 * (int64_t)cus &&
-           (int64_t)m * n * 100 >= 85 * bm * bn * ((blocks + cus - 1) / cus * cus);
+    return (int64_t)m * n * 100 >= 85 * bm * bn * ((blocks + cus - 1) / cus * cus);
+}
+constexpr bool cuts_enough(int bits, int wm, int wn, int wk, int mf, int nf, int m, int n, int k, int cus)
+{
+    return cuts_enough(bits, wm, wn, wk, mf, nf, m, n, k, cus, chains_wanted(m, n, k, cus));
 }
 
 }  // namespace wide

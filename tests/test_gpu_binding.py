@@ -139,6 +139,47 @@ def test_numbers_that_do_not_fit_are_answered_as_before():
         assert B._product(0, x, q, s, 0, 0, True, None, act, None, 0, None) is None
 
 
+@pytest.mark.parametrize("what", ["whole", "one", "wide", "grad", "inference", "dtype", "stride", "dims", "host", "subclass", "block"])
+def test_casts(what, monkeypatch):
+    w = synth.weights_student_t(1 if what == "one" else 37, 96, seed=3, device=DEV)
+    if what == "wide":                              # rows further apart than they are long
+        w = torch.cat([w, w], 1)[:, :96]
+    elif what == "grad":
+        w = torch.nn.Parameter(w)
+    elif what == "dtype":
+        w = w.float()
+    elif what == "stride":
+        w = w.t().contiguous().t()
+    elif what == "dims":
+        w = w[None]
+    elif what == "host":
+        w = w.cpu()
+    elif what == "subclass":
+        w = w.as_subclass(type("Named", (torch.Tensor,), {}))
+    elif what == "block":
+        w = w[:, :80].contiguous()
+
+    def answer():
+        try:
+            with torch.inference_mode(what == "inference"):
+                return B.mxfp4_direct_cast(w)
+        except (ValueError, B.Mxfp4Error) as e:
+            return type(e), str(e)
+
+    B.load()
+    assert (B._cast(w) is not None) == (what in ("whole", "one", "wide", "grad", "inference"))
+    got = answer()
+    with torch.device("cpu"):                       # an active mode: the binding's own way
+        assert B._cast(w) is None
+    monkeypatch.setattr(B, "_cast", lambda w: None)
+    for a, b in zip(got, answer(), strict=True):
+        if isinstance(a, torch.Tensor):
+            assert a.dtype == b.dtype and a.shape == b.shape and a.stride() == b.stride() and not a.requires_grad
+            assert a.is_inference() == b.is_inference() and torch.equal(a, b)
+        else:
+            assert a == b
+
+
 def test_a_status_raises_the_error_of_the_library():
     x, _, q, s = _inputs(4, 2048, 512)
     with pytest.raises(B.Mxfp4Error) as e:
