@@ -241,15 +241,7 @@ __device__ __forceinline__ void pick_rows(const BlockOut& a, const float* tile, 
                 idx = n0 + c;
             }
         }
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) {
-            const float v = __shfl_xor(best, off);
-            const int o = __shfl_xor(idx, off);
-            if (v > best || (v == best && o < idx)) {
-                best = v;
-                idx = o;
-            }
-        }
+        best_of_16(&best, &idx);
         const int row = row_of(r);
         if ((threadIdx.x & 15) == 0 && row < a.m) {
             a.part_val[(int64_t)row * a.parts + part] = best;

@@ -67,9 +67,47 @@ __device__ __forceinline__ float wave_sum(float v)
     v += dpp_f32<0x4E>(v);    // quad_perm [2,3,0,1]
     v += dpp_f32<0x141>(v);   // row_half_mirror
     v += dpp_f32<0x140>(v);   // row_mirror: all 16 lanes of a row now hold the row's sum
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
-    return v;
+    auto pair = __builtin_amdgcn_permlane16_swap(__float_as_int(v), __float_as_int(v), false, false);   // rows 0 0 2 2, 1 1 3 3
+    v = __int_as_float(pair[0]) + __int_as_float(pair[1]);
+    pair = __builtin_amdgcn_permlane32_swap(__float_as_int(v), __float_as_int(v), false, false);       // lower half, upper half
+    return __int_as_float(pair[0]) + __int_as_float(pair[1]);
+}
+
+// The better of two candidates in (value descending, index ascending) order; a NaN is never taken.
+__device__ __forceinline__ void take_better(float v, int i, float* best, int* idx)
+{
+    if (v > *best || (v == *best && i < *idx)) {
+        *best = v;
+        *idx = i;
+    }
+}
+template <int kCtrl>
+__device__ __forceinline__ void dpp_better(float* best, int* idx)
+{
+    take_better(dpp_f32<kCtrl>(*best), __builtin_amdgcn_update_dpp(0, *idx, kCtrl, 0xF, 0xF, false), best, idx);
+}
+// The best candidate of each sixteen lanes, in all of them.  In the vector unit: the two launches of a pick end in one chain of such
+// steps each, and through the LDS crossbar every step waits for its answer.
+__device__ __forceinline__ void best_of_16(float* best, int* idx)
+{
+    dpp_better<0xB1>(best, idx);
+    dpp_better<0x4E>(best, idx);
+    dpp_better<0x141>(best, idx);
+    dpp_better<0x140>(best, idx);
+}
+__device__ __forceinline__ void best_of_64(float* best, int* idx)
+{
+    best_of_16(best, idx);
+    auto v = __builtin_amdgcn_permlane16_swap(__float_as_int(*best), __float_as_int(*best), false, false);
+    auto i = __builtin_amdgcn_permlane16_swap(*idx, *idx, false, false);     // rows 0 0 2 2 and rows 1 1 3 3
+    *best = __int_as_float(v[0]);
+    *idx = i[0];
+    take_better(__int_as_float(v[1]), i[1], best, idx);
+    v = __builtin_amdgcn_permlane32_swap(__float_as_int(*best), __float_as_int(*best), false, false);
+    i = __builtin_amdgcn_permlane32_swap(*idx, *idx, false, false);          // the lower half twice, the upper half twice
+    *best = __int_as_float(v[0]);
+    *idx = i[0];
+    take_better(__int_as_float(v[1]), i[1], best, idx);
 }
 
 // Workgroup barrier that waits for LDS traffic only.  __syncthreads() would also drain the

@@ -97,3 +97,29 @@ def test_verify_errors():
     assert lib.mxfp4_woq_gemm_verify(*args, None, out.data_ptr(), out.data_ptr(), None, ws.data_ptr(), ws.numel(), 0) == 1
     assert lib.mxfp4_woq_gemm_verify(*args, out.data_ptr(), None, out.data_ptr(), None, ws.data_ptr(), ws.numel(), 0) == 1
     assert lib.mxfp4_woq_gemm_verify(*args, out.data_ptr(), out.data_ptr(), out.data_ptr(), None, None, 0, 0) == 4
+
+
+@pytest.mark.parametrize("n", [16, 128, 520, 2048, 34000])
+@pytest.mark.parametrize("m", [1, 2, 3, 17, 40])
+def test_equal_best_values_give_the_lowest_index(m, n):
+    """Whole numbers, exact in every kernel: two equal best columns far apart and next to each other, in every stage of
+    the reduction, and rows without any."""
+    k = 128
+    gen = torch.Generator().manual_seed(m * n)
+    w = torch.zeros((n, k), dtype=torch.bfloat16)
+    x = torch.zeros((m, k), dtype=torch.bfloat16)
+    want = []
+    for r in range(m):
+        a, b = torch.randint(0, n, (2,), generator=gen).tolist()
+        b = b if r % 3 else min(a + 1, n - 1)
+        if r % 5 != 4:                                    # (row 4: all sums are zero)
+            x[r, r] = 2.0
+            w[a, r] = w[b, r] = 4.0
+        want.append(min(a, b) if r % 5 != 4 else 0)
+    q, s = binding.mxfp4_direct_cast(w.to(DEV))
+    draft = torch.tensor(want[:-1], dtype=torch.int32, device=DEV)
+    for accept, idx, val in (binding.mxfp4_woq_gemm_verify(x.to(DEV), q, s, draft), binding.mxfp4_bf16_gemm_verify(x.to(DEV), w.to(DEV), draft)):
+        assert idx.tolist() == want and accept.tolist() == [m - 1, want[-1]]
+        assert val.tolist() == [0.0 if r % 5 == 4 else 8.0 for r in range(m)]
+    idx, val = binding.mxfp4_woq_gemm_argmax(x.to(DEV), q, s)
+    assert idx.tolist() == want
