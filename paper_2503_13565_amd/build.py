@@ -24,9 +24,10 @@ SOURCES = ["api.hip", "cast.hip", "gemv.hip", "gemv_reg.hip", "gemv_short.hip", 
 # packed FP32 instructions are disabled on purpose: see the build notes of this project
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-# per file: the leading scalar kernel arguments arrive in scalar registers when a wave starts
+# per file: the leading scalar kernel arguments arrive in scalar registers when a wave starts (a cast of 735 x 640 2.79 -> 2.52 us,
+# 4008 x 4096 8.2 -> 8.0, 10422 x 7936 36.0 -> 35.9)
 PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
-EXTRA = {"gemv_reg.hip": PRELOAD, "gemv_short.hip": PRELOAD, "gemv_tile.hip": PRELOAD, "chain.hip": PRELOAD, "mfma_tile.hip": PRELOAD, "gemv.hip": PRELOAD, "bf16.hip": PRELOAD, "gemm_wide.hip": PRELOAD, "gemm_wide_fmt.hip": PRELOAD, "gemm_wide_bf16.hip": PRELOAD}
+EXTRA = {"gemv_reg.hip": PRELOAD, "gemv_short.hip": PRELOAD, "gemv_tile.hip": PRELOAD, "chain.hip": PRELOAD, "mfma_tile.hip": PRELOAD, "gemv.hip": PRELOAD, "e4m3.hip": PRELOAD, "e2m3.hip": PRELOAD, "mxfmt.hip": PRELOAD, "cast.hip": PRELOAD, "bf16.hip": PRELOAD, "gemm_wide.hip": PRELOAD, "gemm_wide_fmt.hip": PRELOAD, "gemm_wide_bf16.hip": PRELOAD}
 
 
 def _hipcc() -> str:

@@ -29,6 +29,16 @@ struct GemmArgs {
     int phase_steps;
 };
 
+// What mxfmt.hip's product kernels write, apart from their leading arguments: those are scalars, in registers when a wave starts.
+struct GemvOut {
+    uint16_t* y;
+    int64_t ldy;
+    float* part_val;
+    int32_t* part_idx;
+    int parts;
+};
+inline GemvOut gemv_out(const GemmArgs& a) { return {a.y, a.ldy, a.part_val, a.part_idx, a.parts}; }
+
 // What is fused behind the contraction (see mxfp4_woq_gemm_fused in include/mxfp4.h):
 // z = product + bias[n]; gated: t[c] = silu(z[2c]) * z[2c + 1] (C = N / 2 outputs per row),
 // else t = z; y = t + residual[m][c].  y then has C columns.
