@@ -582,6 +582,18 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
             if (out.part_val != nullptr) {
                 fill();
                 pick_rows<WM * PF * 16, BN, kStride>(out, tile, n0, tn, row_of);
+            } else if (MF * NF < 8 && out.residual && !rows_aligned(out.residual, out.ldr)) {
+                // Small blocks, several on a unit: they hide each other's slow loads, and pieces on the residual's boundaries (one more to a
+                // row, their sums shifted) cost more: 18577 x 256 at 64 rows 6.25 us with those, 4.62; 32011 x 512 at 141 rows 18.2, 13.4.
+                fill();
+                BlockOut rest = out;
+                rest.bias = nullptr;                                   // (is in the sums)
+                for (int e = tid; e < WM * PF * 16 * (BN / 8); e += kThreads) {
+                    const int r = e / (BN / 8), c = e % (BN / 8) * 8;
+                    float sums[8];
+                    row_floats<8, BN>(tile + r * kStride, c, true, sums);
+                    emit_sums(rest, sums, row_of(r), n0 + c);
+                }
             } else {
                 emit_rows<WM * PF * 16, BN, kStride>(out, tile, n0, row_of, fill);
             }

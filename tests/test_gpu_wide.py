@@ -87,7 +87,7 @@ def test_largest_blocks(m, n, k):
     assert_gemm_close(gated[:, even.to(DEV) // 2], out_ref, a_out, tag)
 
 
-@pytest.mark.parametrize("m,n,k,act", [(20, 131, 160, 0), (75, 17661, 128, 0), (75, 9002, 128, 1), (327, 12967, 128, 0), (130, 9002, 256, 1),
+@pytest.mark.parametrize("m,n,k,act", [(20, 131, 160, 0), (75, 17661, 128, 0), (75, 9002, 128, 1), (327, 12967, 128, 0), (130, 9002, 256, 1), (64, 18577, 256, 0), (100, 19938, 256, 1),
                                        (509, 22015, 1024, 0), (509, 22018, 1024, 1)])
 @pytest.mark.parametrize("shift,pad", [(0, 0), (1, 0), (6, 3), (3, 8)])
 def test_residual_rows_on_any_boundary(m, n, k, act, shift, pad):
