@@ -225,7 +225,7 @@ def _check(rc: int) -> None:
 # What surrounds a call costs more host time than the call's checks and as much as its launch, and most of the
 # products here are shorter on the device than that.  So addresses go to ctypes as plain integers, the stream is
 # asked for as the integer it is, and the device is switched only where another one is current (one product
-# 10.9 -> 6.9 us of host time; through the extension module 3.4).
+# 10.9 -> 6.9 us of host time; through the extension module 3.5).
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
 _stay = contextlib.nullcontext()
