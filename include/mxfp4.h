@@ -63,8 +63,8 @@ enum {
 /* Kernel families the dispatcher can be forced to (tests and measurements); AUTO picks by M:
  * one or two rows take VALU_REG when the shape allows it, else VALU_CVT; three or more take MFMA or, where it is faster
  * (many rows, rows that do not fit the LDS whole, a K that is no multiple of 128), blocks of rows that walk K once
- * (a family that cannot be forced); so do products of two rows, and of one on tile-major weights or a K that is no
- * multiple of 128, where K is short. */
+ * (a family that cannot be forced).  A product and its pick (argmax, verify) of one or two rows are of one family at every size:
+ * the pick is the largest of the FP32 sums that the product rounds. */
 enum {
     MXFP4_PATH_AUTO = 0,
     MXFP4_PATH_VALU_BITS = 1, /* wave-per-row GEMV, nibbles decoded with plain integer/FP32 ops  */

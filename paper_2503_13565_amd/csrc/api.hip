@@ -111,12 +111,9 @@ static bool blocks_preferred(const GemmArgs& a, const DeviceInfo& dev, bool tile
     const char* from = knob("MXFP4_WIDE_FROM");                      // measurement only
     if (from)
         return a.m >= atoi(from);
-    const bool pick = a.part_val != nullptr;
     if (a.k % 128 != 0)
-        return a.m < 3 ? !pick && wide_decode_ragged_preferred(a.m, a.n, a.k, dev.cus)
-                       : wide_ragged_preferred(a.m, a.n, a.k, dev.cus, dev.lds_bytes);
-    const TileCall c = {a.m, a.n, a.k, dev.cus, mfma_tile_can_run(a, dev), split, tiled, fused, pick};
-    return a.m < 3 ? wide_decode_preferred(c) : wide_preferred(c);
+        return wide_ragged_preferred(a.m, a.n, a.k, dev.cus, dev.lds_bytes);
+    return wide_preferred({a.m, a.n, a.k, dev.cus, mfma_tile_can_run(a, dev), split, tiled, fused, a.part_val != nullptr});
 }
 
 // AUTO: the vector-ALU GEMV for one or two activation rows (its register-resident form when the
@@ -256,14 +253,13 @@ static int run_gemm(const void* x, int64_t M, int64_t ldx, const void* q, const 
             return !e || atoi(e) != 0;
         }();
         const bool split = splitk_ws && mfma_tiled_split_can_run(a, dev);
-        const bool decode = tiled_decode && !epi && gemv_tile_can_run(a, dev) && (a.m == 1 || !mfma_tile_can_run(a, dev));
-        if (gemm_wide_can_run(a, dev) && blocks_preferred(a, dev, true, split, epi != nullptr) &&
-            (decode || mfma_tile_can_run(a, dev) || split || (!epi && mfma_tile_phased_preferred(a, dev, false)))) {
-            if (go)
-                e = launch_gemm_wide(a, dev, &parts_used, st, true, epi);
-        } else if (decode) {
+        if (tiled_decode && !epi && gemv_tile_can_run(a, dev) && (a.m == 1 || !mfma_tile_can_run(a, dev))) {
             if (go)
                 e = launch_gemv_tile(a, dev, &parts_used, st);
+        } else if (gemm_wide_can_run(a, dev) && blocks_preferred(a, dev, true, split, epi != nullptr) &&
+                   (mfma_tile_can_run(a, dev) || split || (!epi && mfma_tile_phased_preferred(a, dev, false)))) {
+            if (go)
+                e = launch_gemm_wide(a, dev, &parts_used, st, true, epi);
         } else if (mfma_tile_can_run(a, dev)) {
             if (go)
                 e = launch_mfma_tile(a, dev, &parts_used, st, true, epi);
@@ -335,9 +331,7 @@ static bool fmt_blocks_preferred(const GemmArgs& a, const DeviceInfo& dev, int c
     if (from)
         return a.m >= atoi(from);
     const int bits = code == 24 ? 8 : code == 22 ? 6 : code;
-    if (a.m < 3)
-        return a.part_val == nullptr && wide_decode_format_preferred(a.m, a.n, a.k, bits, code == 6, dev.cus);
-    return wide_format_preferred(a.m, a.n, a.k, bits, mfma_tile_can_run(a, dev), dev.cus, dev.lds_bytes);
+    return wide_format_preferred(a.m, a.n, a.k, bits, code == 6, mfma_tile_can_run(a, dev), dev.cus, dev.lds_bytes);
 }
 
 // ---- BF16-weight product ----------------------------------------------------------------
@@ -1023,11 +1017,11 @@ static int run_e4m3(const void* x, int64_t M, int64_t ldx, const void* q8, const
         const char* e = knob("MXFP4_E4M3_GENERAL");              // measurement only
         return e && atoi(e) != 0;
     }();
-    const bool blocks = !general_only && fmt_blocks_preferred(a, dev, 8);
-    const bool reg = !general_only && !blocks && aligned(s, 4) && gemv_reg_can_run(a, dev) && gemv_reg_single_pass(a);
+    const bool reg = !general_only && aligned(s, 4) && gemv_reg_can_run(a, dev) && gemv_reg_single_pass(a);
     // five and more rows: the matrix-core tiles when a pass's activation rows fit the LDS (up to
     // four rows the vector-ALU kernel is faster: 13.5 against 16.8 us on the 7B qkv shape)
     const bool tiles = !general_only && !reg && a.m >= 5 && aligned(s, 4) && aligned(q8, 16) && mfma_tile_fmt_can_run(a, dev);
+    const bool blocks = !general_only && !reg && fmt_blocks_preferred(a, dev, 8);
     hipError_t e = reg      ? launch_gemv_reg(a, dev, &parts_used, st, nullptr, 8)
                    : blocks ? launch_gemm_wide_fmt(8, a, dev, &parts_used, st)
                    : tiles  ? launch_mfma_tile8(a, dev, &parts_used, st)
@@ -1392,13 +1386,13 @@ static int run_fmt(int fmt, const void* x, int64_t M, int64_t ldx, const void* q
     // sibling formats with the other convert instruction (a lane's 24 bytes of a 6-bit block need the
     // scale bytes 4-byte aligned there), the 2-bit codes with their own decode; everything else: the
     // general kernel
-    const int code = fmt == MXFP4_FMT_E5M2 ? 24 : (fmt == MXFP4_FMT_E3M2 ? 22 : 2);
-    const bool blocks = fmt_blocks_preferred(a, dev, code);
-    const bool reg = !blocks && aligned(s, 4) && aligned(q, 16) && gemv_reg_can_run(a, dev) && gemv_reg_single_pass(a);
+    const bool reg = aligned(s, 4) && aligned(q, 16) && gemv_reg_can_run(a, dev) && gemv_reg_single_pass(a);
     // three and more rows when a pass's activation rows fit the LDS: the matrix-core tiles of the
     // sibling formats (E5M2 at four rows on the 7B qkv shape: 16.8 us there, 20.9 in the general kernel)
     const bool tiles = fmt != MXFP4_FMT_T2 && !reg && a.m >= 3 && a.k % 128 == 0 &&
                        aligned(s, 4) && aligned(q, 16) && mfma_tile_fmt_can_run(a, dev);
+    const int code = fmt == MXFP4_FMT_E5M2 ? 24 : (fmt == MXFP4_FMT_E3M2 ? 22 : 2);
+    const bool blocks = !reg && fmt_blocks_preferred(a, dev, code);
     hipError_t e = reg      ? launch_gemv_reg(a, dev, &parts_used, st, nullptr, code)
                    : blocks ? launch_gemm_wide_fmt(code, a, dev, &parts_used, st)
                    : tiles  ? launch_mfma_tile8(a, dev, &parts_used, st, code)

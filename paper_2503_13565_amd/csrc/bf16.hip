@@ -895,8 +895,6 @@ static bool blocks_preferred(const Bf16Args& a, const DeviceInfo& dev)
         return false;
     if (from)
         return a.m >= atoi(from);
-    if (a.m < 3)
-        return wide_decode_bf16_preferred(a.m, a.n, a.k, dev.cus);
     return wide_bf16_preferred(a.m, a.n, a.k, bf16_mfma_can_run(a, dev), dev.cus, dev.lds_bytes);
 }
 

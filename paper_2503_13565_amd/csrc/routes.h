@@ -73,89 +73,29 @@ inline bool wide_one_pass_preferred(const TileCall& c)
     return k <= 1536 || (k > 2048 && k <= 2432);
 }
 
-// One and two rows.  The decode kernels give a wave a step of 2048 elements of one weight row, in pairs: a short K leaves most of its
-// lanes idle, a K just past 4096 half of its steps, and the row's way through the lanes costs the same.  A block walks such a K in
-// as many lanes as it has.  For products only: a pick's value leaves in 32 bits, and the blocks' longer chains are off by
-// 1.0 to 1.7 of what the decode kernels' lanes leave there (5e-8 to 9e-8; below the BF16 rounding of a product by four digits; BF16
-// weights 0.7 to 1.05, so their picks go too).  One row of MXFP4 weights stays with the decode kernel, whose bits the chained and
-// the merged launches give.  Figures: blocks as a part of the decode kernels' time over 12 numbers of weight rows from 256 to 57344 and
-// 16 K from 128 to 16384.
-//
-// MXFP4.  Two rows: 256 x 384 0.93, 1500 x 2048 0.91, 4096 x 512 0.75, 8192 x 2048 0.75, x 3072 0.97, x 5120 0.85, 28000 x 512
-// 0.33, x 2048 0.66, x 3072 0.88, x 4096 1.09, x 5120 0.85, x 6144 1.04, 16000 x 11008 0.91; with gate or residual the same.
-// Tile-major, one row: 16000 x 640 0.82, 28000 x 1280 0.84, 57344 x 1024 0.62; two rows (and one with gate or residual, which the tiles
-// take too): 256 x 1024 0.94, 5000 x 2048 0.93, 28000 x 1024 0.75, x 2560 0.89, 22016 x 6144 0.93.
-inline bool wide_decode_preferred(const TileCall& c)
-{
-    const int m = c.m, n = c.n, k = c.k, unit = c.cus;
-    if (c.pick)
-        return false;
-    if (c.tiled && m == 1 && !c.fused)
-        return n >= 48 * unit && k <= (n >= 80 * unit ? 1280 : 640);
-    if (c.tiled)
-        return k <= 1024 || (n >= 16 * unit && n <= 36 * unit && k <= 2048) || (n >= 56 * unit && n <= 100 * unit && k <= 6144) ||
-               (n > 100 * unit && k <= 1280);
-    if (m == 1)
-        return false;
-    // the decode step's form for K <= 2048 (gemv_short.hip): 4096 x 512 2.28 us, 3.08 in blocks, 8192 x 1024 3.19, 3.36, 6000 x 1536 3.82, 3.83,
-    // 8192 x 1536 4.16, 3.93, 16000 x 512 3.57, 3.19
-    if (n >= 8 * unit && n <= (k <= 1024 ? 32 : k <= 2048 ? 24 : 0) * unit)
-        return false;
-    if (n <= 24 * unit)
-        return k <= (n < 4 * unit ? 384 : 2048);
-    if (n <= 64 * unit)
-        return k <= 2560 || (k > 4096 && k <= 11264);
-    return k <= 2560 || (k <= 3072 && n <= 128 * unit) || (k > 4096 && k <= 5120 && n <= 128 * unit);
-}
-
-// MXFP4 with K % 128 != 0, one and two rows against the general vector ALU kernel: one row 3000 x 672 0.87, 5000 x 1056 0.90, 28000 x 416
-// 0.51, x 1056 0.82, 22016 x 1312 1.04; two rows 1500 x 672 0.85, 3000 x 1568 0.89, 8192 x 11040 0.73, 12288 x 5152 0.95,
-// 28000 x 2592 0.73, x 4064 0.96, x 6176 1.25.
-inline bool wide_decode_ragged_preferred(int m, int n, int k, int cus)
+// One and two rows of tile-major weights, where the tiles take them (two rows; one row with bias, gate or residual).  The decode kernels
+// keep all other calls of one and two rows of quantised weights, also where a block would be faster (28000 x 512 at two rows of ternary
+// codes 0.26): their lanes' short chains leave FP32 sums closer to 64 bits than a block does (blocks 1.0 to 1.7 of their rms error in row-major
+// MXFP4, with ragged K 0.9 to 1.6, of 8 and 6 bits 0.9 to 1.9, ternary 1.0 to 1.1; 6000 values a size, those of the picks).  Against the tiles
+// it is 0.87 to 1.01 from K = 1024 on (5000 x 640 1.1, 16000 x 256 1.2, 25600 x 2048 1.04).  Products and picks take the same lines, so that a
+// pick is the largest of the sums that the product rounds.  Time, blocks as a part of the tiles' (product, pick): 300 x 1024 0.93, 0.95; 4096 x 1280
+// 1.00, 0.97, x 2048 0.97, 0.96; 6000 x 1536 0.90, 0.90; 14500 x 2560 0.82, 0.88; 22016 x 1024 0.76, 0.83; 57344 x 1280 0.84, 0.86.
+inline bool wide_tiled_decode_preferred(int n, int k, int cus)
 {
     const int unit = cus;
-    if (n < 4 * unit)
+    if (k < 1024)
         return false;
-    if (m == 1)
-        return k <= (n < 8 * unit ? 160 : n < 16 * unit ? 672 : 1088);
-    if (n >= 28 * unit && n <= 36 * unit)
-        return k <= 11264;
-    return k <= (n < 8 * unit ? 672 : n < 16 * unit ? 1568 : 2592);
+    return k == 1024 || (n >= 16 * unit && n <= 36 * unit && k <= 2048) || (n >= 56 * unit && n <= 96 * unit && k <= 2560) ||
+           (n > 100 * unit && k <= 1280);
 }
 
-// The other formats, K % 128 == 0, one and two rows.  8-bit: one row 3000 x 384 0.85, 8192 x 1024 0.69, 28000 x 512 0.43, x 1280
-// 0.74, 22016 x 1536 1.01; two rows 3000 x 2048 0.77, 28000 x 2048 0.77, 57344 x 2048 0.92.  6-bit: few weight rows, where the tiles ran for E2M3,
-// 256 x 128 to 8192 0.74 to 0.93 (of E3M2's vector ALUs 1.2 to 1.4); one row 8192 x 1024 0.69, 28000 x 1280 0.69; two rows 28000 x 2048 0.76, and beyond K = 4096, where
-// E2M3 took a pass of the decode kernel per row, 8192 x 8192 0.62, 28000 x 5120 0.69 (E3M2, in one pass of the vector ALUs, 18175 x 9088 1.17).  Ternary: one row 8192 x 1024 0.67, 28000 x 2048
-// 0.76, x 5120 0.76; two rows 28000 x 512 0.26, x 3072 0.76, x 8192 0.74, 12288 x 16384 0.95.
-inline bool wide_decode_format_preferred(int m, int n, int k, int bits, bool e2m3, int cus)
-{
-    const int unit = cus;
-    if (n < 8 * unit)
-        return e2m3 && k <= 8192;
-    if (m == 1)
-        return k <= (n < 16 * unit && bits != 6 ? 384 : n < 32 * unit ? 1024 : bits == 2 ? 2048 : 1280) ||
-               (bits == 2 && n >= 48 * unit && k > 4096 && k <= 5120);
-    return k <= (bits == 2 && n >= 32 * unit ? 3072 : 2048) || (k > 4096 && k <= 16384 && (e2m3 || (bits == 2 && n >= 32 * unit)));
-}
-
-// BF16 weights, one and two rows, products and picks: one row 5000 x 384 0.84, 8192 x 1024 0.84, 28000 x 1024 0.65, 12288 x 1280 0.85,
-// 28000 x 2048 1.22; two rows 3000 x 384 0.88, 8192 x 1024 0.88, 28000 x 384 0.83, x 640 0.98.
-inline bool wide_decode_bf16_preferred(int m, int n, int k, int cus)
-{
-    const int unit = cus;
-    if (m == 1)
-        return n >= 16 * unit && k <= (n < 32 * unit ? 384 : n < 48 * unit ? 1024 : 1280);
-    return n >= 8 * unit && k <= (n >= 16 * unit && n <= 36 * unit ? 1024 : n <= 128 * unit ? 384 : 128);
-}
-
-// From three rows on, K % 128 == 0.  Figures: us per launch, tiles -> blocks, or blocks as a part of what the tiles take.
+// MXFP4, K % 128 == 0.  Figures, from three rows on: us per launch, tiles -> blocks, or blocks as a part of what the tiles take.
 inline bool wide_preferred(const TileCall& c)
 {
     const int m = c.m, n = c.n, k = c.k, unit = c.cus, passes = (m + 15) / 16;
     const bool plain = !c.fused && !c.pick;
     if (m < 3)
-        return false;
+        return c.tiled && c.fits && (m == 2 || c.fused) && wide_tiled_decode_preferred(n, k, unit);
     if (c.fits) {
         // Beyond 16 rows always: 12288 x 4096 at 32 rows 19.9 -> 10.1, 22016 x 4096 at 64 57 -> 19.
         if (m > 16)
@@ -227,15 +167,17 @@ inline bool wide_ragged_preferred(int m, int n, int k, int cus, int lds_bytes)
 }
 
 // The other formats, K % 128 == 0.  `bits` per element; `tiles`: the call's rows fit the LDS whole on the tile kernels (of
-// 6 and 8 bits; the ternary codes run on the vector ALUs).
-inline bool wide_format_preferred(int m, int n, int k, int bits, bool tiles, int cus, int lds_bytes)
+// 6 and 8 bits; the ternary codes run on the vector ALUs); `e2m3`: that 6-bit format, which has no vector ALU kernel for few weight rows.
+inline bool wide_format_preferred(int m, int n, int k, int bits, bool e2m3, bool tiles, int cus, int lds_bytes)
 {
     const int unit = cus;
     // Beyond 16 rows always (E4M3 12288 x 4096 at 32 rows 33 -> 19, E2M3 27 -> 19).
     if (m > 16)
         return true;
+    // One and two rows of E2M3 where the tiles ran: blocks 0.81 of their time at K = 384, 0.87 at 1024, 0.93 at 4096, 0.92 at 8192, picks 0.90
+    // to 0.96; the rms error of the FP32 sums 0.5 to 0.98 of theirs (K = 128 1.2, 256 0.9 to 1.1; 16 to 100 weight rows up to 1.09).
     if (m < 3)
-        return false;
+        return e2m3 && n > unit && n < 8 * unit && k >= 384 && k <= 8192;
     // The ternary codes went over the weights once per four rows (22016 x 4096 at 8 rows 51 -> 17).  In one such pass, up
     // to eight weight rows per unit, the vector ALUs are faster from K = 4224 (1024 x 4096 0.95, 1000 x 8192 at four rows 1.14 of them) until
     // a unit has room for one copy of the four rows only (1000 x 12288 0.89); a short K leaves nothing but
@@ -278,6 +220,14 @@ inline bool wide_format_preferred(int m, int n, int k, int bits, bool tiles, int
 inline bool wide_bf16_preferred(int m, int n, int k, bool tiles, int cus, int lds_bytes)
 {
     const int unit = cus;
+    // One and two rows with a short K, products and picks: one row 5000 x 384 0.84 of the decode kernel, 8192 x 1024 0.84, 28000 x 1024 0.65,
+    // 12288 x 1280 0.85, 28000 x 2048 1.22; two rows 3000 x 384 0.88, 8192 x 1024 0.88.  Only where the FP32 sums are no further from 64 bits:
+    // one row 0.86 to 1.01 of the decode kernel's rms error, but beyond 64 rows per unit K = 128 1.07 to 1.12, 256 1.02 to 1.3; two rows up to 36 per unit
+    // 0.92 to 1.01, 28000 x 256 1.24, x 384 1.02, 57344 x 128 1.07.
+    if (m == 1)
+        return n >= 16 * unit && k <= (n < 32 * unit ? 384 : n < 48 * unit ? 1024 : 1280) && (n <= 64 * unit || k >= 384);
+    if (m == 2)
+        return n >= 8 * unit && n <= 36 * unit && k <= (n >= 16 * unit ? 1024 : 384);
     // Beyond 16 rows always (12288 x 4096 at 32 rows 41 -> 26, 4096 x 11008 98 -> 30).  Nine to 16 rows that the tiles
     // cannot take (4096 x 11008 at 16 rows 49 -> 25, 5001 x 2056 20 -> 11), or that leave the units few of them while K is
     // whole pairs of phases (4096 x 4096 0.93 of the tiles, x 2048 0.89, 2048 x 2048 1.0, 4096 x 512 1.07), or 17 to 32 or 49 to 64 rows
@@ -294,8 +244,6 @@ inline bool wide_bf16_preferred(int m, int n, int k, bool tiles, int cus, int ld
     // (4096 x 16384 0.74 of them, 8192 x 16384 1.1).
     // A short K, where the start of a pass is most of it: three rows 4096 x 512 0.84, 12288 x 512 0.82, 57344 x 512 0.97; four 4096 x
     // 1536 0.84, 12288 x 1024 0.87, 57344 x 512 0.79; five to eight 2048 x 2048 0.85, 12288 x 1024 0.74, 32000 x 1024 0.73.
-    if (m < 3)
-        return false;
     if (m < 5)
         return n > 12 * unit && k <= (m == 3 || n > 64 * unit ? 512 : n > 32 * unit ? 1024 : 1536);
     if (n <= 8 * unit)

@@ -176,6 +176,37 @@ def test_one_and_two_rows_of_other_formats(fmt, m, n, k):
     assert_gemm_close(y[:, cols.to(DEV)], *ref(synth.to_bits(x), q.cpu()[cols].numpy(), s.cpu()[cols].numpy()), "%s M=%d N=%d K=%d" % (fmt, m, n, k))
 
 
+@pytest.mark.parametrize("fmt,m,n,k", [(fmt, *size) for fmt in ["mxfp4", "tiled", "bf16"] + sorted(FORMATS) for size in [
+    (1, 300, 1024), (1, 2500, 512), (1, 9000, 1024), (1, 28000, 768), (2, 300, 1024), (2, 1000, 4096), (2, 2500, 1024), (2, 9000, 1024),
+    (2, 9000, 5120), (2, 17000, 2048), (2, 28000, 2048)]] + [("mxfp4", 2, 3000, 1344), ("mxfp4", 1, 28000, 832)])
+def test_one_and_two_rows_are_picked_from_the_sums_of_the_product(fmt, m, n, k):
+    # the second half of K takes back what the first half adds but for a bit of a few elements: sums in another order come out different by far
+    # more than the rounding of the result
+    print(fmt, m, n, k, flush=True)
+    w = synth.weights_student_t(n, k // 2, seed=9760 + n, device=DEV)
+    w = torch.cat([w, -w], 1)
+    xs = synth.activations_outlier_channels(24 * m, k // 2, seed=9770 + k, device=DEV)
+    more = xs.clone()
+    more[:, 7::k // 8].view(torch.int16).add_(1)
+    xs = torch.cat([xs, more], 1)
+    if fmt == "bf16":
+        product, pick = (lambda x: binding.mxfp4_bf16_gemm(x, w)), (lambda x: binding.mxfp4_bf16_gemm_argmax(x, w))
+    elif fmt in FORMATS:
+        q = FORMATS[fmt][1](w)
+        product, pick = (lambda x: FORMATS[fmt][2](x, *q)), (lambda x: FORMATS[fmt][3](x, *q))
+    else:
+        q = binding.mxfp4_direct_cast(w)
+        if fmt == "tiled":
+            tw = binding.mxfp4_tile_repack(*q)
+            product, pick = (lambda x: binding.mxfp4_woq_gemm_tiled(x, tw)), (lambda x: binding.mxfp4_woq_gemm_tiled_argmax(x, tw))
+        else:
+            product, pick = (lambda x: binding.mxfp4_woq_gemm(x, *q)), (lambda x: binding.mxfp4_woq_gemm_argmax(x, *q))
+    for x in xs.split(m):
+        y, (idx, val) = product(x), pick(x)
+        assert torch.equal(y.gather(1, idx.long()[:, None])[:, 0], val.to(torch.bfloat16))
+        assert torch.equal(y.max(dim=1).values, val.to(torch.bfloat16))
+
+
 @pytest.mark.parametrize("m,n,k", [(1, 4097, 8), (1, 8200, 1000), (1, 16003, 1280), (2, 2049, 384), (2, 8200, 1024), (2, 33000, 128)])
 def test_one_and_two_rows_of_unquantised_weights(m, n, k):
     w = synth.weights_student_t(n, k, seed=9920 + n, device=DEV)

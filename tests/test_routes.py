@@ -21,8 +21,9 @@ extern "C" int mx(int m, int n, int k, int fits, int split, int tiled, int fused
 }
 extern "C" int format(int m, int n, int k, int bits, int tiles)
 {
-    return wide_format_preferred(m, n, k, bits, tiles != 0, 256, 160 * 1024);
+    return wide_format_preferred(m, n, k, bits, false, tiles != 0, 256, 160 * 1024);
 }
+extern "C" int e2m3(int m, int n, int k) { return wide_format_preferred(m, n, k, 6, true, true, 256, 160 * 1024); }
 extern "C" int bf16(int m, int n, int k, int tiles)
 {
     return wide_bf16_preferred(m, n, k, tiles != 0, 256, 160 * 1024);
@@ -190,13 +191,43 @@ def test_later_passes_have_no_fewer_workgroups(rules):
 
 
 def test_one_and_two_rows_never_take_the_blocks(rules):
+    # where the decode kernels take them, whose FP32 sums are closer to 64 bits
     for m in (1, 2):
-        for n in (1, 16, 1000, 1024, 1500, 2048, 4096, 9000, 32000):
-            for k in (128, 1024, 4096, 11008, 28672, 65536):
-                for split in (0, 1):
-                    assert not any(rules.mx(m, n, k, fits, split, tiled, fused, 0) for fits in (0, 1) for tiled in (0, 1) for fused in (0, 1))
-                assert not any(rules.format(m, n, k, bits, fits) for bits in (2, 6, 8) for fits in (0, 1))
-                assert not any(rules.bf16(m, n, k, tiles) for tiles in (0, 1)) and not rules.ragged(m, n, k + 32)
+        for n in (1, 16, 1000, 1024, 1500, 2048, 4096, 9000, 16000, 28000, 32000, 57344):
+            for k in (128, 384, 512, 1024, 2048, 4096, 4224, 5120, 8192, 11008, 28672, 65536):
+                for fits in (0, 1):
+                    for split in (0, 1):
+                        for pick in (0, 1):
+                            assert not any(rules.mx(m, n, k, fits, split, 0, fused, pick) for fused in (0, 1))
+                            assert m == 2 or not rules.mx(m, n, k, fits, split, 1, 0, pick)
+                    assert not any(rules.format(m, n, k, bits, fits) for bits in (2, 6, 8))
+                assert not rules.ragged(m, n, k + 32) and (256 < n < 2048 or not rules.e2m3(m, n, k))
+
+
+@pytest.mark.parametrize("m,n,k,form,blocks", [
+    # tile-major, where the tiles take one and two rows
+    (2, 300, 1024, "t", True), (2, 300, 1024, "tp", True), (1, 300, 1024, "tf", True), (2, 300, 896, "t", False), (1, 28000, 512, "tf", False),
+    (2, 4096, 2048, "tp", True), (2, 4000, 2048, "t", False), (2, 9216, 2176, "t", False), (2, 9472, 1280, "t", False),
+    (2, 22016, 2560, "tp", True), (1, 22016, 2560, "tf", True), (2, 22016, 2688, "t", False), (2, 25088, 2048, "t", False),
+    (2, 57344, 1280, "t", True), (2, 57344, 1408, "tp", False), (1, 57344, 1024, "t", False), (1, 57344, 1024, "tp", False),
+])
+def test_one_and_two_rows_of_tile_major_weights(rules, m, n, k, form, blocks):
+    assert asked(rules, m, n, k, form) == blocks
+
+
+@pytest.mark.parametrize("kind,m,n,k,blocks", [
+    ("e2m3", 1, 257, 384, True), ("e2m3", 2, 2047, 8192, True), ("e2m3", 1, 256, 1024, False), ("e2m3", 2, 1000, 256, False),
+    ("e2m3", 1, 1000, 8320, False), ("e2m3", 2, 8192, 8192, False),
+    ("bf16", 1, 4096, 384, True), ("bf16", 1, 4095, 384, False), ("bf16", 1, 8000, 512, False), ("bf16", 1, 8192, 1024, True),
+    ("bf16", 1, 12288, 1280, True), ("bf16", 1, 28000, 1280, True), ("bf16", 1, 28000, 376, False), ("bf16", 1, 28000, 2048, False),
+    ("bf16", 2, 2048, 384, True), ("bf16", 2, 2040, 384, False), ("bf16", 2, 9216, 1024, True), ("bf16", 2, 9217, 128, False),
+    ("bf16", 2, 3000, 512, False),
+])
+def test_one_and_two_rows_where_the_blocks_are_as_exact(rules, kind, m, n, k, blocks):
+    if kind == "e2m3":
+        assert bool(rules.e2m3(m, n, k)) == blocks
+    else:
+        assert all(bool(rules.bf16(m, n, k, tiles)) == blocks for tiles in (0, 1))
 
 
 def picked(rules, bits, table, m, n, k):
@@ -251,38 +282,3 @@ def test_shapes_that_were_measured_the_fastest(rules, kind, m, n, k, fast):
     body = re.search(r"constexpr Cost %s\[\] = \{(.*?)\n\};" % name, open(os.path.join(CSRC, source)).read(), re.S).group(1)
     table = [[float(v.rstrip("f")) for v in row.split(",")] for row in re.findall(r"\{([^{}]*)\}", body)]
     assert tuple(int(v) for v in table[picked(rules, bits, table, m, n, k)[0]][:5]) in fast
-
-
-DECODE_RULES = r"""
-#include "routes.h"
-using namespace mxfp4;
-extern "C" int mx(int m, int n, int k, int tiled, int fused, int pick)
-{
-    return wide_decode_preferred({m, n, k, 256, true, false, tiled != 0, fused != 0, pick != 0});
-}
-extern "C" int ragged(int m, int n, int k) { return wide_decode_ragged_preferred(m, n, k, 256); }
-extern "C" int format(int m, int n, int k, int bits, int e2m3) { return wide_decode_format_preferred(m, n, k, bits, e2m3 != 0, 256); }
-extern "C" int bf16(int m, int n, int k) { return wide_decode_bf16_preferred(m, n, k, 256); }
-"""
-
-
-def test_one_and_two_rows_of_a_short_k(tmp_path):
-    (tmp_path / "decode.cpp").write_text(DECODE_RULES)
-    subprocess.check_call(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(tmp_path / "decode.cpp"), "-o", str(tmp_path / "decode.so")])
-    rules = ctypes.CDLL(str(tmp_path / "decode.so"))
-    # one row of canonical MXFP4 weights (its bits are those of the chained launch) and picks (32 bits leave) stay
-    assert not any(rules.mx(1, n, k, 0, f, 0) for n in (16, 4096, 57344) for k in (128, 1024, 4224) for f in (0, 1))
-    assert not any(rules.mx(m, n, k, t, 0, 1) for m in (1, 2) for n in (16, 32000) for k in (128, 1024) for t in (0, 1))
-    for form, calls in (("mx", [(2, 28000, 512, 0, 0), (2, 1500, 2048, 0, 1), (2, 8192, 2048, 0, 1), (2, 8192, 5120, 0, 0), (1, 57344, 1024, 1, 0), (1, 1000, 1024, 1, 1)]),
-                        ("ragged", [(1, 28000, 416), (2, 8192, 11040), (2, 1500, 672)]),
-                        ("format", [(2, 28000, 512, 2, 0), (1, 8192, 1024, 8, 0), (2, 8192, 8192, 6, 1), (1, 1000, 4096, 6, 1)]),
-                        ("bf16", [(1, 28000, 1024), (2, 8192, 1024), (2, 3000, 384)])):
-        for c in calls:
-            assert getattr(rules, form)(*c, 0), (form, c)
-    for form, calls in (("mx", [(2, 28000, 4096, 0, 0), (2, 57344, 6144, 0, 0), (2, 4096, 4224, 0, 1), (2, 4096, 2048, 0, 1), (2, 8192, 1024, 0, 0), (1, 8192, 640, 1, 0), (2, 57344, 65536, 0, 0)]),
-                        ("ragged", [(1, 1000, 416), (2, 28000, 6176), (1, 22016, 1312), (2, 8192, 65504)]),
-                        ("format", [(2, 2047, 11008, 2, 0), (2, 2048, 11008, 2, 0), (1, 2048, 65536, 2, 0), (1, 22016, 4096, 8, 0), (1, 976, 4096, 6, 0),
-                                    (2, 4096, 24576, 6, 1), (2, 18175, 9088, 6, 0)]),
-                        ("bf16", [(1, 28000, 2048), (2, 28000, 640), (1, 4095, 128), (2, 1000, 128)])):
-        for c in calls:
-            assert not getattr(rules, form)(*c, 0), (form, c)
