@@ -295,10 +295,12 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
         for (int i = 0; i < CA; ++i) {
             const int T = u * WK + (i * 8 + wave) / kRowGroups;
             const int off = x_off[i] | (kRagged ? past((k >> 3) - 1, T * 16 + xc) : T < steps ? 0 : kOob);
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(
+            // m0: where in the LDS lane 0's bytes go.  The load reads scalar registers that a vector instruction may have written just in
+            // front (a read lane, a restored spill): five wait states, which the compiler does not count into assembly.
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(
                              lds_at + (b * kBuf * 16 + i * 8192)),
                          "v"(off), "s"(rx_words), "s"(T < steps ? T * 256 : 0)
-                         : "memory");
+                         : "memory", "m0");
         }
     };
     auto issue_q = [&](Slot& sl) {
@@ -346,7 +348,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
             xs[b * kBuf + ((xc >> 4) * BM + r) * 16 + (chunk_at(xc & 15) ^ (r & 15))] = xr[i];
         }
     };
-    // The loads of one phase's weights: direct, the only ones that stay in flight across a barrier.
+    // The loads of one phase's weights: direct, the only ones that stay in flight across a barrier.  The counted waits below rely on
+    // issue_q being this many vector memory instructions at the least, none dropped, merged or moved in front of the direct loads (the
+    // scheduling barriers): with fewer behind those, a wait for the weights would not cover them.  True of every instance as compiled.
     constexpr int kQueued = NF * (kRagged ? 2 : kW == kBf16 ? 4 : kBits == 8 || kBits == 6 ? 2 : 1);
     issue_scales(0);
     if constexpr (kDirect)
