@@ -55,6 +55,7 @@
 #include <utility>
 
 #include "block_out.h"
+#include "block_ways.h"
 #include "common.h"
 #include "kernels.h"
 #include "scale_stage.h"
@@ -68,14 +69,6 @@ constexpr int kOob = 0x7FFFFFF0;        // lane offset beyond any descriptor: th
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
 typedef __attribute__((ext_vector_type(6))) unsigned int u32x6_t;
 typedef __attribute__((ext_vector_type(16))) unsigned int u32x16_t;
-
-// The weights: MXFP4 row-major, MXFP4 tile-major, MXFP4 row-major with K % 128 != 0, E4M3 and E5M2 bytes,
-// E2M3 and E3M2 blocks of 24 bytes, ternary blocks of 8 bytes, unquantised BF16 (any K % 8 == 0).
-enum Kind { kMx, kMxTiled, kMxRagged, kE4m3, kE5m2, kE2m3, kE3m2, kT2, kBf16 };
-constexpr int kind_bits(Kind w)
-{
-    return w == kBf16 ? 16 : w == kE4m3 || w == kE5m2 ? 8 : w == kE2m3 || w == kE3m2 ? 6 : w == kT2 ? 2 : 4;
-}
 
 struct Args {
     const uint16_t* x;
@@ -167,21 +160,7 @@ constexpr Cut sum_cut(Kind w, int wk, int mf, int nf)
 }
 constexpr bool each_apart(Kind w, int mf) { return w == kBf16 && mf == 1; }
 
-// The activations' way into the LDS: through registers (asked for two phases ahead, written a phase ahead), or by loads that put
-// them there (kDirect: asked for a phase ahead, into the buffer that the phase before read).  The direct way saves the registers, the
-// writes and their waits, but its loads leave only when the phase's weights have arrived: the compiler counts the weights'
-// loads exactly as long as nothing younger is in flight that it does not know, and a wait too many is a whole latency.  So it is for
-// blocks whose waves all lie along the weight rows (long phases: 22016 x 4096 with the gate at 509 rows 79.1 -> 75.3 us, 13999 x 6016 at
-// 399 rows 0.93), and for calls of few phases, which are mostly start and end: 1016 x 2016 at three rows 3.72 -> 3.42, 14234 x
-// 768 at 17 4.26 -> 4.02, E3M2 1875 x 1152 at 24 3.85 -> 3.57; with nine phases and more 1.05 to 1.15 of the other way, and so are
-// many rows of blocks over few weight rows (302 x 4352 at 173 rows, five phases, 1.09; 542 x 2048 at 475 1.07) and picks (1.00 to 1.02).
-constexpr bool direct_only(Kind w, int wk) { return w != kBf16 && wk == 1; }
-constexpr bool has_direct(Kind w) { return w != kBf16; }
-inline bool takes_direct(Kind w, int wk, const Args& a)
-{
-    return a.out.part_val == nullptr && (a.k + 127) / 128 <= (w == kMxTiled ? 3 : a.tiles_m > 6 ? 2 : 6) * wk;
-}
-
+// kDirect: the activations' way into the LDS (block_ways.h).
 // The leading arguments are scalars that arrive in registers when a wave starts; `out` is for the end.
 template <Kind kW, int WM, int WN, int WK, int MF, int NF, bool kDirect>
 __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* __restrict__ x,
@@ -673,14 +652,12 @@ hipError_t launch_way(const Args& a, const DeviceInfo& dev, hipStream_t stream)
 template <Kind kW, int WM, int WN, int WK, int MF, int NF>
 hipError_t launch_block(const Args& a, const DeviceInfo& dev, hipStream_t stream)
 {
-    if constexpr (direct_only(kW, WK)) {
-        return launch_way<kW, WM, WN, WK, MF, NF, true>(a, dev, stream);
-    } else {
-        if constexpr (has_direct(kW))
-            if (takes_direct(kW, WK, a))
-                return launch_way<kW, WM, WN, WK, MF, NF, true>(a, dev, stream);
+    if constexpr (has_direct(kW, WK, MF, NF))
+        if (takes_direct(kW, WK, MF, NF, a.k, a.tiles_m, a.out.part_val != nullptr))
+            return launch_way<kW, WM, WN, WK, MF, NF, true>(a, dev, stream);
+    if constexpr (has_registers(kW, WK, MF, NF))
         return launch_way<kW, WM, WN, WK, MF, NF, false>(a, dev, stream);
-    }
+    return hipErrorInvalidValue;
 }
 
 // A block shape with what it took, in microseconds: the first block of a compute unit and every further one

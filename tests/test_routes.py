@@ -14,7 +14,16 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 RULES = r"""
 #include "routes.h"
 #include "sum_chains.h"
+#include "block_ways.h"
 using namespace mxfp4;
+extern "C" int ways(int kind, int wk, int mf, int nf)               // 1: the direct form, 2: the one through registers
+{
+    return wide::has_direct((wide::Kind)kind, wk, mf, nf) + 2 * wide::has_registers((wide::Kind)kind, wk, mf, nf);
+}
+extern "C" int direct(int kind, int wk, int mf, int nf, int k, int tiles_m, int pick)
+{
+    return wide::takes_direct((wide::Kind)kind, wk, mf, nf, k, tiles_m, pick != 0);
+}
 extern "C" int mx(int m, int n, int k, int fits, int split, int tiled, int fused, int pick)
 {
     return wide_preferred({m, n, k, 256, fits != 0, split != 0, tiled != 0, fused != 0, pick != 0});
@@ -262,6 +271,17 @@ def test_sizes_that_take_every_block_shape(rules, kind, source, name, never):
             assert rules.bf16(m, n, k, int(k % 128 == 0))
         else:
             assert rules.format(m, n, k, kind, 1)
+
+
+@pytest.mark.parametrize("kind,wk,mf,nf,k,tiles_m,pick,direct", [
+    (0, 8, 1, 1, 6144, 1, 0, True), (0, 8, 1, 1, 6272, 1, 0, False), (0, 8, 1, 1, 128, 1, 1, False), (0, 4, 1, 1, 1024, 7, 0, True),
+    (0, 4, 1, 1, 1152, 7, 0, False), (1, 4, 1, 1, 1536, 6, 0, True), (1, 4, 1, 1, 1664, 6, 0, False), (0, 1, 8, 3, 65536, 1, 0, True),
+    (0, 1, 8, 3, 65536, 1, 1, True), (0, 1, 4, 2, 8192, 1, 0, True), (0, 1, 4, 2, 8320, 1, 0, False), (0, 1, 4, 2, 8320, 1, 1, False),
+    (1, 1, 4, 2, 65536, 1, 0, True), (2, 1, 4, 2, 65504, 1, 0, True), (3, 1, 4, 2, 128, 1, 0, False), (4, 1, 4, 2, 8192, 1, 0, False),
+    (3, 1, 4, 1, 65536, 1, 0, True), (6, 1, 4, 2, 65536, 1, 0, True), (8, 1, 8, 2, 128, 1, 0, False), (0, 4, 2, 4, 128, 1, 0, False),
+])
+def test_which_way_the_activations_take(rules, kind, wk, mf, nf, k, tiles_m, pick, direct):
+    assert bool(rules.direct(kind, wk, mf, nf, k, tiles_m, pick)) == direct
 
 
 @pytest.mark.parametrize("kind,m,n,k,fast", [
