@@ -257,7 +257,7 @@ def test_unquantised_weights(m, n, k):
     assert torch.equal(binding.mxfp4_bf16_gemm(x, wide[:, :k]), y), tag
 
 
-CASES = [(name, *size) for kind, names in (("mxfp4", ["mxfp4"]), ("tiled", ["tiled"]), (8, ["e4m3", "e5m2"]),
+CASES = [(name, *size) for kind, names in (("mxfp4", ["mxfp4"]), ("tiled", ["tiled"]), ("ragged", ["ragged"]), (8, ["e4m3", "e5m2"]),
                                            (6, ["e2m3", "e3m2"]), (2, ["t2"]), ("bf16", ["bf16"]))
          for name in names for size in BLOCK_SIZES[kind]]
 

@@ -253,20 +253,36 @@ def picked(rules, bits, table, m, n, k):
     return cost[0][1], cost[1][0] / cost[0][0] - 1
 
 
-@pytest.mark.parametrize("kind,source,name,never", [
-    ("mxfp4", "gemm_wide.hip", "kCosts", []), ("tiled", "gemm_wide.hip", "kCosts", []), (8, "gemm_wide_fmt.hip", "kCosts8", []),
-    (6, "gemm_wide_fmt.hip", "kCosts6", []), (2, "gemm_wide_fmt.hip", "kCosts2", []), ("bf16", "gemm_wide_bf16.hip", "kCosts", [])])
-def test_sizes_that_take_every_block_shape(rules, kind, source, name, never):
+KINDS = {"mxfp4": (0,), "tiled": (1,), "ragged": (2,), 8: (3, 4), 6: (5, 6), 2: (7,), "bf16": (8,)}       # of csrc/block_ways.h
+
+
+@pytest.mark.parametrize("kind,source,name", [
+    ("mxfp4", "gemm_wide.hip", "kCosts"), ("tiled", "gemm_wide.hip", "kCosts"), ("ragged", "gemm_wide.hip", "kCosts"),
+    (8, "gemm_wide_fmt.hip", "kCosts8"), (6, "gemm_wide_fmt.hip", "kCosts6"), (2, "gemm_wide_fmt.hip", "kCosts2"), ("bf16", "gemm_wide_bf16.hip", "kCosts")])
+def test_sizes_that_take_every_form_of_every_block_shape(rules, kind, source, name):
     body = re.search(r"constexpr Cost %s\[\] = \{(.*?)\n\};" % name, open(os.path.join(CSRC, source)).read(), re.S).group(1)
     table = [[float(v.rstrip("f")) for v in row.split(",")] for row in re.findall(r"\{([^{}]*)\}", body)]
-    bits = {"mxfp4": 4, "tiled": 4, "bf16": 16}.get(kind, kind)
-    assert [picked(rules, bits, table, *size)[0] for size in BLOCK_SIZES[kind]] == [i for i in range(len(table)) if i not in never]
+    bits = {"mxfp4": 4, "tiled": 4, "ragged": 4, "bf16": 16}.get(kind, kind)
+    for number in KINDS[kind]:
+        built = []
+        for i, row in enumerate(table):
+            ways = rules.ways(number, *(int(v) for v in row[2:5]))
+            assert ways
+            built += [(i, way) for way in (1, 0) if ways & (1 if way else 2)]
+        taken = []
+        for m, n, k in BLOCK_SIZES[kind]:
+            i = picked(rules, bits, table, m, n, k)[0]
+            wm, _, wk, mf, nf = (int(v) for v in table[i][:5])
+            taken.append((i, rules.direct(number, wk, mf, nf, k, -(-m // (16 * wm * mf)), 0)))
+        assert taken == built
     for m, n, k in BLOCK_SIZES[kind]:
         assert picked(rules, bits, table, m, n, k)[1] > 0.005                # (the kernel's sums are in 32 bits)
         if kind == "mxfp4":
             assert all(asked(rules, m, n, k, form) for form in ("", "f", "wp"))
         elif kind == "tiled":
             assert asked(rules, m, n, k, "tw") and asked(rules, m, n, k, "twp")
+        elif kind == "ragged":
+            assert k % 128 and rules.ragged(m, n, k)
         elif kind == "bf16":
             assert rules.bf16(m, n, k, int(k % 128 == 0))
         else:
