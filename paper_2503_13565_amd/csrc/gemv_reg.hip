@@ -91,6 +91,11 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
     constexpr bool kOperands = __is_same(Epi, Epilogue);
     const int m0 = a.m0;
     static_assert(STEPS % D == 0, "the buffer of a step must be known at compile time");
+    // The loads of step t + D leave in front of step t's converts, into other registers, so that two steps are in flight beside the one that
+    // is waited for.  Left to the scheduler they went in front of or behind the converts as the code at a row's end happened to be (one
+    // row, us, behind -> in front: 12288 x 5120 9.12 -> 8.05, 28000 x 4224 17.2 -> 14.4, 4096 x 28672 with the gate 14.6 -> 12.4).  The other
+    // formats and shorter rows keep the order that was measured the faster for them (two rows of K <= 4096 1.03 in front).
+    constexpr bool kAhead = kBits == 4 && STEPS >= 4;
     constexpr int T = NW * 64;
     constexpr int XPR = (STEPS * 256 + T - 1) / T;          // 16-byte activation chunks per thread and row
     extern __shared__ __align__(16) uint8_t smem[];
@@ -212,8 +217,11 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
     };
     int grp = row_of(wave);
 #pragma unroll
-    for (int d = 0; d < D; ++d)
+    for (int d = 0; d < D; ++d) {
         issue(grp, d, d, nblk);
+        if constexpr (kAhead)                       // (in the loop's order, which its waits count on)
+            __builtin_amdgcn_sched_barrier(0);
+    }
     // The operands' addresses are not preloaded: fetched here, while the activations are on their way, and not in
     // the first trip.
     if constexpr (kOperands)
@@ -346,10 +354,19 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
         }
 #pragma unroll
         for (int t = 0; t < STEPS; ++t) {
-            const int d = t % D;
-            u32x4_t xq[MT][4];
+            const int d = t % D, tn = t + D;
+            u32x4_t xq[MT][4], wq[R];
             if constexpr (kXLds)
                 __builtin_amdgcn_sched_barrier(0);  // step by step: across steps the scheduler piles up registers
+            const uint32_t ws = bs[d];
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                wq[r] = bq[d][r];
+            auto issue_next = [&]() { tn < STEPS ? issue(grp, tn, d, nb) : issue(grp_n, tn - STEPS, d, nb); };
+            if constexpr (kAhead) {
+                issue_next();
+                __builtin_amdgcn_sched_barrier(0);
+            }
 #pragma unroll
             for (int j = 0; j < 4; ++j)             // in the order of use: chunk j of every activation row
 #pragma unroll
@@ -410,7 +427,7 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
                 // the dword with this lane's scale byte of row r sits in lane r * 16 + lane / 4.
                 // The scaled convert reads only the exponent field of its scale operand (as E8M0),
                 // so the byte goes to bits 30:23 and whatever lands below is ignored.
-                const uint32_t dw = (uint32_t)__builtin_amdgcn_ds_bpermute((r * 16 + (lane >> 2)) * 4, (int)bs[d]);
+                const uint32_t dw = (uint32_t)__builtin_amdgcn_ds_bpermute((r * 16 + (lane >> 2)) * 4, (int)ws);
                 float sc = __uint_as_float((dw << sh_top) >> 1);
                 if (kRagged)
                     sc = (t * 64 + lane < nblk) ? sc : 1.0f;         // no NaN from a neighbour's scale byte
@@ -470,7 +487,7 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
                         w[2] = __builtin_bit_cast(bf16x2_t, w2);
                         w[3] = __builtin_bit_cast(bf16x2_t, w3);
                     } else {
-                        const uint32_t qd = bq[d][r][j];
+                        const uint32_t qd = wq[r][j];
                         w[0] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(qd, sc, 0);
                         w[1] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(qd, sc, 1);
                         w[2] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(qd, sc, 2);
@@ -489,11 +506,8 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
                     }
                 }
             }
-            const int tn = t + D;
-            if (tn < STEPS)
-                issue(grp, tn, d, nb);
-            else
-                issue(grp_n, tn - STEPS, d, nb);
+            if constexpr (!kAhead)
+                issue_next();
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -905,13 +919,21 @@ __global__ __launch_bounds__(1024) void gemv_multi_kernel(const MultiArgs a)
 #pragma unroll
         for (int t = 0; t < STEPS; ++t) {
             const int d = t % D;
-            const uint32_t dw = (uint32_t)__builtin_amdgcn_ds_bpermute((lane >> 2) * 4, (int)bs[d]);
+            const int tn = t + D;
+            const u32x4_t wq = bq[d];
+            const uint32_t ws = bs[d];
+            auto issue_next = [&]() { tn < STEPS ? issue(cur, grp, tn, d) : issue(nxt, grp_n, tn - STEPS, d); };
+            // in front of the converts, as in the single product's kernel: two products of 11008 x 4224 to 6144 1.02 to 1.06 of it behind
+            // them; shorter rows and K = 8192 1.01 in front
+            if constexpr (STEPS >= 4 && kRagged)
+                issue_next();
+            const uint32_t dw = (uint32_t)__builtin_amdgcn_ds_bpermute((lane >> 2) * 4, (int)ws);
             float sc = __uint_as_float((dw << sh_top) >> 1);
             if (kRagged)
                 sc = (t * 64 + lane < nblk) ? sc : 1.0f;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const uint32_t qd = bq[d][j];
+                const uint32_t qd = wq[j];
                 const bf16x2_t w0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(qd, sc, 0);
                 const bf16x2_t w1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(qd, sc, 1);
                 const bf16x2_t w2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(qd, sc, 2);
@@ -922,11 +944,8 @@ __global__ __launch_bounds__(1024) void gemv_multi_kernel(const MultiArgs a)
                 acc = __builtin_amdgcn_fdot2_f32_bf16(w2, __builtin_bit_cast(bf16x2_t, x2), acc, false);
                 acc = __builtin_amdgcn_fdot2_f32_bf16(w3, __builtin_bit_cast(bf16x2_t, x3), acc, false);
             }
-            const int tn = t + D;
-            if (tn < STEPS)
-                issue(cur, grp, tn, d);
-            else
-                issue(nxt, grp_n, tn - STEPS, d);
+            if constexpr (STEPS < 4 || !kRagged)
+                issue_next();
         }
         const float v = wave_sum(acc);
         acc = 0.f;
