@@ -325,17 +325,20 @@ __global__ __launch_bounds__(NW * 64) void bf16_reg_kernel(const uint16_t* __res
         for (int t = 0; t < NS; ++t) {
             const int d = t % D;
             const u32x4_t wv = buf[d];
+            const int tn = t + D;
+            // The loads of step t + D leave in front of step t's products, into other registers (behind them 8192 x 2048 8.08 us, 7.37 in
+            // front; 28000 x 1536 19.3, 16.7; 4096 x 8192 13.3, 11.9).
+            if (tn < NS)
+                issue(row, tn, d);
+            else
+                issue(row_n, tn - NS, d);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const uint32_t wd = wv[j], xd = xr[t][j];            // (a bit cast needs a plain object)
                 acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, wd),
                                                       __builtin_bit_cast(bf16x2_t, xd), acc, false);
             }
-            const int tn = t + D;
-            if (tn < NS)
-                issue(row, tn, d);
-            else
-                issue(row_n, tn - NS, d);
         }
         const float v = wave_sum(acc);
         acc = 0.f;
