@@ -220,14 +220,15 @@ inline bool wide_format_preferred(int m, int n, int k, int bits, bool e2m3, bool
 inline bool wide_bf16_preferred(int m, int n, int k, bool tiles, int cus, int lds_bytes)
 {
     const int unit = cus;
-    // One and two rows with a short K, products and picks: one row 5000 x 384 0.84 of the decode kernel, 8192 x 1024 0.84, 28000 x 1024 0.65,
-    // 12288 x 1280 0.85, 28000 x 2048 1.22; two rows 3000 x 384 0.88, 8192 x 1024 0.88.  Only where the FP32 sums are no further from 64 bits:
-    // one row 0.86 to 1.01 of the decode kernel's rms error, but beyond 64 rows per unit K = 128 1.07 to 1.12, 256 1.02 to 1.3; two rows up to 36 per unit
-    // 0.92 to 1.01, 28000 x 256 1.24, x 384 1.02, 57344 x 128 1.07.
+    // One and two rows with a short K, products and picks, as a part of the decode kernel's time: one row 4096 x 384 1.05, 5000 x 384 0.95, x
+    // 1152 1.09, 8192 x 1024 0.86, 9216 x 1024 0.98, 12288 x 1024 0.87, 20000 x 1024 0.95, x 1152 1.04, 28000 x 512 0.63, x 1024 0.82; two rows 2048 x
+    // 384 1.06, 3000 x 384 0.97, x 512 1.02, 5000 x 768 0.95, 7000 x 1024 0.97, 9216 x 512 0.90, x 768 1.02.  Only where the FP32 sums are no further from 64
+    // bits: one row 0.86 to 1.01 of the decode kernel's rms error, but beyond 64 rows per unit K = 128 1.07 to 1.12, 256 1.02 to 1.3; two rows up to
+    // 36 per unit 0.92 to 1.01, 28000 x 256 1.24, x 384 1.02, 57344 x 128 1.07.
     if (m == 1)
-        return n >= 16 * unit && k <= (n < 32 * unit ? 384 : n < 48 * unit ? 1024 : 1280) && (n <= 64 * unit || k >= 384);
+        return n > 16 * unit && k <= (n < 32 * unit ? 384 : 1024) && (n <= 64 * unit || k >= 384);
     if (m == 2)
-        return n >= 8 * unit && n <= 36 * unit && k <= (n >= 16 * unit ? 1024 : 384);
+        return n > 8 * unit && n <= 36 * unit && k <= (n <= 16 * unit ? 384 : n <= 28 * unit ? 1024 : 512);
     // Beyond 16 rows always (12288 x 4096 at 32 rows 41 -> 26, 4096 x 11008 98 -> 30).  Nine to 16 rows that the tiles
     // cannot take (4096 x 11008 at 16 rows 49 -> 25, 5001 x 2056 20 -> 11), or that leave the units few of them while K is
     // whole pairs of phases (4096 x 4096 0.93 of the tiles, x 2048 0.89, 2048 x 2048 1.0, 4096 x 512 1.07), or 17 to 32 or 49 to 64 rows

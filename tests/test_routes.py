@@ -227,10 +227,10 @@ def test_one_and_two_rows_of_tile_major_weights(rules, m, n, k, form, blocks):
 @pytest.mark.parametrize("kind,m,n,k,blocks", [
     ("e2m3", 1, 257, 384, True), ("e2m3", 2, 2047, 8192, True), ("e2m3", 1, 256, 1024, False), ("e2m3", 2, 1000, 256, False),
     ("e2m3", 1, 1000, 8320, False), ("e2m3", 2, 8192, 8192, False),
-    ("bf16", 1, 4096, 384, True), ("bf16", 1, 4095, 384, False), ("bf16", 1, 8000, 512, False), ("bf16", 1, 8192, 1024, True),
-    ("bf16", 1, 12288, 1280, True), ("bf16", 1, 28000, 1280, True), ("bf16", 1, 28000, 376, False), ("bf16", 1, 28000, 2048, False),
-    ("bf16", 2, 2048, 384, True), ("bf16", 2, 2040, 384, False), ("bf16", 2, 9216, 1024, True), ("bf16", 2, 9217, 128, False),
-    ("bf16", 2, 3000, 512, False),
+    ("bf16", 1, 4097, 384, True), ("bf16", 1, 4096, 384, False), ("bf16", 1, 8000, 512, False), ("bf16", 1, 8192, 1024, True),
+    ("bf16", 1, 12288, 1280, False), ("bf16", 1, 28000, 1024, True), ("bf16", 1, 28000, 376, False), ("bf16", 1, 28000, 2048, False),
+    ("bf16", 2, 2049, 384, True), ("bf16", 2, 2048, 384, False), ("bf16", 2, 7168, 1024, True), ("bf16", 2, 7169, 1024, False), ("bf16", 2, 9216, 512, True),
+    ("bf16", 2, 9217, 128, False), ("bf16", 2, 3000, 512, False),
 ])
 def test_one_and_two_rows_where_the_blocks_are_as_exact(rules, kind, m, n, k, blocks):
     if kind == "e2m3":
