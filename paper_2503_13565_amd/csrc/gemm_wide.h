@@ -598,25 +598,16 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_wide_kernel(const uint16_t* 
                 sum += red[(at * WK + w) * 64 + place];
             return sum;
         };
-        auto rows_at = [&](int r) { return m0 + r; };
-        if (out.part_val != nullptr || (BM * BN >= 4096 && out.residual && !rows_aligned(out.residual, out.ldr))) {
+        if (out.part_val != nullptr) {
             float* tile = reinterpret_cast<float*>(smem + (size_t)8 * MF * NF * 1024);
-            auto fill = [&]() {
-                for (int e = wk; e < MF * NF; e += WK) {
-                    f32x4_t sum = sum_of(base + e, lane);
-                    if (out.bias)
-                        sum += bias_of(out, n0 + (wn * NF + e % NF) * 16 + 4 * lg);
-                    *reinterpret_cast<f32x4_t*>(tile + ((wm * MF + e / NF) * 16 + li) * kStride + (wn * NF + e % NF) * 16 + 4 * lg) = sum;
-                }
-                lds_barrier();
-            };
-            if (out.part_val != nullptr) {
-                fill();
-                pick_rows<BM, BN, kStride>(out, tile, n0, tn, rows_at);
-            } else {
-                emit_rows<BM, BN, kStride>(out, tile, n0, rows_at, fill);
-            }
+            for (int e = wk; e < MF * NF; e += WK)
+                *reinterpret_cast<f32x4_t*>(tile + ((wm * MF + e / NF) * 16 + li) * kStride + (wn * NF + e % NF) * 16 + 4 * lg) =
+                    sum_of(base + e, lane);
+            lds_barrier();
+            pick_rows<BM, BN, kStride>(out, tile, n0, tn, [&](int r) { return m0 + r; });
         } else {
+            // (whole rows through the LDS in pieces on a misaligned residual's boundaries, as the blocks do whose waves do not share K: 0.96 to 1.02
+            // of this without the gate, 1.02 to 1.15 with it, and the code for it took 2 to 4 % of every call of 64 x 192 outputs)
             // straight from the partial sums: sixteen rows side by side, then the next columns; four sums per thread where
             // that takes one turn (748 x 6528 at 20 rows 6.85 us with eight, 6.48), else eight
             constexpr int kCols = BM * BN <= 4 * kThreads ? 4 : 8, kChunks = BN / kCols, kPerTile = 16 / kCols;
