@@ -93,9 +93,9 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
     static_assert(STEPS % D == 0, "the buffer of a step must be known at compile time");
     // The loads of step t + D leave in front of step t's converts, into other registers, so that two steps are in flight beside the one that
     // is waited for.  Left to the scheduler they went in front of or behind the converts as the code at a row's end happened to be (one
-    // row, us, behind -> in front: 12288 x 5120 9.12 -> 8.05, 28000 x 4224 17.2 -> 14.4, 4096 x 28672 with the gate 14.6 -> 12.4).  The other
-    // formats and shorter rows keep the order that was measured the faster for them (two rows of K <= 4096 1.03 in front).
-    constexpr bool kAhead = kBits == 4 && STEPS >= 4;
+    // row, us, behind -> in front: 12288 x 5120 9.12 -> 8.05, 28000 x 4224 17.2 -> 14.4, 4096 x 28672 with the gate 14.6 -> 12.4, ternary 8192 x 14336
+    // 12.1 -> 11.5, x 32768 22.4 -> 20.6).  The other formats and shorter rows keep the order that was measured the faster for them (two rows of K <= 4096 1.03 in front).
+    constexpr bool kAhead = (kBits == 4 && STEPS >= 4) || (kBits == 2 && STEPS >= 8);
     constexpr int T = NW * 64;
     constexpr int XPR = (STEPS * 256 + T - 1) / T;          // 16-byte activation chunks per thread and row
     extern __shared__ __align__(16) uint8_t smem[];
@@ -362,6 +362,11 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
 #pragma unroll
             for (int r = 0; r < R; ++r)
                 wq[r] = bq[d][r];
+            u32x2_t wq2[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if constexpr (kBits == 2)
+                    wq2[r] = bq2[d][r];
             auto issue_next = [&]() { tn < STEPS ? issue(grp, tn, d, nb) : issue(grp_n, tn - STEPS, d, nb); };
             if constexpr (kAhead) {
                 issue_next();
@@ -441,8 +446,8 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
                     if (kRagged)
                         late = (t * 64 + lane < nblk) ? late : 0.f;
                     uint32_t wv[16];
-                    decode_t2(bq2[d][r][0], wv);
-                    decode_t2(bq2[d][r][1], wv + 8);
+                    decode_t2(wq2[r][0], wv);
+                    decode_t2(wq2[r][1], wv + 8);
 #pragma unroll
                     for (int m = 0; m < MT; ++m) {
                         float v = 0.f;
