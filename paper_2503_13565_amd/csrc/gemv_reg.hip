@@ -91,11 +91,13 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
     constexpr bool kOperands = __is_same(Epi, Epilogue);
     const int m0 = a.m0;
     static_assert(STEPS % D == 0, "the buffer of a step must be known at compile time");
-    // The loads of step t + D leave in front of step t's converts, into other registers, so that two steps are in flight beside the one that
-    // is waited for.  Left to the scheduler they went in front of or behind the converts as the code at a row's end happened to be (one
-    // row, us, behind -> in front: 12288 x 5120 9.12 -> 8.05, 28000 x 4224 17.2 -> 14.4, 4096 x 28672 with the gate 14.6 -> 12.4, ternary 8192 x 14336
-    // 12.1 -> 11.5, x 32768 22.4 -> 20.6).  The other formats and shorter rows keep the order that was measured the faster for them (two rows of K <= 4096 1.03 in front).
-    constexpr bool kAhead = (kBits == 4 && STEPS >= 4) || (kBits == 2 && STEPS >= 8);
+    // The loads of step t + D stand in front of step t's converts, so that they leave there, into other registers: two steps are in flight beside the
+    // one that is waited for.  From behind the converts the scheduler hoisted them or not as the code at a row's end happened to be (one
+    // row, us, not hoisted -> in front: 28000 x 4224 17.2 -> 14.7, 12288 x 5120 9.12 -> 8.23, x 7168 9.60 -> 8.88, 4096 x 28672 with the gate 14.6 -> 12.4,
+    // ternary 8192 x 14336 12.1 -> 11.5, x 32768 22.4 -> 20.6).  The other formats and shorter rows keep the order that was measured the faster for
+    // them (two rows of K <= 4096 1.03 in front).  kPinned: nothing moves across; with four steps 0.92 to 0.97 of a free order up to K = 6144, but
+    // 1.03 to 1.07 from 6656 on.
+    constexpr bool kAhead = (kBits == 4 && STEPS >= 4) || (kBits == 2 && STEPS >= 8), kPinned = kAhead && STEPS > 4;
     constexpr int T = NW * 64;
     constexpr int XPR = (STEPS * 256 + T - 1) / T;          // 16-byte activation chunks per thread and row
     extern __shared__ __align__(16) uint8_t smem[];
@@ -219,7 +221,7 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
 #pragma unroll
     for (int d = 0; d < D; ++d) {
         issue(grp, d, d, nblk);
-        if constexpr (kAhead)                       // (in the loop's order, which its waits count on)
+        if constexpr (kPinned)                      // (in the loop's order, which its waits count on)
             __builtin_amdgcn_sched_barrier(0);
     }
     // The operands' addresses are not preloaded: fetched here, while the activations are on their way, and not in
@@ -368,10 +370,10 @@ __device__ __forceinline__ void gemv_reg_body(const RegArgs& a, const Epi& epi)
                 if constexpr (kBits == 2)
                     wq2[r] = bq2[d][r];
             auto issue_next = [&]() { tn < STEPS ? issue(grp, tn, d, nb) : issue(grp_n, tn - STEPS, d, nb); };
-            if constexpr (kAhead) {
+            if constexpr (kAhead)
                 issue_next();
+            if constexpr (kPinned)
                 __builtin_amdgcn_sched_barrier(0);
-            }
 #pragma unroll
             for (int j = 0; j < 4; ++j)             // in the order of use: chunk j of every activation row
 #pragma unroll
