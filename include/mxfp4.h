@@ -327,7 +327,9 @@ int mxfp4_woq_gemm_fused(const void* x_bf16, int64_t M, int64_t ldx,
  *              products with M = 1, no bias, act or residual, at most one with argmax_out, each a
  *              shape of the decode kernel -- K % 128 == 0, K <= 32768, N >= 8 x compute units --
  *              whose activation rows fit the LDS together; same bits as the single calls;
- *              otherwise the flag changes nothing).  Other bits: error
+ *              otherwise the flag changes nothing).  Worth it from K = 3072 on (4096 + 2048 + 2048 rows
+ *              x 3072 6.5 us, 9.4 apart); with K <= 2048 single products have a kernel of their own, and
+ *              two are faster without the flag (2 x 4096 x 1024 4.8 us, 6.6 with it).  Other bits: error
  *   workspace  device scratch shared by all products: optional as in mxfp4_woq_gemm_ws when no
  *              descriptor asks for the argmax, required as in mxfp4_woq_gemm_argmax otherwise;
  *              mxfp4_woq_gemm_grouped_workspace_bytes gives the size that serves every

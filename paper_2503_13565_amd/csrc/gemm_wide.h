@@ -39,13 +39,13 @@
 //     unaligned) every byte pulled a cache line, 104 us instead of 130 on the example below.
 //   - Prompts take blocks of 128 rows with all eight waves side by side along the weight rows, so that no
 //     weight is decoded or fetched twice in a block: 92 us against 104 for 2 x 4 waves.
-//   - A prompt is bound by the matrix pipe and what feeds it at the clock the power limit leaves: the pipe is busy in 60 % of
-//     the cycles at 2.15 GHz, the LDS in 28 %.  (When it took 86 us: 69 with the loads and the LDS reads taken out, 80 with
+//   - A prompt is bound by the matrix pipe and what feeds it at the clock the power limit leaves: the pipe is busy in 62 % of
+//     the cycles at 2.15 GHz, the LDS in 24 %.  (When it took 86 us: 69 with the loads and the LDS reads taken out, 80 with
 //     all-zero operands.)  Some tens of rows are bound by the activations' way through the L2 and LDS (at 32 rows
 //     the waves wait in 45 % of their cycles).  Measured, us from launch to launch, passes of 16 rows -> here:
-//     22016 x 4096 with the gate at 509 rows 436 -> 76 to 81 by the box (a library product of BF16 weights of that
-//     shape: 91), 12288 x 4096 at 32 rows 18.5 -> 10.2 with three sets of weights in rotation, 22016 x 4096 with the
-//     gate at 5 rows 11.1, 32000 x 4096 with the pick at 9 rows 17.7 (two launches).
+//     22016 x 4096 with the gate at 509 rows 436 -> 72 to 75 by the box (a library product of BF16 weights of that
+//     shape: 91), 12288 x 4096 at 32 rows 18.5 -> 10.1 with three sets of weights in rotation, 22016 x 4096 with the
+//     gate at 5 rows 11.0, 32000 x 4096 with the pick at 9 rows 17.0 (two launches).
 //   - A block past the end of K (K % 128 != 0, the steps that round a phase up) is a load past the
 //     descriptor: zero weights against zero activations.
 #pragma once
@@ -652,12 +652,14 @@ hipError_t launch_block(const Args& a, const DeviceInfo& dev, hipStream_t stream
 }
 
 // A block shape with what it took, in microseconds: the first block of a compute unit and every further one
-// as start + step x (steps of 128 along K, whole phases).  Fitted to every shape at 3300 sizes (MXFP4; 1550 each of the 8-bit,
+// as start + step x (steps of 128 along K, whole phases).  Fitted to every shape at 3300 sizes (row-major MXFP4; 1550 each of the 8-bit,
 // 6-bit, ternary and BF16 elements) of 3 to 520 rows, 128 to 65536 weight rows and K = 128 to 12288, six sets of weights in
 // rotation, those near the fastest shape of a size weighing most.  (Fitted up to 34000 weight rows alone: 1.018 of the fastest on average
-// beyond them, 1.004 now.)  At a quarter of the sizes that was left out of the fit the choice is within 5 % of the fastest shape that
-// cuts the sums far enough on 799 of 825, 369 of 389, 379 of 397, 391 of 408 and 353 of 358, on average 1.006, 1.006, 1.007, 1.006 and
-// 1.003 of it, at worst (K of 128 to 512) 1.24, 1.14, 1.18, 1.21 and 1.10.
+// beyond them.)  That was before the activations' direct way and the sums' present way out, which favour the larger blocks: the figures are up to
+// 6 % above what the largest take now, and only their order counts.  On the kernel as it is, at 640 to 725 other sizes each, the choice is within
+// 5 % of the fastest shape that cuts the sums far enough on 684 of 724 (MXFP4), 660 of 725 (its tile-major copy, which takes the same table), 646 of
+// 694 (8 bits), 659 of 700 (6), 690 of 718 (ternary) and 602 of 639 (BF16), on average 1.010, 1.011, 1.008, 1.008, 1.007 and 1.009 of it, at
+// worst 1.40 (519 x 16310 x 7936, a row of blocks for seven rows), 1.25, 1.24, 1.16, 1.42 and 1.16 (there mostly a short K under many weight rows).
 struct Cost {
     int wm, wn, wk, mf, nf;
     float first_start, first_step, next_start, next_step;

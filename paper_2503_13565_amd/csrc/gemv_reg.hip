@@ -10,8 +10,8 @@
 //     waves through an LDS counter, one row at a time: the memory system serves the waves of a
 //     compute unit very unevenly (the first data reaches them 2 to 6 us after the launch), and
 //     with a fixed share per wave the slowest wave set the kernel time.
-//   - One weight row per wave step (1 KiB per load instruction), two steps in flight per wave:
-//     32 KiB in flight per compute unit, which is where a plain read stream peaks here.
+//   - One weight row per wave step (1 KiB per load instruction), two steps in flight per wave (beside the one at work, where
+//     rows are long): 32 KiB in flight per compute unit, which is where a plain read stream peaks here.
 // Decode and multiply-add are as in gemv.hip: the scaled FP4->BF16 convert with the block scale,
 // then v_dot2_f32_bf16 with FP32 accumulation (Eq. 2: scaling a power of two commutes with the
 // sum of the block).

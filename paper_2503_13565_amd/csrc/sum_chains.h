@@ -55,8 +55,8 @@ constexpr int chain_pairs(int phases, int wk, int chains)
 }
 
 // Whether a call may take a shape.  A block that cannot cut its sums is there for the largest products alone, where its outputs
-// fill their rounds over the units to 85 %: there it is the fastest by a tenth (22016 x 4096 at 509 rows 78 us,
-// 89 in blocks that do).
+// fill their rounds over the units to 85 %: there it is the fastest by a fifth (22016 x 4096 at 509 rows 75 us,
+// 94 in blocks that do).
 constexpr bool cuts_enough(int bits, int wm, int wn, int wk, int mf, int nf, int m, int n, int k, int cus, int wanted)
 {
     if (chains_of(bits, wk, mf, nf, (k + 127) / 128) >= wanted)
